@@ -17,15 +17,17 @@
 // refinements of 8 points evenly over [x* - h, x* + h] around the best point so far (h the
 // previous spacing); scanned in increasing x, a point wins only when it lowers G by more than
 // a relative 1e-9 (closer values are ties, the earlier point stays, so that the choice does
-// not depend on rounding where G is flat); a factorization that fails gives G = inf.  Every wave of the workgroup evaluates one point
-// at a time (Cholesky of M in LDS, lanes = rows; the K columns of G_Y and d solved together,
-// lanes = columns).
+// not depend on rounding where G is flat); a factorization that fails gives G = inf.  A wave
+// evaluates four points at a time, one per 16 lanes, with the factor in registers (GcvFactor);
+// where G_Y itself has no Cholesky factor, one point at a time in LDS (gcv_eval).
 //
 // The p = q = 1 variant (MMGKS on the smoothed l1 norms of the data rows and of the flow
 // differences): before every projected solve the weights of the current iterate are formed
 // per pixel (one data weight, four edge weights stored at an edge's left / upper pixel), the
 // weighted Gram matrices, d and b^T W_d b are built from scratch, and GCV, z and the residual
 // are those of the weighted problem.
+#include <type_traits>
+
 #include "dev.h"
 #include "kernels.h"
 
@@ -40,9 +42,7 @@ constexpr int GK_P = GK_KC + 1;   // padded LDS row stride of the factorization 
 constexpr int GK_GRID0 = 32, GK_REFINE = 5, GK_GRIDR = 8;
 constexpr double GK_SPAN = 12.0;
 constexpr double GK_TIE = 1e-9;   // relative improvement of G a later grid point needs to win
-constexpr int GK_G = 4;           // Gram columns per pass
-constexpr int GK_NR = 2 * GK_G + 1;  // values per workgroup sum of a Gram pass
-constexpr int GK_RMAX = GK_NR > 8 ? GK_NR : 8;  // largest workgroup sum
+constexpr int GK_RMAX = 2;        // largest workgroup sum
 
 struct GksLds {
     double GA[GK_KC * GK_KC];     // (Y V)^T Y V
@@ -50,7 +50,10 @@ struct GksLds {
     double d[GK_KC];              // (Y V)^T b
     double z[GK_KC];
     double z0[GK_KC];             // the unregularised projected solution G_Y^-1 d
-    double h[GK_KC];              // Gram-Schmidt coefficients
+    double h[2 * GK_KC];          // Gram-Schmidt coefficients; inner products with one or two vectors
+    double C[GK_KC * GK_P];       // the Cholesky factor of G_Y (lower, zeros above)
+    double y0[GK_KC];             // C^-1 d
+    int c_ok;                     // C and z0 exist
     double M[GK_WAVES][GK_KC * GK_P];
     double X[GK_WAVES][GK_KC * GK_P];
     double part[GK_WAVES * GK_RMAX];
@@ -94,107 +97,392 @@ __device__ void wg_sum(double (&a)[NV], GksLds& s) {
     for (int j = 0; j < NV; ++j) a[j] = s.tot[j];
 }
 
-__device__ double wg_norm(const double* x, int64_t len, GksLds& s) {
-    double a[1] = {0.0};
-    for (int64_t p = threadIdx.x; p < len; p += GK_THREADS) a[0] += x[p] * x[p];
-    wg_sum<1>(a, s);
-    return sqrt(a[0]);
-}
+// Inner products of columns 0..ncols-1 of Q (stride len) with x0 and, for NX = 2, with x1:
+// s.h[c] = Q_c^T x0, s.h[GK_KC + c] = Q_c^T x1.  Each wave takes whole columns, up to four side by
+// side: one butterfly per column and vector, where columns split over the workgroup would cost
+// one per wave (the sums are latency: a 32 x 32 pair has 4 elements per thread and column).
+// VEC = 2: 16-byte loads (the columns of V, whose length is even; the left vectors of odd
+// frames take single loads).
+template <int VEC>
+using GkVec = double __attribute__((ext_vector_type(VEC)));
 
-// x <- x - Q (Q^T x), twice, against columns 0..ncols-1 of Q (column stride len).
-__device__ void reorth(const double* Q, int64_t len, int ncols, double* x, GksLds& s) {
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int c0 = 0; c0 < ncols; c0 += 8) {
-            double a[8];
+template <int NX, int NC, int VEC>
+__device__ __forceinline__ void wave_dots(const double* __restrict__ Q, int64_t len, int c0,
+                                          const double* __restrict__ x0, const double* __restrict__ x1, GksLds& s) {
+    using VT = GkVec<VEC>;
+    const int lane = threadIdx.x % 64;
+    double a[NX][NC];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) a[c] = 0.0;
-            for (int64_t p = threadIdx.x; p < len; p += GK_THREADS) {
-                const double xv = x[p];
+    for (int v = 0; v < NX; ++v)
 #pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    if (c0 + c < ncols) a[c] += Q[(int64_t)(c0 + c) * len + p] * xv;
+        for (int c = 0; c < NC; ++c) a[v][c] = 0.0;
+    const double* q = Q + (int64_t)c0 * len;
+#pragma unroll 4
+    for (int64_t p = VEC * lane; p < len; p += 64 * VEC) {
+        const VT xa = *reinterpret_cast<const VT*>(x0 + p);
+        VT xb = xa;
+        if constexpr (NX == 2) xb = *reinterpret_cast<const VT*>(x1 + p);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const VT qv = *reinterpret_cast<const VT*>(q + (int64_t)c * len + p);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                a[0][c] = fma(qv[e], xa[e], a[0][c]);
+                if constexpr (NX == 2) a[1][c] = fma(qv[e], xb[e], a[1][c]);
             }
-            wg_sum<8>(a, s);
-            if (threadIdx.x < 8 && c0 + (int)threadIdx.x < ncols) s.h[c0 + threadIdx.x] = s.tot[threadIdx.x];
         }
-        __syncthreads();
-        for (int64_t p = threadIdx.x; p < len; p += GK_THREADS) {
-            double acc = 0.0;
-            for (int c = 0; c < ncols; ++c) acc += s.h[c] * Q[(int64_t)c * len + p];
-            x[p] -= acc;
-        }
-        __syncthreads();
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+        for (int v = 0; v < NX; ++v)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) a[v][c] += __shfl_xor(a[v][c], o);
+    if (lane == 0) {
+#pragma unroll
+        for (int v = 0; v < NX; ++v)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) s.h[v * GK_KC + c0 + c] = a[v][c];
     }
 }
 
-// Y v, the x- and y-differences of both components of v at pixel p (0 past the last
-// column / row).
-struct PixVals {
-    double y, dxx, dxy, dyx, dyy;
-};
+template <int NX, int VEC>
+__device__ void wg_dots(const double* Q, int64_t len, int ncols, const double* x0, const double* x1, GksLds& s) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int per = (ncols + GK_WAVES - 1) / GK_WAVES;  // at most 4 (GK_KC = 4 GK_WAVES)
+    const int c0 = w * per, nc = min(per, ncols - c0);
+    if (nc == 4) wave_dots<NX, 4, VEC>(Q, len, c0, x0, x1, s);
+    else if (nc == 3) wave_dots<NX, 3, VEC>(Q, len, c0, x0, x1, s);
+    else if (nc == 2) wave_dots<NX, 2, VEC>(Q, len, c0, x0, x1, s);
+    else if (nc == 1) wave_dots<NX, 1, VEC>(Q, len, c0, x0, x1, s);
+    __syncthreads();
+}
 
-template <class T>
-__device__ __forceinline__ PixVals pix_vals(const double* v, int n, int nx, int p, bool hx, bool hy, T ix, T iy) {
-    const double vx = v[p], vy = v[n + p];
-    PixVals r;
-    r.y = (double)ix * vx + (double)iy * vy;
-    r.dxx = hx ? v[p + 1] - vx : 0.0;
-    r.dxy = hx ? v[n + p + 1] - vy : 0.0;
-    r.dyx = hy ? v[p + nx] - vx : 0.0;
-    r.dyy = hy ? v[n + p + nx] - vy : 0.0;
-    return r;
+// Sum over the first ncols columns of Q (stride len), with the coefficients h, of the VEC
+// elements at p: eight columns' loads in flight ahead of the ordered sum.
+template <int VEC>
+__device__ __forceinline__ GkVec<VEC> combine(const double* __restrict__ Q, int64_t len, int ncols, const double* h,
+                                              int64_t p) {
+    using VT = GkVec<VEC>;
+    VT acc = VT(0.0);
+    int c = 0;
+    for (; c + 8 <= ncols; c += 8) {
+        VT q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = *reinterpret_cast<const VT*>(Q + (int64_t)(c + e) * len + p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc += h[c + e] * q[e];
+    }
+    if (c < ncols) {  // (a column past the last is read as the last and left out)
+        VT q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            q[e] = *reinterpret_cast<const VT*>(Q + (int64_t)min(c + e, ncols - 1) * len + p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (c + e < ncols) acc += h[c + e] * q[e];
+    }
+    return acc;
+}
+
+// x <- x - Q (Q^T x), twice, against columns 0..ncols-1 of Q (column stride len, a multiple of
+// VEC); returns ||x||.  x is written by the thread that owns the element and read by others:
+// callers leave a barrier before.
+template <int VEC>
+__device__ double reorth(const double* Q, int64_t len, int ncols, double* x, GksLds& s) {
+    using VT = GkVec<VEC>;
+    double nrm[1] = {0.0};
+    for (int pass = 0; pass < 2; ++pass) {
+        wg_dots<1, VEC>(Q, len, ncols, x, nullptr, s);
+#pragma unroll 2
+        for (int64_t p = VEC * (int)threadIdx.x; p < len; p += VEC * GK_THREADS) {
+            VT* xp = reinterpret_cast<VT*>(x + p);
+            const VT v = *xp - combine<VEC>(Q, len, ncols, s.h, p);
+            *xp = v;
+            if (pass == 1)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) nrm[0] += v[e] * v[e];
+        }
+        __syncthreads();
+    }
+    wg_sum<1>(nrm, s);
+    return sqrt(nrm[0]);
 }
 
 // Row j of the Gram matrices (against columns 0..j) and d[j]; with W (the p = q = 1 variant)
 // every data row is weighted by W[p] and every difference by its edge weight W[n + 4p + e].
+// The row is V^T (Y^T W_d Y v_j) and V^T (L^T W_r L v_j): the two vectors are formed once (ya, yl)
+// and the K columns then only stream past them.
 template <class T>
 __device__ void gram_row(int j, const double* V, int n, int nx, int ny, const T* Ix, const T* Iy, const T* It,
-                         GksLds& s, const double* W) {
+                         double* ya, double* yl, GksLds& s, const double* W) {
     const int64_t N = 2 * (int64_t)n;
-    const double* vj = V + (int64_t)j * N;
-    for (int i0 = 0; i0 <= j; i0 += GK_G) {
-        double a[GK_NR];
-#pragma unroll
-        for (int c = 0; c < GK_NR; ++c) a[c] = 0.0;
-        for (int p = threadIdx.x; p < n; p += GK_THREADS) {
-            const int x = p % nx, y = p / nx;
-            const bool hx = x + 1 < nx, hy = y + 1 < ny;
-            const T ix = Ix[p], iy = Iy[p];
-            PixVals J = pix_vals(vj, n, nx, p, hx, hy, ix, iy);
-            if (W) {  // weighted copies of the new column's values
-                const double* we = W + n + 4 * (int64_t)p;
-                J.y *= W[p];
-                J.dxx *= we[0];
-                J.dxy *= we[1];
-                J.dyx *= we[2];
-                J.dyy *= we[3];
-            }
-            if (i0 == 0) a[2 * GK_G] += J.y * -(double)It[p];
-#pragma unroll
-            for (int c = 0; c < GK_G; ++c) {
-                if (i0 + c <= j) {
-                    const PixVals Q = pix_vals(V + (int64_t)(i0 + c) * N, n, nx, p, hx, hy, ix, iy);
-                    a[c] += Q.y * J.y;
-                    a[GK_G + c] += Q.dxx * J.dxx + Q.dyx * J.dyx + Q.dxy * J.dxy + Q.dyy * J.dyy;
-                }
-            }
+    const double* vx = V + (int64_t)j * N;
+    const double* vy = vx + n;
+    double dj[1] = {0.0};
+    for (int p = threadIdx.x; p < n; p += GK_THREADS) {
+        const int x = p % nx, y = p / nx;
+        const double ix = (double)Ix[p], iy = (double)Iy[p];
+        const double ax = vx[p], ay = vy[p];
+        double e = ix * ax + iy * ay;
+        if (W) e *= W[p];
+        dj[0] += e * -(double)It[p];
+        ya[p] = ix * e;
+        ya[n + p] = iy * e;
+        // an edge's weight is stored at its left / upper end
+        const double* wp = W ? W + n + 4 * (int64_t)p : nullptr;
+        double lx = 0.0, ly = 0.0;
+        if (x > 0) {
+            const double* wq = W ? wp - 4 : nullptr;
+            lx += (W ? wq[0] : 1.0) * (ax - vx[p - 1]);
+            ly += (W ? wq[1] : 1.0) * (ay - vy[p - 1]);
         }
-        wg_sum<GK_NR>(a, s);
-        if (threadIdx.x < GK_G && i0 + (int)threadIdx.x <= j) {
-            const int i = i0 + threadIdx.x;
-            s.GA[i * GK_KC + j] = s.GA[j * GK_KC + i] = s.tot[threadIdx.x];
-            s.GL[i * GK_KC + j] = s.GL[j * GK_KC + i] = s.tot[GK_G + threadIdx.x];
+        if (x + 1 < nx) {
+            lx += (W ? wp[0] : 1.0) * (ax - vx[p + 1]);
+            ly += (W ? wp[1] : 1.0) * (ay - vy[p + 1]);
         }
-        if (i0 == 0 && threadIdx.x == 0) s.d[j] = s.tot[2 * GK_G];
+        if (y > 0) {
+            const double* wq = W ? wp - 4 * (int64_t)nx : nullptr;
+            lx += (W ? wq[2] : 1.0) * (ax - vx[p - nx]);
+            ly += (W ? wq[3] : 1.0) * (ay - vy[p - nx]);
+        }
+        if (y + 1 < ny) {
+            lx += (W ? wp[2] : 1.0) * (ax - vx[p + nx]);
+            ly += (W ? wp[3] : 1.0) * (ay - vy[p + nx]);
+        }
+        yl[p] = lx;
+        yl[n + p] = ly;
     }
+    wg_sum<1>(dj, s);  // (its barriers also publish ya and yl)
+    wg_dots<2, 2>(V, N, j + 1, ya, yl, s);
+    if (threadIdx.x <= (unsigned)j) {
+        const int i = threadIdx.x;
+        s.GA[i * GK_KC + j] = s.GA[j * GK_KC + i] = s.h[i];
+        s.GL[i * GK_KC + j] = s.GL[j * GK_KC + i] = s.h[GK_KC + i];
+    }
+    if (threadIdx.x == 0) s.d[j] = dj[0];
     __syncthreads();
 }
 
-// G(lambda) on the calling wave; with zout, also writes z (lanes < K) unless the factorization
-// fails (G = inf).  The numerator: with rho0 = ||Y V z0 - b||^2 >= 0 (z0 = s.z0 solving the
-// unregularised projected normal equations), ||Y V z - b||^2 = rho0 + (z - z0)^T G_Y (z - z0)
-// exactly, a sum of non-negative terms; with rho0 < 0, ||b||^2 - 2 z.d + z^T G_Y z.
-__device__ double gcv_eval(int K, double lam, double bb, double rho0, double m, GksLds& s, double* zout) {
+// ---- four GCV points per wave
+//
+// 16 lanes hold one point's matrix M = G_Y + lambda G_L: lane i owns rows i and 16 + i, a row's
+// entries in registers, and an entry of another row arrives by a DPP broadcast within the 16 lanes
+// (no LDS: walking the matrix in LDS, one point per wave, its dependent round trips took half of
+// the solve).  With G_Y = C C^T and the factor M = R R^T, X = R^-1 C is lower triangular and
+//   trace(M^-1 G_Y) = ||X||_F^2,   C^T z = X^T y  (y = R^-1 d),   C^T z0 = C^-1 d = y0,
+// so G needs one factorization and one triangular solve of K columns, no inverse and no backward
+// solve: its numerator is rho0 + ||X^T y - y0||^2, a sum of non-negative terms.  A factorization of
+// 25 columns takes 7.9k cycles and X 5.7k, for one point or four; a wave issues one FP64
+// instruction every 7 to 10 cycles and two waves of a SIMD do not slow each other, so the chain of
+// pivots bounds it.  With the column-per-wave inner products above, a solve of 15 pairs of 32 x 32
+// (ell 10, 20 projected solves) takes 1.94 ms, 12.2 ms before; half of it is this search.
+template <int N>
+__device__ __forceinline__ double row16_bcast(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + N, 0xf, 0xf, true);  // row_newbcast:N
+}
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+// a[e] += (src on lane N + e of the 16) * m for e < L: one v_fmac_f64 with a DPP source each,
+// where a broadcast and an FMA would be two instructions (a wave issues one of either every 7 to 10
+// cycles).  A DPP source may not have been written within two wait states, hence the s_nop.
+// (volatile also keeps the updates here: sunk to the values' next uses, they would hold every
+// step's broadcasts in registers.)
+#define GK_FM(i) "v_fmac_f64_dpp %" #i ", %[s], %[m] row_newbcast:%[n" #i "] row_mask:0xf bank_mask:0xf\n\t"
+template <int N, int L>
+__device__ __forceinline__ void fmac_bcast(double* a, double src, double m) {
+    static_assert(N >= 0 && N + L <= 16, "a lane of the 16");
+    if constexpr (L >= 8) {
+        asm volatile("s_nop 1\n\t" GK_FM(0) GK_FM(1) GK_FM(2) GK_FM(3) GK_FM(4) GK_FM(5) GK_FM(6) GK_FM(7)
+                     : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]),
+                       "+&v"(a[7])
+                     : [s] "v"(src), [m] "v"(m), [n0] "n"(N), [n1] "n"(N + 1), [n2] "n"(N + 2), [n3] "n"(N + 3),
+                       [n4] "n"(N + 4), [n5] "n"(N + 5), [n6] "n"(N + 6), [n7] "n"(N + 7));
+        fmac_bcast<N + 8 <= 16 ? N + 8 : 16, L - 8>(a + 8, src, m);
+    } else if constexpr (L >= 4) {
+        asm volatile("s_nop 1\n\t" GK_FM(0) GK_FM(1) GK_FM(2) GK_FM(3)
+                     : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3])
+                     : [s] "v"(src), [m] "v"(m), [n0] "n"(N), [n1] "n"(N + 1), [n2] "n"(N + 2), [n3] "n"(N + 3));
+        fmac_bcast<N + 4, L - 4>(a + 4, src, m);
+    } else if constexpr (L >= 2) {
+        asm volatile("s_nop 1\n\t" GK_FM(0) GK_FM(1)
+                     : "+&v"(a[0]), "+&v"(a[1])
+                     : [s] "v"(src), [m] "v"(m), [n0] "n"(N), [n1] "n"(N + 1));
+        fmac_bcast<N + 2, L - 2>(a + 2, src, m);
+    } else if constexpr (L == 1) {
+        asm volatile("s_nop 1\n\t" GK_FM(0) : "+&v"(a[0]) : [s] "v"(src), [m] "v"(m), [n0] "n"(N));
+    }
+}
+#undef GK_FM
+__device__ __forceinline__ double row16_sum(double v) {
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+// KB = 16, 24 or 32 >= K.
+template <int KB>
+struct GcvFactor {
+    static constexpr bool TWO = KB > 16;
+    static constexpr int K2 = KB - 16;   // columns held by second rows (K2 <= 0: none)
+    double a1[16], a2[TWO ? KB : 1];     // rows i and 16 + i of R below the diagonal (zeros on and above it)
+    double inv1, inv2;                   // 1 / diagonal of the lane's rows
+    double y1, y2;                       // R^-1 d
+    bool ok;                             // every pivot positive and finite (the same on the 16 lanes)
+
+    // 1 / sqrt(piv): the hardware estimate (relative error e below 2^-22) times 1 + e/2 + 3 e^2/8
+    // (the next term is below 2^-66), a shorter chain than two Newton steps.
+    __device__ __forceinline__ double pivot(double piv) {
+        ok = ok && piv > 0.0 && piv < INFINITY;
+        const double r = __builtin_amdgcn_rsq(piv);
+        const double e = fma(-piv * r, r, 1.0);
+        return fma(r * e, fma(0.375, e, 0.5), r);
+    }
+
+    // Rows and columns from K on hold unused values that never reach the first K.
+    __device__ __forceinline__ void factor(const GksLds& s, int K, double lam) {
+        const int i = threadIdx.x % 16;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a1[c] = fma(lam, s.GL[c * GK_KC + i], s.GA[c * GK_KC + i]);
+        y1 = s.d[i];
+        y2 = 0.0;
+        if constexpr (TWO) {
+#pragma unroll
+            for (int c = 0; c < KB; ++c) a2[c] = fma(lam, s.GL[c * GK_KC + 16 + i], s.GA[c * GK_KC + 16 + i]);
+            y2 = s.d[16 + i];
+        }
+        inv1 = inv2 = 0.0;
+        ok = true;
+        static_for<0, 16>([&](auto J) {
+            constexpr int j = decltype(J)::value;
+            if (!TWO && j >= K) return;  // (KB > 16 has K > 16)
+            const double r = pivot(row16_bcast<j>(a1[j]));
+            const double l1 = i > j ? a1[j] * r : 0.0;
+            a1[j] = l1;
+            if constexpr (TWO) {
+                const double l2 = a2[j] * r;
+                a2[j] = l2;
+                fmac_bcast<j + 1, 15 - j>(a1 + j + 1, l1, -l1);
+                fmac_bcast<j + 1, 15 - j>(a2 + j + 1, l1, -l2);
+                fmac_bcast<0, K2>(a2 + 16, l2, -l2);
+            } else {
+                fmac_bcast<j + 1, 15 - j>(a1 + j + 1, l1, -l1);
+            }
+            const double yj = row16_bcast<j>(y1) * r;
+            inv1 = i == j ? r : inv1;
+            y1 = i == j ? yj : fma(-l1, yj, y1);
+            if constexpr (TWO) y2 = fma(-a2[j], yj, y2);
+        });
+        if constexpr (TWO) {
+            static_for<16, KB>([&](auto J) {
+                constexpr int j = decltype(J)::value;
+                if (j >= K) return;
+                const double r = pivot(row16_bcast<j - 16>(a2[j]));
+                const double l2 = i > j - 16 ? a2[j] * r : 0.0;
+                a2[j] = l2;
+                fmac_bcast<j - 15, KB - 1 - j>(a2 + j + 1, l2, -l2);
+                const double yj = row16_bcast<j - 16>(y2) * r;
+                inv2 = i == j - 16 ? r : inv2;
+                y2 = i == j - 16 ? yj : fma(-l2, yj, y2);
+            });
+        }
+    }
+
+    // G of the factored point (the same on its 16 lanes); lane i owns columns i and 16 + i of X.
+    __device__ __forceinline__ double gcv(const GksLds& s, int K, double rho0, double m) const {
+        const int i = threadIdx.x % 16;
+        double x1[KB], x2[TWO ? K2 : 1];
+#pragma unroll
+        for (int r = 0; r < KB; ++r) x1[r] = s.C[r * GK_P + i];
+        double v1 = -s.y0[i], v2 = 0.0, t1 = 0.0, t2 = 0.0;
+        if constexpr (TWO) {
+#pragma unroll
+            for (int r = 0; r < K2; ++r) x2[r] = s.C[(16 + r) * GK_P + 16 + i];
+            v2 = -s.y0[16 + i];
+        }
+        static_for<0, KB>([&](auto KK) {
+            constexpr int k = decltype(KK)::value;
+            if ((!TWO || k >= 16) && k >= K) return;
+            const double ik = row16_bcast<k % 16>(k < 16 ? inv1 : inv2);
+            const double yk = row16_bcast<k % 16>(k < 16 ? y1 : y2);
+            x1[k] *= ik;
+            const double nx1 = -x1[k];
+            if constexpr (k < 16) {
+                fmac_bcast<k + 1, 15 - k>(x1 + k + 1, a1[k], nx1);
+                if constexpr (TWO) fmac_bcast<0, K2>(x1 + 16, a2[k], nx1);
+            } else {
+                x2[k - 16] *= ik;
+                fmac_bcast<k - 15, KB - 1 - k>(x1 + k + 1, a2[k], nx1);
+                fmac_bcast<k - 15, KB - 1 - k>(x2 + k - 15, a2[k], -x2[k - 16]);
+                v2 = fma(x2[k - 16], yk, v2);
+                t2 = fma(x2[k - 16], x2[k - 16], t2);
+            }
+            v1 = fma(x1[k], yk, v1);
+            t1 = fma(x1[k], x1[k], t1);
+        });
+        double q = i < K ? v1 * v1 : 0.0, t = i < K ? t1 : 0.0;
+        if (TWO && 16 + i < K) {
+            q += v2 * v2;
+            t += t2;
+        }
+        q = row16_sum(q);
+        t = row16_sum(t);
+        const double den = (m - t) * (m - t);
+        const double g = den > 0.0 ? (rho0 + q) / den : INFINITY;
+        return ok && isfinite(g) ? g : INFINITY;
+    }
+
+    // z = R^-T y (lanes 0..15 write) by the wave that holds the factor: R goes through Rl (LDS, KB
+    // rows of GK_P, left there with its diagonal and zero rows from K on), y is left in yl.
+    __device__ __forceinline__ void back(int K, double* Rl, double* yl, double* zl) const {
+        const int lane = threadIdx.x % 64, i = lane % 16;
+        double z1 = i < K ? y1 : 0.0, z2 = TWO && 16 + i < K ? y2 : 0.0;
+        const double d1 = i < K ? inv1 : 0.0, d2 = TWO && 16 + i < K ? inv2 : 0.0;
+        if (lane < 16) {
+#pragma unroll
+            for (int c = 0; c < KB; ++c) Rl[i * GK_P + c] = c < 16 && i < K ? a1[c < 16 ? c : 0] : 0.0;
+            if (i < K) Rl[i * GK_P + i] = 1.0 / inv1;
+            yl[i] = z1;
+            if constexpr (TWO) {
+                if (i < K2) {
+#pragma unroll
+                    for (int c = 0; c < KB; ++c) Rl[(16 + i) * GK_P + c] = 16 + i < K ? a2[c] : 0.0;
+                    if (16 + i < K) Rl[(16 + i) * GK_P + 16 + i] = 1.0 / inv2;
+                }
+                yl[16 + i] = z2;
+            }
+        }
+        wave_sync();
+        if constexpr (TWO) {
+            static_for<0, K2>([&](auto J) {
+                constexpr int j = KB - 1 - decltype(J)::value;
+                const double zj = row16_bcast<j - 16>(z2 * d2);
+                z2 = i == j - 16 ? zj : (i < j - 16 ? fma(-Rl[j * GK_P + 16 + i], zj, z2) : z2);
+                z1 = fma(-Rl[j * GK_P + i], zj, z1);
+            });
+        }
+        static_for<0, 16>([&](auto J) {
+            constexpr int j = 15 - decltype(J)::value;
+            const double zj = row16_bcast<j>(z1 * d1);
+            z1 = i == j ? zj : (i < j ? fma(-Rl[j * GK_P + i], zj, z1) : z1);
+        });
+        if (lane < 16) {
+            zl[i] = z1;
+            if (TWO) zl[16 + i] = z2;
+        }
+        wave_sync();
+    }
+};
+
+// G(lambda) on the calling wave where G_Y has no Cholesky factor (its data rows are dependent, or
+// K exceeds their rank).  One point per wave, Cholesky of M in LDS (lanes = rows), the K columns of G_Y
+// and d solved together (lanes = columns); the numerator is ||b||^2 - 2 z.d + z^T G_Y z.
+__device__ double gcv_eval(int K, double lam, double bb, double m, GksLds& s) {
     const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
     double* M = s.M[w];
     double* X = s.X[w];
@@ -233,36 +521,30 @@ __device__ double gcv_eval(int K, double lam, double bb, double rho0, double m, 
     }
     wave_sync();
     const double t = wave_sum(lane < K ? X[lane * GK_P + lane] : 0.0);
-    double rho;
-    if (rho0 >= 0.0) {
-        double dgd = 0.0;
-        if (lane < K) {
-            double gd = 0.0;
-            for (int k = 0; k < K; ++k) gd += s.GA[lane * GK_KC + k] * (X[k * GK_P + K] - s.z0[k]);
-            dgd = (X[lane * GK_P + K] - s.z0[lane]) * gd;
-        }
-        rho = rho0 + fmax(wave_sum(dgd), 0.0);
-    } else {
-        double zd = 0.0, zgz = 0.0;
-        if (lane < K) {
-            const double zi = X[lane * GK_P + K];
-            double gz = 0.0;
-            for (int k = 0; k < K; ++k) gz += s.GA[lane * GK_KC + k] * X[k * GK_P + K];
-            zd = zi * s.d[lane];
-            zgz = zi * gz;
-        }
-        zd = wave_sum(zd);
-        zgz = wave_sum(zgz);
-        rho = fmax(bb - 2.0 * zd + zgz, 0.0);
+    double zd = 0.0, zgz = 0.0;
+    if (lane < K) {
+        const double zi = X[lane * GK_P + K];
+        double gz = 0.0;
+        for (int k = 0; k < K; ++k) gz += s.GA[lane * GK_KC + k] * X[k * GK_P + K];
+        zd = zi * s.d[lane];
+        zgz = zi * gz;
     }
-    if (zout && lane < K) zout[lane] = X[lane * GK_P + K];
+    zd = wave_sum(zd);
+    zgz = wave_sum(zgz);
+    const double rho = fmax(bb - 2.0 * zd + zgz, 0.0);
     const double den = (m - t) * (m - t);
     const double g = den > 0.0 ? rho / den : INFINITY;
     return isfinite(g) ? g : INFINITY;
 }
 
-// The GCV minimiser (every thread returns the same value).
-__device__ double gcv_search(int K, double bb, double rho0, double m, GksLds& s) {
+// lambda (every thread returns the same value) and, in s.z, the projected solution: the factor of
+// G_Y with y0 and z0, rho0 = residual() of z0 (called by every thread; the sum of squares over the
+// pixels), the grid search, and the solve at the lambda found (fixed_lambda > 0: only that).  One
+// loop, so that its steps share the code of the factorization: the unrolled code is large, and
+// separate copies of it would each run cold.  z is left alone when the last factorization fails.
+template <int KB, class F>
+__device__ __forceinline__ double gcv_lambda(int K, double bb, double m, double fixed_lambda, GksLds& s,
+                                             F&& residual) {
     double tA = 0.0, tL = 0.0;
     for (int i = 0; i < K; ++i) {
         tA += s.GA[i * GK_KC + i];
@@ -270,31 +552,73 @@ __device__ double gcv_search(int K, double bb, double rho0, double m, GksLds& s)
     }
     const double c = log10(fmax(tA, 1e-300) / fmax(tL, 1e-300));
     const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-    double best_g = INFINITY, best_x = c;
+    double best_g = INFINITY, best_x = c, rho0 = -1.0;
     double h = 2.0 * GK_SPAN / (GK_GRID0 - 1);
-    for (int stage = 0; stage <= GK_REFINE; ++stage) {
-        const int npt = stage == 0 ? GK_GRID0 : GK_GRIDR;
+    double lam = 0.0;  // of the single points
+    constexpr int BASE = -1, LAST = GK_REFINE + 1;
+    int stage = BASE;
+    if (fixed_lambda > 0.0) {
+        stage = LAST;
+        lam = fixed_lambda;
+    }
+    for (; stage <= LAST; ++stage) {
+        const bool single = stage == BASE || stage == LAST;
+        const int npt = single ? 1 : stage == 0 ? GK_GRID0 : GK_GRIDR;
         const double lo = stage == 0 ? c - GK_SPAN : best_x - h;
         const double step2 = stage == 0 ? 2.0 * GK_SPAN : 2.0 * h;
         const int den = npt - 1;
-        for (int p = w; p < npt; p += GK_WAVES) {
-            const double x = lo + step2 * p / den;
-            const double g = gcv_eval(K, pow(10.0, x), bb, rho0, m, s, nullptr);
-            if (lane == 0) {
-                s.gval[p] = g;
-                s.gxv[p] = x;
+        if (single || rho0 >= 0.0) {
+            // wave w: points 4 w .. 4 w + 3
+            if (4 * w < npt) {
+                const int p = 4 * w + lane / 16;
+                const double x = single ? 0.0 : lo + step2 * p / den;
+                GcvFactor<KB> f;
+                f.factor(s, K, single ? lam : exp10(x));
+                if (single) {
+                    if (stage == BASE || f.ok)
+                        f.back(K, stage == BASE ? s.C : s.M[0], stage == BASE ? s.y0 : s.X[0],
+                               stage == BASE ? s.z0 : s.z);
+                    if (threadIdx.x == 0) s.c_ok = f.ok;
+                } else {
+                    const double g = f.gcv(s, K, rho0, m);
+                    if (lane % 16 == 0) {
+                        s.gval[p] = g;
+                        s.gxv[p] = x;
+                    }
+                }
+            }
+        } else {
+            for (int p = w; p < npt; p += GK_WAVES) {
+                const double x = lo + step2 * p / den;
+                const double g = gcv_eval(K, exp10(x), bb, m, s);
+                if (lane == 0) {
+                    s.gval[p] = g;
+                    s.gxv[p] = x;
+                }
             }
         }
         __syncthreads();
-        for (int p = 0; p < npt; ++p)
-            if (s.gval[p] < best_g * (1.0 - GK_TIE)) {
-                best_g = s.gval[p];
-                best_x = s.gxv[p];
+        if (stage == BASE) {
+            if (s.c_ok) {
+                rho0 = residual();
+                if (!(rho0 >= 0.0)) rho0 = -1.0;
             }
+            continue;
+        }
+        if (stage == LAST) break;
+#pragma unroll 8
+        for (int p = 0; p < npt; ++p) {
+            const double g = s.gval[p], x = s.gxv[p];
+            if (g < best_g * (1.0 - GK_TIE)) {
+                best_g = g;
+                best_x = x;
+            }
+        }
         __syncthreads();
         if (stage > 0) h = 2.0 * h / (GK_GRIDR - 1);
+        lam = exp10(best_x);
     }
-    return pow(10.0, best_x);
+    return lam;
 }
 
 template <class T>
@@ -360,8 +684,7 @@ __global__ __launch_bounds__(GK_THREADS) void k_of_gks(const Tile* __restrict__ 
         for (int p = tid; p < n; p += GK_THREADS)
             ui[p] = ((double)Ix[p] * vp[p] + (double)Iy[p] * vp[n + p]) - alpha * up[p];
         __syncthreads();
-        reorth(U, n, i, ui, s);
-        beta = wg_norm(ui, n, s);
+        beta = n % 2 == 0 ? reorth<2>(U, n, i, ui, s) : reorth<1>(U, n, i, ui, s);
         for (int p = tid; p < n; p += GK_THREADS) ui[p] = ui[p] / beta;
         if (i == ell) break;
         double* vi = V + (int64_t)i * N;
@@ -370,8 +693,7 @@ __global__ __launch_bounds__(GK_THREADS) void k_of_gks(const Tile* __restrict__ 
             vi[n + p] = (double)Iy[p] * ui[p] - beta * vp[n + p];
         }
         __syncthreads();
-        reorth(V, N, i, vi, s);
-        alpha = wg_norm(vi, N, s);
+        alpha = reorth<2>(V, N, i, vi, s);
         for (int64_t p = tid; p < N; p += GK_THREADS) vi[p] = vi[p] / alpha;
         __syncthreads();  // element n + p of vi is read next by the thread of pixel p
     }
@@ -379,8 +701,14 @@ __global__ __launch_bounds__(GK_THREADS) void k_of_gks(const Tile* __restrict__ 
 
     // generalized Krylov iterations
     int K = ell;
+    // the Gram rows' two vectors: r is free between the residuals, the left vectors' workspace
+    // ((ell + 1) n >= 2 n values) after the start
+    double *ya = r, *yl = U;
+    for (int e = tid; e < GK_KC * GK_KC; e += GK_THREADS) s.GA[e] = s.GL[e] = 0.0;
+    if (tid < GK_KC) s.d[tid] = 0.0;
+    __syncthreads();
     if (!W)
-        for (int j = 0; j < K; ++j) gram_row(j, V, n, nx, ny, Ix, Iy, It, s, (const double*)nullptr);
+        for (int j = 0; j < K; ++j) gram_row(j, V, n, nx, ny, Ix, Iy, It, ya, yl, s, (const double*)nullptr);
     else
         for (int64_t p = tid; p < N; p += GK_THREADS) sv[p] = 0.0;  // s^(0)
     const double m = (double)n;
@@ -409,42 +737,34 @@ __global__ __launch_bounds__(GK_THREADS) void k_of_gks(const Tile* __restrict__ 
             wg_sum<1>(a1w, s);
             bbw = a1w[0];
             __syncthreads();
-            for (int j = 0; j < K; ++j) gram_row(j, V, n, nx, ny, Ix, Iy, It, s, (const double*)W);
+            for (int j = 0; j < K; ++j) gram_row(j, V, n, nx, ny, Ix, Iy, It, ya, yl, s, (const double*)W);
         }
-        double lk = fixed_lambda;
-        if (!(fixed_lambda > 0.0)) {
-            // rho0 = ||Y V z0 - b||^2 from a pass over the pixels (< 0 when G_Y is singular)
-            double st[1] = {0.0};
-            if (tid < 64) {
-                const double g0 = gcv_eval(K, 0.0, bbw, -1.0, m, s, s.z0);
-                st[0] = tid == 0 ? g0 : 0.0;
-            }
-            wg_sum<1>(st, s);  // every thread learns whether z0 exists
-            double rho0 = -1.0;
-            if (isfinite(st[0])) {
-                double e2[1] = {0.0};
-                for (int p = tid; p < n; p += GK_THREADS) {
-                    double acc = 0.0;
-                    for (int j = 0; j < K; ++j) {
-                        const double* vj = V + (int64_t)j * N;
-                        acc += s.z0[j] * ((double)Ix[p] * vj[p] + (double)Iy[p] * vj[n + p]);
+        // ||Y V z0 - b||^2 (weighted for p = q = 1) from a pass over the pixels
+        auto residual = [&]() {
+            double e2[1] = {0.0};
+            auto pass = [&](auto vec) {
+                constexpr int VEC = decltype(vec)::value;
+                for (int p = VEC * tid; p < n; p += VEC * GK_THREADS) {
+                    const GkVec<VEC> sx = combine<VEC>(V, N, K, s.z0, p), sy = combine<VEC>(V, N, K, s.z0, n + p);
+#pragma unroll
+                    for (int q = 0; q < VEC; ++q) {
+                        const double e = (double)Ix[p + q] * sx[q] + (double)Iy[p + q] * sy[q] + (double)It[p + q];
+                        e2[0] += (W ? W[p + q] : 1.0) * e * e;
                     }
-                    const double e = acc + (double)It[p];
-                    e2[0] += (W ? W[p] : 1.0) * e * e;
                 }
-                wg_sum<1>(e2, s);
-                rho0 = e2[0];
-            }
-            lk = gcv_search(K, bbw, rho0, m, s);
-        }
+            };
+            if (n % 2 == 0) pass(std::integral_constant<int, 2>{});
+            else pass(std::integral_constant<int, 1>{});
+            wg_sum<1>(e2, s);
+            return e2[0];
+        };
+        const double lk = K <= 16   ? gcv_lambda<16>(K, bbw, m, fixed_lambda, s, residual)
+                          : K <= 24 ? gcv_lambda<24>(K, bbw, m, fixed_lambda, s, residual)
+                                    : gcv_lambda<32>(K, bbw, m, fixed_lambda, s, residual);
         if (tid == 0) lam[k] = lk;
-        if (tid < 64) (void)gcv_eval(K, lk, bbw, -1.0, m, s, s.z);
-        __syncthreads();
-        for (int64_t p = tid; p < N; p += GK_THREADS) {
-            double acc = 0.0;
-            for (int j = 0; j < K; ++j) acc += s.z[j] * V[(int64_t)j * N + p];
-            sv[p] = acc;
-        }
+#pragma unroll 2
+        for (int64_t p = 2 * tid; p < N; p += 2 * GK_THREADS)
+            *reinterpret_cast<GkVec<2>*>(sv + p) = combine<2>(V, N, K, s.z, p);
         if (k == n_iter - 1) break;
         __syncthreads();
         // r = Y^T W_d (Y s - b) + lambda L^T W_r L s (W = I for p = q = 2)
@@ -479,14 +799,13 @@ __global__ __launch_bounds__(GK_THREADS) void k_of_gks(const Tile* __restrict__ 
             r[n + p] = (double)Iy[p] * e + lk * ly;
         }
         __syncthreads();
-        reorth(V, N, K, r, s);
-        const double nr = wg_norm(r, N, s);
+        const double nr = reorth<2>(V, N, K, r, s);
         if (nr <= 1e-14 * atb) break;  // breakdown: keep the last s
         double* vk = V + (int64_t)K * N;
         for (int64_t p = tid; p < N; p += GK_THREADS) vk[p] = r[p] / nr;
         __syncthreads();
         ++K;
-        if (!W) gram_row(K - 1, V, n, nx, ny, Ix, Iy, It, s, (const double*)nullptr);
+        if (!W) gram_row(K - 1, V, n, nx, ny, Ix, Iy, It, ya, yl, s, (const double*)nullptr);
     }
     __syncthreads();
     for (int64_t p = tid; p < N; p += GK_THREADS) vo[p] = (T)sv[p];
