@@ -2,6 +2,7 @@
 // sweeps for the p = q = 2 flow energy (eq. of_reg), the reverse-flow estimate of the
 // Remark in Sec. 3, and the MM weights of Sec. 4.1.1.
 #include <climits>
+#include <type_traits>
 #include <vector>
 
 #include "dev.h"
@@ -188,6 +189,8 @@ __global__ __launch_bounds__(DV_LW * DV_TH) void k_of_derivs4(const Tile* __rest
 // tile with a 6-pixel halo (6 sweeps per launch, 512 threads) measured 0.72 ms per 8 sweeps
 // of the 1024 x 1024 x 64 stack, against 1.16 ms for 64 x 16 with 8 (640 threads), 0.97 ms for
 // 56 x 24 with 4 and 0.85 ms for 48 x 48 with 8; workgroups of 1024 threads were slower.
+// The sweep loop is unrolled by two so that the buffer folds into the LDS offsets (118 -> 87
+// instructions a sweep of 4 FP32 pixels; 64 registers at most, for eight waves a SIMD).
 static constexpr int HTW = 52, HTH = 20, HS_MAX = 6;
 static constexpr int HRW = HTW + 2 * HS_MAX, HRH = HTH + 2 * HS_MAX;  // 64 x 32 halo region
 static constexpr int HS_THREADS = 512;
@@ -197,8 +200,85 @@ static_assert(HRW * HRH == HS_THREADS * HPT, "halo region must split evenly over
 // (so every pixel reads its four neighbours unconditionally), padded to 64 elements
 static constexpr int HZERO = HRW * HRH, HCS = (HRW * HRH + 64) / 64 * 64;
 
+// The pixels of one thread: a strip of HPT consecutive rows of one column.  The vertical
+// neighbours inside the strip come from its registers (the previous sweep's values), the others
+// from LDS; neighbours outside the image read a zero of the LDS.
+template <class T, int N>
+struct HsStrip {
+    T av[N], bv[N], gx[N], gy[N], gt[N], rden[N], rd[N];
+    int lx[N][2];             // LDS index of the x-1, x+1 neighbours
+    int l_up, l_dn;           // LDS index of the y-1 neighbour of pixel 0, y+1 of pixel N-1
+    bool live[N];
+
+    // pixel r at p of the pair's planes (read when in the image), its neighbours and their LDS
+    // indices (u, d: used for the first and the last pixel)
+    __device__ __forceinline__ void load(int r, bool in, const T* __restrict__ Ip, const T* s, int64_t np, int64_t p,
+                                         T gamma, bool has_u, bool has_d, bool has_l, bool has_r, int u, int d,
+                                         int l, int rt) {
+        live[r] = in;
+        av[r] = bv[r] = T(0);
+        gx[r] = gy[r] = gt[r] = T(0);
+        rden[r] = rd[r] = T(0);
+        if (r == 0) l_up = u;
+        if (r == N - 1) l_dn = d;
+        lx[r][0] = l;
+        lx[r][1] = rt;
+        if (in) {
+            av[r] = s[p];
+            bv[r] = s[np + p];
+            gx[r] = Ip[p];
+            gy[r] = Ip[np + p];
+            gt[r] = Ip[2 * np + p];
+            const int c = (int)has_u + (int)has_d + (int)has_l + (int)has_r;
+            rd[r] = T(1) / T(c);
+            rden[r] = T(1) / (gamma * T(c) + gx[r] * gx[r] + gy[r] * gy[r]);
+        }
+    }
+
+    // one sweep from the LDS planes (cx, cy) of the previous one
+    __device__ __forceinline__ void sweep(const T* cx, const T* cy) {
+        // the LDS neighbours first (all in flight together); a pixel outside the image reads
+        // zeros and has zero weights, so it stays 0 without a branch
+        T la[N][2], lb[N][2];
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                la[r][e] = cx[lx[r][e]];
+                lb[r][e] = cy[lx[r][e]];
+            }
+        const T ua = cx[l_up], ub = cy[l_up], da = cx[l_dn], db = cy[l_dn];
+        T na[N], nb[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            // neighbour order: y-1, y+1, x-1, x+1 (a missing one adds 0: a strip pixel outside the
+            // image stays 0)
+            T ax = T(0), ay = T(0);
+            ax += r == 0 ? ua : av[r - 1];
+            ay += r == 0 ? ub : bv[r - 1];
+            ax += r == N - 1 ? da : av[r + 1];
+            ay += r == N - 1 ? db : bv[r + 1];
+            ax += la[r][0];
+            ay += lb[r][0];
+            ax += la[r][1];
+            ay += lb[r][1];
+            ax *= rd[r];
+            ay *= rd[r];
+            // (contractions written out: the same rounding in every form of the sweep)
+            const T k = (fma(gx[r], ax, gy[r] * ay) + gt[r]) * rden[r];
+            na[r] = fma(-gx[r], k, ax);
+            nb[r] = fma(-gy[r], k, ay);
+        }
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            av[r] = na[r];
+            bv[r] = nb[r];
+        }
+    }
+};
+
 template <class T>
-__global__ __launch_bounds__(HS_THREADS) void k_hs_multi(const Tile* __restrict__ tiles,
+__global__ __launch_bounds__(HS_THREADS, sizeof(T) == 4 ? 8 : 4) void k_hs_multi(const Tile* __restrict__ tiles,
                                                          const FrameInfo* __restrict__ fr, const T* __restrict__ I,
                                                          const T* __restrict__ vin, T* __restrict__ vout, T gamma,
                                                          int nsw) {
@@ -211,104 +291,114 @@ __global__ __launch_bounds__(HS_THREADS) void k_hs_multi(const Tile* __restrict_
     const int ox = tl.x0 - HS_MAX, oy = tl.y0 - HS_MAX;  // image coordinates of the region origin
     const T* sx = vin + 2 * f.pair_off;
     const T* Ip = I + 3 * f.pair_off;
-    // a thread owns a strip of HPT consecutive rows of one column of the region: the vertical
-    // neighbours inside the strip come from its registers (the previous sweep's values), the
-    // others from LDS
     const int rx = (int)threadIdx.x % HRW, ry0 = HPT * ((int)threadIdx.x / HRW);
     const int x = ox + rx;
-    T av[HPT], bv[HPT], gx[HPT], gy[HPT], gt[HPT], rden[HPT], rd[HPT];
-    bool up_in[HPT], dn_in[HPT];  // pixel r's y-1 (y+1) neighbour exists (strip pixels r-1, r+1)
-    int lx[HPT][2];                 // LDS index of the x-1, x+1 neighbours, HZERO outside the image
-    int l_up = HZERO, l_dn = HZERO;  // LDS index of the y-1 neighbour of pixel 0, y+1 of pixel HPT-1
-    bool live[HPT];
+    HsStrip<T, HPT> q;
 #pragma unroll
     for (int r = 0; r < HPT; ++r) {
         const int ry = ry0 + r, idx = ry * HRW + rx;
         const int y = oy + ry;
         const bool in = x >= 0 && x < nx && y >= 0 && y < ny;
-        live[r] = in;
-        av[r] = bv[r] = T(0);
-        gx[r] = gy[r] = gt[r] = T(0);
-        rden[r] = rd[r] = T(0);
-        // neighbours outside the loaded region read the pixel itself (stale halo only)
         const bool has_u = in && y > 0, has_d = in && y < ny - 1;
         const bool has_l = in && x > 0, has_r = in && x < nx - 1;
-        up_in[r] = has_u;
-        dn_in[r] = has_d;
-        if (r == 0) l_up = has_u ? (ry > 0 ? idx - HRW : idx) : HZERO;
-        if (r == HPT - 1) l_dn = has_d ? (ry < HRH - 1 ? idx + HRW : idx) : HZERO;
-        lx[r][0] = has_l ? (rx > 0 ? idx - 1 : idx) : HZERO;
-        lx[r][1] = has_r ? (rx < HRW - 1 ? idx + 1 : idx) : HZERO;
-        if (in) {
-            const int64_t p = (int64_t)y * nx + x;
-            av[r] = sx[p];
-            bv[r] = sx[np + p];
-            gx[r] = Ip[p];
-            gy[r] = Ip[np + p];
-            gt[r] = Ip[2 * np + p];
-            const int d = (int)has_u + (int)has_d + (int)has_l + (int)has_r;
-            rd[r] = T(1) / T(d);
-            rden[r] = T(1) / (gamma * T(d) + gx[r] * gx[r] + gy[r] * gy[r]);
-        }
-        sv[0][0][idx] = av[r];
-        sv[0][1][idx] = bv[r];
+        // neighbours outside the loaded region read the pixel itself (stale halo only)
+        q.load(r, in, Ip, sx, np, (int64_t)y * nx + x, gamma, has_u, has_d, has_l, has_r,
+               has_u ? (ry > 0 ? idx - HRW : idx) : HZERO, has_d ? (ry < HRH - 1 ? idx + HRW : idx) : HZERO,
+               has_l ? (rx > 0 ? idx - 1 : idx) : HZERO, has_r ? (rx < HRW - 1 ? idx + 1 : idx) : HZERO);
+        sv[0][0][idx] = q.av[r];
+        sv[0][1][idx] = q.bv[r];
     }
     if (threadIdx.x < 4) sv[threadIdx.x >> 1][threadIdx.x & 1][HZERO] = T(0);
     __syncthreads();
-    int cur = 0;
-    for (int q = 0; q < nsw; ++q) {
-        const T* cx = sv[cur][0];
-        const T* cy = sv[cur][1];
-        // the LDS neighbours first (all in flight together); a pixel outside the image reads
-        // zeros and has zero weights, so it stays 0 without a branch
-        T la[HPT][2], lb[HPT][2];
-#pragma unroll
-        for (int r = 0; r < HPT; ++r)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                la[r][e] = cx[lx[r][e]];
-                lb[r][e] = cy[lx[r][e]];
-            }
-        const T ua = cx[l_up], ub = cy[l_up], da = cx[l_dn], db = cy[l_dn];
-        T na[HPT], nb[HPT];
-#pragma unroll
-        for (int r = 0; r < HPT; ++r) {
-            // neighbour order: y-1, y+1, x-1, x+1 (a missing one adds 0)
-            T ax = T(0), ay = T(0);
-            ax += r == 0 ? ua : (up_in[r] ? av[r - 1] : T(0));
-            ay += r == 0 ? ub : (up_in[r] ? bv[r - 1] : T(0));
-            ax += r == HPT - 1 ? da : (dn_in[r] ? av[r + 1] : T(0));
-            ay += r == HPT - 1 ? db : (dn_in[r] ? bv[r + 1] : T(0));
-            ax += la[r][0];
-            ay += lb[r][0];
-            ax += la[r][1];
-            ay += lb[r][1];
-            ax *= rd[r];
-            ay *= rd[r];
-            const T k = (gx[r] * ax + gy[r] * ay + gt[r]) * rden[r];
-            na[r] = ax - gx[r] * k;
-            nb[r] = ay - gy[r] * k;
-        }
+    // (the buffer a constant of each call, so that it folds into the LDS instructions' offsets)
+    auto step = [&](auto from) {
+        constexpr int cur = decltype(from)::value;
+        q.sweep(sv[cur][0], sv[cur][1]);
 #pragma unroll
         for (int r = 0; r < HPT; ++r) {
             const int idx = (ry0 + r) * HRW + rx;
-            av[r] = na[r];
-            bv[r] = nb[r];
-            sv[cur ^ 1][0][idx] = na[r];
-            sv[cur ^ 1][1][idx] = nb[r];
+            sv[cur ^ 1][0][idx] = q.av[r];
+            sv[cur ^ 1][1][idx] = q.bv[r];
         }
-        cur ^= 1;
         __syncthreads();
+    };
+    for (int n = 0; n + 1 < nsw; n += 2) {
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
     }
+    if (nsw & 1) step(std::integral_constant<int, 0>{});
     T* o = vout + 2 * f.pair_off;
 #pragma unroll
     for (int r = 0; r < HPT; ++r) {
         const int ry = ry0 + r;
-        if (rx < HS_MAX || rx >= HS_MAX + HTW || ry < HS_MAX || ry >= HS_MAX + HTH || !live[r]) continue;
+        if (rx < HS_MAX || rx >= HS_MAX + HTW || ry < HS_MAX || ry >= HS_MAX + HTH || !q.live[r]) continue;
         const int64_t p = (int64_t)(oy + ry) * nx + x;
-        o[p] = av[r];
-        o[np + p] = bv[r];
+        o[p] = q.av[r];
+        o[np + p] = q.bv[r];
     }
+}
+
+// The sweeps of a small frame without a halo: one workgroup holds a whole pair (a thread a strip of
+// N rows; nx ceil(ny / N) <= HW_THREADS) and runs all sweeps of a call in one launch, in place.
+// The tiled form spends 6.5 to 8 us per launch of 6 sweeps on frames this small, most of it launch,
+// loads and the halo; here a sweep is one round of LDS reads, a few multiply-adds and a barrier.
+// 200 sweeps of 15 pairs, FP32 / FP64: 16 x 16 178 / 252 -> 36 / 45 us, 31 x 33 214 / 277 -> 63 / 84,
+// 45 x 45 211 / 279 -> 109 / 142, 60 x 64 217 / 291 -> 133 / 209; bound by the latency of a sweep on
+// the small frames, by one CU's LDS and vector issue on the large ones.
+static constexpr int HW_THREADS = 1024, HW_SWEEPS = 1024;  // sweeps per launch
+
+template <class T, int N>
+__global__ __launch_bounds__(HW_THREADS) void k_hs_whole(const Tile* __restrict__ pairs,
+                                                         const FrameInfo* __restrict__ fr, const T* __restrict__ I,
+                                                         T* v, T gamma, int nsw) {
+    constexpr int ZERO = HW_THREADS * N;
+    __shared__ T sv[2][2][HW_THREADS * N + 64];  // [buffer][component][pixel], a zero after the pixels
+    const FrameInfo f = fr[pairs[xcd_remap(blockIdx.x, gridDim.x)].frame];
+    const int nx = f.nx, ny = f.ny, tid = (int)threadIdx.x;
+    const int64_t np = (int64_t)nx * ny;
+    T* s = v + 2 * f.pair_off;
+    const T* Ip = I + 3 * f.pair_off;
+    const int x = tid % nx, y0 = N * (tid / nx);
+    HsStrip<T, N> q;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        const int y = y0 + r, idx = y * nx + x;
+        const bool in = y < ny;
+        const bool has_u = in && y > 0, has_d = in && y < ny - 1;
+        const bool has_l = in && x > 0, has_r = in && x < nx - 1;
+        q.load(r, in, Ip, s, np, idx, gamma, has_u, has_d, has_l, has_r, has_u ? idx - nx : ZERO,
+               has_d ? idx + nx : ZERO, has_l ? idx - 1 : ZERO, has_r ? idx + 1 : ZERO);
+        if (in) {
+            sv[0][0][idx] = q.av[r];
+            sv[0][1][idx] = q.bv[r];
+        }
+    }
+    if (tid < 4) sv[tid >> 1][tid & 1][ZERO] = T(0);
+    __syncthreads();
+    auto step = [&](auto from) {
+        constexpr int cur = decltype(from)::value;
+        q.sweep(sv[cur][0], sv[cur][1]);
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+            if (q.live[r]) {
+                const int idx = (y0 + r) * nx + x;
+                sv[cur ^ 1][0][idx] = q.av[r];
+                sv[cur ^ 1][1][idx] = q.bv[r];
+            }
+        __syncthreads();
+    };
+    for (int n = 0; n + 1 < nsw; n += 2) {
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+    }
+    if (nsw & 1) step(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+        if (q.live[r]) {
+            const int64_t p = (int64_t)(y0 + r) * nx + x;
+            s[p] = q.av[r];
+            s[np + p] = q.bv[r];
+        }
 }
 
 // Reverse flow: target q gathers, in raster order of the sources p, every p with
@@ -460,8 +550,43 @@ void launch_of_derivs(Ctx& c, Geom& g, int dt, const void* u, void* I, int dr) {
     });
 }
 
+// Rows per strip of k_hs_whole for a stack, 0 when a frame with a pair is too large for it: the
+// fewest of 1 .. 4 (31 x 33, 15 pairs, 200 FP32 sweeps: 62 us with 1 row, 76 with 2, 89 with 4).  The
+// line is the workgroup's 1024 threads: beyond 4 rows one CU's share of the sweep exceeds what
+// the tiled launches cost (90 x 90 tiled 1.1 us per FP32 sweep, 60 x 64 here 0.75).
+static int hs_whole_rows(const Geom& g, int& threads) {
+    for (int n : {1, 2, 3, 4}) {
+        int64_t most = 0;  // strips of the largest frame
+        for (int q = 0; q < g.n_seq; ++q)
+            if (g.n_t[q] > 1) most = std::max(most, (int64_t)g.nx[q] * ((g.ny[q] + n - 1) / n));
+        threads = (int)((most + 63) / 64 * 64);
+        if (most <= HW_THREADS) return n;
+    }
+    return 0;
+}
+
 int launch_hs_sweeps(Ctx& c, Geom& g, int dt, const void* I, void* v, void* tmp, double gamma, int n_sweeps) {
     if (g.n_pairs == 0 || n_sweeps <= 0) return 0;
+    int threads = 0;
+    if (const int rows = hs_whole_rows(g, threads)) {
+        const TileList& pl = g.tile_list(c.stream, 65535, 65535, true);  // one tile per pair
+        MMOF_CHECK(pl.count == g.n_pairs, MMOF_ERR_SHAPE, "pair list");
+        dispatch(dt, [&](auto z) {
+            using T = decltype(z);
+            auto k = rows == 1   ? k_hs_whole<T, 1>
+                     : rows == 2 ? k_hs_whole<T, 2>
+                     : rows == 3 ? k_hs_whole<T, 3>
+                                 : k_hs_whole<T, 4>;
+            for (int done = 0; done < n_sweeps; done += HW_SWEEPS) {
+                const int q = std::min(HW_SWEEPS, n_sweeps - done);
+                ScopedTime st(&c, "hs_multi", 7.0 * sizeof(T) * g.pair_px, 16.0 * q * g.pair_px);
+                hipLaunchKernelGGL(k, dim3((unsigned)pl.count), dim3(threads), 0, c.stream, pl.buf.as<Tile>(),
+                                   g.dframes(), (const T*)I, (T*)v, (T)gamma, q);
+                MMOF_LAUNCH_CHECK();
+            }
+        });
+        return 0;
+    }
     const TileList& tl = g.tile_list(c.stream, HTW, HTH, true);
     int done = 0, parity = 0;
     dispatch(dt, [&](auto z) {
