@@ -26,8 +26,6 @@ struct RayTile {
     int32_t frame, angle, bin0, pad;
 };
 
-static constexpr int RTW = 16, RTH = 16;  // pixel tiles of the fan-beam transpose
-
 // Per-frame transpose uT[f][x][y] = u[f][y][x] through a 32x33 LDS tile.
 template <class T>
 __global__ __launch_bounds__(256) void k_transpose_frames(const Tile* __restrict__ tiles,
@@ -286,7 +284,7 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
 // each lane's first position in FP64 from its own coordinates, the second 16 cos further.
 // The windows cover the whole tile, also where it overhangs the frame, so every lane's
 // gathers stay inside them; pixels outside the frame are not written.
-static constexpr int ATW = 32, ATH = 16;  // pixel tiles of the transpose (parallel beam)
+static constexpr int ATW = 32, ATH = 16;  // pixel tiles of the transposes (parallel and fan beam)
 static constexpr int AW = 48, AC = 32;
 
 struct AdjAngle {
@@ -428,10 +426,9 @@ void radon_plan_init(Ctx& c, Plan& p, const double* cs) {
                     for (int j0 = 0; j0 < r.n_bins; j0 += 64) rays[gi].push_back(RayTile{(int32_t)fi, k, j0, 0});
                 }
         }
-        // pixel tiles of the transpose: 32 x 16 for the parallel beam, 16 x 16 for the fan beam
-        const int tw = p.kind == 2 ? RTW : ATW, th = p.kind == 2 ? RTH : ATH;
-        for (int y0 = 0; y0 < fr.ny; y0 += th)
-            for (int x0 = 0; x0 < fr.nx; x0 += tw) px.push_back(Tile{(int32_t)fi, y0, x0, 0});
+        // pixel tiles of the transposes
+        for (int y0 = 0; y0 < fr.ny; y0 += ATH)
+            for (int x0 = 0; x0 < fr.nx; x0 += ATW) px.push_back(Tile{(int32_t)fi, y0, x0, 0});
         for (int y0 = 0; y0 < fr.ny; y0 += 32)
             for (int x0 = 0; x0 < fr.nx; x0 += 32) tr.push_back(Tile{(int32_t)fi, y0, x0, 0});
         sino += (int64_t)r.n_ang * r.n_bins;
@@ -464,12 +461,12 @@ void radon_plan_init(Ctx& c, Plan& p, const double* cs) {
 // u_j = (j - (n_d-1)/2) du.  A ray with |d_y| >= |d_x| is sampled on every pixel row at
 // X_c(Y) = S_x + (Y - S_y) d_x / d_y by linear interpolation between the two pixels around
 // it (out-of-frame pixels are 0), each sample weighted by the path length per row
-// |d| / |d_y|; other rays on the columns.  Forward: one lane per ray (four angles x 64 bins
-// per workgroup), column-stepping rays read the transposed frame so that the lanes stay on
-// neighbouring addresses.  Transpose: one lane per pixel; per angle, the rays that can
-// sample the pixel are those whose detector coordinate lies between the projections of its
-// row neighbours (X -+ 1, Y) or of its column neighbours (X, Y -+ 1); each candidate ray's
-// weight on the pixel is recomputed exactly as the forward computes it.
+// |d| / |d_y|; other rays on the columns.  Forward: one lane per ray, column-stepping rays read
+// the transposed frame so that the lanes stay on neighbouring addresses.  Transpose: a lane per
+// pixel or two; per angle, the rays that can sample the pixel are those whose detector
+// coordinate lies between the projections of its row neighbours (X -+ 1, Y) or of its column
+// neighbours (X, Y -+ 1); each candidate ray's weight on the pixel is formed from the same
+// crossing as in the forward.
 
 struct FanGeo {
     double dso, dsd, du;
@@ -518,38 +515,140 @@ __global__ __launch_bounds__(256) void k_fan_rays(const RayTile* __restrict__ ra
     table[f.sino_off + (int64_t)k * f.n_bins + j] = e;
 }
 
-template <class T>
+// G samples of a lane's ray on lines q .. q + G - 1 (q the same for the wave; `line` points to line q
+// of the image): the sample's two neighbours are weighted 1 - f and f.
+// INNER: every lane's samples have both neighbours inside the line.  Otherwise the pair is read at
+// the nearest place inside, and a pixel of it counts where it is within one of the position.
+// FP32: the first position xb in FP64, split into its floor (clamped to just outside the line) and a
+// fraction; line k at fraction + k B in FP32 (error below 1e-6 px for |B| <= 1, k < 8), as in
+// hat_rows3_f32; the pair is one 8-byte load at a 32-bit offset within its line.
+template <bool INNER, int G>
+__device__ __forceinline__ float fan_rows(const float* __restrict__ line, int nline, double xb, double Bs) {
+    const double flb = fmin(fmax(floor(xb), -16.0), (double)nline + 16.0);
+    const float fb = (float)fmin(fmax(xb - flb, -1.0), 2.0);
+    const int ib = (int)flb;
+    const float stepf = (float)Bs;
+    const char* __restrict__ base = reinterpret_cast<const char*>(line);
+    const uint32_t nlineb = (uint32_t)nline * 4u;
+    typedef float F2 __attribute__((ext_vector_type(2), aligned(4)));
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        const float t = fmaf((float)k, stepf, fb);
+        int xr;
+        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(xr) : "v"(t));
+        const float f = __builtin_amdgcn_fractf(t);
+        const char* __restrict__ row = base + (size_t)k * nlineb;
+        if constexpr (INNER) {
+            const F2 v = *reinterpret_cast<const F2*>(row + (uint32_t)((ib + xr) << 2));
+            s0 = fmaf(1.f - f, v.x, s0);
+            s1 = fmaf(f, v.y, s1);
+        } else {
+            const int i = ib + xr, c = min(max(i, 0), nline - 2);
+            const F2 v = *reinterpret_cast<const F2*>(row + (uint32_t)(c << 2));
+            const float d = f + (float)(i - c);
+            const float w0 = 1.f - fabsf(d), w1 = 1.f - fabsf(d - 1.f);
+            s0 = w0 > 0.f ? fmaf(w0, v.x, s0) : s0;
+            s1 = w1 > 0.f ? fmaf(w1, v.y, s1) : s1;
+        }
+    }
+    return s0 + s1;
+}
+template <bool INNER, int G>
+__device__ __forceinline__ double fan_rows(const double* __restrict__ line, int nline, double A, double Bs, int q) {
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        const double pc = fma(Bs, (double)(q + k), A);
+        const double fl = floor(pc), f = pc - fl;
+        const double* __restrict__ row = line + (size_t)k * nline;
+        if constexpr (INNER) {
+            const Pair<double> v = ld2(row + (int)fl);
+            acc += (1.0 - f) * v.a;
+            acc += f * v.b;
+        } else {
+            const int i = (int)fmin(fmax(fl, -2.0), (double)nline + 2.0), c = min(max(i, 0), nline - 2);
+            const Pair<double> v = ld2(row + c);
+            // (one pixel off the pair at most counts: i = c, or i = -1, or i = nline - 1)
+            const double w0 = i == c ? 1.0 - f : (i == c - 1 ? f : 0.0);
+            const double w1 = i == c ? f : (i == c + 1 ? 1.0 - f : 0.0);
+            if (w0 != 0.0) acc += w0 * v.a;
+            if (w1 != 0.0) acc += w1 * v.b;
+        }
+    }
+    return acc;
+}
+
+// A workgroup of 4 waves takes 4 / RSL angles x 64 bins, a ray's lines split over RSL waves (their
+// partial sums added in a fixed order): one lane per ray.  The wave walks the lines together, so that
+// a gather's lanes read one line (with a start of its own per lane a gather touched 24 cache lines,
+// measured 162e6 accesses for 6.7e6 loads); a group of lines takes the unchecked form when the
+// positions of all its rays stay inside, and is skipped when none comes near.  Bound by the cache's
+// accesses (17 per gather: four lanes a cycle) and vector issue.  FP32, 512 x 512 x 16, 90 angles,
+// 725 bins: 474 -> 264 us; 128 x 128 x 16, 30 angles: 45 -> 12 us (the ray split over four waves).
+template <class T, int RSL>
 __global__ __launch_bounds__(256) void k_fan_fwd(const RayTile* __restrict__ rays, const RadonFrame* __restrict__ rf,
                                                  const double4* __restrict__ table, const T* __restrict__ u,
                                                  const T* __restrict__ ut, T* __restrict__ b) {
+    constexpr int G = sizeof(T) == 4 ? 8 : 4;
+    __shared__ T part[4][64];
     const RayTile rt = rays[xcd_remap(blockIdx.x, gridDim.x)];
     const RadonFrame f = rf[rt.frame];
-    const int k = rt.angle + (int)threadIdx.x / 64, j = rt.bin0 + (int)threadIdx.x % 64;
-    if (k >= f.n_ang || j >= f.n_bins) return;
+    const int lane = (int)threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int k = rt.angle + wave / RSL, sl = wave % RSL, j = rt.bin0 + lane;
+    const bool ray = k < f.n_ang && j < f.n_bins;
     const int64_t ri = f.sino_off + (int64_t)k * f.n_bins + j;
-    const double4 e = table[ri];
-    // rows: samples along x of row y; columns: along y of column x (transposed frame)
-    const bool rows = e.w > 0.0;
-    const int nsteps = rows ? f.ny : f.nx, nline = rows ? f.nx : f.ny;
-    const T* img = rows ? u + f.u_off : ut + f.u_off;
+    const double4 e = ray ? table[ri] : make_double4(0.0, 0.0, 0.0, 0.0);
     T acc = T(0);
-    for (int q = 0; q < nsteps; ++q) {
-        const double pc = fma(e.y, (double)q, e.x);
-        const double p0d = floor(pc);
-        if (p0d < -1.0 || p0d > (double)nline) continue;
-        const T fr = (T)(pc - p0d);
-        const int p0 = (int)p0d;
-        const T* line = img + (int64_t)q * nline;
-        if (p0 >= 0 && p0 + 1 < nline) {  // both pixels inside: one 2-element load
-            const Pair<T> pr = ld2(line + p0);
-            acc += (T(1) - fr) * pr.a;
-            acc += fr * pr.b;
-        } else {
-            if (p0 >= 0 && p0 < nline) acc += (T(1) - fr) * line[p0];
-            if (p0 + 1 >= 0 && p0 + 1 < nline) acc += fr * line[p0 + 1];
+    // rows: samples along x of row y; columns: along y of column x (transposed frame).  A wave
+    // whose rays are of both kinds walks both.
+    for (int kind = 0; kind < 2; ++kind) {
+        const bool mine = ray && (e.w > 0.0) == (kind == 0);
+        if (!__any(mine)) continue;
+        const int nsteps = kind == 0 ? f.ny : f.nx, nline = kind == 0 ? f.nx : f.ny;
+        const T* img = (kind == 0 ? u : ut) + f.u_off;
+        const int q_n = ((nsteps + RSL - 1) / RSL + G - 1) / G * G;
+        const int q_hi = min(nsteps, (sl + 1) * q_n);
+        if (mine) {
+            for (int q = sl * q_n; q < q_hi; q += G) {
+                const T* line = img + (int64_t)q * nline;
+                const double xb = fma(e.y, (double)q, e.x);
+                // |B| <= 1: the group's positions stay within G of the first
+                if (!__any(xb > -1.0 - G && xb < (double)(nline + G))) continue;
+                const bool inner = xb >= (double)G && xb < (double)(nline - 1 - G);
+                if constexpr (sizeof(T) == 4) {
+                    if (q + G <= q_hi) {
+                        if (__all(inner)) acc += fan_rows<true, G>(line, nline, xb, e.y);
+                        else acc += fan_rows<false, G>(line, nline, xb, e.y);
+                    } else {
+                        for (int r = q; r < q_hi; ++r, line += nline)
+                            acc += fan_rows<false, 1>(line, nline, fma(e.y, (double)r, e.x), e.y);
+                    }
+                } else {
+                    if (q + G <= q_hi) {
+                        if (__all(inner)) acc += fan_rows<true, G>(line, nline, e.x, e.y, q);
+                        else acc += fan_rows<false, G>(line, nline, e.x, e.y, q);
+                    } else {
+                        for (int r = q; r < q_hi; ++r, line += nline)
+                            acc += fan_rows<false, 1>(line, nline, e.x, e.y, r);
+                    }
+                }
+            }
         }
     }
-    b[ri] = acc * (T)e.z;
+    if constexpr (RSL == 1) {
+        if (ray) b[ri] = acc * (T)e.z;
+    } else {
+        part[wave][lane] = acc;
+        __syncthreads();
+        if (sl == 0 && ray) {
+            T sum = T(0);
+#pragma unroll
+            for (int w = 0; w < RSL; ++w) sum += part[wave + w][lane];
+            b[ri] = sum * (T)e.z;
+        }
+    }
 }
 
 // Detector position (in bin units) of the ray from the source through the point (X, Y); the
@@ -564,137 +663,230 @@ __device__ __forceinline__ double fan_pos_bound(double X, double Y, double c, do
     return g * t * inv + off;
 }
 
-// Detector position in FP32 (bounds only; the caller's margin covers its rounding, the
-// hardware reciprocal's 1 ulp included).
-__device__ __forceinline__ float fan_pos_f32(float t, float den, float g, float off) {
-    return fmaf(g * t, __builtin_amdgcn_rcpf(den), off);
+__device__ __forceinline__ float uniform(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 constexpr int FAC = 16;  // angles per staged chunk of the transpose
-constexpr int FAW = 64;  // staged bins per angle (wider tile windows read the table directly)
+constexpr int FAW = 96;  // staged bins per angle (wider tile windows read the table directly)
 
-// Transpose: one lane per pixel of a 16 x 16 tile.  Per chunk of FAC angles, the bins whose
-// rays can touch the tile (between the projections of the corners of the tile grown by one
-// pixel: the projection is monotone along every line that misses the source, so its extremes
-// over the box are at the corners) are staged in LDS: the line {A, B}, the path length signed
-// by the direction (> 0: rows) and the sinogram value.  Per angle a pixel's candidates lie
-// between the projections of its four neighbours, taken in FP32 with the caller's margin
-// (bins) when FP32_BOUNDS, else in FP64; a window wider than FAW bins reads the table from
-// global memory instead.  Every candidate's weight is the forward's: fma(B, index, A) in FP64.
-template <class T, bool FP32_BOUNDS>
-__global__ __launch_bounds__(256) void k_fan_adj(const Tile* __restrict__ tiles, const RadonFrame* __restrict__ rf,
-                                                 const double2* __restrict__ trig, const double4* __restrict__ table,
-                                                 const T* __restrict__ b, T* __restrict__ u, FanGeo geo,
-                                                 float margin) {
+// What the pixels of a tile share at one angle: the position of a pixel (X, Y) in the staged window
+// is g t / den + off (t = X c + Y s, den = dso - X s + Y c; gc = g c, gs = g s), and the n bins from
+// floor(position - h) + 1 on hold every ray that weighs on it.  The window: cnt bins from j0 on, nray
+// of them on the detector (cnt 0: nothing to add, < 0: not staged).
+struct FanAngle {
+    float c, s, gc, gs, off;  // off includes 1 - h
+    int n, j0, cnt, nray;
+};
+
+// Transpose: a 32 x 16 pixel tile per workgroup, a lane PX = 2 pixels 16 apart in a row (PX = 1: one
+// pixel, twice the lanes, for stacks of too few tiles to fill the chip).  Per chunk of FAC angles, the
+// bins whose rays can touch the tile are staged in LDS as the line {A, B} and the product of path
+// length and sinogram value.  A ray j weighs on a pixel by 1 - |d| with d the distance from the pixel
+// to the ray's crossing of its row (column), where that is positive; it sits at detector position j,
+// and moving the pixel by one along the row (column) moves its own position by at most h (the
+// largest derivative of the position over the tile grown by one pixel), so the rays within h of the
+// pixel's position are the candidates: their number is the same for the whole tile, the loop over
+// them does not diverge, and a candidate that misses the pixel falls out by its weight.  The
+// position only selects candidates: FP32, with the caller's margin in h.  The crossings are the
+// forward's fma(B, index, A) in FP64.  Windows wider than FAW bins, geometries whose FP32 margin
+// would exceed half a bin (fp32 = 0) and angles where the source comes near the tile take the
+// candidates between the FP64 projections of the pixel's four neighbours, from the table.
+// Bound by vector issue: 46 instructions per pixel and angle, about 8 of them per candidate (four
+// projections per pixel and 20 per candidate before).  FP32, 512 x 512 x 16, 90 angles, 725 bins:
+// 1126 -> 595 us; 128 x 128 x 16, 30 angles: 35 -> 29 us.
+template <class T, int PX>
+__global__ __launch_bounds__(512 / PX) void k_fan_adj(const Tile* __restrict__ tiles,
+                                                      const RadonFrame* __restrict__ rf,
+                                                      const double2* __restrict__ trig,
+                                                      const double4* __restrict__ table, const T* __restrict__ b,
+                                                      T* __restrict__ u, FanGeo geo, float margin, int fp32) {
+    constexpr int NT = 512 / PX, TX = ATW / PX;  // threads, lanes per tile row
     __shared__ double2 s_ab[FAC][FAW];
-    __shared__ T s_sb[FAC][FAW][2];  // {signed path length, sinogram value}
-    __shared__ int s_j0[FAC], s_cnt[FAC];
+    __shared__ T s_v[FAC][FAW];
+    __shared__ FanAngle s_ang[FAC];
+    __shared__ int s_ncol[FAC];                  // column rays of the window
+    __shared__ unsigned s_cols[FAC][FAW / 32];   // which they are
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const RadonFrame f = rf[tl.frame];
-    const int x = tl.x0 + (int)threadIdx.x % RTW, y = tl.y0 + (int)threadIdx.x / RTW;
-    const bool inside = x < f.nx && y < f.ny;
+    const int lx = (int)threadIdx.x % TX, y0 = tl.y0 + (int)threadIdx.x / TX;
+    bool in[PX];
+    int xs[PX];
+    double xd[PX];
+    float Xf[PX];
+    T acc[PX];
     const double hx = (f.nx - 1) / 2.0, hy = (f.ny - 1) / 2.0;
-    const double X = x - hx, Y = y - hy, xd = x, yd = y;
+    // pixels beyond the frame compute the nearest one's value and do not store it
+    const int y = min(y0, f.ny - 1);
+    const double yd = (double)y;
+    const float Yf = (float)(y - hy);
+#pragma unroll
+    for (int p = 0; p < PX; ++p) {
+        const int x = tl.x0 + lx + TX * p;
+        in[p] = x < f.nx && y0 < f.ny;
+        xs[p] = min(x, f.nx - 1);
+        xd[p] = (double)xs[p];
+        Xf[p] = (float)(xs[p] - hx);
+        acc[p] = T(0);
+    }
     const int nb = f.n_bins;
     const double gsc = geo.dsd / geo.du, off = (nb - 1) / 2.0;
-    const float Xf = (float)X, Yf = (float)Y, gf = (float)gsc, offf = (float)off, dsof = (float)geo.dso;
-    // the tile grown by one pixel (clipped to the frame first)
-    const double Xa = tl.x0 - hx - 1.0, Xb = min(tl.x0 + RTW, f.nx) - hx, Ya = tl.y0 - hy - 1.0,
-                 Yb = min(tl.y0 + RTH, f.ny) - hy;
-    T acc = T(0);
+    const float dsof = (float)geo.dso;
+    // the tile's pixels, clipped to the frame
+    const double Xa = tl.x0 - hx, Xb = min(tl.x0 + ATW, f.nx) - 1 - hx, Ya = tl.y0 - hy,
+                 Yb = min(tl.y0 + ATH, f.ny) - 1 - hy;
     for (int k0 = 0; k0 < f.n_ang; k0 += FAC) {
         const int nk = min(FAC, f.n_ang - k0);
         __syncthreads();  // the previous chunk is no longer read
-        if (threadIdx.x < nk) {
-            const double2 cs = trig[f.trig_off + k0 + threadIdx.x];
-            const double q0 = fan_pos_bound(Xa, Ya, cs.x, cs.y, geo.dso, gsc, off);
-            const double q1 = fan_pos_bound(Xb, Ya, cs.x, cs.y, geo.dso, gsc, off);
-            const double q2 = fan_pos_bound(Xa, Yb, cs.x, cs.y, geo.dso, gsc, off);
-            const double q3 = fan_pos_bound(Xb, Yb, cs.x, cs.y, geo.dso, gsc, off);
-            const double lo = fmin(fmin(q0, q1), fmin(q2, q3)), hi = fmax(fmax(q0, q1), fmax(q2, q3));
-            const int j0 = (int)fmin(fmax(ceil(lo - 0.05), 0.0), (double)nb);
-            const int j1 = (int)fmax(fmin(floor(hi + 0.05), (double)(nb - 1)), -1.0);
-            const int cnt = max(j1 - j0 + 1, 0);
-            s_j0[threadIdx.x] = j0;
-            s_cnt[threadIdx.x] = cnt <= FAW ? cnt : -1;
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < nk * FAW; i += 256) {
-            const int kk = i / FAW, w = i % FAW;
-            if (w < s_cnt[kk]) {
-                const int64_t ri = f.sino_off + (int64_t)(k0 + kk) * nb + s_j0[kk] + w;
-                const double4 e = table[ri];
-                s_ab[kk][w] = make_double2(e.x, e.y);
-                s_sb[kk][w][0] = e.w > 0.0 ? (T)e.z : -(T)e.z;
-                s_sb[kk][w][1] = b[ri];
+        if (threadIdx.x < 4 * FAC) {
+            // four lanes per angle: one corner each, the extremes over the four
+            const int kk = min((int)threadIdx.x / 4, nk - 1), corner = (int)threadIdx.x % 4;
+            const double2 cs = trig[f.trig_off + k0 + kk];
+            const double X = corner & 1 ? Xb : Xa, Y = corner & 2 ? Yb : Ya;
+            // the corner grown by one pixel
+            const double Xg = corner & 1 ? Xb + 1.0 : Xa - 1.0, Yg = corner & 2 ? Yb + 1.0 : Ya - 1.0;
+            double lo = fan_pos_bound(X, Y, cs.x, cs.y, geo.dso, gsc, off), hi = lo;
+            // derivatives of the position: g (c dso + Y) / den^2 along X, g (s dso - X) / den^2 along Y
+            double den = geo.dso - Xg * cs.y + Yg * cs.x;
+            double mv = fmax(fabs(cs.x * geo.dso + Yg), fabs(cs.y * geo.dso - Xg));
+#pragma unroll
+            for (int o = 1; o < 4; o *= 2) {
+                lo = fmin(lo, __shfl_xor(lo, o));
+                hi = fmax(hi, __shfl_xor(hi, o));
+                den = fmin(den, __shfl_xor(den, o));
+                mv = fmax(mv, __shfl_xor(mv, o));
             }
+            const double h = gsc * mv / (den * den) + (double)margin;
+            FanAngle a{(float)cs.x, (float)cs.y, (float)(gsc * cs.x), (float)(gsc * cs.y), 0.f, 0, 0, -1, 0};
+            if (fp32 && den > 0.0 && h < FAW) {
+                // (FP32 positions reach from lo - margin to hi + margin)
+                a.j0 = (int)fmin(fmax(floor(lo - h - 1.0), -1048576.0), 1048576.0);
+                const double top = fmin(fmax(ceil(hi + h + 1.0), -1048576.0), 1048576.0);
+                a.n = (int)floor(2.0 * h) + 1;
+                a.off = (float)(off - (double)a.j0 - h + 1.0);
+                const double need = top - a.j0 + 1.0 + a.n;
+                if (need <= FAW) {
+                    a.cnt = (int)need;
+                    a.nray = min(a.j0 + a.cnt, nb) - max(a.j0, 0);
+                    if (a.nray <= 0) a.cnt = 0;  // the whole window off the detector
+                }
+            }
+            if (corner == 0 && (int)threadIdx.x / 4 < nk) s_ang[kk] = a;
         }
         __syncthreads();
-        if (!inside) continue;
+        // 32 threads per angle
+        for (int kk = (int)threadIdx.x / 32; kk < nk; kk += NT / 32) {
+            const int cnt = s_ang[kk].cnt, j0 = s_ang[kk].j0;
+            int ncol = 0;
+            for (int w0 = 0; w0 < cnt; w0 += 32) {
+                const int w = w0 + (int)threadIdx.x % 32, j = j0 + w;
+                double2 ab = make_double2(0.0, 0.0);
+                T v = T(0);
+                bool col = false;
+                if (w < cnt && j >= 0 && j < nb) {
+                    const int64_t ri = f.sino_off + (int64_t)(k0 + kk) * nb + j;
+                    const double4 e = table[ri];
+                    ab = make_double2(e.x, e.y);
+                    v = (T)e.z * b[ri];
+                    col = e.w < 0.0;
+                }
+                if (w < cnt) {
+                    s_ab[kk][w] = ab;
+                    s_v[kk][w] = v;
+                }
+                // (the 32 lanes' column rays, from the wave's mask)
+                const unsigned cols = (unsigned)(__ballot(col) >> (threadIdx.x & 32));
+                ncol += __popc(cols);
+                if (threadIdx.x % 32 == 0) s_cols[kk][w0 / 32] = cols;
+            }
+            if (threadIdx.x % 32 == 0) s_ncol[kk] = ncol;
+        }
+        __syncthreads();
         for (int kk = 0; kk < nk; ++kk) {
-            const int cnt = s_cnt[kk];
+            // (uniform: in scalar registers)
+            const FanAngle a = s_ang[kk];
+            const int cnt = __builtin_amdgcn_readfirstlane(a.cnt);
             if (cnt == 0) continue;
-            const int k = k0 + kk;
-            const double2 cs = trig[f.trig_off + k];
-            // candidate bins: ray j lies at detector position j, and it can weigh on the
-            // pixel only strictly between the neighbours' projections (clamped to the
-            // detector, and to the staged window, before the conversion to int)
-            int jlo, jhi;
-            if (FP32_BOUNDS) {
-                const float c = (float)cs.x, sn = (float)cs.y;
-                const float t0 = fmaf(Xf, c, Yf * sn), d0 = dsof - Xf * sn + Yf * c;
-                const float p0 = fan_pos_f32(t0 - c, d0 + sn, gf, offf), p1 = fan_pos_f32(t0 + c, d0 - sn, gf, offf);
-                const float p2 = fan_pos_f32(t0 - sn, d0 - c, gf, offf), p3 = fan_pos_f32(t0 + sn, d0 + c, gf, offf);
-                const float lo = fminf(fminf(p0, p1), fminf(p2, p3)) - margin;
-                const float hi = fmaxf(fmaxf(p0, p1), fmaxf(p2, p3)) + margin;
-                jlo = (int)fminf(fmaxf(ceilf(lo), 0.0f), (float)nb);
-                jhi = (int)fmaxf(fminf(floorf(hi), (float)(nb - 1)), -1.0f);
-            } else {
-                const double p0 = fan_pos_bound(X - 1.0, Y, cs.x, cs.y, geo.dso, gsc, off);
-                const double p1 = fan_pos_bound(X + 1.0, Y, cs.x, cs.y, geo.dso, gsc, off);
-                const double p2 = fan_pos_bound(X, Y - 1.0, cs.x, cs.y, geo.dso, gsc, off);
-                const double p3 = fan_pos_bound(X, Y + 1.0, cs.x, cs.y, geo.dso, gsc, off);
-                const double lo = fmin(fmin(p0, p1), fmin(p2, p3)) - 0.05;
-                const double hi = fmax(fmax(p0, p1), fmax(p2, p3)) + 0.05;
-                jlo = (int)fmin(fmax(ceil(lo), 0.0), (double)nb);
-                jhi = (int)fmax(fmin(floor(hi), (double)(nb - 1)), -1.0);
-            }
             if (cnt > 0) {
-                const int j0 = s_j0[kk];
-                jlo = max(jlo, j0);
-                jhi = min(jhi, j0 + cnt - 1);
-                for (int j = jlo; j <= jhi; ++j) {
-                    const double2 ab = s_ab[kk][j - j0];
-                    const T sp = s_sb[kk][j - j0][0], bv = s_sb[kk][j - j0][1];
-                    const bool rows = sp > T(0);
-                    const double pc = fma(ab.y, rows ? yd : xd, ab.x);
-                    const double p0d = floor(pc);
-                    const T fr = (T)(pc - p0d);
-                    // the pixel is the sample's left (dl = 0) or right (dl = 1) neighbour, or
-                    // untouched (exact: small integers)
-                    const double dl = (rows ? xd : yd) - p0d;
-                    const T w = dl == 0.0 ? T(1) - fr : (dl == 1.0 ? fr : T(0));
-                    const T term = (w * (rows ? sp : -sp)) * bv;
-                    acc = w != T(0) ? acc + term : acc;
+                const int n = __builtin_amdgcn_readfirstlane(a.n), ncol = __builtin_amdgcn_readfirstlane(s_ncol[kk]);
+                const int nray = __builtin_amdgcn_readfirstlane(a.nray);
+                const float ac = uniform(a.c), as = uniform(a.s), agc = uniform(a.gc), ags = uniform(a.gs);
+                const float aoff = uniform(a.off);
+                const double2* l[PX];
+                const T* v[PX];
+                const float ys = Yf * ags, yc = fmaf(Yf, ac, dsof);
+#pragma unroll
+                for (int p = 0; p < PX; ++p) {
+                    const float gt = fmaf(Xf[p], agc, ys), den = fmaf(-Xf[p], as, yc);
+                    const float pos = fmaf(gt, __builtin_amdgcn_rcpf(den), aoff);
+                    int i;
+                    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(pos));
+                    // (inside the window by construction; the clamp keeps every access there)
+                    i = min(max(i, 0), cnt - n);
+                    l[p] = s_ab[kk] + i;
+                    v[p] = s_v[kk] + i;
+                }
+                // candidate q of every pixel: its distance from the crossing of its row (column)
+                auto cand = [&](int q, bool rows) {
+#pragma unroll
+                    for (int p = 0; p < PX; ++p) {
+                        const double2 e = l[p][q];
+                        const double own = rows ? xd[p] : yd, oth = rows ? yd : xd[p];
+                        const T w = T(1) - fabs((T)(own - fma(e.y, oth, e.x)));
+                        const T next = fma(w, v[p][q], acc[p]);
+                        acc[p] = w > T(0) ? next : acc[p];
+                    }
+                };
+                if (ncol == 0) {
+                    cand(0, true);
+                    if (n > 1) cand(1, true);
+                    for (int q = 2; q < n; ++q) cand(q, true);
+                } else if (ncol == nray) {
+                    cand(0, false);
+                    if (n > 1) cand(1, false);
+                    for (int q = 2; q < n; ++q) cand(q, false);
+                } else {
+#pragma unroll
+                    for (int p = 0; p < PX; ++p) {
+                        const int i0 = (int)(v[p] - s_v[kk]);
+                        for (int q = 0; q < n; ++q) {
+                            const double2 e = l[p][q];
+                            const bool col = (s_cols[kk][(i0 + q) >> 5] >> ((i0 + q) & 31)) & 1u;
+                            const double own = col ? yd : xd[p], oth = col ? xd[p] : yd;
+                            const T w = T(1) - fabs((T)(own - fma(e.y, oth, e.x)));
+                            const T next = fma(w, v[p][q], acc[p]);
+                            acc[p] = w > T(0) ? next : acc[p];
+                        }
+                    }
                 }
             } else {
+                const int k = k0 + kk;
+                const double2 cs = trig[f.trig_off + k];
                 const int64_t row = f.sino_off + (int64_t)k * nb;
-                for (int j = jlo; j <= jhi; ++j) {
-                    const double4 e = table[row + j];
-                    const bool rows = e.w > 0.0;
-                    const double pc = fma(e.y, rows ? (double)y : (double)x, e.x);
-                    const double p0d = floor(pc);
-                    const T fr = (T)(pc - p0d);
-                    const double own = rows ? (double)x : (double)y;
-                    T w = T(0);
-                    if (p0d == own) w = T(1) - fr;
-                    else if (p0d + 1.0 == own) w = fr;
-                    if (w != T(0)) acc += (w * (T)e.z) * b[row + j];
+                for (int p = 0; p < PX; ++p) {
+                    const double X = xs[p] - hx, Y = y - hy;
+                    const double p0 = fan_pos_bound(X - 1.0, Y, cs.x, cs.y, geo.dso, gsc, off);
+                    const double p1 = fan_pos_bound(X + 1.0, Y, cs.x, cs.y, geo.dso, gsc, off);
+                    const double p2 = fan_pos_bound(X, Y - 1.0, cs.x, cs.y, geo.dso, gsc, off);
+                    const double p3 = fan_pos_bound(X, Y + 1.0, cs.x, cs.y, geo.dso, gsc, off);
+                    const double lo = fmin(fmin(p0, p1), fmin(p2, p3)) - 0.05;
+                    const double hi = fmax(fmax(p0, p1), fmax(p2, p3)) + 0.05;
+                    const int jlo = (int)fmin(fmax(ceil(lo), 0.0), (double)nb);
+                    const int jhi = (int)fmax(fmin(floor(hi), (double)(nb - 1)), -1.0);
+                    for (int j = jlo; j <= jhi; ++j) {
+                        const double4 e = table[row + j];
+                        const bool rows = e.w > 0.0;
+                        const double own = rows ? xd[p] : yd, oth = rows ? yd : xd[p];
+                        const T w = T(1) - fabs((T)(own - fma(e.y, oth, e.x)));
+                        if (w > T(0)) acc[p] = fma(w, (T)e.z * b[row + j], acc[p]);
+                    }
                 }
             }
         }
     }
-    if (inside) u[f.u_off + (int64_t)y * f.nx + x] = acc;
+#pragma unroll
+    for (int p = 0; p < PX; ++p)
+        if (in[p]) u[f.u_off + (int64_t)y * f.nx + xs[p]] = acc[p];
 }
 
 void fan_plan_init(Ctx& c, Plan& p) {
@@ -726,9 +918,13 @@ void launch_fan_fwd(Ctx& c, Plan& p, int dt, const void* u, void* b) {
         T* ut = static_cast<T*>(c.work("radon_transpose", sizeof(T) * p.n));
         launch_transpose<T>(c, p, (const T*)u, ut);
         ScopedTime st(&c, "fan_fwd", (double)sizeof(T) * (p.n + p.m), 0.0);
-        hipLaunchKernelGGL(k_fan_fwd<T>, dim3((unsigned)p.n_rays[2]), dim3(256), 0, c.stream,
-                           p.d_rays[2].as<RayTile>(), p.d_rinfo.as<RadonFrame>(), p.d_fanrays.as<double4>(),
-                           (const T*)u, (const T*)ut, (T*)b);
+        // the fewest waves per ray that fill the chip twice (2 x 256 CUs x 32 waves), at most 4:
+        // 10 frames of 28 x 36, 46 angles, 17 us with one and 4.4 with four
+        const int64_t waves = 4 * p.n_rays[2], full = 2 * 256 * 32;
+        const int gi = waves >= full ? 2 : 2 * waves >= full ? 1 : 0;  // angles per workgroup: 4, 2, 1
+        auto k = gi == 2 ? k_fan_fwd<T, 1> : gi == 1 ? k_fan_fwd<T, 2> : k_fan_fwd<T, 4>;
+        hipLaunchKernelGGL(k, dim3((unsigned)p.n_rays[gi]), dim3(256), 0, c.stream, p.d_rays[gi].as<RayTile>(),
+                           p.d_rinfo.as<RadonFrame>(), p.d_fanrays.as<double4>(), (const T*)u, (const T*)ut, (T*)b);
         MMOF_LAUNCH_CHECK();
     });
 }
@@ -762,10 +958,13 @@ void launch_fan_adj(Ctx& c, Plan& p, int dt, const void* b, void* u) {
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
         ScopedTime st(&c, "fan_adj", (double)sizeof(T) * (p.n + p.m), 0.0);
-        auto kern = fp32 ? k_fan_adj<T, true> : k_fan_adj<T, false>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)p.n_tiles_a), dim3(256), 0, c.stream, p.d_tiles_a.as<Tile>(),
+        // with less than two tiles per CU a lane takes one pixel: a wave then has half the chain
+        // (10 frames of 28 x 36, 46 angles: 39 us, 66 with two pixels)
+        const bool one = p.n_tiles_a < 2 * 256;
+        auto k = one ? k_fan_adj<T, 1> : k_fan_adj<T, 2>;
+        hipLaunchKernelGGL(k, dim3((unsigned)p.n_tiles_a), dim3(one ? 512 : 256), 0, c.stream, p.d_tiles_a.as<Tile>(),
                            p.d_rinfo.as<RadonFrame>(), p.d_trig.as<double2>(), p.d_fanrays.as<double4>(),
-                           (const T*)b, (T*)u, geo, margin);
+                           (const T*)b, (T*)u, geo, margin, (int)fp32);
         MMOF_LAUNCH_CHECK();
     });
 }
