@@ -82,98 +82,116 @@ __global__ __launch_bounds__(256) void k_transpose_frames4(const Tile* __restric
     }
 }
 
-// Sum over the (at most three) pixels of one row (the row starting at offset roff of the
-// frame img) with non-zero hat weight for a ray whose centre crosses the row at xs: weights 1 - |a| |x - xs| with |a| >= 1/sqrt(2), so the
-// pixels are floor(xs) - 1 .. floor(xs) + 1 when the fraction is below 1/2, else
-// floor(xs) .. floor(xs) + 2.
-template <class T>
-__device__ __forceinline__ T hat_row(const T* __restrict__ img, int roff, int ncol, double xs, T aa) {
-    const double fl = floor(xs);
-    const int xi = (int)fl;
-    const T fr = (T)(xs - fl);
-    const int k0 = fr < T(0.5) ? -1 : 0;
-    T acc = T(0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int x = xi + k0 + k;
-        const T w = T(1) - aa * fabs(T(k0 + k) - fr);
-        if (x >= 0 && x < ncol && w > T(0)) acc += w * img[(uint32_t)(roff + x)];
-    }
-    return acc;
-}
-
-// The same sum for a row where all three candidates lie inside the row (xs in [1, ncol - 2)):
-// pixels floor(xs) and floor(xs) + 1 with weights 1 - |a| f and 1 - |a| (1 - f), and the
-// outer neighbour on the nearer side with weight max(0, 1 - |a| (1 + min(f, 1 - f))).
-template <class T>
-__device__ __forceinline__ T hat_row_inner(const T* __restrict__ img, int roff, int ncol, double xs, T aa) {
-    // xs >= 1: truncation is the floor; the clamp keeps every access inside the row even if
-    // rounding puts xs a hair outside the interior (the weights then still match xs)
-    const int xi = min(max((int)xs, 1), ncol - 3);
-    const T fr = (T)(xs - (double)xi);
-    const bool lo = fr < T(0.5);
-    const T w0 = T(1) - aa * fr;
-    const T w1 = T(1) - aa * (T(1) - fr);
-    const T w2 = fmax(T(1) - aa * (T(1) + (lo ? fr : T(1) - fr)), T(0));
-    // the four pixels xi - 1 .. xi + 2 (all inside the row) as one 4-element load
-    typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
-    const V4 q = *reinterpret_cast<const V4*>(img + (uint32_t)(roff + xi - 1));
-    return w0 * q.y + w1 * q.z + w2 * (lo ? q.x : q.w);
-}
-
-// Interior rows of an FP32 image in groups of G, three taps centred on the nearest pixel: with
-// n = round(xs) and d = xs - n in [-1/2, 1/2], the pixels n - 1, n, n + 1 have the weights
-// max(0, 1 - |a| (1 + d)), 1 - |a| |d| and max(0, 1 - |a| (1 - d)), and no other pixel is
-// within 1/|a| <= sqrt(2) of xs; the products are added to three running sums s0..s2 (one per
-// tap).  The group's first row: xs + 1/2 (xs0h: xs0 + 1/2) in FP64, split into its floor
-// and an FP32 fraction fb; row k at t = fb + k step in FP32 (error below 1e-6 px for
-// |step| <= 1, k < 8), n = floor(t) + that floor through a floor-convert, f = fract(t) = d + 1/2.
-// The three pixels come in one 12-byte load at a 32-bit byte offset (so the frame must hold
-// fewer than 2^30 pixels) from a per-row base that is the same for the whole wave; the outer
-// weights (1 - |a|/2) - |a| f and (1 - 3|a|/2) + |a| f are single FMAs clamped to [0, 1] by the
-// FMA's output clamp.  The caller guarantees 1/2 + INTERIOR_MARGIN <= xs < ncol - 3/2 -
-// INTERIOR_MARGIN on every row it passes, so the FP32 position never leaves the row.
-static constexpr int RG = 8;
+// G rows of a ray whose centre crosses row q (`line`: its first pixel) at xb and moves by step per row:
+// with n = round(xs) and d = xs - n in [-1/2, 1/2], the pixels n - 1, n, n + 1 have the weights
+// max(0, 1 - |a| (1 + d)), 1 - |a| |d| and max(0, 1 - |a| (1 - d)), and no other pixel is within
+// 1/|a| <= sqrt(2) of xs.
+// INNER: all three are inside the line on every row.  Otherwise the three are read at the nearest
+// place inside (lines of at least 3 pixels) and weigh by their own distance.
+// FP32: xb + 1/2 (FP64) is split into its floor and a fraction fb; row k at t = fb + k step in FP32
+// (error below 1e-6 px for |step| <= 1, k < 8), n = floor(t) + that floor through a floor-convert,
+// f = fract(t) = d + 1/2.  The three pixels come in one 12-byte load at a 32-bit offset from a base
+// that is the same for the whole wave, and the outer weights (1 - |a|/2) - |a| f and (1 - 3|a|/2) +
+// |a| f are single FMAs clamped to [0, 1] by the FMA's output clamp.
 static constexpr double INTERIOR_MARGIN = 1e-3;
 
-template <int G>
-__device__ __forceinline__ void hat_rows3_f32(const char* __restrict__ base, int r, int ncol, double xs0h,
-                                              double step, float aa, float& s0, float& s1, float& s2) {
-    const double xb = fma((double)r, step, xs0h);
-    const double flb = floor(xb);
-    const float fb = (float)(xb - flb);
+template <bool INNER, int G>
+__device__ __forceinline__ float hat_rows(const float* __restrict__ line, int ncol, double xb, double step, float aa) {
+    const double xh = xb + 0.5;
+    const double flb = INNER ? floor(xh) : fmin(fmax(floor(xh), -16.0), (double)ncol + 16.0);
+    const float fb = INNER ? (float)(xh - flb) : (float)fmin(fmax(xh - flb, -1.0), 2.0);
+    const int ib = (int)flb - 1;
     const float stepf = (float)step;
     const float cm = 1.f - 0.5f * aa, cp = 1.f - 1.5f * aa;
-    // the group's byte offset, formed once (kept opaque so that each row adds only its own
-    // pixel offset to it)
-    uint32_t rowb;
-    asm("v_mov_b32 %0, %1" : "=v"(rowb) : "v"((uint32_t)(r * ncol + (int)flb - 1) * 4u));
+    const char* __restrict__ base = reinterpret_cast<const char*>(line);
     const uint32_t ncolb = (uint32_t)ncol * 4u;
     typedef float F3 __attribute__((ext_vector_type(3), aligned(4)));
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const float t = fmaf((float)k, stepf, fb);
         int xr;
         asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(xr) : "v"(t));
         const float f = __builtin_amdgcn_fractf(t);
-        const char* __restrict__ rowk = base + (size_t)k * ncolb;
-        const F3 q = *reinterpret_cast<const F3*>(rowk + (rowb + ((uint32_t)xr << 2)));
-        s0 = fmaf(__builtin_amdgcn_fmed3f(fmaf(-aa, f, cm), 0.f, 1.f), q.x, s0);
-        s1 = fmaf(fmaf(-aa, fabsf(f - 0.5f), 1.f), q.y, s1);
-        s2 = fmaf(__builtin_amdgcn_fmed3f(fmaf(aa, f, cp), 0.f, 1.f), q.z, s2);
+        const char* __restrict__ row = base + (size_t)k * ncolb;
+        if constexpr (INNER) {
+            const F3 q = *reinterpret_cast<const F3*>(row + (uint32_t)((ib + xr) << 2));
+            s0 = fmaf(__builtin_amdgcn_fmed3f(fmaf(-aa, f, cm), 0.f, 1.f), q.x, s0);
+            s1 = fmaf(fmaf(-aa, fabsf(f - 0.5f), 1.f), q.y, s1);
+            s2 = fmaf(__builtin_amdgcn_fmed3f(fmaf(aa, f, cp), 0.f, 1.f), q.z, s2);
+        } else {
+            const int i = ib + xr, c = min(max(i, 0), ncol - 3);
+            const F3 q = *reinterpret_cast<const F3*>(row + (uint32_t)(c << 2));
+            const float x = (f + 0.5f) + (float)(i - c);  // the centre, from pixel c
+            const float w0 = fmaf(-aa, fabsf(x), 1.f), w1 = fmaf(-aa, fabsf(x - 1.f), 1.f),
+                        w2 = fmaf(-aa, fabsf(x - 2.f), 1.f);
+            s0 = w0 > 0.f ? fmaf(w0, q.x, s0) : s0;
+            s1 = w1 > 0.f ? fmaf(w1, q.y, s1) : s1;
+            s2 = w2 > 0.f ? fmaf(w2, q.z, s2) : s2;
+        }
     }
+    return (s0 + s2) + s1;
+}
+template <bool INNER, int G>
+__device__ __forceinline__ double hat_rows(const double* __restrict__ line, int ncol, double xb, double step,
+                                           double aa) {
+    typedef double D2 __attribute__((ext_vector_type(2), aligned(8)));
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    const double c0 = 1.0 - aa;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        const double xs = fma((double)k, step, xb);
+        const double n = rint(xs);
+        const double* __restrict__ row = line + (size_t)k * ncol;
+        if constexpr (INNER) {
+            const double d = xs - n;
+            const double* __restrict__ p = row + ((int)n - 1);
+            const D2 q = *reinterpret_cast<const D2*>(p);
+            const double q2 = p[2];
+            s0 = fma(fmax(fma(-aa, d, c0), 0.0), q.x, s0);
+            s1 = fma(fma(-aa, fabs(d), 1.0), q.y, s1);
+            s2 = fma(fmax(fma(aa, d, c0), 0.0), q2, s2);
+        } else {
+            const int i = (int)fmin(fmax(n, -3.0), (double)ncol + 3.0) - 1, c = min(max(i, 0), ncol - 3);
+            const double x = xs - (double)c;
+            const D2 q = *reinterpret_cast<const D2*>(row + c);
+            const double q2 = row[c + 2];
+            const double w0 = fma(-aa, fabs(x), 1.0), w1 = fma(-aa, fabs(x - 1.0), 1.0),
+                         w2 = fma(-aa, fabs(x - 2.0), 1.0);
+            s0 = w0 > 0.0 ? fma(w0, q.x, s0) : s0;
+            s1 = w1 > 0.0 ? fma(w1, q.y, s1) : s1;
+            s2 = w2 > 0.0 ? fma(w2, q2, s2) : s2;
+        }
+    }
+    return (s0 + s2) + s1;
+}
+// One row of two pixels (frames too narrow for the three-pixel form).
+template <class T>
+__device__ __forceinline__ T hat_row2(const T* __restrict__ line, double xs, T aa) {
+    T acc = T(0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const T w = T(1) - aa * (T)fabs((double)x - xs);
+        if (w > T(0)) acc += w * line[x];
+    }
+    return acc;
 }
 
-// One workgroup of 8 waves per (frame, ANG consecutive angles, 64 bins): lane = bin, wave
-// w takes angle w / (8/ANG) and the (w % (8/ANG))-th block of rows, walking four rows per
-// step (FP32 images: eight, see hat_rows_f32) so that their loads are in flight together.
-// The waves of one workgroup read overlapping spans of the same rows, so a wider angle group
-// reuses the image through the cache; partial sums are added in a fixed order.
+// One workgroup of 8 waves per (frame, ANG consecutive angles, 64 bins): lane = bin, wave w takes
+// angle w / (8/ANG) and the (w % (8/ANG))-th block of rows, partial sums added in a fixed order.  The
+// wave walks its rows together in groups of G, so that a gather's lanes read one row; lanes whose ray
+// misses the frame on the whole group sit it out, and the others take the unchecked form when all of
+// them stay inside.  Bound by the cache's accesses (16 to 18 per gather: four lanes a cycle) and vector
+// issue (12.5 instructions per ray and row).  Measured against waves whose lanes started at rows of
+// their own and, on blocks of less than 48 rows, checked every pixel: FP32 128 x 128 x 16, 30 angles
+// 24 -> 11 us, 256 x 256 x 16 63 -> 28 us, 1024 x 1024 x 64, 90 angles 2.99 -> 2.64 ms; FP64 251 x 310 x
+// 16, 45 angles 137 -> 87 us, 1024 x 1024 x 16, 90 angles 1.60 -> 1.49 ms.
 template <class T, int ANG>
 __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ rays, const RadonFrame* __restrict__ rf,
                                                    const double2* __restrict__ trig, const T* __restrict__ u,
                                                    const T* __restrict__ ut, T* __restrict__ b) {
     constexpr int RSL = 8 / ANG;
+    constexpr int G = sizeof(T) == 4 ? 8 : 4;
     __shared__ T part[8][64];
     const RayTile rt = rays[xcd_remap(blockIdx.x, gridDim.x)];
     const RadonFrame f = rf[rt.frame];
@@ -181,11 +199,6 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: angle, image in SGPRs)
     const int ang = rt.angle + wave / RSL, sl = wave % RSL;
     const int j = rt.bin0 + lane;
-    // FP32 interior rows by hat_rows3_f32 (32-bit byte offsets within the frame); FP64 rows by
-    // hat_row_inner (a three-tap FP64 form with one 16-byte and one 8-byte load per row measured
-    // slower: the row's two load instructions bound either form)
-    const bool rows3 = sizeof(T) == 4 && (int64_t)f.ny * f.nx < ((int64_t)1 << 30);
-    const double margin = rows3 ? INTERIOR_MARGIN : 0.0;
     T acc = T(0);
     if (ang < f.n_ang && j < f.n_bins) {
         const double2 cs = trig[f.trig_off + ang];
@@ -202,64 +215,32 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
         // ray centre in row r: xs(r) = ccol + (dj - (r - crow) bb) / a
         const double xs0 = ccol + (dj + crow * bb) / a;
         const double step = -bb / a;
-        const double inv_step = 1.0 / step;  // inf for step 0 (that case is handled apart)
         const T aa = (T)fabs(a);
-        const int q = (nrow + RSL - 1) / RSL;
-        int r_lo = sl * q, r_hi = min(nrow, r_lo + q);
-        // rows where the ray can touch the image (xs in (-1.5, ncol + 0.5)), and among them
-        // the rows where every candidate is inside (xs in [1, ncol - 2)), from xs linear in r
-        auto row_of = [&](double x) { return (x - xs0) * inv_step; };
-        int in_lo = r_lo, in_hi = r_lo;  // [in_lo, in_hi): interior rows
-        // the interior of the three-tap rows, or of hat_row_inner
-        const double x_in_lo = rows3 ? 0.5 + margin : 1.0;
-        const double x_in_hi = rows3 ? (double)ncol - 1.5 - margin : (double)ncol - 2.0;
-        // (bounds are clamped to [0, nrow] in double before the conversion, so near-axis
-        // angles, whose tiny slope puts the crossings far away, give in-range integers)
-        const double dn = (double)nrow;
-        auto clamp_row = [&](double x) { return (int)fmin(fmax(x, 0.0), dn); };
-        if (r_hi - r_lo < 48) {
-            // short row blocks: the bookkeeping below would cost more than it saves
-        } else if (step != 0.0) {
-            const double ra = row_of(-1.5), rb = row_of((double)ncol + 0.5);
-            const double t_lo = fmin(ra, rb), t_hi = fmax(ra, rb);
-            r_lo = max(r_lo, clamp_row(floor(t_lo) - 1.0));
-            r_hi = min(r_hi, clamp_row(ceil(t_hi) + 2.0));
-            const double ia = row_of(x_in_lo), ib = row_of(x_in_hi);
-            in_lo = max(r_lo, clamp_row(ceil(fmin(ia, ib)) + 1.0));
-            in_hi = min(r_hi, clamp_row(floor(fmax(ia, ib)) - 1.0));
-        } else if (xs0 >= x_in_lo && xs0 < x_in_hi) {
-            in_lo = r_lo;
-            in_hi = r_hi;
+        const double x_in_lo = 0.5 + INTERIOR_MARGIN, x_in_hi = (double)ncol - 1.5 - INTERIOR_MARGIN;
+        const int q_n = ((nrow + RSL - 1) / RSL + G - 1) / G * G;
+        const int q_hi = min(nrow, (sl + 1) * q_n);
+        int q = sl * q_n;
+        if (ncol < 3) {
+            for (; q < q_hi; ++q) acc += hat_row2(img + (int64_t)q * ncol, fma((double)q, step, xs0), aa);
         }
-        if (in_hi < in_lo || ncol < 4) in_hi = in_lo = r_lo;  // no interior (also for rows shorter than 4)
-        int r = r_lo;
-        for (; r < min(in_lo, r_hi); ++r) acc += hat_row(img, r * ncol, ncol, fma((double)r, step, xs0), aa);
-        if constexpr (sizeof(T) == 4) {
-            if (rows3) {
-                const char* __restrict__ base = reinterpret_cast<const char*>(img);
-                const double xs0h = xs0 + 0.5;
-                float s0 = 0.f, s1 = 0.f, s2 = 0.f;
-                for (; r < in_hi - (RG - 1); r += RG) hat_rows3_f32<RG>(base, r, ncol, xs0h, step, aa, s0, s1, s2);
-                for (; r < in_hi; ++r) hat_rows3_f32<1>(base, r, ncol, xs0h, step, aa, s0, s1, s2);
-                acc += (s0 + s2) + s1;
+        for (; q < q_hi; q += G) {
+            const T* line = img + (int64_t)q * ncol;
+            const double xb = fma((double)q, step, xs0), xe = fma((double)(G - 1), step, xb);
+            const double lo = fmin(xb, xe), hi = fmax(xb, xe);
+            // (a ray weighs on pixels within sqrt(2) of its centre)
+            const bool near = hi > -1.5 && lo < (double)ncol + 0.5;
+            if (!__any(near)) continue;
+            if (q + G <= q_hi) {
+                const bool inner = __all(!near || (lo >= x_in_lo && hi < x_in_hi));
+                if (near) {
+                    if (inner) acc += hat_rows<true, G>(line, ncol, xb, step, aa);
+                    else acc += hat_rows<false, G>(line, ncol, xb, step, aa);
+                }
+            } else {
+                for (int r = q; r < q_hi; ++r, line += ncol)
+                    acc += hat_rows<false, 1>(line, ncol, fma((double)r, step, xs0), step, aa);
             }
         }
-        for (; r < in_hi - 3; r += 4) {
-            const T a0 = hat_row_inner(img, r * ncol, ncol, fma((double)r, step, xs0), aa);
-            const T a1 = hat_row_inner(img, (r + 1) * ncol, ncol, fma((double)(r + 1), step, xs0), aa);
-            const T a2 = hat_row_inner(img, (r + 2) * ncol, ncol, fma((double)(r + 2), step, xs0), aa);
-            const T a3 = hat_row_inner(img, (r + 3) * ncol, ncol, fma((double)(r + 3), step, xs0), aa);
-            acc += (a0 + a1) + (a2 + a3);
-        }
-        for (; r < in_hi; ++r) acc += hat_row_inner(img, r * ncol, ncol, fma((double)r, step, xs0), aa);
-        for (; r < r_hi - 3; r += 4) {
-            const T a0 = hat_row(img, r * ncol, ncol, fma((double)r, step, xs0), aa);
-            const T a1 = hat_row(img, (r + 1) * ncol, ncol, fma((double)(r + 1), step, xs0), aa);
-            const T a2 = hat_row(img, (r + 2) * ncol, ncol, fma((double)(r + 2), step, xs0), aa);
-            const T a3 = hat_row(img, (r + 3) * ncol, ncol, fma((double)(r + 3), step, xs0), aa);
-            acc += (a0 + a1) + (a2 + a3);
-        }
-        for (; r < r_hi; ++r) acc += hat_row(img, r * ncol, ncol, fma((double)r, step, xs0), aa);
     }
     part[wave][lane] = acc;
     __syncthreads();
@@ -521,7 +502,7 @@ __global__ __launch_bounds__(256) void k_fan_rays(const RayTile* __restrict__ ra
 // the nearest place inside, and a pixel of it counts where it is within one of the position.
 // FP32: the first position xb in FP64, split into its floor (clamped to just outside the line) and a
 // fraction; line k at fraction + k B in FP32 (error below 1e-6 px for |B| <= 1, k < 8), as in
-// hat_rows3_f32; the pair is one 8-byte load at a 32-bit offset within its line.
+// hat_rows; the pair is one 8-byte load at a 32-bit offset within its line.
 template <bool INNER, int G>
 __device__ __forceinline__ float fan_rows(const float* __restrict__ line, int nline, double xb, double Bs) {
     const double flb = fmin(fmax(floor(xb), -16.0), (double)nline + 16.0);
@@ -974,8 +955,9 @@ const int kRadonCandidates = 4;  // angle groups of 1, 2, 4, 8 per workgroup
 int radon_fwd_choice(Plan& p, int dt) {
     auto it = p.geom->tuned.find(std::string("radon_fwd") + (dt == MMOF_F32 ? "/f32" : "/f64"));
     if (it != p.geom->tuned.end()) return it->second;
-    // untuned: one angle per workgroup (more workgroups) on large frames, pairs on small ones
-    return p.geom->max_ny >= 512 ? 0 : 1;
+    // untuned: one angle per workgroup, the best or within 2% of it from 32 x 32 to 1024 x 1024 (16
+    // frames of 256 x 256, 30 angles: 28 us, with 2, 4, 8 angles 32, 33, 42)
+    return 0;
 }
 
 void launch_radon_fwd(Ctx& c, Plan& p, int dt, const void* u, void* b, int choice) {
