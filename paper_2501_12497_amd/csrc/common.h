@@ -143,6 +143,9 @@ struct Geom {
     bool same_as(const mmof_stack& s) const;
     const TileList& tile_list(hipStream_t st, int tw, int th, bool pairs);
     const TileList& adj_tile_list(hipStream_t st, int tw, int th);
+    // chunks of `per` consecutive quads (4 pixels of a row, fewer at its end) of every frame: the
+    // first quad in Tile::x0
+    const TileList& quad_list(hipStream_t st, int per);
     const FrameInfo* dframes() const { return d_frames.as<FrameInfo>(); }
 };
 

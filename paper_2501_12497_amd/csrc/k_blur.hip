@@ -51,77 +51,101 @@ __global__ __launch_bounds__(256) void k_blur(const Tile* __restrict__ tiles, in
     }
 }
 
-// The same sums with the radius R compiled in (the 9-tap case): both passes are unrolled and
-// a thread forms 4 outputs from one register copy of the 4 + 2R inputs they share (a row
-// segment in the horizontal pass, a column segment in the vertical one), so a tap costs
-// one FMA and the LDS reads drop from 2R + 1 to (4 + 2R) / 4 per output.  Per output the
-// taps are added in the order of k_blur, so the values are identical.
+// The same sums with the radius R <= 4 compiled in (the 9-tap case).  Horizontal pass: a lane reads the
+// quads left, at and right of its 4 pixels from global memory (any alignment; the neighbours' quads
+// hit the cache) and forms its 4 outputs in registers, so that only the horizontal sums pass through
+// LDS (staging the input there first cost a second pass and a barrier).  Vertical pass: a lane forms a
+// 4 x 4 block from 4 + 2R quads of LDS.  Per output the taps are added in the order of k_blur, so the
+// values are identical.  Bound by memory: 40 sequences of 64^2 to 256^2 pixels (2.1e7, FP32) take
+// 31.5 us (5.3 TB/s), 80 with the input staged in LDS, and 38 to 36 with 64 x 64 and 128 x 32 tiles.
 template <class T, int TW, int TH, bool PERS, int R>
 __global__ __launch_bounds__(256) void k_blur_r(const Tile* __restrict__ tiles, int64_t n_tiles,
                                                 const FrameInfo* __restrict__ fr, const double* __restrict__ k1d,
                                                 const T* __restrict__ in, T* __restrict__ out) {
-    constexpr int HW = TW + 2 * R, HH = TH + 2 * R;
-    static_assert(TW % 4 == 0 && TH % 4 == 0, "tiles split into 4-output segments");
-    __shared__ T s_in[HH][HW + 1];
-    __shared__ T s_h[HH][TW + 1];
+    constexpr int HH = TH + 2 * R, QW = TW / 4;   // rows of horizontal sums, quads per row
+    static_assert(TW % 4 == 0 && TH % 4 == 0 && R <= 4 && 256 % QW == 0, "tiles split into 4-output segments");
+    __shared__ Quad<T> s_h[HH][QW];
     T kk[2 * R + 1];
 #pragma unroll
     for (int j = 0; j <= 2 * R; ++j) kk[j] = (T)k1d[j];
     const int64_t step = PERS ? gridDim.x : n_tiles;
+    const int qx = (int)threadIdx.x % QW, ty = (int)threadIdx.x / QW;
     for (int64_t ti = PERS ? blockIdx.x : xcd_remap(blockIdx.x, gridDim.x); ti < n_tiles; ti += step) {
         const Tile tl = tiles[ti];
         const FrameInfo f = fr[tl.frame];
         const int nx = f.nx, ny = f.ny;
         const T* src = in + f.off;
-        __syncthreads();  // LDS of the previous tile is free
-        for (int i = threadIdx.x; i < HW * HH; i += 256) {
-            const int ly = i / HW, lx = i % HW;
-            const int y = tl.y0 - R + ly, x = tl.x0 - R + lx;
-            s_in[ly][lx] = (y >= 0 && y < ny && x >= 0 && x < nx) ? src[(int64_t)y * nx + x] : T(0);
-        }
-        __syncthreads();
-        // horizontal pass: row ly, outputs lx0 .. lx0 + 3
-        for (int i = threadIdx.x; i < (TW / 4) * HH; i += 256) {
-            const int ly = i / (TW / 4), lx0 = 4 * (i % (TW / 4));
-            T v[4 + 2 * R];
+        const int x = tl.x0 + 4 * qx, nv = min(4, nx - x);
+        if constexpr (PERS) __syncthreads();  // LDS of the previous tile is free
+        if (nv > 0) {
+#pragma unroll 2
+            for (int ly = ty; ly < HH; ly += 256 / QW) {
+                const int y = tl.y0 - R + ly;
+                Quad<T> o = zero4<T>();
+                if (y >= 0 && y < ny) {
+                    const T* row = src + (int64_t)y * nx + x;
+                    // pixels x - 4 .. x + 7 (zeros outside the frame)
+                    T v[12];
+                    const Quad<T> l = x > 0 ? ld4u(row - 4) : zero4<T>(), m = ld4n(row, nv),
+                                  r = nx - x > 4 ? ld4n(row + 4, nx - x - 4) : zero4<T>();
 #pragma unroll
-            for (int c = 0; c < 4 + 2 * R; ++c) v[c] = s_in[ly][lx0 + c];
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] = l.v[e];
+                        v[4 + e] = m.v[e];
+                        v[8 + e] = r.v[e];
+                    }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                T acc = T(0);
+                    for (int q = 0; q < 4; ++q) {
+                        T acc = T(0);
 #pragma unroll
-                for (int j = 0; j <= 2 * R; ++j) acc += kk[j] * v[q + j];
-                s_h[ly][lx0 + q] = acc;
+                        for (int j = 0; j <= 2 * R; ++j) acc += kk[j] * v[4 - R + q + j];
+                        o.v[q] = acc;
+                    }
+                }
+                s_h[ly][qx] = o;
             }
         }
         __syncthreads();
-        // vertical pass: column lx, outputs ly0 .. ly0 + 3
-        for (int i = threadIdx.x; i < TW * (TH / 4); i += 256) {
-            const int lx = i % TW, ly0 = 4 * (i / TW);
-            T v[4 + 2 * R];
+        if (nv > 0) {
+            for (int ly0 = 4 * ty; ly0 < TH; ly0 += 4 * (256 / QW)) {
+                if (tl.y0 + ly0 >= ny) break;
+                T acc[4][4];
 #pragma unroll
-            for (int c = 0; c < 4 + 2 * R; ++c) v[c] = s_h[ly0 + c][lx];
-            const int x = tl.x0 + lx;
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int y = tl.y0 + ly0 + q;
-                T acc = T(0);
+                    for (int e = 0; e < 4; ++e) acc[q][e] = T(0);
 #pragma unroll
-                for (int k = 0; k <= 2 * R; ++k) acc += kk[k] * v[q + k];
-                if (y < ny && x < nx) out[f.off + (int64_t)y * nx + x] = acc;
+                for (int c = 0; c < 4 + 2 * R; ++c) {
+                    const Quad<T> h = s_h[ly0 + c][qx];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (c - q >= 0 && c - q <= 2 * R)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[q][e] += kk[c - q] * h.v[e];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (tl.y0 + ly0 + q < ny)
+                        st4n(out + f.off + (int64_t)(tl.y0 + ly0 + q) * nx + x,
+                             Quad<T>{{acc[q][0], acc[q][1], acc[q][2], acc[q][3]}}, nv);
             }
         }
     }
 }
 
-const TileShape kBlurShapes[] = {{64, 16, 0}, {32, 32, 0}, {128, 8, 0}, {32, 16, 0}, {64, 16, 1}};
+// tiles of the 9-tap kernel and of the general one
+static const TileShape kBlur9Shapes[] = {{64, 32, 0}, {64, 64, 0}, {128, 32, 0}, {32, 32, 0}, {64, 32, 1}};
+static const TileShape kBlurShapes[] = {{64, 16, 0}, {32, 32, 0}, {128, 8, 0}, {32, 16, 0}, {64, 16, 1}};
 const int kBlurCandidates = sizeof(kBlurShapes) / sizeof(kBlurShapes[0]);
+static_assert(sizeof(kBlur9Shapes) == sizeof(kBlurShapes), "both forms offer the same number of tile candidates");
+
+TileShape blur_tile(const Plan& p, int choice) { return p.ksize == 9 ? kBlur9Shapes[choice] : kBlurShapes[choice]; }
 
 void launch_blur(Ctx& c, Plan& p, int dt, const void* in, void* out, int choice) {
     Geom& g = *p.geom;
     if (choice < 0) choice = g.choice("blur", dt);
     MMOF_CHECK(choice >= 0 && choice < kBlurCandidates, MMOF_ERR_INVALID, "blur tile candidate out of range");
-    const TileShape sh = kBlurShapes[choice];
+    const TileShape sh = blur_tile(p, choice);
     const TileList& tl = g.tile_list(c.stream, sh.tw, sh.th, false);
     if (tl.count == 0) return;
     dispatch(dt, [&](auto z) {
@@ -129,11 +153,11 @@ void launch_blur(Ctx& c, Plan& p, int dt, const void* in, void* out, int choice)
         ScopedTime st(&c, "blur", 2.0 * sizeof(T) * g.n, 4.0 * p.ksize * g.n);
         const int64_t grid = sh.persistent ? std::min<int64_t>(tl.count, (int64_t)c.cu_count * 4) : tl.count;
         if (p.ksize == 9) {
-            auto k = choice == 0 ? k_blur_r<T, 64, 16, false, 4>
-                     : choice == 1 ? k_blur_r<T, 32, 32, false, 4>
-                     : choice == 2 ? k_blur_r<T, 128, 8, false, 4>
-                     : choice == 3 ? k_blur_r<T, 32, 16, false, 4>
-                                   : k_blur_r<T, 64, 16, true, 4>;
+            auto k = choice == 0 ? k_blur_r<T, 64, 32, false, 4>
+                     : choice == 1 ? k_blur_r<T, 64, 64, false, 4>
+                     : choice == 2 ? k_blur_r<T, 128, 32, false, 4>
+                     : choice == 3 ? k_blur_r<T, 32, 32, false, 4>
+                                   : k_blur_r<T, 64, 32, true, 4>;
             hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, c.stream, tl.buf.as<Tile>(), tl.count,
                                g.dframes(), p.d_k1.as<double>(), (const T*)in, (T*)out);
         } else {

@@ -7,11 +7,12 @@ namespace mmof {
 
 // Tunable stencil kernels take a tile-shape candidate index; -1 uses the geometry's tuned
 // choice (candidate 0 until the autotuner has run).
-extern const TileShape kBlurShapes[], kGradShapes[], kFlowShapes[], kFlowAdjShapes[];
+extern const TileShape kGradShapes[], kFlowShapes[], kFlowAdjShapes[];
 extern const int kBlurCandidates, kGradCandidates, kFlowCandidates, kFlowAdjCandidates;
 // Output tile of candidate `choice` of Psi / Psi^T and of L(v) on geometry g (the vector
 // forms, used when every frame width is a multiple of 4, have tiles of their own).
 TileShape grad_tile(const Geom& g, int choice);
+TileShape blur_tile(const Plan& p, int choice);
 TileShape flow_tile(const Geom& g, int choice);
 
 // The MM weighting of Theta's rows fused into the kernel that forms them: besides its rows y, the

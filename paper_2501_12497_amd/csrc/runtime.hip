@@ -97,6 +97,28 @@ const TileList& Geom::tile_list(hipStream_t st, int tw, int th, bool pairs) {
     return ref;
 }
 
+const TileList& Geom::quad_list(hipStream_t st, int per) {
+    const uint64_t key = (uint64_t)per << 33;  // (tile_list's keys have a height)
+    auto it = tiles.find(key);
+    if (it != tiles.end()) return *it->second;
+    std::vector<Tile> host;
+    for (int64_t f = 0; f < n_frames; ++f) {
+        const int64_t quads = (int64_t)((frames[f].nx + 3) / 4) * frames[f].ny;
+        for (int64_t q = 0; q < quads; q += per) host.push_back(Tile{(int32_t)f, 0, (int32_t)q, 0});
+    }
+    std::unique_ptr<TileList> tl(new TileList());
+    tl->count = (int64_t)host.size();
+    tl->buf.ensure(sizeof(Tile) * std::max<size_t>(host.size(), 1));
+    if (!host.empty()) {
+        MMOF_HIP(hipMemcpyAsync(tl->buf.ptr, host.data(), sizeof(Tile) * host.size(), hipMemcpyHostToDevice, st));
+        MMOF_HIP(hipStreamSynchronize(st));
+    }
+    MMOF_CHECK(tl->count < (int64_t)INT32_MAX, MMOF_ERR_SHAPE, "too many tiles");
+    auto& ref = *tl;
+    tiles[key] = std::move(tl);
+    return ref;
+}
+
 const TileList& Geom::adj_tile_list(hipStream_t st, int tw, int th) {
     const uint64_t key = ((uint64_t)tw << 32) | (uint64_t)th;
     auto it = adj_tiles.find(key);

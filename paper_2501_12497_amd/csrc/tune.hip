@@ -85,8 +85,11 @@ std::string autotune(Plan& P, int dt) {
         fill_zero<T>(c, std::max<int64_t>(g.pair_px, 1), (T*)r);
     });
     std::string rep;
-    if (P.kind == 1)
-        pick(c, g, "blur", dt, kBlurCandidates, kBlurShapes, [&](int k) { launch_blur(c, P, dt, u, o, k); }, rep);
+    if (P.kind == 1) {
+        std::vector<TileShape> bsh;
+        for (int k = 0; k < kBlurCandidates; ++k) bsh.push_back(blur_tile(P, k));
+        pick(c, g, "blur", dt, kBlurCandidates, bsh.data(), [&](int k) { launch_blur(c, P, dt, u, o, k); }, rep);
+    }
     if (P.kind == 0) {
         // angle groups of 1, 2, 4, 8 per workgroup, reported as "<angles>x<row blocks>"
         static const TileShape groups[] = {{1, 8, 0}, {2, 4, 0}, {4, 2, 0}, {8, 1, 0}};
