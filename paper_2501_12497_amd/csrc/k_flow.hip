@@ -281,17 +281,45 @@ __device__ __forceinline__ void source_cell(int sx, int sy, T vx, T vy, int nx, 
     }
 }
 
-// Adjoint over an ATX x ATY output tile per workgroup of 256 threads; each thread owns
-// RPT = ATX * ATY / 256 consecutive rows of one column.  The sources within the radius of
-// the tile are loaded together and dropped into the (ATX+1) x (ATY+1) cells whose corners
-// touch the tile: each cell has ADJ_SLOTS slots in LDS (cell fractions, value and the
-// source's raster rank in the window), taken in arrival order through an LDS counter.  An
-// output is a corner of exactly four cells; for each it sums the cell's sources in raster
-// order (the few slots ordered by rank in registers) and adds the four partial sums in a
-// fixed corner order, so its value does not depend on the tile shape or on the arrival
-// order.  A tile where some cell receives more sources than it has slots (a strongly
-// converging flow) forms the same sums by the wide-window path below.
-constexpr int ADJ_SLOTS = 4;
+// Cell of a source pixel that no clip can reach (an interior tile: |v| < radius).
+template <class T, int INTERP>
+__device__ __forceinline__ void source_cell_inner(int sx, int sy, T vx, T vy, int& x0, int& y0, T& fx, T& fy) {
+    if (INTERP == 1) {
+        x0 = rint_shift(sx, vx);
+        y0 = rint_shift(sy, vy);
+        fx = T(0);
+        fy = T(0);
+    } else {
+        const T gx = floor(vx), gy = floor(vy);
+        x0 = sx + (int)gx;
+        y0 = sy + (int)gy;
+        fx = vx - gx;
+        fy = vy - gy;
+    }
+}
+
+// The weighted values a source hands to the four corners of its cell, in the order (1,1), (0,1), (1,0), (0,0) of the
+// corner's offset from the cell's origin.
+template <class T>
+__device__ __forceinline__ void corner_terms(T fx, T fy, T val, T t[4]) {
+    const T gx = T(1) - fx, gy = T(1) - fy;
+    t[0] = fx * fy * val;
+    t[1] = gx * fy * val;
+    t[2] = fx * gy * val;
+    t[3] = gx * gy * val;
+}
+
+// Adjoint over an ATX x ATY output tile per workgroup of 256 threads.  The sources within the radius of the tile are
+// loaded together; each adds its four weighted values into the four corner sums of its cell in LDS, and an output adds
+// the sums of the four cells it is a corner of in a fixed order.  A cell sum of one or two sources does not depend on
+// their order.  A cell with more (a converging flow) takes its sources again from a list in LDS and sums them in raster
+// order, so no value depends on the tile shape or on the order of arrival; a tile whose crowded cells hold more than
+// ADJ_LIST sources forms the same sums by the wide-window path.
+// Bound by the vector instructions of the sources (184 per output and lane, VALU 90% busy; 269 when every output formed
+// the weights of its four cells' sources itself): 576 sources at radius 4 for the 256 outputs of a 16 x 16 tile.
+// Interior tiles skip the clip.  Measured over 31 pairs of 512 x 512 with the radius, before and now: smooth flow 105 ->
+// 68 us (FP32), 145 -> 99 (FP64); a flow of unit noise, whose cells are often crowded, 699 -> 135 and 991 -> 198.
+constexpr int ADJ_LIST = 384;
 
 template <class T, int INTERP, int ATX, int ATY>
 __global__ __launch_bounds__(256) void k_flow_adj(const AdjTile* __restrict__ tiles, const T* __restrict__ r,
@@ -301,19 +329,26 @@ __global__ __launch_bounds__(256) void k_flow_adj(const AdjTile* __restrict__ ti
                                                   double* __restrict__ cout) {
     constexpr int RPT = ATX * ATY / 256;
     constexpr int SMAX = (ATX + 2 * RMAX) * (ATY + 2 * RMAX);  // source window (raster rank < 2^16)
+    constexpr int NI = (SMAX + 255) / 256;
     constexpr int CW = ATX + 1, NC = (ATX + 1) * (ATY + 1);     // cells touching the tile
+    constexpr int CROWDED = 1 << 30;  // s_cnt of a cell with a list: this flag, below it the next free entry
     static_assert(SMAX <= 65536, "source ranks are kept in 16 bits");
-    __shared__ T s_fx[NC * ADJ_SLOTS], s_fy[NC * ADJ_SLOTS], s_val[NC * ADJ_SLOTS];
-    __shared__ unsigned short s_rank[NC * ADJ_SLOTS];
+    // FP64 adds into the corner sums of a cell by LDS atomics; FP32, whose LDS add is several times slower than its
+    // store (32 x 512 x 512: 200 us against 51), stores a cell's first and second source apart
+    constexpr int NS = sizeof(T) == 4 ? 2 : 1;
+    __shared__ T s_sum[NS][4][NC];
     __shared__ int s_cnt[NC];
-    __shared__ int s_over;
+    __shared__ T s_term[4][ADJ_LIST];
+    __shared__ unsigned short s_rank[ADJ_LIST];
+    __shared__ int s_over, s_top;
 
     const AdjTile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const int R = *d_radius;  // (independent of the tile: both loads are in flight together)
     const int nx = tl.nx, ny = tl.ny;
     const int64_t np = (int64_t)nx * ny;
-    const int qx = tl.x0 + (int)(threadIdx.x % ATX);
-    const int qy0 = tl.y0 + (int)(threadIdx.x / ATX) * RPT;
+    const int lx = (int)(threadIdx.x % ATX), ly0 = (int)(threadIdx.x / ATX) * RPT;
+    const int qx = tl.x0 + lx;
+    const int qy0 = tl.y0 + ly0;
     const bool col_in = qx < nx;
 
     // direct terms and the pair whose warp gathers into this frame
@@ -337,104 +372,149 @@ __global__ __launch_bounds__(256) void k_flow_adj(const AdjTile* __restrict__ ti
         const T* rg = r + gp;
         const T* vxg = v + 2 * gp;
         const T* vyg = vxg + np;
-        bool wide = R > RMAX;
+        // (the window is addressed by 32-bit byte offsets: its rows have at most 2^23 pixels)
+        bool wide = R > RMAX || nx > (1 << 23);
         if (!wide) {
             const int sx0 = max(tl.x0 - R, 0), sx1 = min(tl.x0 + ATX - 1 + R, nx - 1);
             const int sy0 = max(tl.y0 - R, 0), sy1 = min(tl.y0 + ATY - 1 + R, ny - 1);
             const int sw = sx1 - sx0 + 1, sh = sy1 - sy0 + 1;
-            for (int i = threadIdx.x; i < NC; i += 256) s_cnt[i] = 0;
-            if (threadIdx.x == 0) s_over = 0;
-            // Staging: a thread first loads all of its sources (independent loads, in flight
-            // together), then forms their cells.  Source i of the window (its raster index,
-            // pitch sw, which is also its rank) is taken by thread i mod 256; the row is
-            // i / sw from an FP32 product (exact: i < 2^16 and the quotient's fraction is
-            // at least 1/(2 sw) away from an integer).
-            constexpr int NI = (SMAX + 255) / 256;
+            const bool inner = tl.x0 - 2 * R >= 0 && tl.x0 + ATX + 2 * R < nx && tl.y0 - 2 * R >= 0 &&
+                               tl.y0 + ATY + 2 * R < ny;
+            for (int i = threadIdx.x; i < NC; i += 256) {
+                s_cnt[i] = 0;
+#pragma unroll
+                for (int q = 0; q < 4 * NS; ++q) s_sum[q >> 2][q & 3][i] = T(0);
+            }
+            if (threadIdx.x == 0) s_over = s_top = 0;
+            // A thread first loads all of its sources (independent loads, in flight together), then forms their cells.
+            // Source i of the window (its raster index, pitch sw, which is also its rank) is taken by thread i mod 256;
+            // the row is i / sw from an FP32 product (exact: i < 2^16 and the quotient's fraction is at least 1/(2 sw)
+            // away from an integer).
             const int nsrc = sw * sh;
             const float inv_sw = 1.0f / (float)sw;
+            const int64_t pw = (int64_t)sy0 * nx + sx0;
+            const char* bx = reinterpret_cast<const char*>(vxg + pw);
+            const char* by = reinterpret_cast<const char*>(vyg + pw);
+            const char* br = reinterpret_cast<const char*>(rg + pw);
             T lvx[NI], lvy[NI], lr[NI];
 #pragma unroll
             for (int k = 0; k < NI; ++k) {
                 const int i = (int)threadIdx.x + 256 * k;
                 lvx[k] = lvy[k] = lr[k] = T(0);
                 if (i < nsrc) {
-                    const int ly = (int)(((float)i + 0.5f) * inv_sw), lx = i - ly * sw;
-                    const int64_t p = (int64_t)(sy0 + ly) * nx + sx0 + lx;
-                    lvx[k] = vxg[p];
-                    lvy[k] = vyg[p];
-                    lr[k] = rg[p];
+                    const int ly = (int)(((float)i + 0.5f) * inv_sw);
+                    const unsigned o = (unsigned)(ly * (nx - sw) + i) * (unsigned)sizeof(T);
+                    lvx[k] = *reinterpret_cast<const T*>(bx + o);
+                    lvy[k] = *reinterpret_cast<const T*>(by + o);
+                    lr[k] = *reinterpret_cast<const T*>(br + o);
                 }
             }
-            __syncthreads();  // counts cleared
+            __syncthreads();  // slots cleared
+            // the cell of every source (-1: it touches no output), its fractions in place of the flow, and its turn there
+            int cell[NI], slot[NI];
+            auto cells = [&](auto in_tag) {
 #pragma unroll
-            for (int k = 0; k < NI; ++k) {
-                const int i = (int)threadIdx.x + 256 * k;
-                if (i < nsrc) {
-                    const int ly = (int)(((float)i + 0.5f) * inv_sw), lx = i - ly * sw;
-                    int x0, y0;
-                    T fx, fy;
-                    source_cell<T, INTERP>(sx0 + lx, sy0 + ly, lvx[k], lvy[k], nx, ny, x0, y0, fx, fy);
-                    const int cx = x0 - tl.x0 + 1, cy = y0 - tl.y0 + 1;
-                    if (cx >= 0 && cx <= ATX && cy >= 0 && cy <= ATY) {
-                        const int cell = cy * CW + cx;
-                        const int slot = atomicAdd(&s_cnt[cell], 1);
-                        if (slot < ADJ_SLOTS) {
-                            const int e = cell * ADJ_SLOTS + slot;
-                            s_fx[e] = fx;
-                            s_fy[e] = fy;
-                            s_val[e] = lr[k];
-                            s_rank[e] = (unsigned short)i;
-                        } else {
-                            atomicOr(&s_over, 1);
+                for (int k = 0; k < NI; ++k) {
+                    const int i = (int)threadIdx.x + 256 * k;
+                    cell[k] = -1;
+                    slot[k] = 0;
+                    if (i < nsrc) {
+                        const int ly = (int)(((float)i + 0.5f) * inv_sw), wx = i - ly * sw;
+                        int x0, y0;
+                        T fx, fy;
+                        if (decltype(in_tag)::value)
+                            source_cell_inner<T, INTERP>(sx0 + wx, sy0 + ly, lvx[k], lvy[k], x0, y0, fx, fy);
+                        else
+                            source_cell<T, INTERP>(sx0 + wx, sy0 + ly, lvx[k], lvy[k], nx, ny, x0, y0, fx, fy);
+                        lvx[k] = fx;
+                        lvy[k] = fy;
+                        const int cx = x0 - tl.x0 + 1, cy = y0 - tl.y0 + 1;
+                        if ((unsigned)cx <= (unsigned)ATX && (unsigned)cy <= (unsigned)ATY) {
+                            cell[k] = cy * CW + cx;
+                            slot[k] = atomicAdd(&s_cnt[cell[k]], 1);
                         }
                     }
                 }
-            }
+            };
+            if (inner)
+                cells(std::true_type{});
+            else
+                cells(std::false_type{});
+            int most = 0;
+#pragma unroll
+            for (int k = 0; k < NI; ++k)
+                if (cell[k] >= 0) {
+                    T t[4];
+                    corner_terms(lvx[k], lvy[k], lr[k], t);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (NS == 2)
+                            s_sum[slot[k] & (NS - 1)][q][cell[k]] = t[q];
+                        else
+                            unsafeAtomicAdd(&s_sum[0][q][cell[k]], t[q]);
+                    }
+                    most = max(most, slot[k]);
+                }
+            if (most > 1) s_over = 1;
             __syncthreads();
-            wide = s_over != 0;  // (the same value on every thread)
-            if (!wide && col_in) {
-                const int lx = qx - tl.x0;
+            if (s_over) {
+                // crowded cells: a run of list entries per cell (its count is kept in its first sum meanwhile)
+                for (int i = threadIdx.x; i < NC; i += 256) {
+                    const int n = s_cnt[i];
+                    if (n > 2) {
+                        s_cnt[i] = CROWDED | atomicAdd(&s_top, n);
+                        s_sum[0][0][i] = (T)n;
+                    }
+                }
+                __syncthreads();
+                wide = s_top > ADJ_LIST;  // (the same value on every thread)
+                if (!wide) {
+#pragma unroll
+                    for (int k = 0; k < NI; ++k)
+                        if (cell[k] >= 0 && (s_cnt[cell[k]] & CROWDED)) {
+                            const int e = atomicAdd(&s_cnt[cell[k]], 1) & (CROWDED - 1);
+                            s_rank[e] = (unsigned short)(threadIdx.x + 256 * k);
+                            T t[4];
+                            corner_terms(lvx[k], lvy[k], lr[k], t);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) s_term[q][e] = t[q];
+                        }
+                    __syncthreads();
+                    for (int i = threadIdx.x; i < NC; i += 256) {
+                        if (!(s_cnt[i] & CROWDED)) continue;
+                        const int e1 = s_cnt[i] & (CROWDED - 1), e0 = e1 - (int)s_sum[0][0][i];
+                        T a[4] = {T(0), T(0), T(0), T(0)};
+                        int last = -1;
+                        for (int n = e0; n < e1; ++n) {  // the entries by increasing rank
+                            int best = INT_MAX, at = e0;
+                            for (int e = e0; e < e1; ++e) {
+                                const int rk = s_rank[e];
+                                if (rk > last && rk < best) {
+                                    best = rk;
+                                    at = e;
+                                }
+                            }
+                            last = best;
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) a[q] += s_term[q][at];
+                        }
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            s_sum[0][q][i] = a[q];
+                            if (NS == 2) s_sum[NS - 1][q][i] = T(0);
+                        }
+                    }
+                    __syncthreads();
+                }
+            }
+            if (!wide) {
+                // the output is corner (1,1), (0,1), (1,0), (0,0) of the cells at (qx-1, qy-1), (qx, qy-1), (qx-1, qy),
+                // (qx, qy)
 #pragma unroll
                 for (int k = 0; k < RPT; ++k) {
-                    const int qy = qy0 + k;
-                    if (qy >= ny) break;
-                    // the output is corner (1,1), (0,1), (1,0), (0,0) of the cells at
-                    // (qx-1, qy-1), (qx, qy-1), (qx-1, qy), (qx, qy): one partial sum per
-                    // corner, each over its cell's sources in raster order
-                    const int c00 = (qy - tl.y0) * CW + lx;
-                    T part[4];
-#pragma unroll
-                    for (int cr = 0; cr < 4; ++cr) {
-                        const int cc = c00 + (cr & 1) + (cr >> 1) * CW;
-                        const int n = s_cnt[cc];
-                        const int e0 = cc * ADJ_SLOTS;
-                        T a = T(0);
-                        if (n == 1) {  // the common case: one source
-                            const T fx = s_fx[e0], fy = s_fy[e0];
-                            const T wx = (cr & 1) ? T(1) - fx : fx;
-                            const T wy = (cr >> 1) ? T(1) - fy : fy;
-                            a += wx * wy * s_val[e0];
-                        } else if (n > 1) {
-                            unsigned key[ADJ_SLOTS];
-#pragma unroll
-                            for (int q = 0; q < ADJ_SLOTS; ++q) key[q] = q < n ? s_rank[e0 + q] : 0xFFFFFu;
-                            // visit the slots by increasing rank (selection over at most 4 keys)
-                            for (int t = 0; t < n; ++t) {
-                                int best = 0;
-#pragma unroll
-                                for (int q = 1; q < ADJ_SLOTS; ++q)
-                                    if (key[q] < key[best]) best = q;
-                                key[best] = 0xFFFFFu;
-                                const int e = e0 + best;
-                                const T fx = s_fx[e], fy = s_fy[e];
-                                const T wx = (cr & 1) ? T(1) - fx : fx;
-                                const T wy = (cr >> 1) ? T(1) - fy : fy;
-                                a += wx * wy * s_val[e];
-                            }
-                        }
-                        part[cr] = a;
-                    }
-                    acc[k] = ((part[0] + part[1]) + part[2]) + part[3];
+                    const int c00 = (ly0 + k) * CW + lx;
+                    auto part = [&](int q, int cell) { return NS == 2 ? s_sum[0][q][cell] + s_sum[NS - 1][q][cell] : s_sum[0][q][cell]; };
+                    acc[k] = ((part(0, c00) + part(1, c00 + 1)) + part(2, c00 + CW)) + part(3, c00 + CW + 1);
                 }
             }
         }
@@ -458,14 +538,16 @@ __global__ __launch_bounds__(256) void k_flow_adj(const AdjTile* __restrict__ ti
                         source_cell<T, INTERP>(px, py, vxg[p], vyg[p], nx, ny, x0, y0, fx, fy);
                         const int ex = qx - x0, ey = qy - y0;  // 1: the output is the cell's far corner
                         if ((unsigned)ex > 1u || (unsigned)ey > 1u) continue;
-                        const T wx = ex ? fx : T(1) - fx;
-                        const T wy = ey ? fy : T(1) - fy;
-                        const T term = wx * wy * rg[p];
+                        T t[4];
+                        corner_terms(fx, fy, rg[p], t);
                         const int cr = (1 - ex) + 2 * (1 - ey);
-                        if (cr == 0) part[0] += term;
-                        else if (cr == 1) part[1] += term;
-                        else if (cr == 2) part[2] += term;
-                        else part[3] += term;
+                        {
+#pragma clang fp contract(off)  // (the product is rounded before the sum, as in the LDS path)
+                            if (cr == 0) part[0] += t[0];
+                            else if (cr == 1) part[1] += t[1];
+                            else if (cr == 2) part[2] += t[2];
+                            else part[3] += t[3];
+                        }
                     }
                 acc[k] = ((part[0] + part[1]) + part[2]) + part[3];
             }
@@ -522,14 +604,14 @@ __global__ __launch_bounds__(256) void k_flow_dv(const Tile* __restrict__ tiles,
     gv[2 * f.pair_off + np + p] = ww * dy;
 }
 
-// out = max(out, floor(max |v|) + 1) over the n values of the flows (a NaN counts as 1e30), the
-// radius of the adjoint's source windows; an integer maximum, so it does not depend on the order.
+// out[blockIdx] = floor(max |v|) + 1 over the workgroup's share of the n values of the flows (a NaN counts as 1e30): the
+// radius of the adjoint's source windows, whole for one workgroup.
 template <class T, int VEC>
-__global__ __launch_bounds__(256) void k_flow_radius(const T* __restrict__ v, int64_t n, int32_t* __restrict__ out) {
+__global__ __launch_bounds__(1024) void k_flow_radius(const T* __restrict__ v, int64_t n, int32_t* __restrict__ out) {
     // VEC values per load (16 bytes when the flow is 16-byte aligned), four loads in flight per
     // step; the last n % VEC values singly
     typedef T VT __attribute__((ext_vector_type(VEC), aligned(sizeof(T) * VEC)));
-    __shared__ T s4[4];
+    __shared__ T s_m[16];
     T m = T(0);
     auto take = [&](T x) {
         x = fabs(x);
@@ -550,41 +632,50 @@ __global__ __launch_bounds__(256) void k_flow_radius(const T* __restrict__ v, in
     }
     for (int64_t i = nv * VEC + tid; i < n; i += stride) take(v[i]);
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-    if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = m;
+    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        m = fmax(fmax(s4[0], s4[1]), fmax(s4[2], s4[3]));
-        const T c = fmin(floor(m), T(1 << 20));
-        atomicMax(out, (int32_t)c + 1);  // integer max: order-independent
+        for (int w = 1; w < (int)blockDim.x / 64; ++w) m = fmax(m, s_m[w]);
+        out[blockIdx.x] = (int32_t)fmin(floor(m), T(1 << 20)) + 1;
     }
 }
 
-__global__ void k_set_int(int32_t* p, int32_t val) { *p = val; }
+// out = the largest of the n values (one wave)
+__global__ __launch_bounds__(64) void k_max_int(const int32_t* __restrict__ p, int n, int32_t* __restrict__ out) {
+    int m = 1;
+    for (int i = (int)threadIdx.x; i < n; i += 64) m = max(m, p[i]);
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o));
+    if (threadIdx.x == 0) *out = m;
+}
 
 void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out) {
-    hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, c.stream, d_out, 1);
-    MMOF_LAUNCH_CHECK();
     const int64_t n = 2 * g.pair_px;
-    if (n == 0) return;
+    if (n == 0) {
+        hipLaunchKernelGGL(k_max_int, dim3(1), dim3(64), 0, c.stream, (const int32_t*)nullptr, 0, d_out);
+        MMOF_LAUNCH_CHECK();
+        return;
+    }
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
-        // one atomic per workgroup: 8 workgroups per CU at most (four waves per SIMD with 16-byte
-        // loads: 0.36 -> 0.1 ms over the flows of the 1024x1024x64 stack, against 2 per CU and
-        // 4-byte loads)
+        // Up to 32768 values: one workgroup, one launch.  More: a workgroup per 32768 values, two per CU at most, whose
+        // maxima a second launch joins.  One integer atomic per workgroup took 15 ns each, one after the other:
+        // 30 us over the flows of 31 pairs of 512 x 512 (2048 workgroups).
         constexpr int VEC = 16 / (int)sizeof(T);
-        if (reinterpret_cast<uintptr_t>(v) % 16 == 0)
-            hipLaunchKernelGGL((k_flow_radius<T, VEC>), grid_for(n / VEC, 256 * 4, 8 * c.cu_count), dim3(256), 0,
-                               c.stream, (const T*)v, n, d_out);
-        else
-            hipLaunchKernelGGL((k_flow_radius<T, 1>), grid_for(n, 256 * 4, 8 * c.cu_count), dim3(256), 0, c.stream,
-                               (const T*)v, n, d_out);
+        const int nb = (int)std::min<int64_t>(cdiv(n, 32768), 2 * c.cu_count);
+        int32_t* part = nb > 1 ? static_cast<int32_t*>(c.work("radius_part", sizeof(int32_t) * 2 * c.cu_count)) : d_out;
+        auto k = reinterpret_cast<uintptr_t>(v) % 16 == 0 ? k_flow_radius<T, VEC> : k_flow_radius<T, 1>;
+        hipLaunchKernelGGL(k, dim3(nb), dim3(1024), 0, c.stream, (const T*)v, n, part);
         MMOF_LAUNCH_CHECK();
+        if (nb > 1) {
+            hipLaunchKernelGGL(k_max_int, dim3(1), dim3(64), 0, c.stream, part, nb, d_out);
+            MMOF_LAUNCH_CHECK();
+        }
     });
 }
 
 const TileShape kFlowShapes[] = {{64, 4, 0}, {32, 8, 0}, {128, 2, 0}, {16, 16, 0}};
 const int kFlowCandidates = sizeof(kFlowShapes) / sizeof(kFlowShapes[0]);
-const TileShape kFlowAdjShapes[] = {{16, 16, 0}, {32, 16, 0}, {64, 8, 0}, {32, 8, 0}};
+const TileShape kFlowAdjShapes[] = {{16, 16, 0}, {32, 16, 0}, {64, 16, 0}, {32, 32, 0}};
 const int kFlowAdjCandidates = sizeof(kFlowAdjShapes) / sizeof(kFlowAdjShapes[0]);
 // vector-form candidates of the forward operator: lanes per tile row (4 pixels each) and
 // waves per workgroup
@@ -617,8 +708,8 @@ template <class T, int INTERP>
 static auto flow_adj_kernel(int choice) {
     return choice == 0 ? k_flow_adj<T, INTERP, 16, 16>
            : choice == 1 ? k_flow_adj<T, INTERP, 32, 16>
-           : choice == 2 ? k_flow_adj<T, INTERP, 64, 8>
-                         : k_flow_adj<T, INTERP, 32, 8>;
+           : choice == 2 ? k_flow_adj<T, INTERP, 64, 16>
+                         : k_flow_adj<T, INTERP, 32, 32>;
 }
 
 void launch_flow_fwd(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v, void* r,
@@ -720,7 +811,9 @@ void launch_flow_adj(Ctx& c, Geom& g, int dt, int direction, int interp, const v
         rad = static_cast<int32_t*>(c.work("flow_radius", 256));
         launch_flow_radius(c, g, dt, v, rad);
     }
-    if (choice < 0) choice = g.choice("flow_adj", dt, 3);
+    // untuned: 16 x 16 for every frame, the fastest or within 3% of it (8 x 32 x 32: 13 us against 15 to 19 for the larger
+    // tiles, 12 x 1024 x 1024: 93 against 93 to 113)
+    if (choice < 0) choice = g.choice("flow_adj", dt, 0);
     MMOF_CHECK(choice >= 0 && choice < kFlowAdjCandidates, MMOF_ERR_INVALID, "flow adjoint tile candidate out of range");
     const TileShape sh = kFlowAdjShapes[choice];
     const TileList& tl = g.adj_tile_list(c.stream, sh.tw, sh.th);
