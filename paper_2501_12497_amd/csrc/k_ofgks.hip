@@ -277,48 +277,6 @@ __device__ void gram_row(int j, const double* V, int n, int nx, int ny, const T*
 // instruction every 7 to 10 cycles and two waves of a SIMD do not slow each other, so the chain of
 // pivots bounds it.  With the column-per-wave inner products above, a solve of 15 pairs of 32 x 32
 // (ell 10, 20 projected solves) takes 1.94 ms, 12.2 ms before; half of it is this search.
-template <int N>
-__device__ __forceinline__ double row16_bcast(double v) {
-    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + N, 0xf, 0xf, true);  // row_newbcast:N
-}
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-// a[e] += (src on lane N + e of the 16) * m for e < L: one v_fmac_f64 with a DPP source each,
-// where a broadcast and an FMA would be two instructions (a wave issues one of either every 7 to 10
-// cycles).  A DPP source may not have been written within two wait states, hence the s_nop.
-// (volatile also keeps the updates here: sunk to the values' next uses, they would hold every
-// step's broadcasts in registers.)
-#define GK_FM(i) "v_fmac_f64_dpp %" #i ", %[s], %[m] row_newbcast:%[n" #i "] row_mask:0xf bank_mask:0xf\n\t"
-template <int N, int L>
-__device__ __forceinline__ void fmac_bcast(double* a, double src, double m) {
-    static_assert(N >= 0 && N + L <= 16, "a lane of the 16");
-    if constexpr (L >= 8) {
-        asm volatile("s_nop 1\n\t" GK_FM(0) GK_FM(1) GK_FM(2) GK_FM(3) GK_FM(4) GK_FM(5) GK_FM(6) GK_FM(7)
-                     : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5]), "+&v"(a[6]),
-                       "+&v"(a[7])
-                     : [s] "v"(src), [m] "v"(m), [n0] "n"(N), [n1] "n"(N + 1), [n2] "n"(N + 2), [n3] "n"(N + 3),
-                       [n4] "n"(N + 4), [n5] "n"(N + 5), [n6] "n"(N + 6), [n7] "n"(N + 7));
-        fmac_bcast<N + 8 <= 16 ? N + 8 : 16, L - 8>(a + 8, src, m);
-    } else if constexpr (L >= 4) {
-        asm volatile("s_nop 1\n\t" GK_FM(0) GK_FM(1) GK_FM(2) GK_FM(3)
-                     : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3])
-                     : [s] "v"(src), [m] "v"(m), [n0] "n"(N), [n1] "n"(N + 1), [n2] "n"(N + 2), [n3] "n"(N + 3));
-        fmac_bcast<N + 4, L - 4>(a + 4, src, m);
-    } else if constexpr (L >= 2) {
-        asm volatile("s_nop 1\n\t" GK_FM(0) GK_FM(1)
-                     : "+&v"(a[0]), "+&v"(a[1])
-                     : [s] "v"(src), [m] "v"(m), [n0] "n"(N), [n1] "n"(N + 1));
-        fmac_bcast<N + 2, L - 2>(a + 2, src, m);
-    } else if constexpr (L == 1) {
-        asm volatile("s_nop 1\n\t" GK_FM(0) : "+&v"(a[0]) : [s] "v"(src), [m] "v"(m), [n0] "n"(N));
-    }
-}
-#undef GK_FM
 __device__ __forceinline__ double row16_sum(double v) {
 #pragma unroll
     for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o);

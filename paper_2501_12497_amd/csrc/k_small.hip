@@ -10,11 +10,10 @@
 // (an end is taken when the root lies beyond it) and found by Newton steps in mu,
 // safeguarded by bisection of the bracket, starting from the previous lambda.
 //
-// K <= 64: one wavefront.  Each evaluation factors M = G_H + lambda G_T with a blocked
-// Cholesky (registers and matrix cores), then solves with the factor: the right-hand side is one entry
-// per lane and each step broadcasts the finished entry with readlane.  D^2 and its
-// derivative only need forward solves (d^T z = ||L^{-1} d||^2, w^T M^{-1} w = ||L^{-1} w||^2)
-// plus one backward solve for z.
+// K <= 64: one wavefront, lane i owning row i; 16-column blocks in registers, matrix cores for the
+// blocks of the factored columns, the factor in LDS.  Broadcasts within 16 lanes are DPP operands of
+// the FMAs.  D^2 and its derivative only need forward solves (d^T z = ||L^{-1} d||^2,
+// w^T M^{-1} w = ||L^{-1} w||^2) plus one backward solve for z.
 // 64 < K <= 256: four wavefronts, thread i owning row i; the factor lives in an L2-resident
 // global workspace (too large for the LDS at these sizes), built and used in 16-column
 // blocks: the wave holding a diagonal block factors it with readlane broadcasts, the other
@@ -37,6 +36,7 @@ struct SmallLds {
     double A[KMAX_SMALL][KP];
     double T[KMAX_SMALL][KP];
     double L[KMAX_SMALL][KP];
+    double piv[KMAX_SMALL], inv[KMAX_SMALL];  // the pivots and their reciprocals
 };
 
 __device__ __forceinline__ double bcast(double v, int lane) {
@@ -68,149 +68,202 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
     return r;
 }
 
-// Blocked Cholesky of M = A + lam T into the lower triangle of s.L, in 16-column block
-// columns (rows and columns K..16*ceil(K/16)-1 are padded with the identity).  Lane i owns
-// row i.  A block column is loaded into registers and factored right-looking there (the
-// pivot and the finished column entries are broadcast with readlane), written back, and
-// the trailing lower blocks are updated on the FP64 matrix cores:
-// M_{I,J'} -= L_{I,J} L_{J',J}^T with v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16]
-// and B[l/16][l%16]; the 16x16 result is D[l/16 + 4v][l%16] in four doubles per lane).
-// Returns false on a non-positive pivot (uniform across the wave); on success *inv holds
-// 1 / L[lane][lane].
-__device__ bool chol(SmallLds& s, int K, double lam, double* inv) {
-    const int i = threadIdx.x;
-    const int nbk = (K + 15) >> 4;
-    const int KP = nbk << 4;
-    // M = A + lam T with the identity on the padded diagonal (A and T are zero outside
-    // K x K); whole rows, without branches, so the LDS loads of 16 columns go out together
-    const double pad = i >= K ? 1.0 : 0.0;
-    for (int c0 = 0; c0 < KP; c0 += 16) {
+// 1/x for x > 0: hardware estimate refined by two Newton steps (each squares the relative error), a
+// short dependency chain on the pivot path.
+__device__ __forceinline__ double rcp_nr(double x) {
+    double r = __builtin_amdgcn_rcp(x);
 #pragma unroll
-        for (int cc = 0; cc < 16; ++cc) {
-            const int c = c0 + cc;
-            s.L[i][c] = fma(lam, s.T[i][c], s.A[i][c]) + (i == c ? pad : 0.0);
-        }
-    }
-    __syncthreads();
-    double my_inv = 0.0;
+    for (int it = 0; it < 2; ++it) r = fma(r, fma(-x, r, 1.0), r);
+    return r;
+}
+
+// Sums of two values over the wave, bitwise identical in every lane (the sums of the four rows of
+// 16 lanes are taken from one lane each).
+__device__ __forceinline__ void wave_sum2(double& a, double& b) {
+    auto row = [](double v) {
+        v += __builtin_amdgcn_update_dpp(0.0, v, 0x128, 0xf, 0xf, true);  // row_ror:8
+        v += __builtin_amdgcn_update_dpp(0.0, v, 0x124, 0xf, 0xf, true);
+        v += __builtin_amdgcn_update_dpp(0.0, v, 0x122, 0xf, 0xf, true);
+        v += __builtin_amdgcn_update_dpp(0.0, v, 0x121, 0xf, 0xf, true);
+        return v;
+    };
+    a = row(a);
+    b = row(b);
+    a = (bcast(a, 0) + bcast(a, 16)) + (bcast(a, 32) + bcast(a, 48));
+    b = (bcast(b, 0) + bcast(b, 16)) + (bcast(b, 32) + bcast(b, 48));
+}
+
+// M = A + lam T = U diag(p) U^T with U unit lower triangular, in 16-column blocks (rows and columns
+// K..16*ceil(K/16)-1 are padded with the identity).  -U goes below the diagonal of s.L, the pivots p
+// to s.piv.  A block column starts as M less the products of the factored columns, on the FP64 matrix
+// cores: M_{I,J} - U_{I,J'} (p U_{J,J'})^T with v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16]
+// and B[l/16][l%16]; the 16x16 result is D[l/16 + 4v][l%16] in four doubles per lane).  Then each
+// lane holds its row's 16 entries and, in every row of 16 lanes, a copy of the diagonal block's row
+// l % 16, so that a pivot and the entries of its column reach all lanes as DPP operands (one FMA per
+// entry; two readlanes and an FMA before).  The last block column has no rows below its diagonal
+// block.  Bound by the instructions one wave issues, 11 cycles apart; the factorization and its solves take 6 us at
+// K <= 16, 12 at 39 and 17 at 64 (9, 22 and 32 with readlane broadcasts and masked steps; a cold start at K = 39, eight
+// of them, 180 -> 95 us).
+// Returns false on a pivot that is not positive (uniform across the wave); on success *inv holds
+// 1 / p[lane].
+__device__ bool factor(SmallLds& s, int K, double lam, double* inv) {
+    const int i = threadIdx.x, r = i & 15, lk = i >> 4;
+    const int nbk = (K + 15) >> 4;
+    bool ok = true;
     for (int J = 0; J < nbk; ++J) {
         const int c0 = J << 4;
-        double a[16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const double v = s.L[i][c0 + c];  // (every row is in the array: loads without branches)
-            a[c] = (i >= c0 + c && i < KP) ? v : 0.0;
-        }
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const double piv = bcast(a[c], c0 + c);
-            if (!(piv > 0.0)) return false;
-            const double r = rsqrt_nr(piv);
-            const double l = a[c] * r;  // L[i][c0+c] for rows below the pivot, L[c0+c][c0+c] on its lane
-            a[c] = l;
-            if (i == c0 + c) my_inv = r;
-#pragma unroll
-            for (int c2 = c + 1; c2 < 16; ++c2) a[c2] -= l * bcast(l, c0 + c2);
-        }
-        // (the entries above the diagonal become zero; nothing reads them)
-#pragma unroll
-        for (int c = 0; c < 16; ++c) s.L[i][c0 + c] = a[c];
-        __syncthreads();
-        // trailing update of the lower blocks (I, J'), J < J' <= I
-        const int lr = i & 15, lk = i >> 4;
-        for (int Jp = J + 1; Jp < nbk; ++Jp) {
-            for (int I = Jp; I < nbk; ++I) {
+        const bool last = J == nbk - 1;
+        if (J > 0) {
+            for (int I = J; I < nbk; ++I) {
                 dbl4 acc;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[v] = s.L[(I << 4) + lk + 4 * v][(Jp << 4) + lr];
+                for (int v = 0; v < 4; ++v) {
+                    const int row = (I << 4) + lk + 4 * v, col = c0 + r;
+                    acc[v] = fma(lam, s.T[row][col], s.A[row][col]) + (row == col && row >= K ? 1.0 : 0.0);
+                }
+                for (int b0 = 0; b0 < c0; b0 += 16) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const double av = -s.L[(I << 4) + lr][c0 + 4 * q + lk];
-                    const double bv = s.L[(Jp << 4) + lr][c0 + 4 * q + lk];
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+                    for (int q = 0; q < 4; ++q) {
+                        const int col = b0 + 4 * q + lk;
+                        // (both factors negated in s.L: the product of the pivot takes the sign)
+                        const double av = s.L[(I << 4) + r][col];
+                        const double bv = -s.piv[col] * s.L[c0 + r][col];
+                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+                    }
                 }
 #pragma unroll
-                for (int v = 0; v < 4; ++v) s.L[(I << 4) + lk + 4 * v][(Jp << 4) + lr] = acc[v];
+                for (int v = 0; v < 4; ++v) s.L[(I << 4) + lk + 4 * v][c0 + r] = acc[v];
             }
+            __syncthreads();
         }
+        auto columns = [&](auto below) {
+            constexpr bool BELOW = decltype(below)::value;
+            double P[16], D[16];
+            if (J == 0) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) {
+                    D[c] = fma(lam, s.T[r][c], s.A[r][c]);
+                    if (!BELOW) D[c] += r == c && r >= K ? 1.0 : 0.0;  // (K <= 16)
+                    P[c] = BELOW ? fma(lam, s.T[i][c], s.A[i][c]) : 0.0;
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) {
+                    D[c] = s.L[c0 + r][c0 + c];
+                    P[c] = BELOW ? s.L[i][c0 + c] : 0.0;  // (rows above the block: nothing reads what they become)
+                }
+            }
+            int at = c0;  // (in a vector register: the stores then take their offset)
+            asm volatile("" : "+v"(at));
+            static_for<0, 16>([&](auto C) {
+                constexpr int c = decltype(C)::value;
+                const double p = row16_bcast<c>(D[c]);
+                ok = ok && p > 0.0;
+                const double q = rcp_nr(p);
+                s.piv[at + c] = p;  // (the same value from every lane)
+                s.inv[at + c] = q;
+                const double nu = D[c] * -q;
+                fmac_bcast<c + 1, 15 - c>(D + c + 1, D[c], nu);
+                if constexpr (BELOW) {
+                    const double nl = P[c] * -q;
+                    fmac_bcast<c + 1, 15 - c>(P + c + 1, D[c], nl);
+                    P[c] = nl;
+                } else {
+                    P[c] = nu;
+                }
+            });
+            if (BELOW || lk == J) {
+                // zeros on and above the diagonal, which the solves multiply by
+                const int rr = i - c0;
+#pragma unroll
+                for (int c = 0; c < 16; ++c) s.L[i][c0 + c] = rr > c ? P[c] : 0.0;
+            }
+        };
+        if (last)
+            columns(std::false_type{});
+        else
+            columns(std::true_type{});
+        if (!ok) return false;
         __syncthreads();
     }
-    *inv = my_inv;
+    *inv = s.inv[i];
     return true;
 }
 
-// The solves below walk the columns in groups of four with the next group's LDS entries
-// loaded ahead, so the LDS latency overlaps the broadcast chain.  The walk runs up to K
-// rounded up to 4 (at most the padded size of the factor): a step j >= K changes nothing,
-// since entry j of the right-hand side is zero and the rows it would update lie outside
-// [0, K).
+// Steps of a block's triangular solve on the copies of its entries x in every row of 16 lanes, four columns N, N + S,
+// N + 2 S, N + 3 S, and what each finished entry adds to the lane's own row (a) and product (w):
+//   x += x(lane c) d[c],   a += x(lane c) l[c],   w += x(lane c) t[c].
+// (A DPP source may not have been written within two wait states.)
+#define SS_FMAC(dst, m, q) \
+    "v_fmac_f64_dpp %[" #dst "], %[x], %[" #m #q "] row_newbcast:%[n" #q "] row_mask:0xf bank_mask:0xf\n\t"
+template <int N, int S>
+__device__ __forceinline__ void solve_steps(double& x, double& a, const double* d, const double* l) {
+#define SS_STEP(q) "s_nop 1\n\t" SS_FMAC(x, d, q) "s_nop 1\n\t" SS_FMAC(a, l, q)
+    asm volatile(SS_STEP(0) SS_STEP(1) SS_STEP(2) SS_STEP(3)
+                 : [x] "+&v"(x), [a] "+&v"(a)
+                 : [d0] "v"(d[0]), [d1] "v"(d[S]), [d2] "v"(d[2 * S]), [d3] "v"(d[3 * S]), [l0] "v"(l[0]),
+                   [l1] "v"(l[S]), [l2] "v"(l[2 * S]), [l3] "v"(l[3 * S]), [n0] "n"(N), [n1] "n"(N + S),
+                   [n2] "n"(N + 2 * S), [n3] "n"(N + 3 * S));
+#undef SS_STEP
+}
+template <int N, int S>
+__device__ __forceinline__ void solve_steps(double& x, double& a, double& w, const double* d, const double* l,
+                                            const double* t) {
+#define SS_STEP(q) "s_nop 1\n\t" SS_FMAC(x, d, q) "s_nop 1\n\t" SS_FMAC(a, l, q) SS_FMAC(w, t, q)
+    asm volatile(SS_STEP(0) SS_STEP(1) SS_STEP(2) SS_STEP(3)
+                 : [x] "+&v"(x), [a] "+&v"(a), [w] "+&v"(w)
+                 : [d0] "v"(d[0]), [d1] "v"(d[S]), [d2] "v"(d[2 * S]), [d3] "v"(d[3 * S]), [l0] "v"(l[0]),
+                   [l1] "v"(l[S]), [l2] "v"(l[2 * S]), [l3] "v"(l[3 * S]), [t0] "v"(t[0]), [t1] "v"(t[S]),
+                   [t2] "v"(t[2 * S]), [t3] "v"(t[3 * S]), [n0] "n"(N), [n1] "n"(N + S), [n2] "n"(N + 2 * S),
+                   [n3] "n"(N + 3 * S));
+#undef SS_STEP
+}
+#undef SS_FMAC
 
-// y = L^{-1} b (one entry per lane)
-__device__ double fwd_solve(const SmallLds& s, int K, double inv, double b) {
-    const int i = threadIdx.x;
-    const int row = min(i, KMAX_SMALL - 1);
-    const int K4 = (K + 3) & ~3;
+// y = U^{-1} b (one entry per lane): each row of 16 lanes solves a copy of a diagonal block, and the
+// rows below take its entries as they are finished.
+__device__ double fwd_solve(const SmallLds& s, int K, double b) {
+    const int i = threadIdx.x, r = i & 15, g = i >> 4;
     double y = i < K ? b : 0.0;
-    double l[4];
+    for (int c0 = 0; c0 < K; c0 += 16) {
+        double l[16], d[16];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) l[q] = s.L[row][q];
-    for (int j = 0; j < K4; j += 4) {
-        double nl[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) nl[q] = s.L[row][min(j + 4 + q, KMAX_SMALL)];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int jj = j + q;
-            const double yj = bcast(y * inv, jj);
-            const double upd = fma(-l[q], yj, y);
-            y = (i == jj) ? yj : ((i > jj && i < K) ? upd : y);
+        for (int c = 0; c < 16; ++c) {
+            d[c] = s.L[c0 + r][c0 + c];
+            l[c] = s.L[i][c0 + c];
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) l[q] = nl[q];
+        double x = __shfl(y, c0 + r), below = y;
+        static_for<0, 4>([&](auto Q) {
+            constexpr int c = 4 * decltype(Q)::value;
+            solve_steps<c, 1>(x, below, d + c, l + c);
+        });
+        y = g == (c0 >> 4) ? x : (i > c0 ? below : y);
     }
     return i < K ? y : 0.0;
 }
 
-// z = L^{-T} y
-__device__ double bwd_solve(const SmallLds& s, int K, double inv, double y) {
-    const int i = threadIdx.x;
-    const int col = min(i, KMAX_SMALL - 1);
-    const int K4 = (K + 3) & ~3;
+// z = U^{-T} y, blocks from the last one up, and w = T z with it.
+__device__ double bwd_solve(const SmallLds& s, int K, double y, double& w) {
+    const int i = threadIdx.x, r = i & 15, g = i >> 4;
     double z = i < K ? y : 0.0;
-    double l[4];
+    w = 0.0;
+    for (int c0 = ((K - 1) >> 4) << 4; c0 >= 0; c0 -= 16) {
+        double l[16], d[16], t[16];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) l[q] = s.L[K4 - 1 - q][col];
-    for (int j = K4 - 1; j >= 0; j -= 4) {
-        double nl[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) nl[q] = s.L[max(j - 4 - q, 0)][col];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int jj = j - q;
-            const double zj = bcast(z * inv, jj);
-            const double upd = fma(-l[q], zj, z);
-            z = (i == jj) ? zj : ((i < jj && i < K) ? upd : z);
+        for (int c = 0; c < 16; ++c) {
+            d[c] = s.L[c0 + c][c0 + r];
+            l[c] = s.L[c0 + c][i];
+            t[c] = s.T[i][c0 + c];
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) l[q] = nl[q];
+        double x = __shfl(z, c0 + r), above = z;
+        static_for<0, 4>([&](auto Q) {
+            constexpr int c = 15 - 4 * decltype(Q)::value;
+            solve_steps<c, -1>(x, above, w, d + c, l + c, t + c);
+        });
+        z = g == (c0 >> 4) ? x : (i < c0 ? above : z);
     }
+    w = i < K ? w : 0.0;
     return i < K ? z : 0.0;
-}
-
-// (T z)_i for the lane's row, z distributed one entry per lane (T is zero outside K x K).
-__device__ double matvec_T(const SmallLds& s, int K, double z) {
-    const int i = threadIdx.x;
-    const int row = min(i, KMAX_SMALL - 1);
-    const int K4 = (K + 3) & ~3;
-    double acc = 0.0;
-    for (int j = 0; j < K4; j += 4) {
-        double t[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) t[q] = s.T[row][j + q];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc += t[q] * bcast(z, j + q);
-    }
-    return i < K ? acc : 0.0;
 }
 
 struct Eval {
@@ -222,17 +275,20 @@ __device__ Eval evaluate(SmallLds& s, int K, double lam, double bb, double d, bo
     Eval e{false, 0.0, 0.0, 0.0};
     ++nfac;
     double inv;
-    if (!chol(s, K, lam, &inv)) return e;
+    if (!factor(s, K, lam, &inv)) return e;
     e.ok = true;
-    const double y = fwd_solve(s, K, inv, d);
-    e.z = bwd_solve(s, K, inv, y);
-    const double w = matvec_T(s, K, e.z);
-    const double dz = wave_sum64(y * y);  // d^T z = ||L^{-1} d||^2
-    const double zw = wave_sum64(e.z * w);
+    const double y = fwd_solve(s, K, d);
+    const double yp = (int)threadIdx.x < K ? y * inv : 0.0;
+    double w;
+    e.z = bwd_solve(s, K, yp, w);
+    double dz = y * yp, zw = e.z * w;  // d^T z = y^T diag(1/p) y
+    wave_sum2(dz, zw);
     e.D2 = bb - dz - lam * zw;
     if (deriv) {
-        const double q = fwd_solve(s, K, inv, w);  // w^T M^{-1} w = ||L^{-1} w||^2
-        e.dD2 = 2.302585092994046 * 2.0 * lam * lam * wave_sum64(q * q);
+        const double q = fwd_solve(s, K, w);
+        double qq = (int)threadIdx.x < K ? q * q * inv : 0.0, none = 0.0;
+        wave_sum2(qq, none);
+        e.dD2 = 2.302585092994046 * 2.0 * lam * lam * qq;
     }
     return e;
 }
@@ -261,7 +317,7 @@ __device__ void dp_root(EV&& ev, double trA, double trT, double target, double b
     // evaluated when a step would leave through it: an interior root proves, by
     // monotonicity of D^2, that neither end needs clamping.
     for (int it = 0; it < 200; ++it) {
-        e = ev(pow(10.0, mu), true);
+        e = ev(exp10(mu), true);
         const double f = e.ok ? e.D2 - target : -target;
         MMOF_SMALL_TRACE(it, mu, e, f, lo, hi);
         if (f < 0.0)
@@ -273,7 +329,7 @@ __device__ void dp_root(EV&& ev, double trA, double trT, double target, double b
         if (!(nmu > lo && nmu < hi)) {
             if (f < 0.0 && !hi_checked && hi == HI) {
                 hi_checked = true;
-                const Eval eh = ev(pow(10.0, HI), false);
+                const Eval eh = ev(exp10(HI), false);
                 if (eh.ok && eh.D2 < target) {
                     e = eh;
                     mu = HI;
@@ -283,7 +339,7 @@ __device__ void dp_root(EV&& ev, double trA, double trT, double target, double b
             }
             if (f > 0.0 && !lo_checked && lo == LO) {
                 lo_checked = true;
-                const Eval el = ev(pow(10.0, LO), false);
+                const Eval el = ev(exp10(LO), false);
                 if (el.ok && el.D2 > target) {
                     e = el;
                     mu = LO;
@@ -298,13 +354,13 @@ __device__ void dp_root(EV&& ev, double trA, double trT, double target, double b
             // D^2 differ from those at the root by the same relative amount) unless it failed
             if (!e.ok) {
                 mu = nmu;
-                e = ev(pow(10.0, mu), false);
+                e = ev(exp10(mu), false);
             }
             break;
         }
         mu = nmu;
     }
-    lam = pow(10.0, mu);
+    lam = exp10(mu);
 }
 
 __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restrict__ GA, const double* __restrict__ GT,
@@ -313,16 +369,22 @@ __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restr
                                                     double* __restrict__ res, double* __restrict__ lam_out) {
     __shared__ SmallLds s;
     const int i = threadIdx.x;
-    // coalesced loads: each instruction moves one contiguous row of the 64-wide matrices;
-    // entries outside K x K are zero
-    for (int r = 0; r < KMAX_SMALL; ++r) {
-        double ga = 0.0, gt = 0.0;
-        if (r < K) {
-            ga = GA[(int64_t)r * KLD + i];
-            gt = GT[(int64_t)r * KLD + i];
+    // coalesced loads: each instruction moves one contiguous row of the matrices, eight rows of both
+    // in flight; entries outside K x K are zero up to the padded size
+    const int KP16 = (K + 15) & ~15;
+    for (int r0 = 0; r0 < KP16; r0 += 8) {
+        double ga[8], gt[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const bool in = r0 + q < K && i < K;
+            ga[q] = in ? GA[(int64_t)(r0 + q) * KLD + i] : 0.0;
+            gt[q] = in ? GT[(int64_t)(r0 + q) * KLD + i] : 0.0;
         }
-        s.A[r][i] = i < K ? ga : 0.0;
-        s.T[r][i] = i < K ? gt : 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            s.A[r0 + q][i] = ga[q];
+            s.T[r0 + q][i] = gt[q];
+        }
     }
     const double d = i < K ? dvec[i] : 0.0;
     __syncthreads();
