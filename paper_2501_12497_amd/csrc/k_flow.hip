@@ -88,8 +88,7 @@ __device__ __forceinline__ T sample_at(const S* __restrict__ src, const SampleCe
 template <class T, int INTERP, int FTW, int FTH>
 __global__ __launch_bounds__(256) void k_flow_fwd(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
                                                   const T* __restrict__ u, const T* __restrict__ v,
-                                                  T* __restrict__ r, int direction, const T* __restrict__ nuw,
-                                                  T* __restrict__ mw, double eps2) {
+                                                  T* __restrict__ r, int direction) {
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
     const int x = tl.x0 + (int)(threadIdx.x % FTW);
@@ -103,9 +102,7 @@ __global__ __launch_bounds__(256) void k_flow_fwd(const Tile* __restrict__ tiles
     const T vxx = vx[p], vyy = vx[np + p];
     const T* src = direction > 0 ? ut1 : ut;
     const T* sub = direction > 0 ? ut : ut1;
-    const T val = warp_sample<T, INTERP>(src, f.nx, f.ny, x, y, vxx, vyy) - sub[p];
-    r[f.pair_off + p] = val;
-    if (mw) mw[f.pair_off + p] = mm_weighted(val, nuw[f.pair_off + p], eps2);
+    r[f.pair_off + p] = warp_sample<T, INTERP>(src, f.nx, f.ny, x, y, vxx, vyy) - sub[p];
 }
 
 // Forward and (when vr is not null) reverse flow rows of Theta for K columns at once:
@@ -142,13 +139,24 @@ __global__ __launch_bounds__(256) void k_flow_fwd_cols(const Tile* __restrict__ 
 // offset); a row whose width is not a multiple of 4 ends with a thread of 1..3 pixels, whose
 // accesses go element by element.  The bilinear samples stay single loads.  Values equal those
 // of the scalar kernels.
-// mw (may be null; the scalar kernel too): the rows weighted by the MM weights of nuw
-// (RowWeighting).
+//
+// One image: the forward, reverse and temporal-difference rows of its pairs, whichever are wanted, from one read of the
+// two frames; each with its MM-weighted copy when its m is not null.  Bound by memory.  One launch for the two flow rows
+// of a small stack (4.1 us each before, 5.3 us together at 7 pairs of 32 x 32, FP64) and 16-byte accesses for the
+// differences (64 x 1024 x 1024, FP32: 238 us with four single accesses per lane, 4 pixels apart; 153 us over the calls
+// of a solve, 29 of 69 with the weighted copy, which took a pass of 490 us over all rows before).
+template <class T>
+struct PairRowsT {
+    const T* __restrict__ v;
+    T* __restrict__ r;
+    const T* __restrict__ nu;
+    T* __restrict__ m;
+};
+
 template <class T, int INTERP, int LW>
-__global__ __launch_bounds__(256) void k_flow_fwd4(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
-                                                   const T* __restrict__ u, const T* __restrict__ v,
-                                                   T* __restrict__ r, int direction, const T* __restrict__ nuw,
-                                                   T* __restrict__ mw, double eps2) {
+__global__ __launch_bounds__(256) void k_pair_rows4(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
+                                                    const T* __restrict__ u, PairRowsT<T> fwd, PairRowsT<T> rev,
+                                                    PairRowsT<T> diff, double eps2) {
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
     const int x = tl.x0 + 4 * (int)(threadIdx.x % LW);
@@ -159,21 +167,35 @@ __global__ __launch_bounds__(256) void k_flow_fwd4(const Tile* __restrict__ tile
     const T* ut = u + f.off;
     const T* ut1 = ut + np;
     const int nv = min(4, f.nx - x);   // (fewer than 4 at the end of a row whose width is not a multiple of 4)
-    const T* vf = v + 2 * f.pair_off;
-    const Quad<T> vx = ld4n(vf + p, nv), vy = ld4n(vf + np + p, nv);
-    const T* src = direction > 0 ? ut1 : ut;
-    const Quad<T> sub = ld4n((direction > 0 ? ut : ut1) + p, nv);
-    Quad<T> o;
+    Quad<T> a = zero4<T>(), b = zero4<T>();
+    if (fwd.r || diff.r) a = ld4n(ut + p, nv);
+    if (rev.r || diff.r) b = ld4n(ut1 + p, nv);
+    auto store = [&](const PairRowsT<T>& w, const Quad<T>& o) {
+        st4n(w.r + f.pair_off + p, o, nv);
+        if (w.m) {
+            const Quad<T> nq = ld4n(w.nu + f.pair_off + p, nv);
+            Quad<T> m;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        o.v[j] = warp_sample<T, INTERP>(src, f.nx, f.ny, x + j, y, vx.v[j], vy.v[j]) - sub.v[j];
-    st4n(r + f.pair_off + p, o, nv);
-    if (mw) {
-        const Quad<T> nq = ld4n(nuw + f.pair_off + p, nv);
-        Quad<T> m;
+            for (int j = 0; j < 4; ++j) m.v[j] = mm_weighted(o.v[j], nq.v[j], eps2);
+            st4n(w.m + f.pair_off + p, m, nv);
+        }
+    };
+    auto warp = [&](const PairRowsT<T>& w, const T* src, const Quad<T>& sub) {
+        const T* vf = w.v + 2 * f.pair_off;
+        const Quad<T> vx = ld4n(vf + p, nv), vy = ld4n(vf + np + p, nv);
+        Quad<T> o;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) m.v[j] = mm_weighted(o.v[j], nq.v[j], eps2);
-        st4n(mw + f.pair_off + p, m, nv);
+        for (int j = 0; j < 4; ++j)
+            o.v[j] = warp_sample<T, INTERP>(src, f.nx, f.ny, x + j, y, vx.v[j], vy.v[j]) - sub.v[j];
+        store(w, o);
+    };
+    if (fwd.r) warp(fwd, ut1, a);
+    if (rev.r) warp(rev, ut, b);
+    if (diff.r) {
+        Quad<T> o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o.v[j] = b.v[j] - a.v[j];
+        store(diff, o);
     }
 }
 
@@ -701,8 +723,8 @@ static auto flow_fwd_kernel(int choice) {
                          : k_flow_fwd<T, INTERP, 16, 16>;
 }
 template <class T, int INTERP>
-static auto flow_fwd4_kernel(int choice) {
-    return kFlow4Shapes[choice].lw == 64 ? k_flow_fwd4<T, INTERP, 64> : k_flow_fwd4<T, INTERP, 32>;
+static auto pair_rows4_kernel(int choice) {
+    return kFlow4Shapes[choice].lw == 64 ? k_pair_rows4<T, INTERP, 64> : k_pair_rows4<T, INTERP, 32>;
 }
 template <class T, int INTERP>
 static auto flow_adj_kernel(int choice) {
@@ -712,31 +734,53 @@ static auto flow_adj_kernel(int choice) {
                          : k_flow_adj<T, INTERP, 32, 32>;
 }
 
-void launch_flow_fwd(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v, void* r,
-                     int choice, const RowWeighting* rw) {
+void launch_pair_rows(Ctx& c, Geom& g, int dt, int interp, const void* u, const PairRows& fwd, const PairRows& rev,
+                      const PairRows& diff, double eps2, int choice) {
     if (g.n_pairs == 0) return;
     if (choice < 0) choice = g.choice("flow_fwd", dt, 1);
     MMOF_CHECK(choice >= 0 && choice < kFlowCandidates, MMOF_ERR_INVALID, "flow tile candidate out of range");
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
-        // (with rw also nu read and the weighted rows written)
-        ScopedTime st(&c, "flow_fwd", (rw ? 7.0 : 5.0) * sizeof(T) * g.pair_px, 12.0 * g.pair_px);
-        const T* nuw = rw ? (const T*)rw->nu_a : nullptr;
-        T* mw = rw ? (T*)rw->m_a : nullptr;
-        const double eps2 = rw ? rw->eps2 : 0.0;
-        if (aligned_to(sizeof(T), {u, v, r, nuw, mw})) {
-            const Flow4Shape sh = kFlow4Shapes[choice];
-            const TileList& tl = g.tile_list(c.stream, sh.tw(), sh.th(), true);
-            auto k = interp == MMOF_INTERP_ROUND ? flow_fwd4_kernel<T, 1>(choice) : flow_fwd4_kernel<T, 0>(choice);
-            hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(64 * sh.nw), 0, c.stream, tl.buf.as<Tile>(),
-                               g.dframes(), (const T*)u, (const T*)v, (T*)r, direction, nuw, mw, eps2);
-        } else {
-            const TileShape sh = kFlowShapes[choice];
-            const TileList& tl = g.tile_list(c.stream, sh.tw, sh.th, true);
-            auto k = interp == MMOF_INTERP_ROUND ? flow_fwd_kernel<T, 1>(choice) : flow_fwd_kernel<T, 0>(choice);
-            hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(256), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
-                               (const T*)u, (const T*)v, (T*)r, direction, nuw, mw, eps2);
-        }
+        // per pixel of a pair: a frame sampled and one subtracted, a flow and a row per flow row; a third of that for
+        // a difference; nu read and the weighted row written
+        double words = 0.0;
+        for (const PairRows* w : {&fwd, &rev}) words += w->r ? (w->m ? 7.0 : 5.0) : 0.0;
+        if (diff.r) words += (diff.m ? 5.0 : 3.0) - (fwd.r || rev.r ? 1.0 : 0.0);
+        ScopedTime st(&c, fwd.r || rev.r ? "flow_fwd" : "tdiff_fwd", words * sizeof(T) * g.pair_px,
+                      ((fwd.r ? 12.0 : 0.0) + (rev.r ? 12.0 : 0.0) + (diff.r ? 1.0 : 0.0)) * g.pair_px);
+        auto typed = [](const PairRows& w) {
+            return PairRowsT<T>{(const T*)w.v, (T*)w.r, (const T*)w.nu, (T*)w.m};
+        };
+        const Flow4Shape sh = kFlow4Shapes[choice];
+        const TileList& tl = g.tile_list(c.stream, sh.tw(), sh.th(), true);
+        auto k = interp == MMOF_INTERP_ROUND ? pair_rows4_kernel<T, 1>(choice) : pair_rows4_kernel<T, 0>(choice);
+        hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(64 * sh.nw), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
+                           (const T*)u, typed(fwd), typed(rev), typed(diff), eps2);
+        MMOF_LAUNCH_CHECK();
+    });
+}
+
+void launch_flow_fwd(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v, void* r,
+                     int choice) {
+    if (g.n_pairs == 0) return;
+    if (aligned_to(dt == MMOF_F32 ? 4 : 8, {u, v, r})) {
+        PairRows w;
+        w.v = v;
+        w.r = r;
+        launch_pair_rows(c, g, dt, interp, u, direction > 0 ? w : PairRows{}, direction > 0 ? PairRows{} : w,
+                         PairRows{}, 0.0, choice);
+        return;
+    }
+    if (choice < 0) choice = g.choice("flow_fwd", dt, 1);
+    MMOF_CHECK(choice >= 0 && choice < kFlowCandidates, MMOF_ERR_INVALID, "flow tile candidate out of range");
+    dispatch(dt, [&](auto z) {
+        using T = decltype(z);
+        ScopedTime st(&c, "flow_fwd", 5.0 * sizeof(T) * g.pair_px, 12.0 * g.pair_px);
+        const TileShape sh = kFlowShapes[choice];
+        const TileList& tl = g.tile_list(c.stream, sh.tw, sh.th, true);
+        auto k = interp == MMOF_INTERP_ROUND ? flow_fwd_kernel<T, 1>(choice) : flow_fwd_kernel<T, 0>(choice);
+        hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(256), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
+                           (const T*)u, (const T*)v, (T*)r, direction);
         MMOF_LAUNCH_CHECK();
     });
 }

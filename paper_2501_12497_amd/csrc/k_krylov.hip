@@ -1020,15 +1020,6 @@ __global__ void k_weight_mul(int64_t n, const double* __restrict__ w, const TX* 
         y[i] = (TX)((double)x[i] * w[i]);
 }
 
-// y = x w with w = mm_weight(nu) formed here (the weights of k_mm_weights_f64).
-template <class TX>
-__global__ void k_weight_mul_nu(int64_t n, const TX* __restrict__ nu, double eps2, const TX* __restrict__ x,
-                                TX* __restrict__ y) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        y[i] = (TX)((double)x[i] * mm_weight((double)nu[i], eps2));
-    }
-}
-
 // ------------------------------------------------------------------------ host launchers
 
 template <class T>
@@ -1068,13 +1059,6 @@ void weight_mul(Ctx& c, int64_t n, const double* w, const TX* x, TX* y) {
 template void weight_mul<float>(Ctx&, int64_t, const double*, const float*, float*);
 template void weight_mul<double>(Ctx&, int64_t, const double*, const double*, double*);
 
-template <class TX>
-void weight_mul_nu(Ctx& c, int64_t n, const TX* nu, double eps, const TX* x, TX* y) {
-    hipLaunchKernelGGL(k_weight_mul_nu<TX>, grid_for(n, KB, 8192), dim3(KB), 0, c.stream, n, nu, eps * eps, x, y);
-    MMOF_LAUNCH_CHECK();
-}
-template void weight_mul_nu<float>(Ctx&, int64_t, const float*, double, const float*, float*);
-template void weight_mul_nu<double>(Ctx&, int64_t, const double*, double, const double*, double*);
 
 
 // Two rows per lane (k_mdot2) when every column, y and xe are element-aligned (2-element

@@ -18,7 +18,7 @@ TileShape flow_tile(const Geom& g, int choice);
 // The MM weighting of Theta's rows fused into the kernel that forms them: besides its rows y, the
 // kernel writes m = y / sqrt(nu^2 + eps^2) (the weight in FP64, the product rounded to the row
 // type, as the separate weighting pass computes it), nu and m laid out like y.  a: the rows of the
-// first output (gx, or the flow rows), b: those of the second (gy).
+// first output (gx), b: those of the second (gy).
 struct RowWeighting {
     const void* nu_a = nullptr;
     void* m_a = nullptr;
@@ -35,7 +35,18 @@ void launch_grad_adj(Ctx& c, Geom& g, int dt, const void* gx, const void* gy, co
 
 // L(v) = -M-bar (direction +1) / -M-bar' (direction -1) and relatives.
 void launch_flow_fwd(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v, void* r,
-                     int choice = -1, const RowWeighting* rw = nullptr);
+                     int choice = -1);
+// One kind of Theta's rows over the pairs of frames: r (null: not wanted) and, when m is not null, its rows weighted by
+// the MM weights of nu (RowWeighting).
+struct PairRows {
+    const void* v = nullptr;  // the flow (flow rows)
+    void* r = nullptr;
+    const void* nu = nullptr;
+    void* m = nullptr;
+};
+// The forward-flow, reverse-flow and temporal-difference rows of one image in one launch.
+void launch_pair_rows(Ctx& c, Geom& g, int dt, int interp, const void* u, const PairRows& fwd, const PairRows& rev,
+                      const PairRows& diff, double eps2 = 0.0, int choice = -1);
 // The residual formed where the last Theta^T kernel writes its output: instead of u, the kernel
 // writes out = x + lambda u in FP64 (x in the operator precision, lambda on the device), the
 // arithmetic of the separate combination pass.
@@ -59,8 +70,10 @@ void launch_flow_dv(Ctx& c, Geom& g, int dt, int direction, int interp, const vo
 void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out);
 
 // Temporal first difference L_t of the spatio-temporal regularisers: forward r = u(t+1) - u(t)
-// per pair ([pairs][ny][nx]); transpose (accumulating into u or overwriting it).
-void launch_tdiff(Ctx& c, Geom& g, int dt, bool transpose, const void* in, void* out, bool accumulate);
+// per pair ([pairs][ny][nx]); transpose (accumulating into u or overwriting it; res, transpose only, as in
+// launch_flow_adj).
+void launch_tdiff(Ctx& c, Geom& g, int dt, bool transpose, const void* in, void* out, bool accumulate,
+                  const ResidualOut* res = nullptr);
 // MM weights of the grouped rows of Theta (reg MMOF_REG_ISO: per pixel over its horizontal
 // and vertical difference; MMOF_REG_GS: per difference location over the frames of its
 // sequence): nu holds Theta u from its start (gx rows, then gy rows), w2 (FP64) likewise;

@@ -102,9 +102,6 @@ void put_rowcol(Ctx& c, double* G, int ldg, int j, const double* h);
 // y = w * x
 template <class TX>
 void weight_mul(Ctx& c, int64_t n, const double* w, const TX* x, TX* y);
-// y = w * x with w = 1/sqrt(nu^2 + eps^2) formed from nu (the arithmetic of mm_weights_f64)
-template <class TX>
-void weight_mul_nu(Ctx& c, int64_t n, const TX* nu, double eps, const TX* x, TX* y);
 
 // Small projected solve (one wavefront for K <= 64, four above).  Inputs on the device: GA, GT
 // (K x K, leading dimension KLD),

@@ -214,53 +214,51 @@ struct Solver {
             launch_blur(c, P, dt, in, out);
         if (rep) rep->n_At++;
     }
-    void theta_flow(const TX* in, TX* out) {
-        if (!flow) return;
-        launch_flow_fwd(c, g, dt, +1, p.interp, in, flow_v, out + oRF);
-        if (p.use_reverse) launch_flow_fwd(c, g, dt, -1, p.interp, in, flow_vr, out + oRR);
-        if (rep) rep->n_L += p.use_reverse ? 2 : 1;
+    // the flow and temporal-difference rows of Theta in, with nu_ also weighted into outw
+    void theta_pairs(const TX* in, TX* out, const TX* nu_, TX* outw) {
+        if (!flow && !tdiff) return;
+        auto rows = [&](bool wanted, const TX* v, int64_t o) {
+            PairRows w;
+            if (!wanted) return w;
+            w.v = v;
+            w.r = out + o;
+            if (nu_) {
+                w.nu = nu_ + o;
+                w.m = outw + o;
+            }
+            return w;
+        };
+        MMOF_CHECK(!tdiff || g.n_frames <= 65535, MMOF_ERR_SHAPE, "too many frames for one launch (at most 65535)");
+        launch_pair_rows(c, g, dt, p.interp, in, rows(flow, flow_v, oRF), rows(flow && p.use_reverse, flow_vr, oRR),
+                         rows(tdiff, nullptr, oTD), p.eps * p.eps);
+        if (flow && rep) rep->n_L += p.use_reverse ? 2 : 1;
     }
     void theta(const TX* in, TX* out) {
         launch_grad_fwd(c, g, dt, in, nullptr, nullptr, out + oGX, out + oGY);
-        if (tdiff) launch_tdiff(c, g, dt, false, in, out + oTD, false);
-        theta_flow(in, out);
+        theta_pairs(in, out, nullptr, nullptr);
         if (rep) rep->n_theta++;
     }
     // theta(in, out) and, in the same kernels, its rows weighted by the MM weights of nu_
     // (1/sqrt(nu^2 + eps^2)) into outw: the residual's W Theta u without a pass of its own
-    // (per-row weights from nu, no temporal-difference rows)
+    // (per-row weights from nu)
     void theta_weighted(const TX* in, TX* out, const TX* nu_, TX* outw) {
-        const double eps2 = p.eps * p.eps;
         RowWeighting gw;
         gw.nu_a = nu_ + oGX;
         gw.m_a = outw + oGX;
         gw.nu_b = nu_ + oGY;
         gw.m_b = outw + oGY;
-        gw.eps2 = eps2;
+        gw.eps2 = p.eps * p.eps;
         launch_grad_fwd(c, g, dt, in, nullptr, nullptr, out + oGX, out + oGY, -1, &gw);
-        if (flow) {
-            RowWeighting fw;
-            fw.nu_a = nu_ + oRF;
-            fw.m_a = outw + oRF;
-            fw.eps2 = eps2;
-            launch_flow_fwd(c, g, dt, +1, p.interp, in, flow_v, out + oRF, -1, &fw);
-            if (p.use_reverse) {
-                RowWeighting rw;
-                rw.nu_a = nu_ + oRR;
-                rw.m_a = outw + oRR;
-                rw.eps2 = eps2;
-                launch_flow_fwd(c, g, dt, -1, p.interp, in, flow_vr, out + oRR, -1, &rw);
-            }
-            if (rep) rep->n_L += p.use_reverse ? 2 : 1;
-        }
+        theta_pairs(in, out, nu_, outw);
         if (rep) rep->n_theta++;
     }
-    // out = Theta^T in; with res (only when flows are on: the last flow adjoint forms it), the
-    // residual res->out = res->x + lambda out instead of out.  Returns whether it was formed.
+    // out = Theta^T in; with res (only when flows or temporal differences are on: their last
+    // adjoint forms it), the residual res->out = res->x + lambda out instead of out.  Returns
+    // whether it was formed.
     bool thetaT(const TX* in, TX* out, const ResidualOut* res = nullptr) {
         launch_grad_adj(c, g, dt, in + oGX, in + oGY, nullptr, nullptr, out, false);
-        if (tdiff) launch_tdiff(c, g, dt, true, in + oTD, out, true);
-        bool formed = false;
+        if (tdiff) launch_tdiff(c, g, dt, true, in + oTD, out, true, flow ? nullptr : res);
+        bool formed = tdiff && res != nullptr;
         if (flow) {
             launch_flow_adj(c, g, dt, +1, p.interp, in + oRF, flow_v, out, true, rad_v, -1,
                             p.use_reverse ? nullptr : res);
@@ -615,14 +613,11 @@ struct Solver {
                        std::to_string(reinterpret_cast<uintptr_t>(wsrc));
                 replayable(key, [&] {
                     At(vin_m, out_n);
-                    if (wsrc && !tdiff) {
+                    if (wsrc) {
                         theta_weighted(u_op, yR, wsrc, yW);
                     } else {
                         theta(u_op, yR);
-                        if (wsrc)
-                            weight_mul_nu<TX>(c, R, wsrc, p.eps, yR, yW);
-                        else
-                            weight_mul<TX>(c, R, w2, yR, yW);
+                        weight_mul<TX>(c, R, w2, yR, yW);
                     }
                     ResidualOut ro;
                     ro.x = out_n;
