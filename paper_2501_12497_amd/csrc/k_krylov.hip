@@ -387,9 +387,12 @@ __global__ __launch_bounds__(KB) void k_gemv_mdot(int64_t n, int K, const double
 
 // out[0] = sum of nb partials in a fixed order: thread t of 1024 sums t, t + 1024, ... in eight
 // interleaved running sums (the eight loads of a step in flight together) combined in a fixed
-// order, then the waves' sums in wave order.
+// order, then the waves' sums in wave order.  With keep (may be null), the second-pass test of
+// cgs_once on the sum: keep[0] = 1 (skip the second pass) when the first pass kept at least
+// 1/sqrt(2) of the norm, ||x'||^2 >= ||x||^2 / 2 (xx[0] = ||x||^2).
 __global__ __launch_bounds__(1024) void k_sum_final(int nb, const double* __restrict__ part, double* __restrict__ out,
-                                                   const int* __restrict__ skip) {
+                                                   const int* __restrict__ skip, const double* __restrict__ xx,
+                                                   int* __restrict__ keep) {
     if (skip && *skip) return;
     __shared__ double s16[16];
     double a8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -406,6 +409,7 @@ __global__ __launch_bounds__(1024) void k_sum_final(int nb, const double* __rest
         double t = 0.0;
         for (int w = 0; w < 16; ++w) t += s16[w];
         out[0] = t;
+        if (keep) keep[0] = t >= 0.5 * xx[0] ? 1 : 0;
     }
 }
 
@@ -834,8 +838,17 @@ __global__ __launch_bounds__(1024) void k_wgram_final_quad(int nb, int K, int NQ
     const int ne = NQ * (NQ + 1) / 2 * 16;
     const int e = blockIdx.x * GRAM_SLAB + lane;
     double acc = 0.0;
-    if (e < ne)
-        for (int b = wave; b < nb; b += 16) acc += part[(int64_t)b * ne + e];
+    if (e < ne) {
+        int b = wave;
+        for (; b + 7 * 16 < nb; b += 8 * 16) {  // (eight loads in flight)
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = part[(int64_t)(b + 16 * q) * ne + e];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += v[q];
+        }
+        for (; b < nb; b += 16) acc += part[(int64_t)b * ne + e];
+    }
     s[wave][lane] = acc;
     __syncthreads();
     if (wave != 0 || e >= ne) return;
@@ -1144,11 +1157,11 @@ template void gram_row<float>(Ctx&, int64_t, int, const float*, int64_t, const d
 template void gram_row<double>(Ctx&, int64_t, int, const double*, int64_t, const double*, double*, int, double*);
 
 // gemv_fused; with skip, every launch returns at once when *skip is non-zero on the device
-// (timed under the name tname)
+// (timed under the name tname); xx and keep as in k_sum_final
 template <class TX, class TO>
 static void gemv_fused_impl(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, const double* h, double alpha,
                             const double* y, double beta, double* out_d, TO* out_t, const double* cv, double* sq,
-                            const int* skip, const char* tname) {
+                            const int* skip, const char* tname, const double* xx = nullptr, int* keep = nullptr) {
     MMOF_CHECK(K >= 0 && K <= KMAX, MMOF_ERR_SHAPE, "too many Krylov columns");
     if (n == 0) {
         if (sq && !skip) set_scalar(c, sq, 0.0);
@@ -1178,7 +1191,8 @@ static void gemv_fused_impl(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, c
         MMOF_LAUNCH_CHECK();
     }
     if (sq) {
-        hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(1024), 0, c.stream, (int)grid.x, (const double*)part, sq, skip);
+        hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(1024), 0, c.stream, (int)grid.x, (const double*)part, sq, skip,
+                           xx, keep);
         MMOF_LAUNCH_CHECK();
     }
 }
@@ -1194,12 +1208,6 @@ template void gemv_fused<double, double>(Ctx&, int64_t, int, const double*, int6
                                          const double*, double, double*, double*, const double*, double*);
 template void gemv_fused<float, float>(Ctx&, int64_t, int, const float*, int64_t, const double*, double,
                                        const double*, double, double*, float*, const double*, double*);
-
-// Second-pass test of cgs_once: flag[0] = 1 (skip the second pass) when the first pass kept at
-// least 1/sqrt(2) of the norm, ||x'||^2 >= ||x||^2 / 2.
-__global__ void k_cgs_keep(const double* __restrict__ xx, const double* __restrict__ sq, int* __restrict__ flag) {
-    flag[0] = (sq[0] >= 0.5 * xx[0]) ? 1 : 0;
-}
 
 void cgs_once(Ctx& c, int64_t n, int K, const double* Q, int64_t ld, double* x, double* sq, double* h) {
     MMOF_CHECK(K >= 1 && K <= KMAX, MMOF_ERR_SHAPE, "too many Krylov columns");
@@ -1218,9 +1226,7 @@ void cgs_once(Ctx& c, int64_t n, int K, const double* Q, int64_t ld, double* x, 
     dots(x, nullptr, "mdot");
     // x <- x - Q h in place (each row read before it is written), ||x||^2 into sq
     gemv_fused_impl<double, double>(c, n, K, Q, ld, h, -1.0, x, 1.0, x, (double*)nullptr, nullptr, sq, nullptr,
-                                    "gemv");
-    hipLaunchKernelGGL(k_cgs_keep, dim3(1), dim3(1), 0, c.stream, (const double*)(h + K), (const double*)sq, flag);
-    MMOF_LAUNCH_CHECK();
+                                    "gemv", h + K, flag);
     // the second pass, carried out only where the test asks for it
     dots(nullptr, flag, "cgs_second");
     gemv_fused_impl<double, double>(c, n, K, Q, ld, h, -1.0, x, 1.0, x, (double*)nullptr, nullptr, sq, flag,
@@ -1232,9 +1238,8 @@ void cgs_once(Ctx& c, int64_t n, int K, const double* Q, int64_t ld, double* x, 
 // (column-major, leading dimension KLD: T(i, j) = T[j * KLD + i], column j = the coefficients
 // of v_j in Vs).  One workgroup of KB threads; K <= KMAX.
 
-// g = T^T h (g_i = sum_{k <= i} T(k, i) h_k), into LDS, and its squared norm (thread 0).
-__device__ double basis_coeffs(int K, const double* __restrict__ T, const double* __restrict__ h, double* g,
-                               double* s4) {
+// g = T^T h (g_i = sum_{k <= i} T(k, i) h_k; h in LDS), into LDS, and its squared norm (thread 0).
+__device__ double basis_coeffs(int K, const double* __restrict__ T, const double* h, double* g, double* s4) {
     double e2 = 0.0;
     for (int i = threadIdx.x; i < K; i += KB) {
         const double* ti = T + (int64_t)i * KLD;
@@ -1247,18 +1252,45 @@ __device__ double basis_coeffs(int K, const double* __restrict__ T, const double
     return block_sum(e2, s4);  // (also orders the writes of g before any later read)
 }
 
+// The fixed-order sums of the chunk partials of h = Vs^T r and ||r||^2 (columns 0 .. K, nb of them
+// each) by one workgroup, a wave per column, into LDS and h; nb = 0: h[0..K] is already formed.
+__device__ void basis_sums(int K, int nb, const double* __restrict__ part, double* h, double* hs) {
+    if (nb == 0) {
+        for (int j = threadIdx.x; j <= K; j += KB) hs[j] = h[j];
+    } else {
+        const int lane = threadIdx.x & 63;
+        for (int j0 = (int)(threadIdx.x >> 6); j0 <= K; j0 += 4 * (KB / 64)) {
+            double a[4];  // four columns' loads in flight
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j = j0 + q * (KB / 64);
+                a[q] = 0.0;
+                for (int b = lane; j <= K && b < nb; b += 64) a[q] += part[(int64_t)j * nb + b];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j = j0 + q * (KB / 64);
+                const double s = wave_sum(a[q]);
+                if (lane == 0 && j <= K) hs[j] = h[j] = s;
+            }
+        }
+    }
+    __syncthreads();
+}
+
 // keep[0] = 1 when ||r||^2 - ||g||^2 >= ||r||^2 / 2 (r keeps at least 1/sqrt(2) of its norm
 // outside the basis: no explicit pass); otherwise keep[0] = 0 and hc = T g, the coefficients
-// in Vs of the part of r along the basis.
-__global__ __launch_bounds__(KB) void k_basis_check(int K, const double* __restrict__ T,
-                                                    const double* __restrict__ h, const double* __restrict__ rr2,
+// in Vs of the part of r along the basis.  h[0..K] from basis_sums.
+__global__ __launch_bounds__(KB) void k_basis_check(int K, int nb, const double* __restrict__ part,
+                                                    const double* __restrict__ T, double* h,
                                                     double* __restrict__ hc, int* __restrict__ keep) {
-    __shared__ double g[KMAX];
+    __shared__ double g[KMAX], hs[KMAX + 1];
     __shared__ double s4[4];
     __shared__ int need;
-    const double G2 = basis_coeffs(K, T, h, g, s4);
+    basis_sums(K, nb, part, h, hs);
+    const double G2 = basis_coeffs(K, T, hs, g, s4);
     if (threadIdx.x == 0) {
-        need = !(rr2[0] - G2 >= 0.5 * rr2[0]);
+        need = !(hs[K] - G2 >= 0.5 * hs[K]);
         keep[0] = need ? 0 : 1;
     }
     __syncthreads();
@@ -1272,15 +1304,18 @@ __global__ __launch_bounds__(KB) void k_basis_check(int K, const double* __restr
 
 // Appends column K of T for a new stored column vs_K = r / rho: g = T^T h with h = Vs^T r,
 // rho^2 = ||r||^2 - ||g||^2 (written to sq[0]), T(:, K) = e_K - T g / rho, so that
-// v_K = vs_K - V g / rho = (r - V V^T r) / rho.
-__global__ __launch_bounds__(KB) void k_basis_append(int K, double* __restrict__ T, const double* __restrict__ h,
-                                                     const double* __restrict__ rr2, double* __restrict__ sq) {
-    __shared__ double g[KMAX];
+// v_K = vs_K - V g / rho = (r - V V^T r) / rho.  h[0..K] from basis_sums unless *keep (h is still
+// that of the check).
+__global__ __launch_bounds__(KB) void k_basis_append(int K, int nb, const double* __restrict__ part,
+                                                     double* __restrict__ T, double* h, const int* __restrict__ keep,
+                                                     double* __restrict__ sq) {
+    __shared__ double g[KMAX], hs[KMAX + 1];
     __shared__ double s4[4];
     __shared__ double inv;
-    const double G2 = basis_coeffs(K, T, h, g, s4);
+    basis_sums(K, *keep ? 0 : nb, part, h, hs);
+    const double G2 = basis_coeffs(K, T, hs, g, s4);
     if (threadIdx.x == 0) {
-        const double rho2 = fmax(rr2[0] - G2, 0.0);
+        const double rho2 = fmax(hs[K] - G2, 0.0);
         sq[0] = rho2;
         inv = rho2 > 0.0 ? 1.0 / sqrt(rho2) : 0.0;
     }
@@ -1297,42 +1332,61 @@ __global__ __launch_bounds__(KB) void k_basis_append(int K, double* __restrict__
     }
 }
 
-// W(a, j) = sum_{b <= j} Gs(a, b) T(b, j) for a, j < K (one thread per entry).
-__global__ __launch_bounds__(KB) void k_basis_right(int K, const double* __restrict__ Gs, int ldg,
-                                                    const double* __restrict__ T, double* __restrict__ W) {
-    const int64_t e = (int64_t)blockIdx.x * KB + threadIdx.x;
-    if (e >= (int64_t)K * K) return;
-    const int a = (int)(e % K), j = (int)(e / K);
-    const double* tj = T + (int64_t)j * KLD;
-    double s = Gs[(int64_t)a * ldg + j];  // T(j, j) = 1
-    for (int b = 0; b < j; ++b) s = fma(Gs[(int64_t)a * ldg + b], tj[b], s);
-    W[(int64_t)j * KLD + a] = s;
-}
-
-// G(i, j) = G(j, i) = sum_{a <= i} T(a, i) W(a, j) for i <= j < K, and (d != null)
-// d_i = sum_{a <= i} T(a, i) ds_a.
-__global__ __launch_bounds__(KB) void k_basis_left(int K, const double* __restrict__ T, const double* __restrict__ W,
-                                                   double* __restrict__ G, int ldg, const double* __restrict__ ds,
+// Column j = blockIdx.x of G = T^T Gs T (both triangles) for one of two Gram matrices (blockIdx.y),
+// Gs symmetric and T unit upper triangular: w = Gs t_j, then G(i, j) = t_i^T w for i <= j; and for the
+// first d = T^T ds.  Four groups of 64 threads share a sum over 16-row pieces (their loads in flight
+// together).  Bound by the latency of its loads: one launch for both matrices (K = 20: 5 us) where
+// the two products of each were a launch (3.6 to 4 us each).
+__global__ __launch_bounds__(KB) void k_basis_gram(int K, const double* __restrict__ T, const double* __restrict__ Gs0,
+                                                   const double* __restrict__ Gs1, const double* __restrict__ ds,
+                                                   double* __restrict__ G0, double* __restrict__ G1,
                                                    double* __restrict__ d) {
-    const int64_t e = (int64_t)blockIdx.x * KB + threadIdx.x;
-    if (e < (int64_t)K * K) {
-        const int i = (int)(e % K), j = (int)(e / K);
-        if (i <= j) {
-            const double* ti = T + (int64_t)i * KLD;
-            const double* wj = W + (int64_t)j * KLD;
-            double s = wj[i];
-            for (int a = 0; a < i; ++a) s = fma(ti[a], wj[a], s);
-            G[(int64_t)i * ldg + j] = s;
-            G[(int64_t)j * ldg + i] = s;
+    __shared__ double t[KMAX], w[KMAX], p[4][64];
+    const int j = blockIdx.x, lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+    const double* __restrict__ Gs = blockIdx.y ? Gs1 : Gs0;
+    double* __restrict__ G = blockIdx.y ? G1 : G0;
+    for (int b = threadIdx.x; b < K; b += KB) t[b] = b <= j ? T[(int64_t)j * KLD + b] : 0.0;
+    __syncthreads();
+    // sum over k of f(k), the four groups' pieces added in a fixed order; valid in group 0
+    auto shared_sum = [&](int n, auto f) {
+        double s = 0.0;
+        for (int k0 = 16 * grp; k0 < n; k0 += 64) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int k = k0 + q;
+                s = f(min(k, n - 1), k < n, s);
+            }
+        }
+        p[grp][lane] = s;
+        __syncthreads();
+        const double r = (p[0][lane] + p[1][lane]) + (p[2][lane] + p[3][lane]);
+        __syncthreads();
+        return r;
+    };
+    for (int a0 = 0; a0 < K; a0 += 64) {
+        const int a = min(a0 + lane, K - 1);
+        const double s = shared_sum(j + 1, [&](int b, bool in, double acc) {
+            return fma(Gs[(int64_t)b * KLD + a], in ? t[b] : 0.0, acc);
+        });
+        if (grp == 0 && a0 + lane < K) w[a0 + lane] = s;
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 <= j; i0 += 64) {
+        const int i = min(i0 + lane, j);
+        const double s = shared_sum(min(i0 + 64, j + 1), [&](int a, bool in, double acc) {
+            const int c = min(a, i);  // (T holds column i down to its diagonal)
+            return fma(T[(int64_t)i * KLD + c], in && a <= i ? w[a] : 0.0, acc);
+        });
+        if (grp == 0 && i0 + lane <= j) {
+            G[(int64_t)i * KLD + j] = s;
+            G[(int64_t)j * KLD + i] = s;
         }
     }
-    if (d && blockIdx.x == 0) {
-        for (int i = threadIdx.x; i < K; i += KB) {
-            const double* ti = T + (int64_t)i * KLD;
-            double s = ds[i];
-            for (int a = 0; a < i; ++a) s = fma(ti[a], ds[a], s);
-            d[i] = s;
-        }
+    if (blockIdx.y == 0) {  // d_j = t_j^T ds
+        const double s = shared_sum(j + 1, [&](int a, bool in, double acc) {
+            return fma(ds[a], in && lane == 0 ? t[a] : 0.0, acc);
+        });
+        if (threadIdx.x == 0) d[j] = s;
     }
 }
 
@@ -1366,36 +1420,35 @@ void basis_extend(Ctx& c, int64_t n, int K, const double* Vs, int64_t ld, double
     double* part = static_cast<double*>(c.work("mdot_part", sizeof(double) * (size_t)MAX_PART * (KMAX + 1)));
     int* keep = static_cast<int*>(c.work("cgs_flag", sizeof(int)));
     double* hc = static_cast<double*>(c.work("basis_hc", sizeof(double) * KMAX));
-    auto dots = [&](const double* xe, const int* skip, const char* tname) {
-        const int Kt = K + (xe ? 1 : 0);
-        {
-            ScopedTime st(&c, tname, skip ? 0.0 : (double)n * (8.0 * K + 8.0), skip ? 0.0 : 2.0 * n * Kt);
-            launch_mdot<double, double>(c, nb, n, K, Vs, ld, (const double*)r, xe, part, skip);
-        }
-        mdot_final(c, nb, Kt, part, 1.0, h, nullptr, 0, 0, nullptr, skip);
-    };
+    // up to 256 chunks the check and the append sum the partials themselves (Kt x 256 loads by one
+    // workgroup); with more, a launch of a workgroup per column does
+    const bool own = nb <= 256;
     // h = Vs^T r and h[K] = ||r||^2 in one pass
-    dots(r, nullptr, "mdot");
-    hipLaunchKernelGGL(k_basis_check, dim3(1), dim3(KB), 0, c.stream, K, (const double*)T, (const double*)h,
-                       (const double*)(h + K), hc, keep);
+    auto dots = [&](const int* skip, const char* tname) {
+        {
+            ScopedTime st(&c, tname, skip ? 0.0 : (double)n * (8.0 * K + 8.0), skip ? 0.0 : 2.0 * n * (K + 1));
+            launch_mdot<double, double>(c, nb, n, K, Vs, ld, (const double*)r, r, part, skip);
+        }
+        if (!own) mdot_final(c, nb, K + 1, part, 1.0, h, nullptr, 0, 0, nullptr, skip);
+    };
+    dots(nullptr, "mdot");
+    hipLaunchKernelGGL(k_basis_check, dim3(1), dim3(KB), 0, c.stream, K, own ? nb : 0, (const double*)part,
+                       (const double*)T, h, hc, keep);
     MMOF_LAUNCH_CHECK();
-    // where r lies mostly in the basis: r <- r - V V^T r explicitly (||r||^2 into h[K]) and
-    // h = Vs^T r again; these launches return at once otherwise
-    gemv_fused_impl<double, double>(c, n, K, Vs, ld, hc, -1.0, r, 1.0, r, (double*)nullptr, nullptr, h + K, keep,
+    // where r lies mostly in the basis: r <- r - V V^T r explicitly and h = Vs^T r, ||r||^2 again;
+    // these launches return at once otherwise
+    gemv_fused_impl<double, double>(c, n, K, Vs, ld, hc, -1.0, r, 1.0, r, (double*)nullptr, nullptr, nullptr, keep,
                                     "cgs_second");
-    dots(nullptr, keep, "cgs_second");
-    hipLaunchKernelGGL(k_basis_append, dim3(1), dim3(KB), 0, c.stream, K, T, (const double*)h,
-                       (const double*)(h + K), sq);
+    dots(keep, "cgs_second");
+    hipLaunchKernelGGL(k_basis_append, dim3(1), dim3(KB), 0, c.stream, K, own ? nb : 0, (const double*)part, T, h,
+                       (const int*)keep, sq);
     MMOF_LAUNCH_CHECK();
 }
 
-void basis_gram(Ctx& c, int K, const double* T, const double* Gs, const double* ds, double* G, double* d) {
+void basis_gram(Ctx& c, int K, const double* T, const double* Gs0, const double* Gs1, const double* ds, double* G0,
+                double* G1, double* d) {
     if (K <= 0) return;
-    double* W = static_cast<double*>(c.work("basis_W", sizeof(double) * KLD * KLD));
-    const unsigned nb = (unsigned)cdiv((int64_t)K * K, KB);
-    hipLaunchKernelGGL(k_basis_right, dim3(nb), dim3(KB), 0, c.stream, K, Gs, KLD, T, W);
-    MMOF_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_basis_left, dim3(nb), dim3(KB), 0, c.stream, K, T, (const double*)W, G, KLD, ds, d);
+    hipLaunchKernelGGL(k_basis_gram, dim3((unsigned)K, 2), dim3(KB), 0, c.stream, K, T, Gs0, Gs1, ds, G0, G1, d);
     MMOF_LAUNCH_CHECK();
 }
 

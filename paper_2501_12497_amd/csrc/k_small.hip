@@ -366,7 +366,8 @@ __device__ void dp_root(EV&& ev, double trA, double trT, double target, double b
 __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restrict__ GA, const double* __restrict__ GT,
                                                     const double* __restrict__ dvec, const double* __restrict__ sc,
                                                     double fixed_lambda, double* __restrict__ zout,
-                                                    double* __restrict__ res, double* __restrict__ lam_out) {
+                                                    double* __restrict__ res, double* __restrict__ lam_out,
+                                                    const double* __restrict__ Tb, double* __restrict__ zt) {
     __shared__ SmallLds s;
     const int i = threadIdx.x;
     // coalesced loads: each instruction moves one contiguous row of the matrices, eight rows of both
@@ -398,7 +399,8 @@ __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restr
     dp_root([&](double l, bool deriv) { return evaluate(s, K, l, bb, d, deriv, nfac); }, trA, trT, target, bb, sc[2],
             fixed_lambda, e, lam, status);
     if (!e.ok) status = 4;
-    if (i < K) zout[i] = e.ok ? e.z : 0.0;
+    const double z = e.ok && i < K ? e.z : 0.0;
+    if (i < K) zout[i] = z;
     if (i == 0) {
         res[0] = lam;
         res[1] = e.D2;
@@ -406,6 +408,17 @@ __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restr
         res[3] = (double)nfac;
         if (lam_out) lam_out[0] = lam;
     }
+    if (!zt) return;
+    // T z (T(k, j) = Tb[j * KLD + k], unit diagonal): the columns' entries eight at a time
+    double a = z;
+    for (int j0 = 1; Tb && j0 < K; j0 += 8) {
+        double t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t[q] = j0 + q < K && i < j0 + q ? Tb[(int64_t)(j0 + q) * KLD + i] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) a = fma(t[q], bcast(z, min(j0 + q, KMAX_SMALL - 1)), a);
+    }
+    if (i < K) zt[i] = a;
 }
 
 // ----------------------------------------------------------------------------- 64 < K <= 256
@@ -691,16 +704,20 @@ __global__ __launch_bounds__(BIG_T) void k_small_solve_big(int K, const double* 
 
 
 void small_solve(Ctx& c, int K, const double* GA, const double* GT, const double* d, const double* sc,
-                 double fixed_lambda, double* z, double* res, double* lam_out) {
+                 double fixed_lambda, double* z, double* res, double* lam_out, const double* T, double* zt) {
     MMOF_CHECK(K >= 1 && K <= KMAX, MMOF_ERR_SHAPE, "Krylov basis size out of range");
     ScopedTime st(&c, "small_solve");
     if (K <= KMAX_SMALL) {
         hipLaunchKernelGGL(k_small_solve, dim3(1), dim3(64), 0, c.stream, K, GA, GT, d, sc, fixed_lambda, z, res,
-                           lam_out);
+                           lam_out, T, zt);
     } else {
         double* Lg = static_cast<double*>(c.work("small_L", sizeof(double) * (size_t)KLD * KLD));
         hipLaunchKernelGGL(k_small_solve_big, dim3(1), dim3(BIG_T), 0, c.stream, K, GA, GT, d, sc, fixed_lambda, Lg,
                            z, res, lam_out);
+        if (zt && T)
+            basis_coef(c, K, T, z, zt);
+        else if (zt)
+            MMOF_HIP(hipMemcpyAsync(zt, z, sizeof(double) * (size_t)K, hipMemcpyDeviceToDevice, c.stream));
     }
     MMOF_LAUNCH_CHECK();
 }

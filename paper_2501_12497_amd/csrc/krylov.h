@@ -51,9 +51,10 @@ void basis_identity(Ctx& c, int K0, double* T);
 // launches of that pass return at once otherwise).  K < KMAX.
 void basis_extend(Ctx& c, int64_t n, int K, const double* Vs, int64_t ld, double* r, double* T, double* h,
                   double* sq);
-// G = T^T Gs T (K x K, leading dimension KLD, written symmetric) and, when ds is not null,
+// G = T^T Gs T for two symmetric matrices (K x K, leading dimension KLD, written symmetric) and
 // d = T^T ds.
-void basis_gram(Ctx& c, int K, const double* T, const double* Gs, const double* ds, double* G, double* d);
+void basis_gram(Ctx& c, int K, const double* T, const double* Gs0, const double* Gs1, const double* ds, double* G0,
+                double* G1, double* d);
 // zt = T z: the coefficients in Vs of V z.
 void basis_coef(Ctx& c, int K, const double* T, const double* z, double* zt);
 // s = sqrt(s2[0]) (written to s1 when not null); out_d = x / s and out_t = (TO)(x / s)
@@ -109,8 +110,10 @@ void weight_mul(Ctx& c, int64_t n, const double* w, const TX* x, TX* y);
 // Writes z (K), and res[0] = lambda, res[1] = discrepancy^2, res[2] = status (0 root, 2 clamped,
 // 4 factorization failure), res[3] = factorizations done.  fixed_lambda > 0 skips the
 // discrepancy principle.  sc[2] is the warm start (previous lambda, 0: none); when
-// lam_out is not null the chosen lambda is also written there.
+// lam_out is not null the chosen lambda is also written there.  zt (may be null) = T z (basis_coef),
+// or z where T is null.
 void small_solve(Ctx& c, int K, const double* GA, const double* GT, const double* d, const double* sc,
-                 double fixed_lambda, double* z, double* res, double* lam_out = nullptr);
+                 double fixed_lambda, double* z, double* res, double* lam_out = nullptr, const double* T = nullptr,
+                 double* zt = nullptr);
 
 }  // namespace mmof

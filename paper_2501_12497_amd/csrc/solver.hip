@@ -422,16 +422,9 @@ struct Solver {
     // The Gram matrices and d of the true basis from those of the stored columns, the
     // projected solve, and the coefficients of u = V z in the stored columns.
     void projected(int Kg) {
-        if (implicit) {
-            basis_gram(c, Kg, Tb, GAs, ds, GA, dvec);
-            basis_gram(c, Kg, Tb, GTs, nullptr, GT, nullptr);
-        }
-        small_solve(c, Kg, GA, GT, dvec, sc, p.fixed_lambda, z, scal + 8, sc + 2);
+        if (implicit) basis_gram(c, Kg, Tb, GAs, GTs, ds, GA, GT, dvec);
         std::swap(zt, zt_prev);
-        if (implicit)
-            basis_coef(c, Kg, Tb, z, zt);
-        else
-            MMOF_HIP(hipMemcpyAsync(zt, z, sizeof(double) * (size_t)Kg, hipMemcpyDeviceToDevice, c.stream));
+        small_solve(c, Kg, GA, GT, dvec, sc, p.fixed_lambda, z, scal + 8, sc + 2, implicit ? Tb : nullptr, zt);
     }
     // The new direction r against the basis of K columns: ||r'||^2 into sq; r' / ||r'|| becomes
     // column K of V (explicit passes) or of Vs (implicit basis: r' = r, T gets column K).
