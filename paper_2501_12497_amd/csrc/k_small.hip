@@ -14,12 +14,8 @@
 // blocks of the factored columns, the factor in LDS.  Broadcasts within 16 lanes are DPP operands of
 // the FMAs.  D^2 and its derivative only need forward solves (d^T z = ||L^{-1} d||^2,
 // w^T M^{-1} w = ||L^{-1} w||^2) plus one backward solve for z.
-// 64 < K <= 256: four wavefronts, thread i owning row i; the factor lives in an L2-resident
-// global workspace (too large for the LDS at these sizes), built and used in 16-column
-// blocks: the wave holding a diagonal block factors it with readlane broadcasts, the other
-// waves form their panel rows from it through the LDS, and every thread updates its own row
-// of the trailing matrix; the triangular solves go block by block the same way (one barrier
-// per block).  The root search is the same for both.
+// 64 < K <= 256: eight wavefronts by the same steps, the matrix in their accumulators and the factor in
+// an L2-resident global workspace.  The root search is the same for both.
 #include "dev.h"
 #include "krylov.h"
 
@@ -55,18 +51,6 @@ __device__ __forceinline__ double wave_sum64(double v) {
 }
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
-
-// 1/sqrt(x) for x > 0: hardware estimate refined by two Newton steps r <- r (3 - x r^2) / 2
-// (each step squares the relative error), a short dependency chain on the pivot path.
-__device__ __forceinline__ double rsqrt_nr(double x) {
-    double r = __builtin_amdgcn_rsq(x);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const double e = fma(-x * r, r, 1.0);
-        r = fma(0.5 * r, e, r);
-    }
-    return r;
-}
 
 // 1/x for x > 0: hardware estimate refined by two Newton steps (each squares the relative error), a
 // short dependency chain on the pivot path.
@@ -422,250 +406,229 @@ __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restr
 }
 
 // ----------------------------------------------------------------------------- 64 < K <= 256
+//
+// Eight waves.  The lower 16 x 16 blocks of M stay in the accumulators of the waves (block b of the column-major list on
+// wave b % 8: 17 blocks each at K = 256), a block column passes through the LDS to be factored by the waves that own its
+// rows, with the steps of factor(), and updates the blocks right of it on the matrix cores from there.  The factor goes to an
+// L2-resident workspace, by columns and by rows, for the triangular solves: thread i < 256 owns row i, and every row of
+// 16 lanes solves a copy of the diagonal block (one barrier per block).  An evaluation takes 34 us at K = 80, 67 at 130
+// and 112 at 200 (126, 261 and 514 with the trailing matrix in L2, updated entry by entry).
 
-static constexpr int BIG_T = KMAX;   // threads of the multi-wave solve: thread i owns row i
+static constexpr int BIG_T = 512, BIG_W = BIG_T / 64;  // threads, waves
+static constexpr int BIG_NB = KMAX / 16;                // block columns
+static constexpr int BIG_SLOTS = (BIG_NB * (BIG_NB + 1) / 2 + BIG_W - 1) / BIG_W;  // blocks per wave
 
 struct BigLds {
-    double P[KMAX][17];   // panel rows L[i][c0..c0+15] of the current block column (padded)
-    double D[16][17];     // the diagonal block L_JJ
-    double inv_d[16];     // 1 / L_JJ diagonal
-    double vec[KMAX];     // finished entries of a triangular solve / the vector of a product
-    double red[BIG_T / 64];
+    double P[2][KMAX][17];  // the current block column (padded), two in turn
+    double piv[KMAX], inv[KMAX];
+    double vec[KMAX];       // the vector of a product
+    double x[2][16];        // a block's right-hand side, two in turn
+    double red[BIG_W], red2[BIG_W];
     int fail;
 };
 
-// Sum over the workgroup, bitwise identical in every thread (wave sums broadcast from lane
-// 0, then the wave totals added in a fixed order from the LDS).
-__device__ __forceinline__ double block_sum_uniform(BigLds& s, double v) {
-    v = wave_sum64(v);
+// Sums of two values over the workgroup, bitwise identical in every thread (the wave totals added in a fixed order).
+__device__ __forceinline__ void block_sum2(BigLds& s, double& a, double& b) {
+    wave_sum2(a, b);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) s.red[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 0) {
+        s.red[threadIdx.x >> 6] = a;
+        s.red2[threadIdx.x >> 6] = b;
+    }
     __syncthreads();
-    double r = 0.0;
+    a = b = 0.0;
 #pragma unroll
-    for (int w = 0; w < BIG_T / 64; ++w) r += s.red[w];
-    return r;
+    for (int w = 0; w < BIG_W; ++w) {
+        a += s.red[w];
+        b += s.red2[w];
+    }
 }
 
-// Cholesky of M = A + lam T (A, T row-major with leading dimension KLD, symmetric) into the
-// lower triangle of Lg (column-major: L[r][c] at Lg[c * KLD + r]).  Returns false, uniformly,
-// on a non-positive pivot; on success inv = 1 / L[i][i] for this thread's row.
-__device__ bool chol_big(BigLds& s, double* __restrict__ Lg, const double* __restrict__ A,
-                         const double* __restrict__ T, int K, double lam, double& inv) {
-    const int i = threadIdx.x;
-    const bool mine = i < K;
-    const int lane = i & 63, wave = i >> 6;
-    // (every thread is past the previous factorization's reads of Lg and s.fail)
-    __syncthreads();
-    // M (lower triangle and the diagonal; A[i][c] = A[c][i] is read along row c: coalesced)
-    if (mine)
-        for (int c = 0; c <= i; ++c) Lg[(int64_t)c * KLD + i] = fma(lam, T[(int64_t)c * KLD + i], A[(int64_t)c * KLD + i]);
-    if (i == 0) s.fail = 0;
-    __syncthreads();
-    double my_inv = 0.0;
-    const int nbk = (K + 15) >> 4;
+// M = A + lam T = U diag(p) U^T as in factor() (A, T row-major with leading dimension KLD): -U by columns to
+// L[c * KLD + r] and by rows to L[(KMAX + r) * KLD + c], zeros on and above the diagonal of its diagonal blocks; p and 1/p
+// to the LDS.  Returns false, uniformly, on a pivot that is not positive.
+__device__ bool factor_big(BigLds& s, double* L, const double* __restrict__ A, const double* __restrict__ T, int K,
+                           double lam) {
+    const int lane = threadIdx.x & 63, r = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nbk = (K + 15) >> 4, nblk = nbk * (nbk + 1) / 2;
+    if (threadIdx.x == 0) s.fail = 0;
+    dbl4 acc[BIG_SLOTS];
+    int bi[BIG_SLOTS], bj[BIG_SLOTS];  // block row and column of a slot (uniform)
+#pragma unroll
+    for (int q = 0; q < BIG_SLOTS; ++q) {
+        int b = q * BIG_W + wave, J = 0;
+        const bool used = b < nblk;
+        while (used && b >= nbk - J) b -= nbk - J++;
+        bi[q] = used ? J + b : -1;
+        bj[q] = used ? J : -1;
+        if (!used) continue;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = (bi[q] << 4) + lk + 4 * v, col = (bj[q] << 4) + r;
+            const bool in = row < K && col < K;
+            const int64_t o = (int64_t)min(row, K - 1) * KLD + min(col, K - 1);
+            const double m = fma(lam, T[o], A[o]);
+            acc[q][v] = in ? m : (row == col ? 1.0 : 0.0);
+        }
+    }
     for (int J = 0; J < nbk; ++J) {
         const int c0 = J << 4;
-        const int nc = min(16, K - c0);
-        const int w0 = c0 >> 6;   // the wave holding rows c0 .. c0 + 15
-        double a[16];
+        double(*P)[17] = s.P[J & 1];
 #pragma unroll
-        for (int c = 0; c < 16; ++c) a[c] = (mine && c < nc && i >= c0 + c) ? Lg[(int64_t)(c0 + c) * KLD + i] : 0.0;
-        if (wave == w0) {
-            // right-looking factorization of the block column in registers: the pivot and the
-            // finished entries of the diagonal rows come from their lanes (readlane)
-            // (fully unrolled with guards: a register array indexed by a loop bound known only at
-            // run time would be placed in scratch memory)
-            bool ok = true;
+        for (int q = 0; q < BIG_SLOTS; ++q) {
+            if (bj[q] != J) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) P[(bi[q] << 4) + lk + 4 * v][r] = acc[q][v];
+        }
+        __syncthreads();
+        const int i = (wave << 6) + lane;
+        if (wave < 4 && (wave << 6) + 63 >= c0 && (wave << 6) < (nbk << 4)) {
+            double D[16], Pr[16];
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                if (c < nc && ok) {
-                    const double piv = bcast(a[c], (c0 + c) & 63);
-                    if (!(piv > 0.0)) {
-                        ok = false;   // uniform: the pivot is broadcast
-                    } else {
-                        const double r = rsqrt_nr(piv);
-                        const double l = a[c] * r;
-                        a[c] = l;
-                        if (i == c0 + c) my_inv = r;
-#pragma unroll
-                        for (int c2 = c + 1; c2 < 16; ++c2)
-                            if (c2 < nc) a[c2] -= l * bcast(l, (c0 + c2) & 63);
-                    }
-                }
+                D[c] = P[c0 + r][c];
+                Pr[c] = P[i][c];  // (rows above the block: nothing reads what they become)
             }
-            if (!ok) {
-                if (lane == 0) s.fail = 1;
-            } else if (i >= c0 && i < c0 + nc) {
+            bool ok = true;
+            double pv = 1.0, iv = 1.0;
+            static_for<0, 16>([&](auto C) {
+                constexpr int c = decltype(C)::value;
+                const double p = row16_bcast<c>(D[c]);
+                ok = ok && p > 0.0;
+                const double q = rcp_nr(p);
+                pv = r == c ? p : pv;
+                iv = r == c ? q : iv;
+                const double nu = D[c] * -q, nl = Pr[c] * -q;
+                fmac_bcast<c + 1, 15 - c>(D + c + 1, D[c], nu);
+                fmac_bcast<c + 1, 15 - c>(Pr + c + 1, D[c], nl);
+                Pr[c] = nl;
+            });
+            if (!ok) s.fail = 1;  // (the same on every wave that factors the block)
+            const int rr = i - c0;
+            if (rr >= 0 && rr < 16) {
+                s.piv[i] = pv;
+                s.inv[i] = iv;
+            }
+            if (rr >= 0 && i < (nbk << 4)) {
 #pragma unroll
-                for (int c = 0; c < 16; ++c) s.D[i - c0][c] = (c <= i - c0) ? a[c] : 0.0;
-                s.inv_d[i - c0] = my_inv;
+                for (int c = 0; c < 16; ++c) {
+                    const double v = rr > c ? Pr[c] : 0.0;
+                    P[i][c] = v;
+                    L[(int64_t)(c0 + c) * KLD + i] = v;
+                    L[(int64_t)(KMAX + i) * KLD + c0 + c] = v;
+                }
             }
         }
         __syncthreads();
         if (s.fail) return false;
-        if (wave != w0 && mine && i >= c0 + 16) {
-            // panel rows of the other waves: a_i L_JJ^{-T}, the same operations in the same order
-            // as the in-wave factorization performs on its own rows
 #pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                if (c < nc) {
-                    double v = a[c];
+        for (int q = 0; q < BIG_SLOTS; ++q) {
+            if (bj[q] <= J) continue;
 #pragma unroll
-                    for (int c2 = 0; c2 < 16; ++c2)
-                        if (c2 < c) v -= a[c2] * s.D[c][c2];
-                    a[c] = v * s.inv_d[c];
-                }
+            for (int k = 0; k < 4; ++k) {
+                const double av = P[(bi[q] << 4) + r][4 * k + lk];
+                const double bv = -s.piv[c0 + 4 * k + lk] * P[(bj[q] << 4) + r][4 * k + lk];
+                acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[q], 0, 0, 0);
             }
         }
-        if (mine && i >= c0) {
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                if (c < nc) {
-                    const double v = (i >= c0 + c) ? a[c] : 0.0;
-                    Lg[(int64_t)(c0 + c) * KLD + i] = v;
-                    s.P[i][c] = v;
-                }
-            }
-        }
-        __syncthreads();
-        // trailing update of this thread's row: M[i][j] -= sum_c L[i][c0+c] L[j][c0+c], c0+16 <= j <= i,
-        // four columns j at a time (independent sums), each sum in column order
-        if (mine && i >= c0 + 16) {
-            int j = c0 + 16;
-            for (; j + 3 <= i; j += 4) {
-                double m[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) m[q] = Lg[(int64_t)(j + q) * KLD + i];
-#pragma unroll
-                for (int c = 0; c < 16; ++c)
-                    if (c < nc) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) m[q] -= a[c] * s.P[j + q][c];
-                    }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) Lg[(int64_t)(j + q) * KLD + i] = m[q];
-            }
-            for (; j <= i; ++j) {
-                double m = Lg[(int64_t)j * KLD + i];
-#pragma unroll
-                for (int c = 0; c < 16; ++c)
-                    if (c < nc) m -= a[c] * s.P[j][c];
-                Lg[(int64_t)j * KLD + i] = m;
-            }
-        }
-        __syncthreads();
     }
-    inv = my_inv;
     return true;
 }
 
-// y = L^{-1} b, one entry per thread; block by block: the wave of a diagonal block solves its
-// 16 entries with readlane broadcasts and publishes them, then every row below subtracts the
-// block's contribution (the subtractions of a row in column order, as in the one-wave solve).
-__device__ double fwd_big(BigLds& s, const double* __restrict__ Lg, int K, double inv, double b) {
-    const int i = threadIdx.x;
-    const bool mine = i < K;
-    const int wave = i >> 6;
-    double y = mine ? b : 0.0;
-    __syncthreads();
-    const int nbk = (K + 15) >> 4;
+// y = U^{-1} b, one entry per thread i < KMAX.
+__device__ double fwd_big(BigLds& s, const double* L, int K, double b) {
+    const int i = threadIdx.x, r = i & 15, nbk = (K + 15) >> 4;
+    double y = i < K ? b : 0.0;
     for (int J = 0; J < nbk; ++J) {
         const int c0 = J << 4;
-        const int nc = min(16, K - c0);
-        if (wave == (c0 >> 6)) {
-            double l[16];
-#pragma unroll
-            for (int c = 0; c < 16; ++c) l[c] = (mine && c < nc && i > c0 + c) ? Lg[(int64_t)(c0 + c) * KLD + i] : 0.0;
+        const bool work = (i | 63) >= c0 && (i & ~63) < (nbk << 4);  // (whole waves)
+        double l[16], d[16];
+        if (work) {
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                if (c < nc) {
-                    const double yc = bcast(y * inv, (c0 + c) & 63);
-                    if (i == c0 + c)
-                        y = yc;
-                    else if (i > c0 + c && i < c0 + nc)
-                        y = fma(-l[c], yc, y);
-                }
+                d[c] = L[(int64_t)(c0 + c) * KLD + c0 + r];
+                l[c] = L[(int64_t)(c0 + c) * KLD + i];
             }
-            if (i >= c0 && i < c0 + nc) s.vec[i] = y;
         }
+        if ((i >> 4) == J) s.x[J & 1][r] = y;
         __syncthreads();
-        if (mine && i >= c0 + 16) {
-            double l[16];
-#pragma unroll
-            for (int c = 0; c < 16; ++c) l[c] = c < nc ? Lg[(int64_t)(c0 + c) * KLD + i] : 0.0;
-#pragma unroll
-            for (int c = 0; c < 16; ++c)
-                if (c < nc) y = fma(-l[c], s.vec[c0 + c], y);
+        if (work) {
+            double x = s.x[J & 1][r], below = y;
+            static_for<0, 4>([&](auto Q) {
+                constexpr int c = 4 * decltype(Q)::value;
+                solve_steps<c, 1>(x, below, d + c, l + c);
+            });
+            y = (i >> 4) == J ? x : (i > c0 ? below : y);
         }
     }
-    return mine ? y : 0.0;
+    return i < K ? y : 0.0;
 }
 
-// z = L^{-T} y, blocks from the last one up; a row reads the entries of its own column of L.
-__device__ double bwd_big(BigLds& s, const double* __restrict__ Lg, int K, double inv, double y) {
-    const int i = threadIdx.x;
-    const bool mine = i < K;
-    const int wave = i >> 6;
-    double z = mine ? y : 0.0;
-    __syncthreads();
-    const int nbk = (K + 15) >> 4;
+// z = U^{-T} y, blocks from the last one up.
+__device__ double bwd_big(BigLds& s, const double* L, int K, double y) {
+    const int i = threadIdx.x, r = i & 15, nbk = (K + 15) >> 4;
+    const double* R = L + (int64_t)KMAX * KLD;  // by rows
+    double z = i < K ? y : 0.0;
+    __syncthreads();  // (the last block of a forward solve is still read from s.x)
     for (int J = nbk - 1; J >= 0; --J) {
         const int c0 = J << 4;
-        const int nc = min(16, K - c0);
-        if (wave == (c0 >> 6)) {
-            double l[16];   // L[c0 + c][i] for c0 + c > i
+        const bool work = (i & ~63) <= c0 + 15;  // (whole waves)
+        double l[16], d[16];
+        if (work) {
 #pragma unroll
-            for (int c = 0; c < 16; ++c) l[c] = (mine && c < nc && c0 + c > i) ? Lg[(int64_t)i * KLD + c0 + c] : 0.0;
-#pragma unroll
-            for (int c = 15; c >= 0; --c) {
-                if (c < nc) {
-                    const double zc = bcast(z * inv, (c0 + c) & 63);
-                    if (i == c0 + c)
-                        z = zc;
-                    else if (i >= c0 && i < c0 + c)
-                        z = fma(-l[c], zc, z);
-                }
+            for (int c = 0; c < 16; ++c) {
+                d[c] = R[(int64_t)(c0 + c) * KLD + c0 + r];
+                l[c] = R[(int64_t)(c0 + c) * KLD + i];
             }
-            if (i >= c0 && i < c0 + nc) s.vec[i] = z;
         }
+        if ((i >> 4) == J) s.x[J & 1][r] = z;
         __syncthreads();
-        if (mine && i < c0) {
-            double l[16];
-#pragma unroll
-            for (int c = 0; c < 16; ++c) l[c] = c < nc ? Lg[(int64_t)i * KLD + c0 + c] : 0.0;
-#pragma unroll
-            for (int c = 15; c >= 0; --c)
-                if (c < nc) z = fma(-l[c], s.vec[c0 + c], z);
+        if (work) {
+            double x = s.x[J & 1][r], above = z;
+            static_for<0, 4>([&](auto Q) {
+                constexpr int c = 15 - 4 * decltype(Q)::value;
+                solve_steps<c, -1>(x, above, d + c, l + c);
+            });
+            z = (i >> 4) == J ? x : (i < c0 ? above : z);
         }
     }
-    return mine ? z : 0.0;
+    __syncthreads();
+    return i < K ? z : 0.0;
 }
 
-__device__ Eval evaluate_big(BigLds& s, double* __restrict__ Lg, const double* __restrict__ GA,
-                             const double* __restrict__ GT, int K, double lam, double bb, double d, bool deriv,
-                             int& nfac) {
+__device__ Eval evaluate_big(BigLds& s, double* L, const double* __restrict__ GA, const double* __restrict__ GT, int K,
+                             double lam, double bb, double d, bool deriv, int& nfac) {
     const int i = threadIdx.x;
     Eval e{false, 0.0, 0.0, 0.0};
     ++nfac;
-    double inv = 0.0;
-    if (!chol_big(s, Lg, GA, GT, K, lam, inv)) return e;
+    __syncthreads();  // (every thread is past the previous evaluation's reads)
+    if (!factor_big(s, L, GA, GT, K, lam)) return e;
     e.ok = true;
-    const double y = fwd_big(s, Lg, K, inv, d);
-    e.z = bwd_big(s, Lg, K, inv, y);
-    // w = T z (T symmetric: row i read along column i, coalesced)
+    const double inv = i < K ? s.inv[i] : 0.0;
+    const double y = fwd_big(s, L, K, d), yp = y * inv;
+    e.z = bwd_big(s, L, K, yp);
+    // w = T z (T symmetric: row i read along column i, coalesced), the odd columns by the upper threads
+    if (i < KMAX) s.vec[i] = e.z;
     __syncthreads();
-    s.vec[i] = e.z;
-    __syncthreads();
+    const int row = i & (KMAX - 1);
     double w = 0.0;
-    if (i < K)
-        for (int j = 0; j < K; ++j) w += GT[(int64_t)j * KLD + i] * s.vec[j];
-    const double dz = block_sum_uniform(s, y * y);
-    const double zw = block_sum_uniform(s, e.z * w);
+    if (row < K) {
+#pragma unroll 8
+        for (int j = i >> 8; j < K; j += 2) w = fma(GT[(int64_t)j * KLD + row], s.vec[j], w);
+    }
+    __syncthreads();
+    if (i >= KMAX) s.vec[row] = w;
+    __syncthreads();
+    w = i < K ? w + s.vec[i] : 0.0;
+    double dz = y * yp, zw = e.z * w;  // d^T z = y^T diag(1/p) y
+    block_sum2(s, dz, zw);
     e.D2 = bb - dz - lam * zw;
     if (deriv) {
-        const double q = fwd_big(s, Lg, K, inv, w);
-        e.dD2 = 2.302585092994046 * 2.0 * lam * lam * block_sum_uniform(s, q * q);
+        const double q = fwd_big(s, L, K, w);
+        double qq = q * q * inv, none = 0.0;
+        block_sum2(s, qq, none);
+        e.dD2 = 2.302585092994046 * 2.0 * lam * lam * qq;
     }
     return e;
 }
@@ -674,7 +637,7 @@ __global__ __launch_bounds__(BIG_T) void k_small_solve_big(int K, const double* 
                                                            const double* __restrict__ GT,
                                                            const double* __restrict__ dvec,
                                                            const double* __restrict__ sc, double fixed_lambda,
-                                                           double* __restrict__ Lg, double* __restrict__ zout,
+                                                           double* L, double* __restrict__ zout,
                                                            double* __restrict__ res, double* __restrict__ lam_out) {
     __shared__ BigLds s;
     const int i = threadIdx.x;
@@ -686,10 +649,11 @@ __global__ __launch_bounds__(BIG_T) void k_small_solve_big(int K, const double* 
     Eval e{false, 0.0, 0.0, 0.0};
     double trA = 0.0, trT = 0.0;
     if (!(fixed_lambda > 0.0)) {
-        trA = block_sum_uniform(s, i < K ? GA[(int64_t)i * KLD + i] : 0.0);
-        trT = block_sum_uniform(s, i < K ? GT[(int64_t)i * KLD + i] : 0.0);
+        trA = i < K ? GA[(int64_t)i * KLD + i] : 0.0;
+        trT = i < K ? GT[(int64_t)i * KLD + i] : 0.0;
+        block_sum2(s, trA, trT);
     }
-    dp_root([&](double l, bool deriv) { return evaluate_big(s, Lg, GA, GT, K, l, bb, d, deriv, nfac); }, trA, trT,
+    dp_root([&](double l, bool deriv) { return evaluate_big(s, L, GA, GT, K, l, bb, d, deriv, nfac); }, trA, trT,
             target, bb, sc[2], fixed_lambda, e, lam, status);
     if (!e.ok) status = 4;
     if (i < K) zout[i] = e.ok ? e.z : 0.0;
@@ -702,7 +666,6 @@ __global__ __launch_bounds__(BIG_T) void k_small_solve_big(int K, const double* 
     }
 }
 
-
 void small_solve(Ctx& c, int K, const double* GA, const double* GT, const double* d, const double* sc,
                  double fixed_lambda, double* z, double* res, double* lam_out, const double* T, double* zt) {
     MMOF_CHECK(K >= 1 && K <= KMAX, MMOF_ERR_SHAPE, "Krylov basis size out of range");
@@ -711,7 +674,7 @@ void small_solve(Ctx& c, int K, const double* GA, const double* GT, const double
         hipLaunchKernelGGL(k_small_solve, dim3(1), dim3(64), 0, c.stream, K, GA, GT, d, sc, fixed_lambda, z, res,
                            lam_out, T, zt);
     } else {
-        double* Lg = static_cast<double*>(c.work("small_L", sizeof(double) * (size_t)KLD * KLD));
+        double* Lg = static_cast<double*>(c.work("small_L", sizeof(double) * 2 * (size_t)KLD * KLD));
         hipLaunchKernelGGL(k_small_solve_big, dim3(1), dim3(BIG_T), 0, c.stream, K, GA, GT, d, sc, fixed_lambda, Lg,
                            z, res, lam_out);
         if (zt && T)
