@@ -40,10 +40,21 @@ def _release_all():
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # (every pointer argument is declared c_void_p)
 
 
 def _dt(*ts: torch.Tensor) -> int:
+    first = None
+    for t in ts:
+        if t is not None:
+            d = t.dtype
+            if first is None:
+                first = d
+            elif d is not first:
+                break
+    else:
+        if first in _DT:
+            return _DT[first]
     dts = {t.dtype for t in ts if t is not None}
     if len(dts) != 1 or next(iter(dts)) not in _DT:
         raise TypeError(f"tensors must share one dtype, float32 or float64 (got {dts})")
@@ -86,7 +97,8 @@ class Context:
 
     def bind(self):
         """Point the context at torch's current stream (call before every launch)."""
-        check(self.lib.mmof_set_stream(self.h, C.c_void_p(torch.cuda.current_stream(self.device).cuda_stream)))
+        # (the stream's handle without the Stream object of torch.cuda.current_stream: 0.3 us a call for 1.5)
+        check(self.lib.mmof_set_stream(self.h, torch._C._cuda_getCurrentRawStream(self.device)))
         return self.h
 
     def close(self):
@@ -131,6 +143,7 @@ class Stack:
     sizes: List[Tuple[int, int, int]]
     _arrs: tuple = field(default=None, repr=False)
     _s: object = field(default=None, repr=False)
+    _n: tuple = field(default=None, repr=False)   # lengths, fixed with the library's copy of the sizes
 
     def __post_init__(self):
         self.sizes = [tuple(int(v) for v in s) for s in self.sizes]
@@ -139,6 +152,8 @@ class Stack:
         nx = (C.c_int32 * len(self.sizes))(*[s[2] for s in self.sizes])
         self._arrs = (nt, ny, nx)
         self._s = _lib.mmof_stack(len(self.sizes), nt, ny, nx)
+        self._n = (sum(t * y * x for t, y, x in self.sizes), sum((t - 1) * y * x for t, y, x in self.sizes),
+                   sum(t * y * (x - 1) for t, y, x in self.sizes), sum(t * (y - 1) * x for t, y, x in self.sizes))
 
     @classmethod
     def single(cls, n_t: int, ny: int, nx: int) -> "Stack":
@@ -150,19 +165,19 @@ class Stack:
 
     @property
     def n(self) -> int:
-        return sum(t * y * x for t, y, x in self.sizes)
+        return self._n[0]
 
     @property
     def n_pair_px(self) -> int:
-        return sum((t - 1) * y * x for t, y, x in self.sizes)
+        return self._n[1]
 
     @property
     def n_gx(self) -> int:
-        return sum(t * y * (x - 1) for t, y, x in self.sizes)
+        return self._n[2]
 
     @property
     def n_gy(self) -> int:
-        return sum(t * (y - 1) * x for t, y, x in self.sizes)
+        return self._n[3]
 
 
 # ----------------------------------------------------------------------------- plans
@@ -518,9 +533,15 @@ def projected_solve(GA: torch.Tensor, GT: torch.Tensor, d: torch.Tensor, bnorm2:
     K = d.numel()
     if not 1 <= K <= KRYLOV_MAX:
         raise ValueError(f"K must be in [1, {KRYLOV_MAX}] (got {K})")
-    pad = lambda M: torch.nn.functional.pad(M.to(torch.float64), (0, KRYLOV_MAX - K, 0, KRYLOV_MAX - K)).contiguous()
-    A64, T64 = pad(GA), pad(GT)
-    sc = torch.tensor([bnorm2, target, prev_lambda], dtype=torch.float64, device=d.device)
+    # (the solve reads the K x K entries only; the scalars by fills on the stream: a copy from the host would wait for
+    # the Gram matrices queued before)
+    AT = torch.empty((2, KRYLOV_MAX, KRYLOV_MAX), dtype=torch.float64, device=d.device)
+    A64, T64 = AT[0], AT[1]
+    A64[:K, :K].copy_(GA)
+    T64[:K, :K].copy_(GT)
+    sc = torch.empty(3, dtype=torch.float64, device=d.device)
+    for q, val in enumerate((bnorm2, target, prev_lambda)):
+        sc[q].fill_(float(val))
     z = torch.empty(K, dtype=torch.float64, device=d.device)
     res = torch.empty(4, dtype=torch.float64, device=d.device)
     dd = d.to(torch.float64).contiguous()
