@@ -189,16 +189,12 @@ __global__ __launch_bounds__(DV_LW * DV_TH) void k_of_derivs4(const Tile* __rest
 // tile with a 6-pixel halo (6 sweeps per launch, 512 threads) measured 0.72 ms per 8 sweeps
 // of the 1024 x 1024 x 64 stack, against 1.16 ms for 64 x 16 with 8 (640 threads), 0.97 ms for
 // 56 x 24 with 4 and 0.85 ms for 48 x 48 with 8; workgroups of 1024 threads were slower.
+// The planes of a strip are loaded together before anything is formed from them (a pixel at a time,
+// behind its own test, 11.8 us a launch over 15 pairs of 256 x 256 against 10.8).
 // The sweep loop is unrolled by two so that the buffer folds into the LDS offsets (118 -> 87
 // instructions a sweep of 4 FP32 pixels; 64 registers at most, for eight waves a SIMD).
-static constexpr int HTW = 52, HTH = 20, HS_MAX = 6;
-static constexpr int HRW = HTW + 2 * HS_MAX, HRH = HTH + 2 * HS_MAX;  // 64 x 32 halo region
-static constexpr int HS_THREADS = 512;
-static constexpr int HPT = HRW * HRH / HS_THREADS;                   // pixels per thread (4)
-static_assert(HRW * HRH == HS_THREADS * HPT, "halo region must split evenly over the workgroup");
-// LDS per buffer and component: the region, then a zero that neighbours outside the image read
-// (so every pixel reads its four neighbours unconditionally), padded to 64 elements
-static constexpr int HZERO = HRW * HRH, HCS = (HRW * HRH + 64) / 64 * 64;
+static constexpr int HTW = 52, HS_MAX = 6, HRW = HTW + 2 * HS_MAX, HS_THREADS = 512;
+constexpr int hs_tile_rows(int hpt) { return hpt * (HS_THREADS / HRW) - 2 * HS_MAX; }
 
 // The pixels of one thread: a strip of HPT consecutive rows of one column.  The vertical
 // neighbours inside the strip come from its registers (the previous sweep's values), the others
@@ -210,29 +206,37 @@ struct HsStrip {
     int l_up, l_dn;           // LDS index of the y-1 neighbour of pixel 0, y+1 of pixel N-1
     bool live[N];
 
-    // pixel r at p of the pair's planes (read when in the image), its neighbours and their LDS
-    // indices (u, d: used for the first and the last pixel)
-    __device__ __forceinline__ void load(int r, bool in, const T* __restrict__ Ip, const T* s, int64_t np, int64_t p,
-                                         T gamma, bool has_u, bool has_d, bool has_l, bool has_r, int u, int d,
-                                         int l, int rt) {
+    // The strip's planes are read first, all loads in flight together, at an offset that is inside the
+    // image also for a pixel that is not (off: of row 0, from the planes' row base; nrow rows of
+    // the strip are inside); then set() takes each pixel, its neighbours and their LDS indices
+    // (u, d: used for the first and the last pixel).  Off: unsigned, 32 bits unless the frame is wider
+    // than they reach.
+    template <class Off>
+    __device__ __forceinline__ void fetch(const T* Ip, const T* s, int64_t np, Off off, Off pitch, int r_lo,
+                                          int r_hi) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const Off o = (off + (Off)min(max(r, r_lo), r_hi) * pitch) * (Off)sizeof(T);
+            auto at = [&](const T* p) { return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + o); };
+            av[r] = at(s);
+            bv[r] = at(s + np);
+            gx[r] = at(Ip);
+            gy[r] = at(Ip + np);
+            gt[r] = at(Ip + 2 * np);
+        }
+    }
+    __device__ __forceinline__ void set(int r, bool in, T gamma, bool has_u, bool has_d, bool has_l, bool has_r, int u,
+                                        int d, int l, int rt) {
         live[r] = in;
-        av[r] = bv[r] = T(0);
-        gx[r] = gy[r] = gt[r] = T(0);
-        rden[r] = rd[r] = T(0);
         if (r == 0) l_up = u;
         if (r == N - 1) l_dn = d;
         lx[r][0] = l;
         lx[r][1] = rt;
-        if (in) {
-            av[r] = s[p];
-            bv[r] = s[np + p];
-            gx[r] = Ip[p];
-            gy[r] = Ip[np + p];
-            gt[r] = Ip[2 * np + p];
-            const int c = (int)has_u + (int)has_d + (int)has_l + (int)has_r;
-            rd[r] = T(1) / T(c);
-            rden[r] = T(1) / (gamma * T(c) + gx[r] * gx[r] + gy[r] * gy[r]);
-        }
+        const int c = (int)has_u + (int)has_d + (int)has_l + (int)has_r;
+        // (1 / c, rounded: selected, not divided)
+        rd[r] = c == 4 ? T(0.25) : c == 3 ? T(1) / T(3) : c == 2 ? T(0.5) : c == 1 ? T(1) : T(INFINITY);
+        rden[r] = T(1) / (gamma * T(c) + gx[r] * gx[r] + gy[r] * gy[r]);
+        if (!in) av[r] = bv[r] = gx[r] = gy[r] = gt[r] = rden[r] = rd[r] = T(0);
     }
 
     // one sweep from the LDS planes (cx, cy) of the previous one
@@ -277,23 +281,34 @@ struct HsStrip {
     }
 };
 
-template <class T>
-__global__ __launch_bounds__(HS_THREADS, sizeof(T) == 4 ? 8 : 4) void k_hs_multi(const Tile* __restrict__ tiles,
+template <class T, int HPT, class Off>
+__global__ __launch_bounds__(HS_THREADS, sizeof(T) == 4 && HPT <= 4 ? 8 : 4) void k_hs_multi(const Tile* __restrict__ tiles,
                                                          const FrameInfo* __restrict__ fr, const T* __restrict__ I,
                                                          const T* __restrict__ vin, T* __restrict__ vout, T gamma,
                                                          int nsw) {
+    static_assert(HS_THREADS % HRW == 0, "strips must tile the halo region");
+    constexpr int HTH = hs_tile_rows(HPT), HRH = HTH + 2 * HS_MAX;  // a 64 x 8 HPT halo region
+    // LDS per buffer and component: the region, then a zero that neighbours outside the image read
+    // (so every pixel reads its four neighbours unconditionally), padded to 64 elements
+    constexpr int HZERO = HRW * HRH, HCS = (HRW * HRH + 64) / 64 * 64;
     __shared__ T sv[2][2][HCS];  // [buffer][component][pixel]
-    static_assert(HRH == HPT * (HS_THREADS / HRW) && HS_THREADS % HRW == 0, "strips must tile the halo region");
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
     const int nx = f.nx, ny = f.ny;
     const int64_t np = (int64_t)nx * ny;
     const int ox = tl.x0 - HS_MAX, oy = tl.y0 - HS_MAX;  // image coordinates of the region origin
+    const int64_t rows = (int64_t)max(oy, 0) * nx;       // the region's first row of the image
     const T* sx = vin + 2 * f.pair_off;
     const T* Ip = I + 3 * f.pair_off;
     const int rx = (int)threadIdx.x % HRW, ry0 = HPT * ((int)threadIdx.x / HRW);
     const int x = ox + rx;
     HsStrip<T, HPT> q;
+    {
+        // rows r_lo .. r_hi of the strip are inside the image (none: the nearest row, for all)
+        const int y0 = oy + ry0, ya = min(max(y0, 0), ny - 1), yb = min(max(y0 + HPT - 1, 0), ny - 1);
+        const int xc = min(max(x, 0), nx - 1);
+        q.fetch(Ip + rows, sx + rows, np, (Off)(y0 - max(oy, 0)) * (Off)nx + (Off)xc, (Off)nx, ya - y0, yb - y0);
+    }
 #pragma unroll
     for (int r = 0; r < HPT; ++r) {
         const int ry = ry0 + r, idx = ry * HRW + rx;
@@ -302,9 +317,9 @@ __global__ __launch_bounds__(HS_THREADS, sizeof(T) == 4 ? 8 : 4) void k_hs_multi
         const bool has_u = in && y > 0, has_d = in && y < ny - 1;
         const bool has_l = in && x > 0, has_r = in && x < nx - 1;
         // neighbours outside the loaded region read the pixel itself (stale halo only)
-        q.load(r, in, Ip, sx, np, (int64_t)y * nx + x, gamma, has_u, has_d, has_l, has_r,
-               has_u ? (ry > 0 ? idx - HRW : idx) : HZERO, has_d ? (ry < HRH - 1 ? idx + HRW : idx) : HZERO,
-               has_l ? (rx > 0 ? idx - 1 : idx) : HZERO, has_r ? (rx < HRW - 1 ? idx + 1 : idx) : HZERO);
+        q.set(r, in, gamma, has_u, has_d, has_l, has_r, has_u ? (ry > 0 ? idx - HRW : idx) : HZERO,
+              has_d ? (ry < HRH - 1 ? idx + HRW : idx) : HZERO, has_l ? (rx > 0 ? idx - 1 : idx) : HZERO,
+              has_r ? (rx < HRW - 1 ? idx + 1 : idx) : HZERO);
         sv[0][0][idx] = q.av[r];
         sv[0][1][idx] = q.bv[r];
     }
@@ -360,14 +375,18 @@ __global__ __launch_bounds__(HW_THREADS) void k_hs_whole(const Tile* __restrict_
     const T* Ip = I + 3 * f.pair_off;
     const int x = tid % nx, y0 = N * (tid / nx);
     HsStrip<T, N> q;
+    {
+        const int yc = min(y0, ny - 1);  // (a strip below the frame reads its last row)
+        q.fetch(Ip, s, np, (unsigned)(yc * nx + x), (unsigned)nx, 0, min(N - 1, ny - 1 - yc));
+    }
 #pragma unroll
     for (int r = 0; r < N; ++r) {
         const int y = y0 + r, idx = y * nx + x;
         const bool in = y < ny;
         const bool has_u = in && y > 0, has_d = in && y < ny - 1;
         const bool has_l = in && x > 0, has_r = in && x < nx - 1;
-        q.load(r, in, Ip, s, np, idx, gamma, has_u, has_d, has_l, has_r, has_u ? idx - nx : ZERO,
-               has_d ? idx + nx : ZERO, has_l ? idx - 1 : ZERO, has_r ? idx + 1 : ZERO);
+        q.set(r, in, gamma, has_u, has_d, has_l, has_r, has_u ? idx - nx : ZERO, has_d ? idx + nx : ZERO,
+              has_l ? idx - 1 : ZERO, has_r ? idx + 1 : ZERO);
         if (in) {
             sv[0][0][idx] = q.av[r];
             sv[0][1][idx] = q.bv[r];
@@ -565,6 +584,30 @@ static int hs_whole_rows(const Geom& g, int& threads) {
     return 0;
 }
 
+// Rows per strip of k_hs_multi: the fewest microseconds a launch by what was measured over 1 to 22
+// pairs of 96 x 96 to 512 x 512: the time of one workgroup on every CU at most, c(h), and of each
+// further one a CU holds, d(h) (FP64: 5 rows leave room for one workgroup).  200 sweeps with 3, 4 and
+// 5 rows, FP32: 3 pairs of 128 x 128 165, 187, 215 us, 15 of 256 x 256 455, 377, 382, of 512 x 512 1350,
+// 1095, 1085; FP64: 15 pairs of 128 x 128 320, 377, 312, of 256 x 256 760, 676, 868.
+static int hs_multi_rows(const Geom& g, int dt, int cu_count) {
+    int best = 4;
+    double best_us = 1e300;
+    static const double c[2][3] = {{4.85, 5.5, 6.45}, {6.35, 7.6, 8.8}}, d[2][3] = {{1.6, 1.95, 2.5}, {2.8, 3.9, 8.2}};
+    const int f64 = dt == MMOF_F32 ? 0 : 1;
+    for (int h : {3, 4, 5}) {
+        int64_t tiles = 0;
+        for (int q = 0; q < g.n_seq; ++q)
+            tiles += (int64_t)(g.n_t[q] - 1) * cdiv(g.nx[q], HTW) * cdiv(g.ny[q], hs_tile_rows(h));
+        const double more = (double)(std::max<int64_t>(cdiv(tiles, cu_count), 1) - 1);
+        const double us = c[f64][h - 3] + more * d[f64][h - 3];
+        if (us < best_us) {
+            best_us = us;
+            best = h;
+        }
+    }
+    return best;
+}
+
 int launch_hs_sweeps(Ctx& c, Geom& g, int dt, const void* I, void* v, void* tmp, double gamma, int n_sweeps) {
     if (g.n_pairs == 0 || n_sweeps <= 0) return 0;
     int threads = 0;
@@ -587,7 +630,8 @@ int launch_hs_sweeps(Ctx& c, Geom& g, int dt, const void* I, void* v, void* tmp,
         });
         return 0;
     }
-    const TileList& tl = g.tile_list(c.stream, HTW, HTH, true);
+    const int rows = hs_multi_rows(g, dt, c.cu_count);
+    const TileList& tl = g.tile_list(c.stream, HTW, hs_tile_rows(rows), true);
     int done = 0, parity = 0;
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
@@ -596,7 +640,13 @@ int launch_hs_sweeps(Ctx& c, Geom& g, int dt, const void* I, void* v, void* tmp,
         while (done < n_sweeps) {
             const int q = std::min(HS_MAX, n_sweeps - done);
             ScopedTime st(&c, "hs_multi", 7.0 * sizeof(T) * g.pair_px, 16.0 * q * g.pair_px);
-            hipLaunchKernelGGL(k_hs_multi<T>, dim3((unsigned)tl.count), dim3(HS_THREADS), 0, c.stream, tl.buf.as<Tile>(),
+            auto pick = [&](auto off) {
+                using Off = decltype(off);
+                return rows == 3 ? k_hs_multi<T, 3, Off> : rows == 4 ? k_hs_multi<T, 4, Off> : k_hs_multi<T, 5, Off>;
+            };
+            // (a strip's offsets: the region's rows of the frame in bytes)
+            auto k = g.max_nx < (1 << 22) ? pick(uint32_t{}) : pick(uint64_t{});
+            hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(HS_THREADS), 0, c.stream, tl.buf.as<Tile>(),
                                g.dframes(), (const T*)I, (const T*)a, b, (T)gamma, q);
             MMOF_LAUNCH_CHECK();
             std::swap(a, b);
