@@ -447,7 +447,8 @@ int mmof_projected_solve(mmof_ctx ctx, int32_t K, const double* GA, const double
 /* Time every launch of the named kernel with HIP events on the context's stream
  * (name NULL or "" switches timing off; names: radon_fwd, radon_adj, blur, grad_fwd,
  * grad_adj, flow_fwd, flow_adj, flow_dv, of_derivs, hs_multi, reverse_flow, mdot, wgram,
- * small_solve).  mmof_kernel_timing returns the number of timed launches, their summed
+ * small_solve, theta: all rows of Theta u in one launch, which a solve times also under the
+ * names of its kinds of rows).  mmof_kernel_timing returns the number of timed launches, their summed
  * duration in milliseconds and their summed algorithmic work (bytes that must move, each
  * input read and each output written once; flops the method needs), and synchronizes the
  * stream.  Any output pointer may be NULL. */

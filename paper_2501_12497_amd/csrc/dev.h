@@ -125,6 +125,24 @@ __device__ __forceinline__ Quad<T> zero4() {
     return Quad<T>{{T(0), T(0), T(0), T(0)}};
 }
 
+// The quad (4 pixels of a row, fewer at its end) of a thread in a chunk of consecutive quads of a frame
+// (Geom::quad_list).
+struct QuadPos {
+    int x, y, nv;      // first pixel, its row, pixels
+    bool in, edge_r, edge_l;  // in the frame; the next / previous quad of the row is on another wave
+};
+__device__ __forceinline__ QuadPos quad_pos(const Tile& tl, int nx, int ny) {
+    const unsigned qpr = (unsigned)(nx + 3) / 4u, i = (unsigned)tl.x0 + threadIdx.x;
+    QuadPos q;
+    q.y = (int)(i / qpr);
+    q.x = 4 * (int)(i - (unsigned)q.y * qpr);
+    q.nv = min(4, nx - q.x);
+    q.in = q.y < ny;
+    q.edge_r = threadIdx.x % 64 == 63;
+    q.edge_l = threadIdx.x % 64 == 0;
+    return q;
+}
+
 // Half-sample-symmetric mirror of an index into [0, n): -1 -> 0, n -> n-1.
 __device__ __forceinline__ int mirror(int i, int n) {
     if (i < 0) i = -i - 1;

@@ -139,24 +139,10 @@ __global__ __launch_bounds__(256) void k_flow_fwd_cols(const Tile* __restrict__ 
 // offset); a row whose width is not a multiple of 4 ends with a thread of 1..3 pixels, whose
 // accesses go element by element.  The bilinear samples stay single loads.  Values equal those
 // of the scalar kernels.
-//
-// One image: the forward, reverse and temporal-difference rows of its pairs, whichever are wanted, from one read of the
-// two frames; each with its MM-weighted copy when its m is not null.  Bound by memory.  One launch for the two flow rows
-// of a small stack (4.1 us each before, 5.3 us together at 7 pairs of 32 x 32, FP64) and 16-byte accesses for the
-// differences (64 x 1024 x 1024, FP32: 238 us with four single accesses per lane, 4 pixels apart; 153 us over the calls
-// of a solve, 29 of 69 with the weighted copy, which took a pass of 490 us over all rows before).
-template <class T>
-struct PairRowsT {
-    const T* __restrict__ v;
-    T* __restrict__ r;
-    const T* __restrict__ nu;
-    T* __restrict__ m;
-};
-
 template <class T, int INTERP, int LW>
-__global__ __launch_bounds__(256) void k_pair_rows4(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
-                                                    const T* __restrict__ u, PairRowsT<T> fwd, PairRowsT<T> rev,
-                                                    PairRowsT<T> diff, double eps2) {
+__global__ __launch_bounds__(256) void k_flow_fwd4(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
+                                                   const T* __restrict__ u, const T* __restrict__ v,
+                                                   T* __restrict__ r, int direction) {
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
     const int x = tl.x0 + 4 * (int)(threadIdx.x % LW);
@@ -167,35 +153,87 @@ __global__ __launch_bounds__(256) void k_pair_rows4(const Tile* __restrict__ til
     const T* ut = u + f.off;
     const T* ut1 = ut + np;
     const int nv = min(4, f.nx - x);   // (fewer than 4 at the end of a row whose width is not a multiple of 4)
-    Quad<T> a = zero4<T>(), b = zero4<T>();
-    if (fwd.r || diff.r) a = ld4n(ut + p, nv);
-    if (rev.r || diff.r) b = ld4n(ut1 + p, nv);
-    auto store = [&](const PairRowsT<T>& w, const Quad<T>& o) {
-        st4n(w.r + f.pair_off + p, o, nv);
+    const T* vf = v + 2 * f.pair_off;
+    const Quad<T> vx = ld4n(vf + p, nv), vy = ld4n(vf + np + p, nv);
+    const T* src = direction > 0 ? ut1 : ut;
+    const Quad<T> sub = ld4n((direction > 0 ? ut : ut1) + p, nv);
+    Quad<T> o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        o.v[j] = warp_sample<T, INTERP>(src, f.nx, f.ny, x + j, y, vx.v[j], vy.v[j]) - sub.v[j];
+    st4n(r + f.pair_off + p, o, nv);
+}
+
+// All rows of Theta u from one read of u: a thread takes a quad (4 pixels of a row, any frame width; QuadPos) of a frame
+// and forms its horizontal and vertical differences and, where the frame begins a pair, the pair's forward, reverse and
+// temporal-difference rows, whichever are wanted, each with its MM-weighted copy when its m is not null.  Values equal
+// those of the separate kernels.  Bound by memory.  Measured against a launch per kind of row: 8 x 32 x 32, FP64,
+// with both flows 5.2 us (4.0 and 5.2 us in two launches, 12.2 in three); 64 x 1024 x 1024, FP32, with temporal
+// differences 333 us over the calls of a solve, 29 of 69 weighted (226 and 153, and once a weighting pass of 490).
+template <class T>
+struct ThetaRowsT {
+    const T* __restrict__ v;
+    T* __restrict__ r;
+    const T* __restrict__ nu;
+    T* __restrict__ m;
+};
+
+template <class T, int INTERP>
+__global__ __launch_bounds__(256) void k_theta(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
+                                               const T* __restrict__ u, ThetaRowsT<T> gx, ThetaRowsT<T> gy,
+                                               ThetaRowsT<T> fwd, ThetaRowsT<T> rev, ThetaRowsT<T> diff, double eps2) {
+    const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
+    const FrameInfo f = fr[tl.frame];
+    const int nx = f.nx, ny = f.ny;
+    const QuadPos q = quad_pos(tl, nx, ny);
+    if (!q.in) return;  // (the frame's last quads: no lane reads from one past them)
+    const int64_t np = (int64_t)nx * ny;
+    const int64_t p = (int64_t)q.y * nx + q.x;
+    const T* ut = u + f.off;
+    const bool pair = f.t + 1 < f.n_t, has_y = q.y < ny - 1;
+    const Quad<T> c = ld4n(ut + p, q.nv);
+    Quad<T> below = zero4<T>(), next = zero4<T>();
+    if (has_y) below = ld4n(ut + p + nx, q.nv);
+    if (pair && (rev.r || diff.r)) next = ld4n(ut + np + p, q.nv);
+    T right = __shfl_down(c.v[0], 1);
+    if (q.edge_r && q.x + 4 < nx) right = ut[p + 4];
+    auto put = [&](const ThetaRowsT<T>& w, int64_t o, const Quad<T>& d, int n) {
+        st4n(w.r + o, d, n);
         if (w.m) {
-            const Quad<T> nq = ld4n(w.nu + f.pair_off + p, nv);
+            const Quad<T> nq = ld4n(w.nu + o, n);
             Quad<T> m;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) m.v[j] = mm_weighted(o.v[j], nq.v[j], eps2);
-            st4n(w.m + f.pair_off + p, m, nv);
+            for (int j = 0; j < 4; ++j) m.v[j] = mm_weighted(d.v[j], nq.v[j], eps2);
+            st4n(w.m + o, m, n);
         }
     };
-    auto warp = [&](const PairRowsT<T>& w, const T* src, const Quad<T>& sub) {
+    Quad<T> d;
+    const int ngx = min(4, nx - 1 - q.x);
+    if (ngx > 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d.v[j] = (j < 3 ? c.v[j + 1] : right) - c.v[j];
+        put(gx, f.gx_off + (int64_t)q.y * (nx - 1) + q.x, d, ngx);
+    }
+    if (has_y) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d.v[j] = below.v[j] - c.v[j];
+        put(gy, f.gy_off + p, d, q.nv);
+    }
+    if (!pair) return;
+    auto warp = [&](const ThetaRowsT<T>& w, const T* src, const Quad<T>& sub) {
         const T* vf = w.v + 2 * f.pair_off;
-        const Quad<T> vx = ld4n(vf + p, nv), vy = ld4n(vf + np + p, nv);
-        Quad<T> o;
+        const Quad<T> vx = ld4n(vf + p, q.nv), vy = ld4n(vf + np + p, q.nv);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            o.v[j] = warp_sample<T, INTERP>(src, f.nx, f.ny, x + j, y, vx.v[j], vy.v[j]) - sub.v[j];
-        store(w, o);
+            d.v[j] = warp_sample<T, INTERP>(src, nx, ny, q.x + j, q.y, vx.v[j], vy.v[j]) - sub.v[j];
+        put(w, f.pair_off + p, d, q.nv);
     };
-    if (fwd.r) warp(fwd, ut1, a);
-    if (rev.r) warp(rev, ut, b);
+    if (fwd.r) warp(fwd, ut + np, c);
+    if (rev.r) warp(rev, ut, next);
     if (diff.r) {
-        Quad<T> o;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) o.v[j] = b.v[j] - a.v[j];
-        store(diff, o);
+        for (int j = 0; j < 4; ++j) d.v[j] = next.v[j] - c.v[j];
+        put(diff, f.pair_off + p, d, q.nv);
     }
 }
 
@@ -627,9 +665,10 @@ __global__ __launch_bounds__(256) void k_flow_dv(const Tile* __restrict__ tiles,
 }
 
 // out[blockIdx] = floor(max |v|) + 1 over the workgroup's share of the n values of the flows (a NaN counts as 1e30): the
-// radius of the adjoint's source windows, whole for one workgroup.
+// radius of the adjoint's source windows, whole for one workgroup (then also into out2, when not null).
 template <class T, int VEC>
-__global__ __launch_bounds__(1024) void k_flow_radius(const T* __restrict__ v, int64_t n, int32_t* __restrict__ out) {
+__global__ __launch_bounds__(1024) void k_flow_radius(const T* __restrict__ v, int64_t n, int32_t* __restrict__ out,
+                                                      int32_t* __restrict__ out2) {
     // VEC values per load (16 bytes when the flow is 16-byte aligned), four loads in flight per
     // step; the last n % VEC values singly
     typedef T VT __attribute__((ext_vector_type(VEC), aligned(sizeof(T) * VEC)));
@@ -658,22 +697,28 @@ __global__ __launch_bounds__(1024) void k_flow_radius(const T* __restrict__ v, i
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < (int)blockDim.x / 64; ++w) m = fmax(m, s_m[w]);
-        out[blockIdx.x] = (int32_t)fmin(floor(m), T(1 << 20)) + 1;
+        const int32_t r = (int32_t)fmin(floor(m), T(1 << 20)) + 1;
+        out[blockIdx.x] = r;
+        if (out2) *out2 = r;
     }
 }
 
-// out = the largest of the n values (one wave)
-__global__ __launch_bounds__(64) void k_max_int(const int32_t* __restrict__ p, int n, int32_t* __restrict__ out) {
+// out (and out2, when not null) = the largest of the n values (one wave)
+__global__ __launch_bounds__(64) void k_max_int(const int32_t* __restrict__ p, int n, int32_t* __restrict__ out,
+                                                int32_t* __restrict__ out2) {
     int m = 1;
     for (int i = (int)threadIdx.x; i < n; i += 64) m = max(m, p[i]);
     for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o));
-    if (threadIdx.x == 0) *out = m;
+    if (threadIdx.x == 0) {
+        *out = m;
+        if (out2) *out2 = m;
+    }
 }
 
-void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out) {
+void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out, int32_t* d_out2) {
     const int64_t n = 2 * g.pair_px;
     if (n == 0) {
-        hipLaunchKernelGGL(k_max_int, dim3(1), dim3(64), 0, c.stream, (const int32_t*)nullptr, 0, d_out);
+        hipLaunchKernelGGL(k_max_int, dim3(1), dim3(64), 0, c.stream, (const int32_t*)nullptr, 0, d_out, d_out2);
         MMOF_LAUNCH_CHECK();
         return;
     }
@@ -686,10 +731,11 @@ void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out) 
         const int nb = (int)std::min<int64_t>(cdiv(n, 32768), 2 * c.cu_count);
         int32_t* part = nb > 1 ? static_cast<int32_t*>(c.work("radius_part", sizeof(int32_t) * 2 * c.cu_count)) : d_out;
         auto k = reinterpret_cast<uintptr_t>(v) % 16 == 0 ? k_flow_radius<T, VEC> : k_flow_radius<T, 1>;
-        hipLaunchKernelGGL(k, dim3(nb), dim3(1024), 0, c.stream, (const T*)v, n, part);
+        hipLaunchKernelGGL(k, dim3(nb), dim3(1024), 0, c.stream, (const T*)v, n, part,
+                           nb > 1 ? nullptr : d_out2);
         MMOF_LAUNCH_CHECK();
         if (nb > 1) {
-            hipLaunchKernelGGL(k_max_int, dim3(1), dim3(64), 0, c.stream, part, nb, d_out);
+            hipLaunchKernelGGL(k_max_int, dim3(1), dim3(64), 0, c.stream, part, nb, d_out, d_out2);
             MMOF_LAUNCH_CHECK();
         }
     });
@@ -723,8 +769,8 @@ static auto flow_fwd_kernel(int choice) {
                          : k_flow_fwd<T, INTERP, 16, 16>;
 }
 template <class T, int INTERP>
-static auto pair_rows4_kernel(int choice) {
-    return kFlow4Shapes[choice].lw == 64 ? k_pair_rows4<T, INTERP, 64> : k_pair_rows4<T, INTERP, 32>;
+static auto flow_fwd4_kernel(int choice) {
+    return kFlow4Shapes[choice].lw == 64 ? k_flow_fwd4<T, INTERP, 64> : k_flow_fwd4<T, INTERP, 32>;
 }
 template <class T, int INTERP>
 static auto flow_adj_kernel(int choice) {
@@ -734,28 +780,28 @@ static auto flow_adj_kernel(int choice) {
                          : k_flow_adj<T, INTERP, 32, 32>;
 }
 
-void launch_pair_rows(Ctx& c, Geom& g, int dt, int interp, const void* u, const PairRows& fwd, const PairRows& rev,
-                      const PairRows& diff, double eps2, int choice) {
-    if (g.n_pairs == 0) return;
-    if (choice < 0) choice = g.choice("flow_fwd", dt, 1);
-    MMOF_CHECK(choice >= 0 && choice < kFlowCandidates, MMOF_ERR_INVALID, "flow tile candidate out of range");
+void launch_theta(Ctx& c, Geom& g, int dt, int interp, const void* u, const ThetaRows& gx, const ThetaRows& gy,
+                  const ThetaRows& fwd, const ThetaRows& rev, const ThetaRows& diff, double eps2) {
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
-        // per pixel of a pair: a frame sampled and one subtracted, a flow and a row per flow row; a third of that for
-        // a difference; nu read and the weighted row written
-        double words = 0.0;
-        for (const PairRows* w : {&fwd, &rev}) words += w->r ? (w->m ? 7.0 : 5.0) : 0.0;
-        if (diff.r) words += (diff.m ? 5.0 : 3.0) - (fwd.r || rev.r ? 1.0 : 0.0);
-        ScopedTime st(&c, fwd.r || rev.r ? "flow_fwd" : "tdiff_fwd", words * sizeof(T) * g.pair_px,
-                      ((fwd.r ? 12.0 : 0.0) + (rev.r ? 12.0 : 0.0) + (diff.r ? 1.0 : 0.0)) * g.pair_px);
-        auto typed = [](const PairRows& w) {
-            return PairRowsT<T>{(const T*)w.v, (T*)w.r, (const T*)w.nu, (T*)w.m};
+        // u read, the rows written, a flow read per flow row; nu read and the weighted rows written.  The launch is
+        // timed under the name of each kind of row, with that kind's work, and under its own with all of it.
+        const double per = gx.m ? 3.0 : 1.0, flows = (fwd.r ? 1.0 : 0.0) + (rev.r ? 1.0 : 0.0);
+        const double ng = (double)(g.gx_len + g.gy_len), np = (double)g.pair_px, td = diff.r ? 1.0 : 0.0, es = sizeof(T);
+        ScopedTime t0(&c, "theta", es * ((double)g.n + per * ng + (flows * (per + 2.0) + td * per) * np),
+                      ng + (12.0 * flows + td) * np);
+        ScopedTime t1(&c, "grad_fwd", es * ((double)g.n + per * ng), ng);
+        ScopedTime t2(flows > 0.0 ? &c : nullptr, "flow_fwd", es * flows * (per + 4.0) * np, 12.0 * flows * np);
+        ScopedTime t3(diff.r ? &c : nullptr, "tdiff_fwd", es * (per + 2.0) * np, np);
+        auto typed = [](const ThetaRows& w) {
+            return ThetaRowsT<T>{(const T*)w.v, (T*)w.r, (const T*)w.nu, (T*)w.m};
         };
-        const Flow4Shape sh = kFlow4Shapes[choice];
-        const TileList& tl = g.tile_list(c.stream, sh.tw(), sh.th(), true);
-        auto k = interp == MMOF_INTERP_ROUND ? pair_rows4_kernel<T, 1>(choice) : pair_rows4_kernel<T, 0>(choice);
-        hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(64 * sh.nw), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
-                           (const T*)u, typed(fwd), typed(rev), typed(diff), eps2);
+        // a wave per workgroup while that leaves CUs free (8 x 32 x 32: 32 workgroups, where 256 threads make 8)
+        const int per_wg = g.n / 4 < (int64_t)256 * 4 * c.cu_count ? 64 : 256;
+        const TileList& tl = g.quad_list(c.stream, per_wg);
+        auto k = interp == MMOF_INTERP_ROUND ? k_theta<T, 1> : k_theta<T, 0>;
+        hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(per_wg), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
+                           (const T*)u, typed(gx), typed(gy), typed(fwd), typed(rev), typed(diff), eps2);
         MMOF_LAUNCH_CHECK();
     });
 }
@@ -763,24 +809,24 @@ void launch_pair_rows(Ctx& c, Geom& g, int dt, int interp, const void* u, const 
 void launch_flow_fwd(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v, void* r,
                      int choice) {
     if (g.n_pairs == 0) return;
-    if (aligned_to(dt == MMOF_F32 ? 4 : 8, {u, v, r})) {
-        PairRows w;
-        w.v = v;
-        w.r = r;
-        launch_pair_rows(c, g, dt, interp, u, direction > 0 ? w : PairRows{}, direction > 0 ? PairRows{} : w,
-                         PairRows{}, 0.0, choice);
-        return;
-    }
     if (choice < 0) choice = g.choice("flow_fwd", dt, 1);
     MMOF_CHECK(choice >= 0 && choice < kFlowCandidates, MMOF_ERR_INVALID, "flow tile candidate out of range");
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
         ScopedTime st(&c, "flow_fwd", 5.0 * sizeof(T) * g.pair_px, 12.0 * g.pair_px);
-        const TileShape sh = kFlowShapes[choice];
-        const TileList& tl = g.tile_list(c.stream, sh.tw, sh.th, true);
-        auto k = interp == MMOF_INTERP_ROUND ? flow_fwd_kernel<T, 1>(choice) : flow_fwd_kernel<T, 0>(choice);
-        hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(256), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
-                           (const T*)u, (const T*)v, (T*)r, direction);
+        if (aligned_to(sizeof(T), {u, v, r})) {
+            const Flow4Shape sh = kFlow4Shapes[choice];
+            const TileList& tl = g.tile_list(c.stream, sh.tw(), sh.th(), true);
+            auto k = interp == MMOF_INTERP_ROUND ? flow_fwd4_kernel<T, 1>(choice) : flow_fwd4_kernel<T, 0>(choice);
+            hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(64 * sh.nw), 0, c.stream, tl.buf.as<Tile>(),
+                               g.dframes(), (const T*)u, (const T*)v, (T*)r, direction);
+        } else {
+            const TileShape sh = kFlowShapes[choice];
+            const TileList& tl = g.tile_list(c.stream, sh.tw, sh.th, true);
+            auto k = interp == MMOF_INTERP_ROUND ? flow_fwd_kernel<T, 1>(choice) : flow_fwd_kernel<T, 0>(choice);
+            hipLaunchKernelGGL(k, dim3((unsigned)tl.count), dim3(256), 0, c.stream, tl.buf.as<Tile>(), g.dframes(),
+                               (const T*)u, (const T*)v, (T*)r, direction);
+        }
         MMOF_LAUNCH_CHECK();
     });
 }
@@ -802,10 +848,14 @@ void launch_flow_fwd_cols(Ctx& c, Geom& g, int dt, int interp, const void* Uv, b
                 const TileList& tl = g.tile_list(c.stream, sh.tw(), sh.th(), true);
                 if ((int64_t)g.max_ny * g.max_nx < ((int64_t)1 << 31)) {
                     // (prepared cells hold 32-bit offsets within a frame)
-                    constexpr int JC = 8;   // columns per thread
+                    // columns per thread: 8, or 2 while that leaves fewer than two workgroups per CU (a thread
+                    // walks its columns one after the other: 7 pairs of 32 x 32, 30 FP64 columns 15 us with 8,
+                    // 6.9 with 2)
+                    const int JC = (int64_t)tl.count * cdiv(K, 8) < 2 * c.cu_count ? 2 : 8;
                     auto pick = [&](auto interp_tag) {
                         constexpr int I = decltype(interp_tag)::value;
-                        return sh.lw == 64 ? k_flow_fwd_colsJ<T, S, I, 64, JC> : k_flow_fwd_colsJ<T, S, I, 32, JC>;
+                        return JC == 2 ? (sh.lw == 64 ? k_flow_fwd_colsJ<T, S, I, 64, 2> : k_flow_fwd_colsJ<T, S, I, 32, 2>)
+                                       : (sh.lw == 64 ? k_flow_fwd_colsJ<T, S, I, 64, 8> : k_flow_fwd_colsJ<T, S, I, 32, 8>);
                     };
                     auto k = interp == MMOF_INTERP_ROUND ? pick(std::integral_constant<int, 1>{})
                                                          : pick(std::integral_constant<int, 0>{});

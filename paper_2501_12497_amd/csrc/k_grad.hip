@@ -13,29 +13,10 @@ namespace mmof {
 // lane, or from memory at the edge of a wave.  Bound by memory: on 40 sequences of 64^2 to 256^2 pixels
 // (2.1e7, FP32, weighted) the forward takes 80 us (5.2 TB/s) and the transpose 85 us; one pixel a
 // lane over 64 x 4 tiles took 165 and 149.
-// mx, my (may be null): gx and gy weighted by the MM weights of nux, nuy (RowWeighting).
-struct QuadPos {
-    int x, y, nv;      // first pixel, its row, pixels
-    bool in, edge_r, edge_l;  // in the frame; the next / previous quad of the row is on another wave
-};
-__device__ __forceinline__ QuadPos quad_pos(const Tile& tl, int nx, int ny) {
-    const unsigned qpr = (unsigned)(nx + 3) / 4u, i = (unsigned)tl.x0 + threadIdx.x;
-    QuadPos q;
-    q.y = (int)(i / qpr);
-    q.x = 4 * (int)(i - (unsigned)q.y * qpr);
-    q.nv = min(4, nx - q.x);
-    q.in = q.y < ny;
-    q.edge_r = threadIdx.x % 64 == 63;
-    q.edge_l = threadIdx.x % 64 == 0;
-    return q;
-}
-
 template <class T>
 __global__ __launch_bounds__(512) void k_grad_fwd(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
                                                   const T* __restrict__ u, const T* __restrict__ wx,
-                                                  const T* __restrict__ wy, T* __restrict__ gx, T* __restrict__ gy,
-                                                  const T* __restrict__ nux, const T* __restrict__ nuy,
-                                                  T* __restrict__ mx, T* __restrict__ my, double eps2) {
+                                                  const T* __restrict__ wy, T* __restrict__ gx, T* __restrict__ gy) {
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
     const int nx = f.nx, ny = f.ny;
@@ -49,30 +30,24 @@ __global__ __launch_bounds__(512) void k_grad_fwd(const Tile* __restrict__ tiles
     if (has_y) below = ld4n(uf + p + nx, q.nv);
     T right = __shfl_down(c.v[0], 1);
     if (q.edge_r && q.x + 4 < nx) right = uf[p + 4];
-    // the values of one array: weighted, stored, and their MM-weighted copies
-    auto put = [&](T* g, const T* w, T* m, const T* nu, int64_t o, Quad<T> d, int n) {
+    // the values of one array: weighted, stored
+    auto put = [&](T* g, const T* w, int64_t o, Quad<T> d, int n) {
         if (w) {
             const Quad<T> wq = ld4n(w + o, n);
 #pragma unroll
             for (int j = 0; j < 4; ++j) d.v[j] = wq.v[j] * d.v[j];
         }
         st4n(g + o, d, n);
-        if (m) {
-            const Quad<T> nq = ld4n(nu + o, n);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) d.v[j] = mm_weighted(d.v[j], nq.v[j], eps2);
-            st4n(m + o, d, n);
-        }
     };
     Quad<T> d;
 #pragma unroll
     for (int j = 0; j < 4; ++j) d.v[j] = (j < 3 ? c.v[j + 1] : right) - c.v[j];
     const int ngx = min(4, nx - 1 - q.x);
-    if (ngx > 0) put(gx, wx, mx, nux, f.gx_off + (int64_t)q.y * (nx - 1) + q.x, d, ngx);
+    if (ngx > 0) put(gx, wx, f.gx_off + (int64_t)q.y * (nx - 1) + q.x, d, ngx);
     if (has_y) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) d.v[j] = below.v[j] - c.v[j];
-        put(gy, wy, my, nuy, f.gy_off + p, d, q.nv);
+        put(gy, wy, f.gy_off + p, d, q.nv);
     }
 }
 
@@ -129,17 +104,7 @@ __global__ __launch_bounds__(512) void k_grad_adj(const Tile* __restrict__ tiles
 template <class T, int LW, int RPT>
 __global__ __launch_bounds__(256) void k_grad_fwd4(const Tile* __restrict__ tiles, const FrameInfo* __restrict__ fr,
                                                    const T* __restrict__ u, const T* __restrict__ wx,
-                                                   const T* __restrict__ wy, T* __restrict__ gx, T* __restrict__ gy,
-                                                   const T* __restrict__ nux, const T* __restrict__ nuy,
-                                                   T* __restrict__ mx, T* __restrict__ my, double eps2) {
-    // the MM-weighted copies of four aligned values and of one value (mx, my may be null)
-    auto mw4 = [&](T* m, const T* nu, int64_t o, const Quad<T>& q) {
-        const Quad<T> nq = ld4(nu + o);
-        Quad<T> r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.v[i] = mm_weighted(q.v[i], nq.v[i], eps2);
-        st4(m + o, r);
-    };
+                                                   const T* __restrict__ wy, T* __restrict__ gx, T* __restrict__ gy) {
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
     const int lx = (int)(threadIdx.x % LW);
@@ -183,24 +148,15 @@ __global__ __launch_bounds__(256) void k_grad_fwd4(const Tile* __restrict__ tile
                 for (int i = 0; i < 4; ++i) g.v[i] = w.v[i] * g.v[i];
             }
             st4(gx + B + e0, g);
-            if (mx) mw4(mx, nux, B + e0, g);
         } else if (e0 < n_el) {  // the tail (fewer than 4 values)
 #pragma unroll
             for (int i = 0; i < 3; ++i)
-                if (e0 + i < n_el) {
-                    const T val = wx ? wx[B + e0 + i] * g.v[i] : g.v[i];
-                    gx[B + e0 + i] = val;
-                    if (mx) mx[B + e0 + i] = mm_weighted(val, nux[B + e0 + i], eps2);
-                }
+                if (e0 + i < n_el) gx[B + e0 + i] = wx ? wx[B + e0 + i] * g.v[i] : g.v[i];
         }
         if (lx == 0) {  // the head, before the first aligned element
 #pragma unroll
             for (int i = 0; i < 3; ++i)
-                if (i < t0 && i < n_el) {
-                    const T val = wx ? wx[B + i] * d[i] : d[i];
-                    gx[B + i] = val;
-                    if (mx) mx[B + i] = mm_weighted(val, nux[B + i], eps2);
-                }
+                if (i < t0 && i < n_el) gx[B + i] = wx ? wx[B + i] * d[i] : d[i];
         }
         Quad<T> below = zero4<T>();
         if (y < ny - 1) {
@@ -215,7 +171,6 @@ __global__ __launch_bounds__(256) void k_grad_fwd4(const Tile* __restrict__ tile
                 for (int j = 0; j < 4; ++j) d.v[j] = w.v[j] * d.v[j];
             }
             st4(gy + og, d);
-            if (my) mw4(my, nuy, og, d);
         }
         c = below;
     }
@@ -309,34 +264,27 @@ static auto grad_adj4_kernel(int choice) {
 }
 
 void launch_grad_fwd(Ctx& c, Geom& g, int dt, const void* u, const void* wx, const void* wy, void* gx, void* gy,
-                     int choice, const RowWeighting* rw) {
+                     int choice) {
     if (choice < 0) choice = g.choice("grad_fwd", dt, 2);
     MMOF_CHECK(choice >= 0 && choice < kGradCandidates, MMOF_ERR_INVALID, "grad tile candidate out of range");
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
-        // u read, gx and gy written, weights read when given; with rw also nu read and the
-        // weighted rows written
-        const double per_row = (rw ? 3.0 : 1.0);
-        const double bytes = sizeof(T) * ((double)g.n + (per_row + (wx ? 1.0 : 0.0)) * g.gx_len +
-                                          (per_row + (wy ? 1.0 : 0.0)) * g.gy_len);
+        // u read, gx and gy written, weights read when given
+        const double bytes =
+            sizeof(T) * ((double)g.n + (wx ? 2.0 : 1.0) * g.gx_len + (wy ? 2.0 : 1.0) * g.gy_len);
         ScopedTime st(&c, "grad_fwd", bytes, (wx ? 2.0 : 1.0) * g.gx_len + (wy ? 2.0 : 1.0) * g.gy_len);
-        const T* nux = rw ? (const T*)rw->nu_a : nullptr;
-        const T* nuy = rw ? (const T*)rw->nu_b : nullptr;
-        T* mx = rw ? (T*)rw->m_a : nullptr;
-        T* my = rw ? (T*)rw->m_b : nullptr;
-        const double eps2 = rw ? rw->eps2 : 0.0;
-        if (g.vec4 && aligned_to(4 * sizeof(T), {u, wx, wy, gx, gy, nux, nuy, mx, my})) {
+        if (g.vec4 && aligned_to(4 * sizeof(T), {u, wx, wy, gx, gy})) {
             const Grad4Shape sh = kGrad4Shapes[choice];
             const TileList& tl = g.tile_list(c.stream, sh.tw(), sh.th(), false);
             hipLaunchKernelGGL(grad_fwd4_kernel<T>(choice), dim3((unsigned)tl.count), dim3(64 * sh.nw), 0, c.stream,
                                tl.buf.as<Tile>(), g.dframes(), (const T*)u, (const T*)wx, (const T*)wy, (T*)gx,
-                               (T*)gy, nux, nuy, mx, my, eps2);
+                               (T*)gy);
         } else {
             const TileShape sh = kGradShapes[choice];
             const TileList& tl = g.quad_list(c.stream, sh.tw / 4);
             hipLaunchKernelGGL(k_grad_fwd<T>, dim3((unsigned)tl.count), dim3(sh.tw / 4), 0, c.stream,
                                tl.buf.as<Tile>(), g.dframes(), (const T*)u, (const T*)wx, (const T*)wy, (T*)gx,
-                               (T*)gy, nux, nuy, mx, my, eps2);
+                               (T*)gy);
         }
         MMOF_LAUNCH_CHECK();
     });

@@ -15,38 +15,28 @@ TileShape grad_tile(const Geom& g, int choice);
 TileShape blur_tile(const Plan& p, int choice);
 TileShape flow_tile(const Geom& g, int choice);
 
-// The MM weighting of Theta's rows fused into the kernel that forms them: besides its rows y, the
-// kernel writes m = y / sqrt(nu^2 + eps^2) (the weight in FP64, the product rounded to the row
-// type, as the separate weighting pass computes it), nu and m laid out like y.  a: the rows of the
-// first output (gx), b: those of the second (gy).
-struct RowWeighting {
-    const void* nu_a = nullptr;
-    void* m_a = nullptr;
-    const void* nu_b = nullptr;
-    void* m_b = nullptr;
-    double eps2 = 0.0;
-};
-
-// Psi and Psi^T (eq. L); weights optional; rw: the MM weighting of the rows (may be null).
+// Psi and Psi^T (eq. L); weights optional.
 void launch_grad_fwd(Ctx& c, Geom& g, int dt, const void* u, const void* wx, const void* wy, void* gx, void* gy,
-                     int choice = -1, const RowWeighting* rw = nullptr);
+                     int choice = -1);
 void launch_grad_adj(Ctx& c, Geom& g, int dt, const void* gx, const void* gy, const void* wx, const void* wy,
                      void* u, bool accumulate, int choice = -1);
 
 // L(v) = -M-bar (direction +1) / -M-bar' (direction -1) and relatives.
 void launch_flow_fwd(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v, void* r,
                      int choice = -1);
-// One kind of Theta's rows over the pairs of frames: r (null: not wanted) and, when m is not null, its rows weighted by
-// the MM weights of nu (RowWeighting).
-struct PairRows {
+// One kind of Theta's rows: r (null: not wanted) and, when m is not null, its rows weighted by the MM
+// weights of nu: m = r / sqrt(nu^2 + eps^2) (the weight in FP64, the product rounded to the row type,
+// as the separate weighting pass computes it), nu and m laid out like r.
+struct ThetaRows {
     const void* v = nullptr;  // the flow (flow rows)
     void* r = nullptr;
     const void* nu = nullptr;
     void* m = nullptr;
 };
-// The forward-flow, reverse-flow and temporal-difference rows of one image in one launch.
-void launch_pair_rows(Ctx& c, Geom& g, int dt, int interp, const void* u, const PairRows& fwd, const PairRows& rev,
-                      const PairRows& diff, double eps2 = 0.0, int choice = -1);
+// All rows of Theta u in one launch: the horizontal and vertical differences, and the forward-flow,
+// reverse-flow and temporal-difference rows of the pairs.  Element-aligned arrays.
+void launch_theta(Ctx& c, Geom& g, int dt, int interp, const void* u, const ThetaRows& gx, const ThetaRows& gy,
+                  const ThetaRows& fwd, const ThetaRows& rev, const ThetaRows& diff, double eps2);
 // The residual formed where the last Theta^T kernel writes its output: instead of u, the kernel
 // writes out = x + lambda u in FP64 (x in the operator precision, lambda on the device), the
 // arithmetic of the separate combination pass.
@@ -67,7 +57,8 @@ void launch_flow_fwd_cols(Ctx& c, Geom& g, int dt, int interp, const void* U, bo
 void launch_flow_dv(Ctx& c, Geom& g, int dt, int direction, int interp, const void* u, const void* v,
                     const void* w, void* gv);
 // Device int *d_out = floor(max |v|) + 1 over all pairs (saturating at 1<<20, NaN -> saturate).
-void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out);
+// d_out2 (may be null): the same.
+void launch_flow_radius(Ctx& c, Geom& g, int dt, const void* v, int32_t* d_out, int32_t* d_out2 = nullptr);
 
 // Temporal first difference L_t of the spatio-temporal regularisers: forward r = u(t+1) - u(t)
 // per pair ([pairs][ny][nx]); transpose (accumulating into u or overwriting it; res, transpose only, as in

@@ -214,11 +214,11 @@ struct Solver {
             launch_blur(c, P, dt, in, out);
         if (rep) rep->n_At++;
     }
-    // the flow and temporal-difference rows of Theta in, with nu_ also weighted into outw
-    void theta_pairs(const TX* in, TX* out, const TX* nu_, TX* outw) {
-        if (!flow && !tdiff) return;
-        auto rows = [&](bool wanted, const TX* v, int64_t o) {
-            PairRows w;
+    // out = Theta in and, with nu_, its rows weighted by the MM weights of nu_ (1/sqrt(nu^2 + eps^2))
+    // into outw: the residual's W Theta u without a pass of its own (per-row weights from nu)
+    void theta(const TX* in, TX* out, const TX* nu_ = nullptr, TX* outw = nullptr) {
+        auto rows = [&](bool wanted, int64_t o, const TX* v = nullptr) {
+            ThetaRows w;
             if (!wanted) return w;
             w.v = v;
             w.r = out + o;
@@ -229,28 +229,12 @@ struct Solver {
             return w;
         };
         MMOF_CHECK(!tdiff || g.n_frames <= 65535, MMOF_ERR_SHAPE, "too many frames for one launch (at most 65535)");
-        launch_pair_rows(c, g, dt, p.interp, in, rows(flow, flow_v, oRF), rows(flow && p.use_reverse, flow_vr, oRR),
-                         rows(tdiff, nullptr, oTD), p.eps * p.eps);
-        if (flow && rep) rep->n_L += p.use_reverse ? 2 : 1;
-    }
-    void theta(const TX* in, TX* out) {
-        launch_grad_fwd(c, g, dt, in, nullptr, nullptr, out + oGX, out + oGY);
-        theta_pairs(in, out, nullptr, nullptr);
-        if (rep) rep->n_theta++;
-    }
-    // theta(in, out) and, in the same kernels, its rows weighted by the MM weights of nu_
-    // (1/sqrt(nu^2 + eps^2)) into outw: the residual's W Theta u without a pass of its own
-    // (per-row weights from nu)
-    void theta_weighted(const TX* in, TX* out, const TX* nu_, TX* outw) {
-        RowWeighting gw;
-        gw.nu_a = nu_ + oGX;
-        gw.m_a = outw + oGX;
-        gw.nu_b = nu_ + oGY;
-        gw.m_b = outw + oGY;
-        gw.eps2 = p.eps * p.eps;
-        launch_grad_fwd(c, g, dt, in, nullptr, nullptr, out + oGX, out + oGY, -1, &gw);
-        theta_pairs(in, out, nu_, outw);
-        if (rep) rep->n_theta++;
+        launch_theta(c, g, dt, p.interp, in, rows(true, oGX), rows(true, oGY), rows(flow, oRF, flow_v),
+                     rows(flow && p.use_reverse, oRR, flow_vr), rows(tdiff, oTD), p.eps * p.eps);
+        if (rep) {
+            if (flow) rep->n_L += p.use_reverse ? 2 : 1;
+            rep->n_theta++;
+        }
     }
     // out = Theta^T in; with res (only when flows or temporal differences are on: their last
     // adjoint forms it), the residual res->out = res->x + lambda out instead of out.  Returns
@@ -570,11 +554,10 @@ struct Solver {
                         w.gks = gks;
                         fm.gamma = gamma;
                         flow_update_core(c, g, gs, dt, u_op, flow_v, fscale, p.delta_r, fm, w);
-                        launch_flow_radius(c, g, dt, flow_v, rad_v);
-                        if (p.use_reverse) {
-                            launch_reverse_flow(c, g, dt, flow_v, flow_vr, rad_v);
-                            launch_flow_radius(c, g, dt, flow_vr, rad_vr);
-                        }
+                        // (a reverse flow is a mean of the flow's velocities, so none is longer; the adjoint's
+                        // values do not depend on the radius of the window that holds them)
+                        launch_flow_radius(c, g, dt, flow_v, rad_v, rad_vr);
+                        if (p.use_reverse) launch_reverse_flow(c, g, dt, flow_v, flow_vr, rad_v);
                     });
                     launch_flow_fwd_cols(c, g, dt, p.interp, col_op ? (const void*)V32 : (const void*)V, col_op, n, K,
                                          flow_v, p.use_reverse ? flow_vr : nullptr, TV, R,
@@ -606,12 +589,8 @@ struct Solver {
                        std::to_string(reinterpret_cast<uintptr_t>(wsrc));
                 replayable(key, [&] {
                     At(vin_m, out_n);
-                    if (wsrc) {
-                        theta_weighted(u_op, yR, wsrc, yW);
-                    } else {
-                        theta(u_op, yR);
-                        weight_mul<TX>(c, R, w2, yR, yW);
-                    }
+                    theta(u_op, yR, wsrc, yW);
+                    if (!wsrc) weight_mul<TX>(c, R, w2, yR, yW);
                     ResidualOut ro;
                     ro.x = out_n;
                     ro.lam = res;
