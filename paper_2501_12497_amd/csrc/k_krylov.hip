@@ -250,6 +250,56 @@ __global__ __launch_bounds__(KB) void k_mdot_final(int nb, int Kt, const double*
     }
 }
 
+// Short columns (at most MDOT_ONE rows): one workgroup per column forms its whole sum, with the outputs of
+// k_mdot_final and no partials.  Bound by the latency of its loads (two rows of the column and of y per
+// load, four loads of each in flight).
+static constexpr int MDOT_ONE = 32768;
+template <class TX, class TY>
+__global__ __launch_bounds__(1024) void k_mdot_one(int n, int K, int Kt, const TX* __restrict__ X, int64_t ld,
+                                                   const TY* __restrict__ y, const double* __restrict__ xe,
+                                                   double alpha, double* __restrict__ out, double* __restrict__ G,
+                                                   int ldg, int row, double* __restrict__ dj,
+                                                   const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    typedef TY VY __attribute__((ext_vector_type(2), aligned(sizeof(TY))));
+    __shared__ double s16[16];
+    const int j = blockIdx.x, t = (int)threadIdx.x;
+    auto sum = [&](auto* x) {
+        using TC = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
+        typedef TC VX __attribute__((ext_vector_type(2), aligned(sizeof(TC))));
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        const int pairs = n / 2;
+        for (int p0 = t; p0 < pairs; p0 += 4 * 1024) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int p = p0 + 1024 * u;
+                if (p < pairs) {
+                    const VX xv = *reinterpret_cast<const VX*>(x + 2 * p);
+                    const VY yv = *reinterpret_cast<const VY*>(y + 2 * p);
+                    a[u] = fma((double)xv.x, (double)yv.x, a[u]);
+                    a[u] = fma((double)xv.y, (double)yv.y, a[u]);
+                }
+            }
+        }
+        if ((n & 1) && t == 0) a[0] = fma((double)x[n - 1], (double)y[n - 1], a[0]);
+        return (a[0] + a[1]) + (a[2] + a[3]);
+    };
+    const double a = wave_sum(j < K ? sum(X + (int64_t)j * ld) : sum(xe));
+    if ((t & 63) == 0) s16[t >> 6] = a;
+    __syncthreads();
+    if (t != 0) return;
+    double s = 0.0;
+    for (int w = 0; w < 16; ++w) s += s16[w];
+    if (!G)
+        out[j] = alpha * s;
+    else if (j < Kt - 1) {
+        G[(int64_t)row * ldg + j] = s;
+        G[(int64_t)j * ldg + row] = s;
+    } else {
+        dj[0] = s;
+    }
+}
+
 // out[i] = beta * out[i] + alpha * sum_j X_j[i] * h[j]   (h on the device)
 template <class TX>
 __global__ __launch_bounds__(KB) void k_gemv_cols(int64_t n, int K, const TX* __restrict__ X, int64_t ld,
@@ -1113,17 +1163,38 @@ static void mdot_final(Ctx& c, int nb, int Kt, const double* part, double alpha,
 }
 
 
+// Inner products and their sums (launch_mdot, mdot_final; k_mdot_one for short columns), under the timer's
+// name tname (a conditional launch may do nothing: no work is credited to it).
+template <class TX, class TY>
+static void mdot_all(Ctx& c, const char* tname, int64_t n, int K, const TX* X, int64_t ld, const TY* y,
+                     const double* xe, double alpha, double* out, double* G, int ldg, int row, double* dj,
+                     const int* skip) {
+    const int Kt = K + (xe ? 1 : 0);
+    const double bytes = skip ? 0.0 : (double)n * ((double)sizeof(TX) * K + sizeof(TY));
+    const double flops = skip ? 0.0 : 2.0 * n * Kt;
+    // one launch while a workgroup reads its column in the time of two (8192 rows, 10 columns: 3.9 us against
+    // 3.6 and 2.4 and the gap between them; 32768 rows 6.4, 65536 9.8)
+    if (n <= MDOT_ONE && mdot_pairs(X, ld, y, xe)) {
+        ScopedTime st(&c, tname, bytes, flops);
+        hipLaunchKernelGGL((k_mdot_one<TX, TY>), dim3((unsigned)Kt), dim3(1024), 0, c.stream, (int)n, K, Kt, X, ld, y,
+                           xe, alpha, out, G, ldg, row, dj, skip);
+        MMOF_LAUNCH_CHECK();
+        return;
+    }
+    const int nb = mdot_blocks(n);
+    double* part = static_cast<double*>(c.work("mdot_part", sizeof(double) * (size_t)MAX_PART * (KMAX + 1)));
+    {
+        ScopedTime st(&c, tname, bytes, flops);
+        launch_mdot<TX, TY>(c, nb, n, K, X, ld, y, xe, part, skip);
+    }
+    mdot_final(c, nb, Kt, part, alpha, out, G, ldg, row, dj, skip);
+}
+
 template <class TX, class TY>
 void mdot(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, const TY* y, double alpha, double* out) {
     if (K <= 0) return;
-    const int nb = mdot_blocks(n);
     MMOF_CHECK(K <= KMAX, MMOF_ERR_SHAPE, "too many columns for a block inner product");
-    double* part = static_cast<double*>(c.work("mdot_part", sizeof(double) * (size_t)MAX_PART * (KMAX + 1)));
-    {
-        ScopedTime st(&c, "mdot", (double)n * ((double)sizeof(TX) * K + sizeof(TY)), 2.0 * n * K);
-        launch_mdot<TX, TY>(c, nb, n, K, X, ld, y, nullptr, part, nullptr);
-    }
-    mdot_final(c, nb, K, part, alpha, out, nullptr, 0, 0, nullptr, nullptr);
+    mdot_all<TX, TY>(c, "mdot", n, K, X, ld, y, nullptr, alpha, out, nullptr, 0, 0, nullptr, nullptr);
 }
 template void mdot<float, double>(Ctx&, int64_t, int, const float*, int64_t, const double*, double, double*);
 template void mdot<double, double>(Ctx&, int64_t, int, const double*, int64_t, const double*, double, double*);
@@ -1147,11 +1218,7 @@ void gemv_mdot(Ctx& c, int64_t n, int K, const double* Q, int64_t ld, const doub
 template <class TX>
 void gram_row(Ctx& c, int64_t n, int j, const TX* X, int64_t ld, const double* e, double* G, int ldg, double* dj) {
     MMOF_CHECK(j >= 0 && j < KMAX, MMOF_ERR_SHAPE, "too many Krylov columns");
-    const int nb = mdot_blocks(n);
-    double* part = static_cast<double*>(c.work("mdot_part", sizeof(double) * (size_t)MAX_PART * (KMAX + 1)));
-    const TX* xj = X + (int64_t)j * ld;
-    launch_mdot<TX, TX>(c, nb, n, j + 1, X, ld, xj, e, part, nullptr);
-    mdot_final(c, nb, j + 2, part, 1.0, nullptr, G, ldg, j, dj, nullptr);
+    mdot_all<TX, TX>(c, "gram_row", n, j + 1, X, ld, X + (int64_t)j * ld, e, 1.0, nullptr, G, ldg, j, dj, nullptr);
 }
 template void gram_row<float>(Ctx&, int64_t, int, const float*, int64_t, const double*, double*, int, double*);
 template void gram_row<double>(Ctx&, int64_t, int, const double*, int64_t, const double*, double*, int, double*);
@@ -1211,17 +1278,10 @@ template void gemv_fused<float, float>(Ctx&, int64_t, int, const float*, int64_t
 
 void cgs_once(Ctx& c, int64_t n, int K, const double* Q, int64_t ld, double* x, double* sq, double* h) {
     MMOF_CHECK(K >= 1 && K <= KMAX, MMOF_ERR_SHAPE, "too many Krylov columns");
-    const int nb = mdot_blocks(n);
-    double* part = static_cast<double*>(c.work("mdot_part", sizeof(double) * (size_t)MAX_PART * (KMAX + 1)));
     int* flag = static_cast<int*>(c.work("cgs_flag", sizeof(int)));
     // h[0..K-1] = Q^T x and h[K] = ||x||^2 (x as the extra column), one pass over Q and x
     auto dots = [&](const double* xe, const int* skip, const char* tname) {
-        const int Kt = K + (xe ? 1 : 0);
-        {
-            ScopedTime st(&c, tname, skip ? 0.0 : (double)n * (8.0 * K + 8.0), skip ? 0.0 : 2.0 * n * Kt);
-            launch_mdot<double, double>(c, nb, n, K, Q, ld, (const double*)x, xe, part, skip);
-        }
-        mdot_final(c, nb, Kt, part, 1.0, h, nullptr, 0, 0, nullptr, skip);
+        mdot_all<double, double>(c, tname, n, K, Q, ld, x, xe, 1.0, h, nullptr, 0, 0, nullptr, skip);
     };
     dots(x, nullptr, "mdot");
     // x <- x - Q h in place (each row read before it is written), ||x||^2 into sq
