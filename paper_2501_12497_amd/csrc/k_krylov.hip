@@ -1563,14 +1563,23 @@ void mm_weights_f64(Ctx& c, int64_t n, const TX* nu, double eps, double* w) {
 template void mm_weights_f64<float>(Ctx&, int64_t, const float*, double, double*);
 template void mm_weights_f64<double>(Ctx&, int64_t, const double*, double, double*);
 
+// Stage-1 workgroups of W waves for `steps` steps: about 16 steps a wave on large columns, a workgroup
+// per CU on the others as far as the steps go.  A step's latency then counts once, not 16 times:
+// unweighted, 72000 FP32 rows, 39 columns 38 -> 16 us, 64 columns 55 -> 21, 200 columns 677 -> 243; 4000
+// rows, 39 columns 41 -> 14.  Equal from 1e6 rows on.
+static int64_t gram_blocks(const Ctx& c, int64_t steps, int W) {
+    const int64_t spread = std::min<int64_t>(c.cu_count, cdiv(steps, W));
+    return std::max<int64_t>(1, std::max<int64_t>(cdiv(steps, 16 * W), spread));
+}
+
 template <class TX, int G, bool VEC, bool NU>
 static void wgram_launch(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, const void* w, double eps2,
                          double* part, int max_blocks, int& nb) {
     // 16 waves per workgroup where the registers allow (4 per SIMD, to overlap the loads with
-    // the matrix-core work), about 16 16-row steps per wave, at most max_blocks partials
+    // the matrix-core work), at most max_blocks partials
     constexpr int W = (sizeof(TX) == 4 && G <= 2) ? 16 : 8;
     const int64_t steps = (n + 15) / 16;
-    nb = (int)std::max<int64_t>(1, std::min<int64_t>(max_blocks, cdiv(steps, 16 * W)));
+    nb = (int)std::min<int64_t>(max_blocks, gram_blocks(c, steps, W));
     hipLaunchKernelGGL((k_wgram_part<TX, G, VEC, W, NU>), dim3(nb), dim3(64 * W), 0, c.stream, n, K, X, ld, w, eps2,
                        part);
 }
@@ -1591,11 +1600,11 @@ template <class TX, int NQ, bool NU>
 static void wgram_quad_launch(Ctx& c, bool vec, int64_t n, int K, const TX* X, int64_t ld, const void* w,
                               double eps2, double* part, int max_blocks, int& nb) {
     // four waves per workgroup (the largest forms hold one wave per SIMD: 294 registers at
-    // 10 FP32 quads), at least 16 steps per wave, at most max_blocks partials
+    // 10 FP32 quads), at most max_blocks partials
     constexpr int W = 4;
     constexpr int STEP = 16 * QuadRows<TX, NQ>::RPL;
     const int64_t steps = (n + STEP - 1) / STEP;
-    nb = (int)std::max<int64_t>(1, std::min<int64_t>(max_blocks, cdiv(steps, 16 * W)));
+    nb = (int)std::min<int64_t>(max_blocks, gram_blocks(c, steps, W));
     constexpr int WN = NU ? QW_NU : QW_BUF;
     if (vec) {
         if (NU || w)
@@ -1704,7 +1713,7 @@ void wgram(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, const double* w, d
             const int Kb = std::min(64, K - 64 * b2);
             constexpr int W = sizeof(TX) == 4 ? 8 : 4;   // (FP64 rows need twice the registers)
             const int64_t steps = (n + 15) / 16;
-            const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(GRAM_BLOCKS, cdiv(steps, 16 * W)));
+            const int nb = (int)std::min<int64_t>(GRAM_BLOCKS, gram_blocks(c, steps, W));
             const TX* XI = X + (int64_t)64 * a * ld;
             const TX* XJ = X + (int64_t)64 * b2 * ld;
             {
