@@ -492,6 +492,16 @@ int mmof_weighted_gram(mmof_ctx ctx, mmof_dtype dt, int64_t n, int32_t K, const 
         need(G, "G");
         MMOF_CHECK(n >= 1 && K >= 1 && K <= KMAX && ld >= n && ldg >= K, MMOF_ERR_SHAPE, "bad Gram sizes");
         MMOF_CHECK(!nu || eps > 0, MMOF_ERR_INVALID, "eps must be > 0");
+        // weights formed inside the Gram (the same formula) where it reads nu by vectors and its 4 x 4 form
+        // hides them: 39 columns of 2.1e6 rows 92 us FP32, 151 FP64, against 106 and 168 with a buffer's
+        // pass and 8 bytes per row; 48 columns on the 16 x 16 form 187 against 156
+        if (nu && K <= GRAM_QUAD_COLS && reinterpret_cast<uintptr_t>(nu) % 16 == 0) {
+            if (dt == MMOF_F32)
+                wgram_nu<float>(*ctx, n, K, (const float*)X, ld, (const float*)nu, eps, G, ldg);
+            else
+                wgram_nu<double>(*ctx, n, K, (const double*)X, ld, (const double*)nu, eps, G, ldg);
+            return MMOF_OK;
+        }
         double* w = nullptr;
         if (nu) {
             w = static_cast<double*>(ctx->work("gram_w", sizeof(double) * (size_t)n));

@@ -700,7 +700,7 @@ __global__ __launch_bounds__(1024) void k_wgram_final(int nb, int K, int G, cons
 // step's loads are issued before the current step's MFMAs.  At the end the four row groups of
 // a result are summed across lanes (l, l^4, l^8, l^12), the waves of a workgroup in LDS in a
 // fixed order, and stage 2 sums the workgroups' partials in a fixed order.
-static constexpr int GRAM_QUADS = 10;   // most column quads of the 4x4x4 form (K <= 40)
+static constexpr int GRAM_QUADS = GRAM_QUAD_COLS / 4;   // most column quads of the 4x4x4 form
 
 template <class TX, int NQ>
 struct QuadRows {

@@ -6,6 +6,7 @@
 namespace mmof {
 
 static constexpr int KMAX = 256;        // largest Krylov basis (columns of V)
+static constexpr int GRAM_QUAD_COLS = 40;  // most columns of the Gram's 4 x 4 form
 static constexpr int KLD = 256;         // leading dimension of the projected matrices G_H, G_T
 static constexpr int KMAX_SMALL = 64;   // largest basis of the one-wave projected solve (and of
                                         // the allocation-free Gram)
