@@ -216,6 +216,7 @@ struct Plan {
     DeviceBuffer d_trig;            // float2/double2 per (frame, angle): cos, sin  (double)
     DeviceBuffer d_rinfo;           // RadonFrame[n_frames]
     DeviceBuffer d_rays[4];         // ray tiles of the forward projector (angle groups 1, 2, 4, 8)
+    DeviceBuffer d_ray_recs;        // those of one angle with all a workgroup needs (parallel beam)
     DeviceBuffer d_tiles_a;         // pixel tiles of the back-projector
     DeviceBuffer d_tiles_b;         // 32x32 tiles of the frame transpose
     bool tr_vec = false;            // every frame side and offset a multiple of 4 (vector transpose)
