@@ -658,7 +658,15 @@ __global__ __launch_bounds__(1024) void k_wgram_final(int nb, int K, int G, cons
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int e = blockIdx.x * GRAM_SLAB + lane;
     double acc = 0.0;
-    for (int b = wave; b < nb; b += 16) acc += part[(int64_t)b * (GRAM_PAIRS * 256) + e];
+    int b = wave;
+    for (; b + 7 * 16 < nb; b += 8 * 16) {  // (eight loads in flight)
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = part[(int64_t)(b + 16 * q) * (GRAM_PAIRS * 256) + e];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc += v[q];
+    }
+    for (; b < nb; b += 16) acc += part[(int64_t)b * (GRAM_PAIRS * 256) + e];
     s[wave][lane] = acc;
     __syncthreads();
     if (wave != 0) return;
@@ -991,8 +999,17 @@ __global__ __launch_bounds__(1024) void k_wgram_final_rect(int nb, int GJ, int n
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int e = blockIdx.x * GRAM_SLAB + lane;
     double acc = 0.0;
-    if (e < np * 256)
-        for (int b = wave; b < nb; b += 16) acc += part[(int64_t)b * (np * 256) + e];
+    if (e < np * 256) {
+        int b = wave;
+        for (; b + 7 * 16 < nb; b += 8 * 16) {  // (eight loads in flight)
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = part[(int64_t)(b + 16 * q) * (np * 256) + e];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc += v[q];
+        }
+        for (; b < nb; b += 16) acc += part[(int64_t)b * (np * 256) + e];
+    }
     s[wave][lane] = acc;
     __syncthreads();
     if (wave != 0 || e >= np * 256) return;
@@ -1710,7 +1727,7 @@ void wgram(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, const double* w, d
         wgram_stages<TX, false>(c, n, Ka, X + (int64_t)64 * a * ld, ld, w, 0.0, G + (int64_t)64 * a * ldg + 64 * a,
                                 ldg, part, GRAM_BLOCKS, true);
         for (int b2 = a + 1; b2 < nsb; ++b2) {
-            const int Kb = std::min(64, K - 64 * b2);
+            const int Kb = std::min(64, K - 64 * b2), GJ = (Kb + 15) / 16;
             constexpr int W = sizeof(TX) == 4 ? 8 : 4;   // (FP64 rows need twice the registers)
             const int64_t steps = (n + 15) / 16;
             const int nb = (int)std::min<int64_t>(GRAM_BLOCKS, gram_blocks(c, steps, W));
@@ -1719,16 +1736,23 @@ void wgram(Ctx& c, int64_t n, int K, const TX* X, int64_t ld, const double* w, d
             {
                 ScopedTime st(&c, "wgram", (double)n * ((double)sizeof(TX) * (Ka + Kb) + 8.0),
                               2.0 * (double)n * Ka * Kb);
-                if (vec)
-                    hipLaunchKernelGGL((k_wgram_rect<TX, GRAM_RECT, GRAM_RECT, sizeof(TX) == 4, W>), dim3(nb),
-                                       dim3(64 * W), 0, c.stream, n, Ka, Kb, XI, XJ, ld, w, part);
-                else
-                    hipLaunchKernelGGL((k_wgram_rect<TX, GRAM_RECT, GRAM_RECT, false, W>), dim3(nb), dim3(64 * W),
-                                       0, c.stream, n, Ka, Kb, XI, XJ, ld, w, part);
+                // (the last tile of columns by its 16-column blocks: the whole Gram of 73 columns of 2.5e6 FP32 rows
+                // 539 us, 780 with four blocks of which three are empty; 95 columns 680, 846)
+                auto pick = [&](auto gj) {
+                    constexpr int GJ = decltype(gj)::value;
+                    return vec ? k_wgram_rect<TX, GRAM_RECT, GJ, sizeof(TX) == 4, W>
+                               : k_wgram_rect<TX, GRAM_RECT, GJ, false, W>;
+                };
+                auto k = GJ == 1   ? pick(std::integral_constant<int, 1>{})
+                         : GJ == 2 ? pick(std::integral_constant<int, 2>{})
+                         : GJ == 3 ? pick(std::integral_constant<int, 3>{})
+                                   : pick(std::integral_constant<int, GRAM_RECT>{});
+                hipLaunchKernelGGL(k, dim3(nb), dim3(64 * W), 0, c.stream, n, Ka, Kb, XI, XJ, ld, w, part);
                 MMOF_LAUNCH_CHECK();
             }
-            hipLaunchKernelGGL(k_wgram_final_rect, dim3((unsigned)cdiv((int64_t)RP * 256, GRAM_SLAB)), dim3(1024), 0,
-                               c.stream, nb, GRAM_RECT, RP, Ka, Kb, 64 * a, 64 * b2, (const double*)part, G, ldg);
+            const int np = GRAM_RECT * GJ;
+            hipLaunchKernelGGL(k_wgram_final_rect, dim3((unsigned)cdiv((int64_t)np * 256, GRAM_SLAB)), dim3(1024), 0,
+                               c.stream, nb, GJ, np, Ka, Kb, 64 * a, 64 * b2, (const double*)part, G, ldg);
             MMOF_LAUNCH_CHECK();
         }
     }

@@ -1,5 +1,6 @@
 """GPU parity of the weighted Gram on columns of few rows, where waves have one step or none: one row to a few thousand,
-at the edges of a step (16, 32 and 64 rows) and of a workgroup's steps, for the 4 x 4, the 16 x 16 and the tiled forms;
+at the edges of a step (16, 32 and 64 rows) and of a workgroup's steps, for the 4 x 4, the 16 x 16 and the tiled forms (the
+last tile of 1 to 4 blocks);
 and the form without allocation, which has its own limit of workgroups.  1e-12 of the largest entry."""
 import numpy as np
 import pytest
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("which", ["f64", "f32"])
-@pytest.mark.parametrize("K", [1, 4, 39, 40, 41, 64, 65, 130])
+@pytest.mark.parametrize("K", [1, 4, 39, 40, 41, 64, 65, 80, 81, 97, 113, 130])
 def test_few_rows(which, K):
     import torch
     from paper_2501_12497_amd import binding as B
