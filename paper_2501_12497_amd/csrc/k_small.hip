@@ -409,17 +409,25 @@ __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restr
 //
 // Eight waves.  The lower 16 x 16 blocks of M stay in the accumulators of the waves (block b of the column-major list on
 // wave b % 8: 17 blocks each at K = 256), a block column passes through the LDS to be factored by the waves that own its
-// rows, with the steps of factor(), and updates the blocks right of it on the matrix cores from there.  The factor goes to an
-// L2-resident workspace, by columns and by rows, for the triangular solves: thread i < 256 owns row i, and every row of
-// 16 lanes solves a copy of the diagonal block (one barrier per block).  An evaluation takes 34 us at K = 80, 67 at 130
-// and 112 at 200 (126, 261 and 514 with the trailing matrix in L2, updated entry by entry).
+// rows, with the steps of factor(), and updates the blocks right of it on the matrix cores from there.  The factor stays
+// in the LDS up to 128 columns (the largest square that fits beside the rest) and goes to an L2-resident workspace
+// beyond, by columns and by rows, for the triangular solves: thread i < 256 owns row i, and every row of 16 lanes solves
+// a copy of the diagonal block (one barrier per block).  An evaluation takes 24 us at K = 80, 40 at 120, 67 at 130 and
+// 112 at 200 (34 and 57 at 80 and 120 with the factor in L2; 126, 261 and 514 at 80, 130 and 200 with the trailing matrix
+// there too, updated entry by entry).
 
 static constexpr int BIG_T = 512, BIG_W = BIG_T / 64;  // threads, waves
-static constexpr int BIG_NB = KMAX / 16;                // block columns
-static constexpr int BIG_SLOTS = (BIG_NB * (BIG_NB + 1) / 2 + BIG_W - 1) / BIG_W;  // blocks per wave
 
+// NB block columns at most: 8 (K <= 128), the factor in the LDS, or 16, in L2.
+template <int NB>
 struct BigLds {
-    double P[2][KMAX][17];  // the current block column (padded), two in turn
+    static constexpr bool IN_LDS = NB <= 8;
+    static constexpr int SLOTS = (NB * (NB + 1) / 2 + BIG_W - 1) / BIG_W;  // blocks per wave
+    static constexpr int RW = NB / 4;                                      // waves that own rows
+    static constexpr int LD = IN_LDS ? 16 * NB + 1 : 17;
+    // IN_LDS: the factor, block column by block column; otherwise the current block column, two in turn (padded rows)
+    double F[IN_LDS ? 1 : 2][16 * NB][LD];
+    __device__ __forceinline__ double* row(int J, int i) { return IN_LDS ? &F[0][i][16 * J] : &F[J & 1][i][0]; }
     double piv[KMAX], inv[KMAX];
     double vec[KMAX];       // the vector of a product
     double x[2][16];        // a block's right-hand side, two in turn
@@ -428,7 +436,8 @@ struct BigLds {
 };
 
 // Sums of two values over the workgroup, bitwise identical in every thread (the wave totals added in a fixed order).
-__device__ __forceinline__ void block_sum2(BigLds& s, double& a, double& b) {
+template <int NB>
+__device__ __forceinline__ void block_sum2(BigLds<NB>& s, double& a, double& b) {
     wave_sum2(a, b);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
@@ -444,19 +453,21 @@ __device__ __forceinline__ void block_sum2(BigLds& s, double& a, double& b) {
     }
 }
 
-// M = A + lam T = U diag(p) U^T as in factor() (A, T row-major with leading dimension KLD): -U by columns to
-// L[c * KLD + r] and by rows to L[(KMAX + r) * KLD + c], zeros on and above the diagonal of its diagonal blocks; p and 1/p
-// to the LDS.  Returns false, uniformly, on a pivot that is not positive.
-__device__ bool factor_big(BigLds& s, double* L, const double* __restrict__ A, const double* __restrict__ T, int K,
+// M = A + lam T = U diag(p) U^T as in factor() (A, T row-major with leading dimension KLD): -U to the LDS, or by columns
+// to L[c * KLD + r] and by rows to L[(KMAX + r) * KLD + c], zeros on and above the diagonal of its diagonal blocks; p and
+// 1/p to the LDS.  Returns false, uniformly, on a pivot that is not positive.
+template <int NB>
+__device__ bool factor_big(BigLds<NB>& s, double* L, const double* __restrict__ A, const double* __restrict__ T, int K,
                            double lam) {
     const int lane = threadIdx.x & 63, r = lane & 15, lk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nbk = (K + 15) >> 4, nblk = nbk * (nbk + 1) / 2;
     if (threadIdx.x == 0) s.fail = 0;
-    dbl4 acc[BIG_SLOTS];
-    int bi[BIG_SLOTS], bj[BIG_SLOTS];  // block row and column of a slot (uniform)
+    constexpr int SLOTS = BigLds<NB>::SLOTS;
+    dbl4 acc[SLOTS];
+    int bi[SLOTS], bj[SLOTS];  // block row and column of a slot (uniform)
 #pragma unroll
-    for (int q = 0; q < BIG_SLOTS; ++q) {
+    for (int q = 0; q < SLOTS; ++q) {
         int b = q * BIG_W + wave, J = 0;
         const bool used = b < nblk;
         while (used && b >= nbk - J) b -= nbk - J++;
@@ -474,21 +485,20 @@ __device__ bool factor_big(BigLds& s, double* L, const double* __restrict__ A, c
     }
     for (int J = 0; J < nbk; ++J) {
         const int c0 = J << 4;
-        double(*P)[17] = s.P[J & 1];
 #pragma unroll
-        for (int q = 0; q < BIG_SLOTS; ++q) {
+        for (int q = 0; q < SLOTS; ++q) {
             if (bj[q] != J) continue;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) P[(bi[q] << 4) + lk + 4 * v][r] = acc[q][v];
+            for (int v = 0; v < 4; ++v) s.row(J, (bi[q] << 4) + lk + 4 * v)[r] = acc[q][v];
         }
         __syncthreads();
         const int i = (wave << 6) + lane;
-        if (wave < 4 && (wave << 6) + 63 >= c0 && (wave << 6) < (nbk << 4)) {
+        if (wave < BigLds<NB>::RW && (wave << 6) + 63 >= c0 && (wave << 6) < (nbk << 4)) {
             double D[16], Pr[16];
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                D[c] = P[c0 + r][c];
-                Pr[c] = P[i][c];  // (rows above the block: nothing reads what they become)
+                D[c] = s.row(J, c0 + r)[c];
+                Pr[c] = s.row(J, i)[c];  // (rows above the block: nothing reads what they become)
             }
             bool ok = true;
             double pv = 1.0, iv = 1.0;
@@ -514,21 +524,23 @@ __device__ bool factor_big(BigLds& s, double* L, const double* __restrict__ A, c
 #pragma unroll
                 for (int c = 0; c < 16; ++c) {
                     const double v = rr > c ? Pr[c] : 0.0;
-                    P[i][c] = v;
-                    L[(int64_t)(c0 + c) * KLD + i] = v;
-                    L[(int64_t)(KMAX + i) * KLD + c0 + c] = v;
+                    s.row(J, i)[c] = v;
+                    if (!BigLds<NB>::IN_LDS) {
+                        L[(int64_t)(c0 + c) * KLD + i] = v;
+                        L[(int64_t)(KMAX + i) * KLD + c0 + c] = v;
+                    }
                 }
             }
         }
         __syncthreads();
         if (s.fail) return false;
 #pragma unroll
-        for (int q = 0; q < BIG_SLOTS; ++q) {
+        for (int q = 0; q < SLOTS; ++q) {
             if (bj[q] <= J) continue;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const double av = P[(bi[q] << 4) + r][4 * k + lk];
-                const double bv = -s.piv[c0 + 4 * k + lk] * P[(bj[q] << 4) + r][4 * k + lk];
+                const double av = s.row(J, (bi[q] << 4) + r)[4 * k + lk];
+                const double bv = -s.piv[c0 + 4 * k + lk] * s.row(J, (bj[q] << 4) + r)[4 * k + lk];
                 acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[q], 0, 0, 0);
             }
         }
@@ -537,7 +549,8 @@ __device__ bool factor_big(BigLds& s, double* L, const double* __restrict__ A, c
 }
 
 // y = U^{-1} b, one entry per thread i < KMAX.
-__device__ double fwd_big(BigLds& s, const double* L, int K, double b) {
+template <int NB>
+__device__ double fwd_big(BigLds<NB>& s, const double* L, int K, double b) {
     const int i = threadIdx.x, r = i & 15, nbk = (K + 15) >> 4;
     double y = i < K ? b : 0.0;
     for (int J = 0; J < nbk; ++J) {
@@ -547,8 +560,8 @@ __device__ double fwd_big(BigLds& s, const double* L, int K, double b) {
         if (work) {
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                d[c] = L[(int64_t)(c0 + c) * KLD + c0 + r];
-                l[c] = L[(int64_t)(c0 + c) * KLD + i];
+                d[c] = BigLds<NB>::IN_LDS ? s.row(J, c0 + r)[c] : L[(int64_t)(c0 + c) * KLD + c0 + r];
+                l[c] = BigLds<NB>::IN_LDS ? s.row(J, i)[c] : L[(int64_t)(c0 + c) * KLD + i];
             }
         }
         if ((i >> 4) == J) s.x[J & 1][r] = y;
@@ -566,7 +579,8 @@ __device__ double fwd_big(BigLds& s, const double* L, int K, double b) {
 }
 
 // z = U^{-T} y, blocks from the last one up.
-__device__ double bwd_big(BigLds& s, const double* L, int K, double y) {
+template <int NB>
+__device__ double bwd_big(BigLds<NB>& s, const double* L, int K, double y) {
     const int i = threadIdx.x, r = i & 15, nbk = (K + 15) >> 4;
     const double* R = L + (int64_t)KMAX * KLD;  // by rows
     double z = i < K ? y : 0.0;
@@ -578,8 +592,8 @@ __device__ double bwd_big(BigLds& s, const double* L, int K, double y) {
         if (work) {
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                d[c] = R[(int64_t)(c0 + c) * KLD + c0 + r];
-                l[c] = R[(int64_t)(c0 + c) * KLD + i];
+                d[c] = BigLds<NB>::IN_LDS ? s.row(J, c0 + c)[r] : R[(int64_t)(c0 + c) * KLD + c0 + r];
+                l[c] = BigLds<NB>::IN_LDS ? s.F[0][c0 + c][i] : R[(int64_t)(c0 + c) * KLD + i];
             }
         }
         if ((i >> 4) == J) s.x[J & 1][r] = z;
@@ -597,7 +611,8 @@ __device__ double bwd_big(BigLds& s, const double* L, int K, double y) {
     return i < K ? z : 0.0;
 }
 
-__device__ Eval evaluate_big(BigLds& s, double* L, const double* __restrict__ GA, const double* __restrict__ GT, int K,
+template <int NB>
+__device__ Eval evaluate_big(BigLds<NB>& s, double* L, const double* __restrict__ GA, const double* __restrict__ GT, int K,
                              double lam, double bb, double d, bool deriv, int& nfac) {
     const int i = threadIdx.x;
     Eval e{false, 0.0, 0.0, 0.0};
@@ -633,13 +648,14 @@ __device__ Eval evaluate_big(BigLds& s, double* L, const double* __restrict__ GA
     return e;
 }
 
+template <int NB>
 __global__ __launch_bounds__(BIG_T) void k_small_solve_big(int K, const double* __restrict__ GA,
                                                            const double* __restrict__ GT,
                                                            const double* __restrict__ dvec,
                                                            const double* __restrict__ sc, double fixed_lambda,
                                                            double* L, double* __restrict__ zout,
                                                            double* __restrict__ res, double* __restrict__ lam_out) {
-    __shared__ BigLds s;
+    __shared__ BigLds<NB> s;
     const int i = threadIdx.x;
     const double d = i < K ? dvec[i] : 0.0;
     const double bb = sc[0], target = sc[1];
@@ -674,9 +690,11 @@ void small_solve(Ctx& c, int K, const double* GA, const double* GT, const double
         hipLaunchKernelGGL(k_small_solve, dim3(1), dim3(64), 0, c.stream, K, GA, GT, d, sc, fixed_lambda, z, res,
                            lam_out, T, zt);
     } else {
-        double* Lg = static_cast<double*>(c.work("small_L", sizeof(double) * 2 * (size_t)KLD * KLD));
-        hipLaunchKernelGGL(k_small_solve_big, dim3(1), dim3(BIG_T), 0, c.stream, K, GA, GT, d, sc, fixed_lambda, Lg,
-                           z, res, lam_out);
+        const bool lds = K <= 128;
+        double* Lg = lds ? nullptr
+                         : static_cast<double*>(c.work("small_L", sizeof(double) * 2 * (size_t)KLD * KLD));
+        hipLaunchKernelGGL(lds ? k_small_solve_big<8> : k_small_solve_big<16>, dim3(1), dim3(BIG_T), 0, c.stream, K, GA,
+                           GT, d, sc, fixed_lambda, Lg, z, res, lam_out);
         if (zt && T)
             basis_coef(c, K, T, z, zt);
         else if (zt)
