@@ -1313,100 +1313,106 @@ void cgs_once(Ctx& c, int64_t n, int K, const double* Q, int64_t ld, double* x, 
 // ---------------------------------------------------------------- implicit basis
 // The true basis is V = Vs T with Vs the stored columns and T unit upper triangular
 // (column-major, leading dimension KLD: T(i, j) = T[j * KLD + i], column j = the coefficients
-// of v_j in Vs).  One workgroup of KB threads; K <= KMAX.
+// of v_j in Vs); K <= KMAX.
 
-// g = T^T h (g_i = sum_{k <= i} T(k, i) h_k; h in LDS), into LDS, and its squared norm (thread 0).
-__device__ double basis_coeffs(int K, const double* __restrict__ T, const double* h, double* g, double* s4) {
-    double e2 = 0.0;
-    for (int i = threadIdx.x; i < K; i += KB) {
-        const double* ti = T + (int64_t)i * KLD;
+static constexpr int BT = 1024;  // threads of the one-workgroup steps: 16 waves
+
+struct BasisLds {
+    double h[KMAX + 1], g[KMAX], p[BT / 64][64], g2;
+};
+
+// out(i, sum over k < n of f(i, k)) for i < K: lane l of every wave takes i = i0 + l, wave w the k's of 4 w .. 4 w + 3 of
+// every 64, the waves' parts added in wave order (f is called with k inside [0, n) only as far as `in` says).
+template <class F, class OUT>
+__device__ void basis_product(BasisLds& s, int K, int n, F&& f, OUT&& out) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int i0 = 0; i0 < K; i0 += 64) {
+        const int i = min(i0 + lane, K - 1);
         double a = 0.0;
-        for (int k = 0; k < i; ++k) a = fma(ti[k], h[k], a);
-        a += h[i];  // T(i, i) = 1
-        g[i] = a;
-        e2 = fma(a, a, e2);
+        for (int k0 = 4 * w; k0 < n; k0 += 64) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a = f(i, min(k0 + q, n - 1), k0 + q < n, a);
+        }
+        s.p[w][lane] = a;
+        __syncthreads();
+        if (w == 0 && i0 + lane < K) {
+            double r = 0.0;
+#pragma unroll
+            for (int q = 0; q < BT / 64; ++q) r += s.p[q][lane];
+            out(i, r);
+        }
+        __syncthreads();
     }
-    return block_sum(e2, s4);  // (also orders the writes of g before any later read)
 }
 
-// The fixed-order sums of the chunk partials of h = Vs^T r and ||r||^2 (columns 0 .. K, nb of them
-// each) by one workgroup, a wave per column, into LDS and h; nb = 0: h[0..K] is already formed.
-__device__ void basis_sums(int K, int nb, const double* __restrict__ part, double* h, double* hs) {
+// s.h[0..K] = the fixed-order sums of the chunk partials of h = Vs^T r and ||r||^2 (columns 0 .. K, nb of them each), a
+// wave per column, also into h; nb = 0: h[0..K] is already formed.  s.g = T^T h (h in the LDS) and s.g2 = ||g||^2.
+__device__ void basis_coeffs(BasisLds& s, int K, int nb, const double* __restrict__ part, const double* __restrict__ T,
+                             double* h) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (nb == 0) {
-        for (int j = threadIdx.x; j <= K; j += KB) hs[j] = h[j];
+        for (int j = threadIdx.x; j <= K; j += BT) s.h[j] = h[j];
     } else {
-        const int lane = threadIdx.x & 63;
-        for (int j0 = (int)(threadIdx.x >> 6); j0 <= K; j0 += 4 * (KB / 64)) {
-            double a[4];  // four columns' loads in flight
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = j0 + q * (KB / 64);
-                a[q] = 0.0;
-                for (int b = lane; j <= K && b < nb; b += 64) a[q] += part[(int64_t)j * nb + b];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = j0 + q * (KB / 64);
-                const double s = wave_sum(a[q]);
-                if (lane == 0 && j <= K) hs[j] = h[j] = s;
-            }
+        for (int j = w; j <= K; j += BT / 64) {
+            double a = 0.0;
+#pragma unroll 4
+            for (int b = lane; b < nb; b += 64) a += part[(int64_t)j * nb + b];
+            a = wave_sum(a);
+            if (lane == 0) s.h[j] = h[j] = a;
         }
     }
     __syncthreads();
+    basis_product(s, K, K, [&](int i, int k, bool in, double a) {  // T(i, i) = 1; column i holds rows up to i
+        return fma(T[(int64_t)i * KLD + min(k, i)], in && k <= i ? s.h[k] : 0.0, a);
+    }, [&](int i, double v) { s.g[i] = v; });
+    if (w == 0) {
+        double e = 0.0;
+        for (int i = lane; i < K; i += 64) e = fma(s.g[i], s.g[i], e);
+        e = wave_sum(e);
+        if (lane == 0) s.g2 = e;
+    }
+    __syncthreads();
+}
+
+// out(k, (T g)_k)
+template <class OUT>
+__device__ void basis_apply(BasisLds& s, int K, const double* __restrict__ T, OUT&& out) {
+    basis_product(s, K, K, [&](int k, int i, bool in, double a) {
+        return fma(T[(int64_t)max(i, k) * KLD + k], in && i >= k ? s.g[i] : 0.0, a);
+    }, out);
 }
 
 // keep[0] = 1 when ||r||^2 - ||g||^2 >= ||r||^2 / 2 (r keeps at least 1/sqrt(2) of its norm
 // outside the basis: no explicit pass); otherwise keep[0] = 0 and hc = T g, the coefficients
-// in Vs of the part of r along the basis.  h[0..K] from basis_sums.
-__global__ __launch_bounds__(KB) void k_basis_check(int K, int nb, const double* __restrict__ part,
+// in Vs of the part of r along the basis.  Bound by the latency of its loads, which the waves share
+// (up to 30 columns with 32 chunks 3.6 us, 5.9 with a thread per coefficient; with 256 chunks 4.9, 11.4).
+__global__ __launch_bounds__(BT) void k_basis_check(int K, int nb, const double* __restrict__ part,
                                                     const double* __restrict__ T, double* h,
                                                     double* __restrict__ hc, int* __restrict__ keep) {
-    __shared__ double g[KMAX], hs[KMAX + 1];
-    __shared__ double s4[4];
-    __shared__ int need;
-    basis_sums(K, nb, part, h, hs);
-    const double G2 = basis_coeffs(K, T, hs, g, s4);
-    if (threadIdx.x == 0) {
-        need = !(hs[K] - G2 >= 0.5 * hs[K]);
-        keep[0] = need ? 0 : 1;
-    }
-    __syncthreads();
-    if (!need) return;
-    for (int k = threadIdx.x; k < K; k += KB) {
-        double a = g[k];  // T(k, k) = 1
-        for (int i = k + 1; i < K; ++i) a = fma(T[(int64_t)i * KLD + k], g[i], a);
-        hc[k] = a;
-    }
+    __shared__ BasisLds s;
+    basis_coeffs(s, K, nb, part, T, h);
+    const bool need = !(s.h[K] - s.g2 >= 0.5 * s.h[K]);  // (the same on every thread)
+    if (threadIdx.x == 0) keep[0] = need ? 0 : 1;
+    if (need) basis_apply(s, K, T, [&](int k, double v) { hc[k] = v; });
 }
 
 // Appends column K of T for a new stored column vs_K = r / rho: g = T^T h with h = Vs^T r,
 // rho^2 = ||r||^2 - ||g||^2 (written to sq[0]), T(:, K) = e_K - T g / rho, so that
-// v_K = vs_K - V g / rho = (r - V V^T r) / rho.  h[0..K] from basis_sums unless *keep (h is still
+// v_K = vs_K - V g / rho = (r - V V^T r) / rho.  h[0..K] from the partials unless *keep (h is still
 // that of the check).
-__global__ __launch_bounds__(KB) void k_basis_append(int K, int nb, const double* __restrict__ part,
+__global__ __launch_bounds__(BT) void k_basis_append(int K, int nb, const double* __restrict__ part,
                                                      double* __restrict__ T, double* h, const int* __restrict__ keep,
                                                      double* __restrict__ sq) {
-    __shared__ double g[KMAX], hs[KMAX + 1];
-    __shared__ double s4[4];
-    __shared__ double inv;
-    basis_sums(K, *keep ? 0 : nb, part, h, hs);
-    const double G2 = basis_coeffs(K, T, hs, g, s4);
-    if (threadIdx.x == 0) {
-        const double rho2 = fmax(hs[K] - G2, 0.0);
-        sq[0] = rho2;
-        inv = rho2 > 0.0 ? 1.0 / sqrt(rho2) : 0.0;
-    }
-    __syncthreads();
+    __shared__ BasisLds s;
+    basis_coeffs(s, K, *keep ? 0 : nb, part, T, h);
+    const double rho2 = fmax(s.h[K] - s.g2, 0.0);
+    const double inv = rho2 > 0.0 ? 1.0 / sqrt(rho2) : 0.0;
     double* tK = T + (int64_t)K * KLD;
-    for (int k = threadIdx.x; k <= K; k += KB) {
-        if (k == K) {
-            tK[k] = 1.0;
-            continue;
-        }
-        double a = g[k];
-        for (int i = k + 1; i < K; ++i) a = fma(T[(int64_t)i * KLD + k], g[i], a);
-        tK[k] = -a * inv;
+    if (threadIdx.x == 0) {
+        sq[0] = rho2;
+        tK[K] = 1.0;
     }
+    basis_apply(s, K, T, [&](int k, double v) { tK[k] = -v * inv; });
 }
 
 // Column j = blockIdx.x of G = T^T Gs T (both triangles) for one of two Gram matrices (blockIdx.y),
@@ -1509,7 +1515,7 @@ void basis_extend(Ctx& c, int64_t n, int K, const double* Vs, int64_t ld, double
         if (!own) mdot_final(c, nb, K + 1, part, 1.0, h, nullptr, 0, 0, nullptr, skip);
     };
     dots(nullptr, "mdot");
-    hipLaunchKernelGGL(k_basis_check, dim3(1), dim3(KB), 0, c.stream, K, own ? nb : 0, (const double*)part,
+    hipLaunchKernelGGL(k_basis_check, dim3(1), dim3(BT), 0, c.stream, K, own ? nb : 0, (const double*)part,
                        (const double*)T, h, hc, keep);
     MMOF_LAUNCH_CHECK();
     // where r lies mostly in the basis: r <- r - V V^T r explicitly and h = Vs^T r, ||r||^2 again;
@@ -1517,7 +1523,7 @@ void basis_extend(Ctx& c, int64_t n, int K, const double* Vs, int64_t ld, double
     gemv_fused_impl<double, double>(c, n, K, Vs, ld, hc, -1.0, r, 1.0, r, (double*)nullptr, nullptr, nullptr, keep,
                                     "cgs_second");
     dots(keep, "cgs_second");
-    hipLaunchKernelGGL(k_basis_append, dim3(1), dim3(KB), 0, c.stream, K, own ? nb : 0, (const double*)part, T, h,
+    hipLaunchKernelGGL(k_basis_append, dim3(1), dim3(BT), 0, c.stream, K, own ? nb : 0, (const double*)part, T, h,
                        (const int*)keep, sq);
     MMOF_LAUNCH_CHECK();
 }
