@@ -272,49 +272,59 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
     }
 }
 
-// Transpose: one workgroup per ATW x ATH = 32 x 16 pixel tile, each lane two pixels 16 apart in
-// a row (x and x + 16).  For each angle the tile projects onto fewer than AW - 2 consecutive
-// bins (its extent sqrt(31^2 + 15^2) < 35 bins); those sinogram windows are staged in LDS, AC
+// Transpose: one workgroup per 32 x 16 PY pixel tile, each lane 2 PY pixels 16 apart in its rows
+// and columns.  For each angle the tile projects onto fewer than AW - 2 consecutive bins (its
+// extent sqrt(31^2 + 31^2) < 44 bins for PY = 2); those sinogram windows are staged in LDS, AC
 // angles at a time, as pairs (b_j, b_{j+1} - b_j) with zeros outside the detector, and a pixel
-// then gathers b_j0 + f (b_j0+1 - b_j0) per angle with one LDS load.  FP32: per (tile, angle)
-// the detector coordinate of the tile centre in FP64, split into its floor J and an FP32
-// fraction; the lane's first pixel at (dx, dy) from the centre (|dx| <= 15.5, |dy| <= 7.5) is at
-// J + t, t = frac + dx cos + dy sin in FP32, the second at t + 16 cos (error below 5e-6 bins),
-// and the weights come from floor(t) and fract(t); the window has one bin of margin on each
-// side, so a floor one off at an integer stays inside it (and gives the same value).  FP64:
-// each lane's first position in FP64 from its own coordinates, the second 16 cos further.
+// then gathers b_j0 + f (b_j0+1 - b_j0) per angle with one LDS load.  FP32: per 16 rows of
+// the tile and angle the detector coordinate of their centre in FP64, split into its floor J and an
+// FP32 fraction; the lane's first pixel at (dx, dy) from that centre (|dx| <= 15.5, |dy| <= 7.5) is
+// at J + t, t = frac + dx cos + dy sin in FP32, the second at t + 16 cos (error below 5e-6 bins,
+// whatever PY), and the weights come from floor(t) and fract(t); the window has one bin of margin on
+// each side, so a floor one off at an integer stays inside it (and gives the same value).  FP64: each lane's first position in FP64 from its own coordinates, the others 16 cos and 16 sin further,
+// counted from the window's first bin: at least 1, so that the bin is one conversion and the weight
+// one fract.
 // The windows cover the whole tile, also where it overhangs the frame, so every lane's
 // gathers stay inside them; pixels outside the frame are not written.
-static constexpr int ATW = 32, ATH = 16;  // pixel tiles of the transposes (parallel and fan beam)
+// Bound by the reads of the LDS (per angle and lane the record of the angle, 16 or 24 bytes, and a
+// pair per pixel) and by vector issue: four pixels share a record and a window where two did.
+// 1024 x 1024 x 16, 90 angles: FP32 280 -> 265 us, FP64 565 -> 367 (470 from the cheaper positions
+// alone); 16 x 128 x 128, 30 angles, FP64 (PY = 1) 6.4 -> 5.8; 251 x 310 x 16, 45 angles, FP64 26 -> 18.
+static constexpr int ATW = 32, ATH = 16;  // pixel tiles of the transposes (parallel with PY = 1, and fan beam)
 static constexpr int AW = 48, AC = 32;
 
 struct AdjAngle {
-    float frac, c, s;
+    float frac;
     uint32_t base;   // LDS byte offset of bin J in the angle's window (from the window array)
+    float c, s;
 };
 
-template <class T>
-__global__ __launch_bounds__(256) void k_radon_adj(const Tile* __restrict__ tiles, const RadonFrame* __restrict__ rf,
-                                                   const double2* __restrict__ trig, const T* __restrict__ b,
-                                                   T* __restrict__ u) {
+struct AdjAngle64 {
+    double c, s, at;   // at: the detector coordinate of the frame's centre, counted from the window's first bin
+};
+
+template <class T, int PY>
+__global__ __launch_bounds__(256, PY == 1 && sizeof(T) == 4 ? 6 : 4) void k_radon_adj(
+    const Tile* __restrict__ tiles, const RadonFrame* __restrict__ rf, const double2* __restrict__ trig,
+    const T* __restrict__ b, T* __restrict__ u) {
+    constexpr int TH = ATH * PY;
     typedef T P2 __attribute__((ext_vector_type(2)));  // {b_j, b_{j+1} - b_j}
     __shared__ P2 win[AC][AW];
     __shared__ int jlo[AC];
-    __shared__ double2 scs[AC];
-    __shared__ AdjAngle aa[AC];
+    __shared__ AdjAngle64 scs[AC];
+    __shared__ AdjAngle aa[PY][AC];
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const RadonFrame f = rf[tl.frame];
     const int lx = (int)(threadIdx.x % 16), ly = (int)(threadIdx.x / 16);
-    const int x = tl.x0 + lx, y = tl.y0 + ly;  // the lane's pixels: (x, y) and (x + 16, y)
-    const bool in0 = x < f.nx && y < f.ny, in1 = x + 16 < f.nx && y < f.ny;
+    const int x = tl.x0 + lx, y = tl.y0 + ly;  // the lane's first pixel
     const double hx = 0.5 * (f.nx - 1), hy = 0.5 * (f.ny - 1);
     const double X = x - hx, Y = y - hy;
     const double cd = 0.5 * (f.n_bins - 1);
     // corners of the whole tile for the window bounds
     const double X0 = tl.x0 - hx, X1 = tl.x0 + ATW - 1 - hx;
-    const double Y0 = tl.y0 - hy, Y1 = tl.y0 + ATH - 1 - hy;
+    const double Y0 = tl.y0 - hy, Y1 = tl.y0 + TH - 1 - hy;
     const T* sino = b + f.sino_off;
-    T acc0 = T(0), acc1 = T(0);
+    T acc[PY][2] = {};
     const double XC = tl.x0 + 0.5 * (ATW - 1) - hx, YC = tl.y0 + 0.5 * (ATH - 1) - hy;
     const float dxc = (float)lx - 0.5f * (ATW - 1);
     const float dyc = (float)ly - 0.5f * (ATH - 1);
@@ -326,12 +336,17 @@ __global__ __launch_bounds__(256) void k_radon_adj(const Tile* __restrict__ tile
             const double pmin = cd + fmin(X0 * cs.x, X1 * cs.x) + fmin(Y0 * cs.y, Y1 * cs.y);
             const int lo = (int)floor(pmin) - 1;
             jlo[threadIdx.x] = lo;
-            scs[threadIdx.x] = cs;
-            if constexpr (sizeof(T) == 4) {
-                const double pc = fma(XC, cs.x, fma(YC, cs.y, cd));
-                const double J = floor(pc);
-                aa[threadIdx.x] = AdjAngle{(float)(pc - J), (float)cs.x, (float)cs.y,
-                                           (uint32_t)((int)threadIdx.x * AW + (int)J - lo) * (uint32_t)sizeof(P2)};
+            if constexpr (sizeof(T) == 8) {
+                scs[threadIdx.x] = AdjAngle64{cs.x, cs.y, cd - lo};
+            } else {
+#pragma unroll
+                for (int r = 0; r < PY; ++r) {
+                    const double pc = fma(XC, cs.x, fma(YC + ATH * r, cs.y, cd));
+                    const double J = floor(pc);
+                    aa[r][threadIdx.x] =
+                        AdjAngle{(float)(pc - J), (uint32_t)((int)threadIdx.x * AW + (int)J - lo) * (uint32_t)sizeof(P2),
+                                 (float)cs.x, (float)cs.y};
+                }
             }
         }
         __syncthreads();
@@ -355,24 +370,26 @@ __global__ __launch_bounds__(256) void k_radon_adj(const Tile* __restrict__ tile
             if (i / AW < nk) win[i / AW][i % AW] = P2{v0[m], v1[m] - v0[m]};
         }
         __syncthreads();
-        if (!in0) continue;
+        if (x >= f.nx || y >= f.ny) continue;
         if constexpr (sizeof(T) == 4) {
             const char* wb = reinterpret_cast<const char*>(&win[0][0]);
-            float a0 = 0.f, d0 = 0.f, a1 = 0.f, d1 = 0.f;
+            float a[PY][2] = {}, d[PY][2] = {};
             auto one = [&](int kk) {
-                const AdjAngle g = aa[kk];
-                const float t0 = fmaf(dxc, g.c, fmaf(dyc, g.s, g.frac));
-                const float t1 = fmaf(16.f, g.c, t0);
-                int w0, w1;
-                asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(w0) : "v"(t0));
-                asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(w1) : "v"(t1));
-                const float f0 = __builtin_amdgcn_fractf(t0), f1 = __builtin_amdgcn_fractf(t1);
-                const P2 q0 = *reinterpret_cast<const P2*>(wb + (g.base + ((uint32_t)w0 << 3)));
-                const P2 q1 = *reinterpret_cast<const P2*>(wb + (g.base + ((uint32_t)w1 << 3)));
-                a0 += q0.x;
-                d0 = fmaf(f0, q0.y, d0);
-                a1 += q1.x;
-                d1 = fmaf(f1, q1.y, d1);
+                const float gc = aa[0][kk].c, gs = aa[0][kk].s;
+#pragma unroll
+                for (int r = 0; r < PY; ++r) {
+                    const float tr = fmaf(dxc, gc, fmaf(dyc, gs, aa[r][kk].frac));
+                    const uint32_t base = aa[r][kk].base;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float t = e ? fmaf(16.f, gc, tr) : tr;
+                        int w;
+                        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(w) : "v"(t));
+                        const P2 v = *reinterpret_cast<const P2*>(wb + (base + ((uint32_t)w << 3)));
+                        a[r][e] += v.x;
+                        d[r][e] = fmaf(__builtin_amdgcn_fractf(t), v.y, d[r][e]);
+                    }
+                }
             };
             int kk = 0;
             for (; kk + 4 <= nk; kk += 4) {
@@ -382,24 +399,29 @@ __global__ __launch_bounds__(256) void k_radon_adj(const Tile* __restrict__ tile
                 one(kk + 3);
             }
             for (; kk < nk; ++kk) one(kk);
-            acc0 += a0 + d0;
-            acc1 += a1 + d1;
+#pragma unroll
+            for (int q = 0; q < 2 * PY; ++q) acc[q / 2][q % 2] += a[q / 2][q % 2] + d[q / 2][q % 2];
         } else {
 #pragma unroll 4
             for (int kk = 0; kk < nk; ++kk) {
-                const double2 cs = scs[kk];
-                const double p0 = fma(X, cs.x, fma(Y, cs.y, cd));
-                const double p1 = fma(16.0, cs.x, p0);
-                const double fl0 = floor(p0), fl1 = floor(p1);
-                const P2 q0 = win[kk][(int)fl0 - jlo[kk]];
-                const P2 q1 = win[kk][(int)fl1 - jlo[kk]];
-                acc0 += q0.x + (T)(p0 - fl0) * q0.y;
-                acc1 += q1.x + (T)(p1 - fl1) * q1.y;
+                const AdjAngle64 g = scs[kk];
+                const double pf = fma(X, g.c, fma(Y, g.s, g.at));
+#pragma unroll
+                for (int q = 0; q < 2 * PY; ++q) {
+                    const int r = q / 2, e = q % 2;
+                    const double pr = r ? fma(16.0, g.s, pf) : pf;
+                    const double t = e ? fma(16.0, g.c, pr) : pr;
+                    const P2 v = win[kk][(int)t];  // (t >= 1, so truncation is the floor)
+                    acc[r][e] += v.x + (T)__builtin_amdgcn_fract(t) * v.y;
+                }
             }
         }
     }
-    if (in0) u[f.u_off + (int64_t)y * f.nx + x] = acc0;
-    if (in1) u[f.u_off + (int64_t)y * f.nx + x + 16] = acc1;
+#pragma unroll
+    for (int q = 0; q < 2 * PY; ++q) {
+        const int px = x + 16 * (q % 2), py = y + 16 * (q / 2);
+        if (px < f.nx && py < f.ny) u[f.u_off + (int64_t)py * f.nx + px] = acc[q / 2][q % 2];
+    }
 }
 
 // ----------------------------------------------------------------------------- host side
@@ -1024,9 +1046,18 @@ void launch_radon_adj(Ctx& c, Plan& p, int dt, const void* b, void* u) {
     dispatch(dt, [&](auto z) {
         using T = decltype(z);
         ScopedTime st(&c, "radon_adj", (double)sizeof(T) * (p.n + p.m), p.radon_flops);
-        hipLaunchKernelGGL(k_radon_adj<T>, dim3((unsigned)p.n_tiles_a), dim3(256), 0, c.stream,
-                           p.d_tiles_a.as<Tile>(), p.d_rinfo.as<RadonFrame>(), p.d_trig.as<double2>(), (const T*)b,
-                           (T*)u);
+        // Tiles of 32 rows where enough of them keep each CU busy to its end: in FP64 from 4 per CU on (16 frames of
+        // 256 x 256, 45 angles 17.2 us against 20.2 with 16 rows, 12 frames the same, 8 frames 12.5 against 11.1), in
+        // FP32, which gains less, from 16 (16 frames of 256 x 256, 4 per CU, 12.9 against 13.9, but 20 of 250 x 250, 5 per CU, 12.1
+        // against 11.5; 32 of 512 x 512, 32 per CU, 94 against 100); and where the rows that they overhang the frames by
+        // cost less than they gain (0.95 of the time per pixel in FP32, 0.81 in FP64).
+        const int64_t per_cu = sizeof(T) == 4 ? 16 : 4;
+        const double cost = sizeof(T) == 4 ? 0.95 : 0.81;
+        const bool two = p.n_tiles_b >= per_cu * c.cu_count && 2.0 * cost * (double)p.n_tiles_b < (double)p.n_tiles_a;
+        auto k = two ? k_radon_adj<T, 2> : k_radon_adj<T, 1>;
+        hipLaunchKernelGGL(k, dim3((unsigned)(two ? p.n_tiles_b : p.n_tiles_a)), dim3(256), 0, c.stream,
+                           (two ? p.d_tiles_b : p.d_tiles_a).as<Tile>(), p.d_rinfo.as<RadonFrame>(),
+                           p.d_trig.as<double2>(), (const T*)b, (T*)u);
         MMOF_LAUNCH_CHECK();
     });
 }
