@@ -434,6 +434,11 @@ void radon_plan_init(Ctx& c, Plan& p, const double* cs) {
     std::vector<Tile> px, tr;
     int64_t sino = 0, trig = 0;
     p.tr_vec = true;
+    size_t n_recs = 0;
+    for (int64_t fi = 0; fi < g.n_frames; ++fi)
+        n_recs += (size_t)p.n_ang[g.frames[fi].seq] * (size_t)cdiv(p.n_bins[g.frames[fi].seq], 64);
+    rays[0].reserve(n_recs);
+    if (p.kind == 0) recs.reserve(n_recs);
     for (int64_t fi = 0; fi < g.n_frames; ++fi) {
         const FrameInfo& fr = g.frames[fi];
         // the projectors address pixels by 32-bit offsets within a frame
