@@ -289,7 +289,7 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
 // Bound by the reads of the LDS (per angle and lane the record of the angle, 16 or 24 bytes, and a
 // pair per pixel) and by vector issue: four pixels share a record and a window where two did.
 // 1024 x 1024 x 16, 90 angles: FP32 280 -> 265 us, FP64 565 -> 367 (470 from the cheaper positions
-// alone); 16 x 128 x 128, 30 angles, FP64 (PY = 1) 6.4 -> 5.8; 251 x 310 x 16, 45 angles, FP64 26 -> 18.
+// alone); 16 x 128 x 128, 30 angles, FP64 (PY = 1) 6.4 -> 5.8; 251 x 310 x 16, 45 angles, FP64 32 -> 23.
 static constexpr int ATW = 32, ATH = 16;  // pixel tiles of the transposes (parallel with PY = 1, and fan beam)
 static constexpr int AW = 48, AC = 32;
 
