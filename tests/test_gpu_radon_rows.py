@@ -1,6 +1,6 @@
 """GPU parity of the parallel-beam projector.  The transpose on tiles of 32 rows; the forward at the edges of its row
-groups and lines: frames of 2 and 3 columns, row counts around the groups of 4 and 8 and their split over waves, rays along the
-axes, on the diagonal and nearly along an axis, detectors narrower and wider than the frame; every
+groups and lines: frames of 2 and 3 columns, row counts around the groups of 4 and 8 and their split over waves, rays
+along the axes, on the diagonal and nearly along an axis, detectors narrower and wider than the frame; every
 angle grouping.  FP64 1e-12, FP32 1e-5 of the projection of |u|."""
 import numpy as np
 import pytest
