@@ -493,13 +493,15 @@ __device__ bool factor_big(BigLds<NB>& s, double* L, const double* __restrict__ 
         }
         __syncthreads();
         const int i = (wave << 6) + lane;
-        if (wave < BigLds<NB>::RW && (wave << 6) + 63 >= c0 && (wave << 6) < (nbk << 4)) {
-            double D[16], Pr[16];
+        double D[16];
 #pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                D[c] = s.row(J, c0 + r)[c];
-                Pr[c] = s.row(J, i)[c];  // (rows above the block: nothing reads what they become)
-            }
+        for (int c = 0; c < 16; ++c) D[c] = s.row(J, c0 + r)[c];
+        // every wave has read the diagonal block: the one that owns its rows writes their factor over it
+        __syncthreads();
+        if (wave < BigLds<NB>::RW && (wave << 6) + 63 >= c0 && (wave << 6) < (nbk << 4)) {
+            double Pr[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c) Pr[c] = s.row(J, i)[c];  // (rows above the block: nothing reads what they become)
             bool ok = true;
             double pv = 1.0, iv = 1.0;
             static_for<0, 16>([&](auto C) {
