@@ -8,8 +8,9 @@
 // Steep angles use the same loop over the columns of a transposed copy of the frame,
 // so every lane of a wavefront walks contiguous memory.  Transpose (pixel-driven
 // gather, one lane per pixel): each angle contributes (1-f) b[j0] + f b[j0+1] with
-// j0 + f = tau_p + (n_d-1)/2.  Sample positions are formed in double; the weights are
-// evaluated in the operator's precision.
+// j0 + f = tau_p + (n_d-1)/2.  Sample positions are formed in double (the FP32 forward steps
+// through a group of rows in 64-bit fixed point, the FP32 transpose from a tile's centre in FP32);
+// the weights are evaluated in the operator's precision.
 #include "dev.h"
 #include "kernels.h"
 
@@ -96,43 +97,67 @@ __global__ __launch_bounds__(256) void k_transpose_frames4(const Tile* __restric
 // 1/|a| <= sqrt(2) of xs.
 // INNER: all three are inside the line on every row.  Otherwise the three are read at the nearest
 // place inside (lines of at least 3 pixels) and weigh by their own distance.
-// FP32: xb + 1/2 (FP64) is split into its floor and a fraction fb; row k at t = fb + k step in FP32
-// (error below 1e-6 px for |step| <= 1, k < 8), n = floor(t) + that floor through a floor-convert,
-// f = fract(t) = d + 1/2.  The three pixels come in one 12-byte load at a 32-bit offset from a base
+// FP32: xb - 1/2 (FP64) and step are taken as fixed-point numbers of 32 fraction bits, so that row k is at the sum of
+// the first and k steps within 2^-29 px, n - 1 is its upper word and f = d + 1/2 its lower one, rounded to FP32 as a
+// fraction formed in FP64 would be.  That is three instructions a row, as many as positions held in FP32 take, which
+// are off by up to 1e-6 px: 16 frames of 128 x 128 of either sign, 30 angles: error of H u 1.5e-7 with those, 0.9e-7 so,
+// at the same time.  The three pixels come in one 12-byte load at a 32-bit offset from a base
 // that is the same for the whole wave, and the outer weights (1 - |a|/2) - |a| f and (1 - 3|a|/2) +
 // |a| f are single FMAs clamped to [0, 1] by the FMA's output clamp.
 static constexpr double INTERIOR_MARGIN = 1e-3;
+static constexpr float FIX_ONE = 4294967296.f;  // 2^32: a whole pixel in units of the last fraction bit
+
+// A number in 32.32 fixed point.
+struct Fixed {
+    int32_t whole;
+    uint32_t frac;
+    __device__ __forceinline__ void add(Fixed o) {
+        unsigned c;
+        frac = __builtin_addc(frac, o.frac, 0u, &c);
+        whole = (int32_t)((uint32_t)whole + (uint32_t)o.whole + c);
+    }
+};
+
+// v in fixed point, its floor clamped to lo .. hi.
+__device__ __forceinline__ Fixed fixed32(double v, double lo, double hi) {
+    const double fl = floor(v);
+    return Fixed{(int32_t)fmin(fmax(fl, lo), hi), (uint32_t)fmin((v - fl) * (double)FIX_ONE, 4294967295.0)};
+}
+
+// A position's step per row as hat_rows and fan_rows take it (|step| <= 1).
+template <class T>
+__device__ __forceinline__ auto row_step(double step) {
+    if constexpr (sizeof(T) == 4) return fixed32(step, -1.0, 1.0);
+    else return step;
+}
 
 template <bool INNER, int G>
-__device__ __forceinline__ float hat_rows(const float* __restrict__ line, int ncol, double xb, double step, float aa) {
-    const double xh = xb + 0.5;
-    const double flb = INNER ? floor(xh) : fmin(fmax(floor(xh), -16.0), (double)ncol + 16.0);
-    const float fb = INNER ? (float)(xh - flb) : (float)fmin(fmax(xh - flb, -1.0), 2.0);
-    const int ib = (int)flb - 1;
-    const float stepf = (float)step;
-    const float cm = 1.f - 0.5f * aa, cp = 1.f - 1.5f * aa;
+__device__ __forceinline__ float hat_rows(const float* __restrict__ line, int ncol, double xb, Fixed step, float aa) {
+    // pixel n - 1 and f (positions beyond the line are only known to be beyond it)
+    Fixed at = fixed32(xb - 0.5, -16.0, (double)ncol + 16.0);
+    const float am = aa / FIX_ONE, cm = 1.f - 0.5f * aa, cp = 1.f - 1.5f * aa;
     const char* __restrict__ base = reinterpret_cast<const char*>(line);
     const uint32_t ncolb = (uint32_t)ncol * 4u;
     typedef float F3 __attribute__((ext_vector_type(3), aligned(4)));
     float s0 = 0.f, s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int k = 0; k < G; ++k) {
-        const float t = fmaf((float)k, stepf, fb);
-        int xr;
-        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(xr) : "v"(t));
-        const float f = __builtin_amdgcn_fractf(t);
+        const int i = at.whole;
+        const float f = (float)at.frac;  // (times 2^32)
+        at.add(step);
         const char* __restrict__ row = base + (size_t)k * ncolb;
         if constexpr (INNER) {
-            const F3 q = *reinterpret_cast<const F3*>(row + (uint32_t)((ib + xr) << 2));
-            s0 = fmaf(__builtin_amdgcn_fmed3f(fmaf(-aa, f, cm), 0.f, 1.f), q.x, s0);
-            s1 = fmaf(fmaf(-aa, fabsf(f - 0.5f), 1.f), q.y, s1);
-            s2 = fmaf(__builtin_amdgcn_fmed3f(fmaf(aa, f, cp), 0.f, 1.f), q.z, s2);
+            const F3 q = *reinterpret_cast<const F3*>(row + (uint32_t)(i << 2));
+            s0 = fmaf(__builtin_amdgcn_fmed3f(fmaf(-am, f, cm), 0.f, 1.f), q.x, s0);
+            s1 = fmaf(fmaf(-am, fabsf(f - 0.5f * FIX_ONE), 1.f), q.y, s1);
+            s2 = fmaf(__builtin_amdgcn_fmed3f(fmaf(am, f, cp), 0.f, 1.f), q.z, s2);
         } else {
-            const int i = ib + xr, c = min(max(i, 0), ncol - 3);
+            const int c = min(max(i, 0), ncol - 3);
             const F3 q = *reinterpret_cast<const F3*>(row + (uint32_t)(c << 2));
-            const float x = (f + 0.5f) + (float)(i - c);  // the centre, from pixel c
-            const float w0 = fmaf(-aa, fabsf(x), 1.f), w1 = fmaf(-aa, fabsf(x - 1.f), 1.f),
-                        w2 = fmaf(-aa, fabsf(x - 2.f), 1.f);
+            // the centre's distances from the pixels, each rounded once
+            const float m = (float)(i - c);
+            auto from = [&](float whole) { return fabsf(fmaf(f, 1.f / FIX_ONE, m + whole)); };
+            const float w0 = fmaf(-aa, from(0.5f), 1.f), w1 = fmaf(-aa, from(-0.5f), 1.f), w2 = fmaf(-aa, from(-1.5f), 1.f);
             s0 = w0 > 0.f ? fmaf(w0, q.x, s0) : s0;
             s1 = w1 > 0.f ? fmaf(w1, q.y, s1) : s1;
             s2 = w2 > 0.f ? fmaf(w2, q.z, s2) : s2;
@@ -235,6 +260,7 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
         // ray centre in row r: xs(r) = ccol + (dj - (r - crow) bb) / a
         const double xs0 = ccol + (dj + crow * bb) / a;
         const double step = -bb / a;
+        const auto row_st = row_step<T>(step);
         const T aa = (T)fabs(a);
         const double x_in_lo = 0.5 + INTERIOR_MARGIN, x_in_hi = (double)ncol - 1.5 - INTERIOR_MARGIN;
         const int q_n = ((nrow + RSL - 1) / RSL + G - 1) / G * G;
@@ -253,22 +279,26 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
             if (q + G <= q_hi) {
                 const bool inner = __all(!near || (lo >= x_in_lo && hi < x_in_hi));
                 if (near) {
-                    if (inner) acc += hat_rows<true, G>(line, ncol, xb, step, aa);
-                    else acc += hat_rows<false, G>(line, ncol, xb, step, aa);
+                    if (inner) acc += hat_rows<true, G>(line, ncol, xb, row_st, aa);
+                    else acc += hat_rows<false, G>(line, ncol, xb, row_st, aa);
                 }
             } else {
                 for (int r = q; r < q_hi; ++r, line += ncol)
-                    acc += hat_rows<false, 1>(line, ncol, fma((double)r, step, xs0), step, aa);
+                    acc += hat_rows<false, 1>(line, ncol, fma((double)r, step, xs0), row_st, aa);
             }
         }
     }
     part[wave][lane] = acc;
     __syncthreads();
     if (sl == 0 && have && j < f.n_bins) {
-        T sum = T(0);
+        T sum[RSL];
 #pragma unroll
-        for (int k = 0; k < RSL; ++k) sum += part[wave + k][lane];
-        b[f.out_off + j] = sum;
+        for (int k = 0; k < RSL; ++k) sum[k] = part[wave + k][lane];
+#pragma unroll
+        for (int h = RSL / 2; h >= 1; h /= 2)  // (pairwise: fewer roundings than one after the other)
+#pragma unroll
+            for (int k = 0; k < h; ++k) sum[k] += sum[k + h];
+        b[f.out_off + j] = sum[0];
     }
 }
 
@@ -569,35 +599,31 @@ __global__ __launch_bounds__(256) void k_fan_rays(const RayTile* __restrict__ ra
 // of the image): the sample's two neighbours are weighted 1 - f and f.
 // INNER: every lane's samples have both neighbours inside the line.  Otherwise the pair is read at
 // the nearest place inside, and a pixel of it counts where it is within one of the position.
-// FP32: the first position xb in FP64, split into its floor (clamped to just outside the line) and a
-// fraction; line k at fraction + k B in FP32 (error below 1e-6 px for |B| <= 1, k < 8), as in
-// hat_rows; the pair is one 8-byte load at a 32-bit offset within its line.
+// FP32: positions in fixed point with 32 fraction bits, as in hat_rows; the pair is one 8-byte load at a 32-bit offset
+// within its line.
 template <bool INNER, int G>
-__device__ __forceinline__ float fan_rows(const float* __restrict__ line, int nline, double xb, double Bs) {
-    const double flb = fmin(fmax(floor(xb), -16.0), (double)nline + 16.0);
-    const float fb = (float)fmin(fmax(xb - flb, -1.0), 2.0);
-    const int ib = (int)flb;
-    const float stepf = (float)Bs;
+__device__ __forceinline__ float fan_rows(const float* __restrict__ line, int nline, double xb, Fixed step) {
+    Fixed at = fixed32(xb, -16.0, (double)nline + 16.0);
     const char* __restrict__ base = reinterpret_cast<const char*>(line);
     const uint32_t nlineb = (uint32_t)nline * 4u;
     typedef float F2 __attribute__((ext_vector_type(2), aligned(4)));
     float s0 = 0.f, s1 = 0.f;
 #pragma unroll
     for (int k = 0; k < G; ++k) {
-        const float t = fmaf((float)k, stepf, fb);
-        int xr;
-        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(xr) : "v"(t));
-        const float f = __builtin_amdgcn_fractf(t);
+        const int i = at.whole;
+        const float f = (float)at.frac;  // (times 2^32)
+        at.add(step);
         const char* __restrict__ row = base + (size_t)k * nlineb;
         if constexpr (INNER) {
-            const F2 v = *reinterpret_cast<const F2*>(row + (uint32_t)((ib + xr) << 2));
-            s0 = fmaf(1.f - f, v.x, s0);
-            s1 = fmaf(f, v.y, s1);
+            const F2 v = *reinterpret_cast<const F2*>(row + (uint32_t)(i << 2));
+            s0 = fmaf(fmaf(f, -1.f / FIX_ONE, 1.f), v.x, s0);
+            s1 = fmaf(f * (1.f / FIX_ONE), v.y, s1);
         } else {
-            const int i = ib + xr, c = min(max(i, 0), nline - 2);
+            const int c = min(max(i, 0), nline - 2);
             const F2 v = *reinterpret_cast<const F2*>(row + (uint32_t)(c << 2));
-            const float d = f + (float)(i - c);
-            const float w0 = 1.f - fabsf(d), w1 = 1.f - fabsf(d - 1.f);
+            // the position, from each pixel of the pair
+            const float m = (float)(i - c);
+            const float w0 = 1.f - fabsf(fmaf(f, 1.f / FIX_ONE, m)), w1 = 1.f - fabsf(fmaf(f, 1.f / FIX_ONE, m - 1.f));
             s0 = w0 > 0.f ? fmaf(w0, v.x, s0) : s0;
             s1 = w1 > 0.f ? fmaf(w1, v.y, s1) : s1;
         }
@@ -651,6 +677,7 @@ __global__ __launch_bounds__(256) void k_fan_fwd(const RayTile* __restrict__ ray
     const int64_t ri = f.sino_off + (int64_t)k * f.n_bins + j;
     const double4 e = ray ? table[ri] : make_double4(0.0, 0.0, 0.0, 0.0);
     T acc = T(0);
+    const auto row_st = row_step<T>(e.y);
     // rows: samples along x of row y; columns: along y of column x (transposed frame).  A wave
     // whose rays are of both kinds walks both.
     for (int kind = 0; kind < 2; ++kind) {
@@ -666,14 +693,15 @@ __global__ __launch_bounds__(256) void k_fan_fwd(const RayTile* __restrict__ ray
                 const double xb = fma(e.y, (double)q, e.x);
                 // |B| <= 1: the group's positions stay within G of the first
                 if (!__any(xb > -1.0 - G && xb < (double)(nline + G))) continue;
-                const bool inner = xb >= (double)G && xb < (double)(nline - 1 - G);
+                const double xe = fma((double)(G - 1), e.y, xb);
+                const bool inner = fmin(xb, xe) >= INTERIOR_MARGIN && fmax(xb, xe) < (double)(nline - 1) - INTERIOR_MARGIN;
                 if constexpr (sizeof(T) == 4) {
                     if (q + G <= q_hi) {
-                        if (__all(inner)) acc += fan_rows<true, G>(line, nline, xb, e.y);
-                        else acc += fan_rows<false, G>(line, nline, xb, e.y);
+                        if (__all(inner)) acc += fan_rows<true, G>(line, nline, xb, row_st);
+                        else acc += fan_rows<false, G>(line, nline, xb, row_st);
                     } else {
                         for (int r = q; r < q_hi; ++r, line += nline)
-                            acc += fan_rows<false, 1>(line, nline, fma(e.y, (double)r, e.x), e.y);
+                            acc += fan_rows<false, 1>(line, nline, fma(e.y, (double)r, e.x), row_st);
                     }
                 } else {
                     if (q + G <= q_hi) {
