@@ -83,12 +83,22 @@ def _need(t: torch.Tensor, numel: int, name: str):
 # ----------------------------------------------------------------------------- context
 
 
+def _device_index(device) -> int:
+    """The index of a device named as torch names them: None (the current one), an index, "cuda:0", torch.device."""
+    if isinstance(device, int):
+        return device
+    d = None if device is None else torch.device(device)
+    if d is not None and d.type != "cuda":
+        raise ValueError(f"device must be a GPU (got {device})")
+    return torch.cuda.current_device() if d is None or d.index is None else d.index
+
+
 class Context:
     """A library context bound to the current torch stream of one device."""
 
-    def __init__(self, device: Optional[int] = None):
+    def __init__(self, device=None):
         self.lib = _lib.load()
-        self.device = torch.cuda.current_device() if device is None else device
+        self.device = _device_index(device)
         with torch.cuda.device(self.device):
             h = C.c_void_p()
             check(self.lib.mmof_create(C.byref(h), C.c_void_p(torch.cuda.current_stream().cuda_stream)))
@@ -127,8 +137,8 @@ class Context:
 _CTX = {}
 
 
-def context(device: Optional[int] = None) -> Context:
-    d = torch.cuda.current_device() if device is None else device
+def context(device=None) -> Context:
+    d = _device_index(device)
     if d not in _CTX:
         _CTX[d] = Context(d)
     return _CTX[d]
