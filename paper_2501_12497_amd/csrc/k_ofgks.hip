@@ -102,9 +102,15 @@ __device__ void wg_sum(double (&a)[NV], GksLds& s) {
 // side: one butterfly per column and vector, where columns split over the workgroup would cost
 // one per wave (the sums are latency: a 32 x 32 pair has 4 elements per thread and column).
 // VEC = 2: 16-byte loads (the columns of V, whose length is even; the left vectors of odd
-// frames take single loads).
+// frames take single loads).  The address is aligned to one element only: a pair's left vectors start
+// (ell + 1) times the pixels of the pairs before it into their array, which may be an odd number.
 template <int VEC>
-using GkVec = double __attribute__((ext_vector_type(VEC)));
+struct GkVecOf {
+    typedef double type __attribute__((ext_vector_type(VEC), aligned(sizeof(double))));
+};
+template <int VEC>
+using GkVec = typename GkVecOf<VEC>::type;
+static_assert(alignof(GkVec<2>) == alignof(double), "addresses of one element's alignment");
 
 template <int NX, int NC, int VEC>
 __device__ __forceinline__ void wave_dots(const double* __restrict__ Q, int64_t len, int c0,
