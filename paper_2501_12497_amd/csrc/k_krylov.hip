@@ -783,7 +783,7 @@ __device__ __forceinline__ void quad_load_guarded(QuadRows<TX, NQ>& st, const TX
         const int64_t r = rb + t;
         const bool in = r < n;
         if constexpr (WK == QW_NU)
-            st.w[t] = in ? (double)static_cast<const TX*>(wv)[r] : 0.0;   // (nu; zero rows stay zero below)
+            st.w[t] = in ? (double)static_cast<const TX*>(wv)[r] : 1.0;   // (nu; 1: a finite weight for any eps)
         else if constexpr (WK == QW_BUF)
             st.w[t] = in ? static_cast<const double*>(wv)[r] : 0.0;
         else
