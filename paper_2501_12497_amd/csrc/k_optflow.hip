@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256) void k_rev_boxes(const Tile* __restrict__ tile
 }
 
 // The sums of target (qx, qy) over the sources within the flow radius R that round to it, in raster order of the
-// sources, and the largest magnitudes among them.  Source blocks whose target box does not hold q are skipped (a block is
+// sources.  Source blocks whose target box does not hold q are skipped (a block is
 // tested once per block row; a bit mask keeps up to 64 block columns), and so are the row
 // strips of a candidate block whose boxes do not hold q, so large or uneven displacements do
 // not make every target scan its (2R + 1)^2 window: a smooth flow leaves a few candidate
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(256) void k_rev_boxes(const Tile* __restrict__ tile
 template <class T>
 __device__ void reverse_by_boxes(const T* __restrict__ vx, const T* __restrict__ vy, int nx, int ny, int qx, int qy,
                                  int R, const int4* __restrict__ bb, const int4* __restrict__ sb, T& ax, T& ay,
-                                 T& mx, T& my, int& cnt) {
+                                 int& cnt) {
     const int nbx = (nx + 15) / 16;
     const int py_lo = max(qy - R, 0), py_hi = min(qy + R, ny - 1);
     const int px_lo = max(qx - R, 0), px_hi = min(qx + R, nx - 1);
@@ -517,17 +517,13 @@ __device__ void reverse_by_boxes(const T* __restrict__ vx, const T* __restrict__
                     if (rint_shift(px, a) != qx || rint_shift(py, b) != qy) continue;
                     ax -= a;
                     ay -= b;
-                    mx = fmax(mx, fabs(a));
-                    my = fmax(my, fabs(b));
                     ++cnt;
                 }
             }
     }
 }
 
-// s'(rint(p + s(p))) = -s(p), averaged over collisions, 0 at holes.  The mean of three or more, which rounding can
-// carry past all of them, is held to the largest magnitude among them (that of two cannot leave it), so that no
-// reverse velocity is longer than the flow's radius allows for.  A 16 x 16 target tile per workgroup: the sources
+// s'(rint(p + s(p))) = -s(p), averaged over collisions, 0 at holes.  A 16 x 16 target tile per workgroup: the sources
 // within the radius of the tile are loaded together and each drops its velocity into its target's two slots in LDS; a
 // sum of one or two does not depend on their order.  A target with more takes its sources again from a list in LDS, in
 // raster order; a tile whose list overflows scans its targets' windows in memory.  Bound by the sources' vector
@@ -556,12 +552,12 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
     const int64_t np = (int64_t)nx * ny;
     const T* vx = v + 2 * f.pair_off;
     const T* vy = vx + np;
-    T ax = T(0), ay = T(0), mx = T(0), my = T(0);  // (mx, my: used for three sources and more)
+    T ax = T(0), ay = T(0);
     int cnt = 0;
     if (!reverse_staged(R, max_nx)) {
         if (live)
             reverse_by_boxes<T>(vx, vy, nx, ny, qx, qy, R, boxes + f.blk_off, strips + 16 * (int64_t)f.blk_off, ax, ay,
-                                mx, my, cnt);
+                                cnt);
     } else {
         const int sx0 = max(tl.x0 - R, 0), sx1 = min(tl.x0 + RVT - 1 + R, nx - 1);
         const int sy0 = max(tl.y0 - R, 0), sy1 = min(tl.y0 + RVT - 1 + R, ny - 1);
@@ -633,8 +629,6 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
                         if (rint_shift(px, pa) != qx || rint_shift(py, pb) != qy) continue;
                         ax -= pa;
                         ay -= pb;
-                        mx = fmax(mx, fabs(pa));
-                        my = fmax(my, fabs(pb));
                     }
             } else {
                 const int e1 = s_cnt[tid] & (CROWDED - 1), e0 = e1 - cnt;
@@ -651,8 +645,6 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
                     last = best;
                     ax -= s_val[0][at];
                     ay -= s_val[1][at];
-                    mx = fmax(mx, fabs(s_val[0][at]));
-                    my = fmax(my, fabs(s_val[1][at]));
                 }
             }
         } else if (cnt > 0) {
@@ -667,12 +659,8 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
     if (!live) return;
     const int64_t q = (int64_t)qy * nx + qx;
     T* o = vr + 2 * f.pair_off;
-    auto mean = [&](T sum, T most) {
-        const T m = cnt ? sum / T(cnt) : T(0);
-        return cnt > 2 ? fmin(fmax(m, -most), most) : m;
-    };
-    o[q] = mean(ax, mx);
-    o[np + q] = mean(ay, my);
+    o[q] = cnt ? ax / T(cnt) : T(0);
+    o[np + q] = cnt ? ay / T(cnt) : T(0);
 }
 
 template <class T>
