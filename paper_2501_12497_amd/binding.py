@@ -138,7 +138,7 @@ _CTX = {}
 
 
 def context(device=None) -> Context:
-    d = _device_index(device)
+    d = torch.cuda.current_device() if device is None else _device_index(device)
     if d not in _CTX:
         _CTX[d] = Context(d)
     return _CTX[d]
