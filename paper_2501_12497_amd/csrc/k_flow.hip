@@ -373,8 +373,10 @@ __device__ __forceinline__ void corner_terms(T fx, T fy, T val, T t[4]) {
 // loaded together; each adds its four weighted values into the four corner sums of its cell in LDS, and an output adds
 // the sums of the four cells it is a corner of in a fixed order.  A cell sum of one or two sources does not depend on
 // their order.  A cell with more (a converging flow) takes its sources again from a list in LDS and sums them in raster
-// order, so no value depends on the tile shape or on the order of arrival; a tile whose crowded cells hold more than
-// ADJ_LIST sources forms the same sums by the wide-window path.
+// order, so no value depends on the tile shape or on the order of arrival (each source finds its place in its cell's
+// run by counting the ranks below its own: 16 x 128 x 128, FP32, a flow that leaves the frame by up to 7.5 px and clips
+// 64 sources into a corner cell 14 us, 121 when one thread per cell picked them in order); a tile whose crowded cells
+// hold more than ADJ_LIST sources forms the same sums by the wide-window path.
 // Bound by the vector instructions of the sources (184 per output and lane, VALU 90% busy; 269 when every output formed
 // the weights of its four cells' sources itself): 576 sources at radius 4 for the 256 outputs of a 16 x 16 tile.
 // Interior tiles skip the clip.  Measured over 31 pairs of 512 x 512 with the radius, before and now: smooth flow 105 ->
@@ -534,30 +536,30 @@ __global__ __launch_bounds__(256) void k_flow_adj(const AdjTile* __restrict__ ti
                         if (cell[k] >= 0 && (s_cnt[cell[k]] & CROWDED)) {
                             const int e = atomicAdd(&s_cnt[cell[k]], 1) & (CROWDED - 1);
                             s_rank[e] = (unsigned short)(threadIdx.x + 256 * k);
+                        }
+                    __syncthreads();
+                    // each source goes to its place by rank in its cell's run, found by the ranks below its own
+#pragma unroll
+                    for (int k = 0; k < NI; ++k)
+                        if (cell[k] >= 0 && (s_cnt[cell[k]] & CROWDED)) {
+                            const int e1 = s_cnt[cell[k]] & (CROWDED - 1), e0 = e1 - (int)s_sum[0][0][cell[k]];
+                            int at = e0;
+#pragma unroll 8
+                            for (int e = e0; e < e1; ++e) at += s_rank[e] < threadIdx.x + 256 * k ? 1 : 0;
                             T t[4];
                             corner_terms(lvx[k], lvy[k], lr[k], t);
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) s_term[q][e] = t[q];
+                            for (int q = 0; q < 4; ++q) s_term[q][at] = t[q];
                         }
                     __syncthreads();
                     for (int i = threadIdx.x; i < NC; i += 256) {
                         if (!(s_cnt[i] & CROWDED)) continue;
                         const int e1 = s_cnt[i] & (CROWDED - 1), e0 = e1 - (int)s_sum[0][0][i];
                         T a[4] = {T(0), T(0), T(0), T(0)};
-                        int last = -1;
-                        for (int n = e0; n < e1; ++n) {  // the entries by increasing rank
-                            int best = INT_MAX, at = e0;
-                            for (int e = e0; e < e1; ++e) {
-                                const int rk = s_rank[e];
-                                if (rk > last && rk < best) {
-                                    best = rk;
-                                    at = e;
-                                }
-                            }
-                            last = best;
+#pragma unroll 4
+                        for (int e = e0; e < e1; ++e)
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) a[q] += s_term[q][at];
-                        }
+                            for (int q = 0; q < 4; ++q) a[q] += s_term[q][e];
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             s_sum[0][q][i] = a[q];

@@ -526,7 +526,7 @@ __device__ void reverse_by_boxes(const T* __restrict__ vx, const T* __restrict__
 // s'(rint(p + s(p))) = -s(p), averaged over collisions, 0 at holes.  A 16 x 16 target tile per workgroup: the sources
 // within the radius of the tile are loaded together and each drops its velocity into its target's two slots in LDS; a
 // sum of one or two does not depend on their order.  A target with more takes its sources again from a list in LDS, in
-// raster order; a tile whose list overflows scans its targets' windows in memory.  Bound by the sources' vector
+// raster order (each source finds its place by counting the ranks below its own); a tile whose list overflows scans its targets' windows in memory.  Bound by the sources' vector
 // instructions.  15 pairs of 256 x 256, FP32: 13 us with the boxes' launch (which returns), 51 with the boxes, which
 // larger displacements take.
 template <class T>
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
     static_assert(NC == 256, "a thread per target");
     __shared__ T s_slot[2][2][NC], s_val[2][RV_LIST];
     __shared__ unsigned short s_rank[RV_LIST];
-    __shared__ int s_cnt[NC];
+    __shared__ int s_cnt[NC], s_num[NC];
     __shared__ int s_over, s_top;
     const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const FrameInfo f = fr[tl.frame];
@@ -609,13 +609,24 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
             __syncthreads();
             scan = s_top > RV_LIST;  // (the same value on every thread)
             if (!scan) {
+                s_num[tid] = cnt;
 #pragma unroll
                 for (int k = 0; k < NI; ++k)
                     if (cell[k] >= 0 && (s_cnt[cell[k]] & CROWDED)) {
                         const int e = atomicAdd(&s_cnt[cell[k]], 1) & (CROWDED - 1);
                         s_rank[e] = (unsigned short)(tid + 256 * k);
-                        s_val[0][e] = a[k];
-                        s_val[1][e] = b[k];
+                    }
+                __syncthreads();
+                // each source goes to its place by rank in its target's run, found by the ranks below its own
+#pragma unroll
+                for (int k = 0; k < NI; ++k)
+                    if (cell[k] >= 0 && (s_cnt[cell[k]] & CROWDED)) {
+                        const int e1 = s_cnt[cell[k]] & (CROWDED - 1), e0 = e1 - s_num[cell[k]];
+                        int at = e0;
+#pragma unroll 8
+                        for (int e = e0; e < e1; ++e) at += s_rank[e] < tid + 256 * k ? 1 : 0;
+                        s_val[0][at] = a[k];
+                        s_val[1][at] = b[k];
                     }
                 __syncthreads();
             }
@@ -631,20 +642,11 @@ __global__ __launch_bounds__(256) void k_reverse_flow(const Tile* __restrict__ t
                         ay -= pb;
                     }
             } else {
-                const int e1 = s_cnt[tid] & (CROWDED - 1), e0 = e1 - cnt;
-                int last = -1;
-                for (int n = 0; n < cnt; ++n) {  // the entries by increasing rank
-                    int best = INT_MAX, at = e0;
-                    for (int e = e0; e < e1; ++e) {
-                        const int rk = s_rank[e];
-                        if (rk > last && rk < best) {
-                            best = rk;
-                            at = e;
-                        }
-                    }
-                    last = best;
-                    ax -= s_val[0][at];
-                    ay -= s_val[1][at];
+                const int e1 = s_cnt[tid] & (CROWDED - 1);
+#pragma unroll 4
+                for (int e = e1 - cnt; e < e1; ++e) {
+                    ax -= s_val[0][e];
+                    ay -= s_val[1][e];
                 }
             }
         } else if (cnt > 0) {
