@@ -265,18 +265,17 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
         const double x_in_lo = 0.5 + INTERIOR_MARGIN, x_in_hi = (double)ncol - 1.5 - INTERIOR_MARGIN;
         const int q_n = ((nrow + RSL - 1) / RSL + G - 1) / G * G;
         const int q_hi = min(nrow, (sl + 1) * q_n);
-        int q = sl * q_n;
-        if (ncol < 3) {
-            for (; q < q_hi; ++q) acc += hat_row2(img + (int64_t)q * ncol, fma((double)q, step, xs0), aa);
-        }
-        for (; q < q_hi; q += G) {
+        for (int q = sl * q_n; q < q_hi; q += G) {
             const T* line = img + (int64_t)q * ncol;
             const double xb = fma((double)q, step, xs0), xe = fma((double)(G - 1), step, xb);
             const double lo = fmin(xb, xe), hi = fmax(xb, xe);
             // (a ray weighs on pixels within sqrt(2) of its centre)
             const bool near = hi > -1.5 && lo < (double)ncol + 0.5;
             if (!__any(near)) continue;
-            if (q + G <= q_hi) {
+            if (ncol < 3) {
+                for (int r = q; r < min(q + G, q_hi); ++r, line += ncol)
+                    acc += hat_row2(line, fma((double)r, step, xs0), aa);
+            } else if (q + G <= q_hi) {
                 const bool inner = __all(!near || (lo >= x_in_lo && hi < x_in_hi));
                 if (near) {
                     // (the unchecked form also multiplies pixels of weight 0, which must not count when they are not
