@@ -148,6 +148,9 @@ __global__ __launch_bounds__(256) void k_grad_fwd4(const Tile* __restrict__ tile
                 for (int i = 0; i < 4; ++i) g.v[i] = w.v[i] * g.v[i];
             }
             st4(gx + B + e0, g);
+            // (keeps the compiler from joining this store with the tail's into one of 12 and one of 4 bytes: 16 x 512 x
+            // 512 without weights 9.6 -> 8.7 us in FP32, 20.5 -> 19.0 in FP64)
+            __builtin_amdgcn_sched_barrier(0);
         } else if (e0 < n_el) {  // the tail (fewer than 4 values)
 #pragma unroll
             for (int i = 0; i < 3; ++i)
