@@ -756,12 +756,12 @@ constexpr int FAW = 96;  // staged bins per angle (wider tile windows read the t
 // floor(position - h) + 1 on hold every ray that weighs on it.  The window: cnt bins from j0 on, nray
 // of them on the detector (cnt 0: nothing to add, < 0: not staged).
 struct FanAngle {
-    float c, s, gc, gs, off;  // off includes 1 - h
+    float c, s, gc, gs, off, h;  // off includes 1 - h
     int n, j0, cnt, nray;
 };
 
-// Transpose: a 32 x 16 pixel tile per workgroup, a lane PX = 2 pixels 16 apart in a row (PX = 1: one
-// pixel, twice the lanes, for stacks of too few tiles to fill the chip).  Per chunk of FAC angles, the
+// Transpose: a 32 x 16 pixel tile per workgroup (TH = 8: half a tile, for small frames), a lane PX = 2 pixels 16 apart in a
+// row (PX = 1: one pixel, twice the lanes, for stacks of too few tiles to fill the chip).  Per chunk of FAC angles, the
 // bins whose rays can touch the tile are staged in LDS as the line {A, B} and the product of path
 // length and sinogram value.  A ray j weighs on a pixel by 1 - |d| with d the distance from the pixel
 // to the ray's crossing of its row (column), where that is positive; it sits at detector position j,
@@ -776,20 +776,25 @@ struct FanAngle {
 // Bound by vector issue: 46 instructions per pixel and angle, about 8 of them per candidate (four
 // projections per pixel and 20 per candidate before).  FP32, 512 x 512 x 16, 90 angles, 725 bins:
 // 1126 -> 595 us; 128 x 128 x 16, 30 angles: 35 -> 29 us.
-template <class T, int PX>
-__global__ __launch_bounds__(512 / PX) void k_fan_adj(const Tile* __restrict__ tiles,
+template <class T, int PX, int TH>
+__global__ __launch_bounds__(ATW * TH / PX) void k_fan_adj(const Tile* __restrict__ tiles,
                                                       const RadonFrame* __restrict__ rf,
                                                       const double2* __restrict__ trig,
                                                       const double4* __restrict__ table, const T* __restrict__ b,
                                                       T* __restrict__ u, FanGeo geo, float margin, int fp32) {
-    constexpr int NT = 512 / PX, TX = ATW / PX;  // threads, lanes per tile row
+    constexpr int NT = ATW * TH / PX, TX = ATW / PX, PARTS = ATH / TH;  // threads, lanes per tile row, workgroups per tile
+    constexpr bool OWN = TH < ATH;  // candidates by the lane's own half-width (one pixel a lane)
+    static_assert(!OWN || PX == 1, "one pixel a lane");
     __shared__ double2 s_ab[FAC][FAW];
     __shared__ T s_v[FAC][FAW];
     __shared__ FanAngle s_ang[FAC];
     __shared__ int s_ncol[FAC];                  // column rays of the window
     __shared__ unsigned s_cols[FAC][FAW / 32];   // which they are
-    const Tile tl = tiles[xcd_remap(blockIdx.x, gridDim.x)];
+    const int64_t item = xcd_remap(blockIdx.x, gridDim.x);
+    Tile tl = tiles[item / PARTS];
+    tl.y0 += TH * (int)(item % PARTS);
     const RadonFrame f = rf[tl.frame];
+    if (tl.y0 >= f.ny) return;
     const int lx = (int)threadIdx.x % TX, y0 = tl.y0 + (int)threadIdx.x / TX;
     bool in[PX];
     int xs[PX];
@@ -812,10 +817,10 @@ __global__ __launch_bounds__(512 / PX) void k_fan_adj(const Tile* __restrict__ t
     }
     const int nb = f.n_bins;
     const double gsc = geo.dsd / geo.du, off = (nb - 1) / 2.0;
-    const float dsof = (float)geo.dso;
+    const float dsof = (float)geo.dso, gscf = (float)gsc;
     // the tile's pixels, clipped to the frame
     const double Xa = tl.x0 - hx, Xb = min(tl.x0 + ATW, f.nx) - 1 - hx, Ya = tl.y0 - hy,
-                 Yb = min(tl.y0 + ATH, f.ny) - 1 - hy;
+                 Yb = min(tl.y0 + TH, f.ny) - 1 - hy;
     for (int k0 = 0; k0 < f.n_ang; k0 += FAC) {
         const int nk = min(FAC, f.n_ang - k0);
         __syncthreads();  // the previous chunk is no longer read
@@ -838,7 +843,7 @@ __global__ __launch_bounds__(512 / PX) void k_fan_adj(const Tile* __restrict__ t
                 mv = fmax(mv, __shfl_xor(mv, o));
             }
             const double h = gsc * mv / (den * den) + (double)margin;
-            FanAngle a{(float)cs.x, (float)cs.y, (float)(gsc * cs.x), (float)(gsc * cs.y), 0.f, 0, 0, -1, 0};
+            FanAngle a{(float)cs.x, (float)cs.y, (float)(gsc * cs.x), (float)(gsc * cs.y), 0.f, (float)h, 0, 0, -1, 0};
             if (fp32 && den > 0.0 && h < FAW) {
                 // (FP32 positions reach from lo - margin to hi + margin)
                 a.j0 = (int)fmin(fmax(floor(lo - h - 1.0), -1048576.0), 1048576.0);
@@ -907,6 +912,19 @@ __global__ __launch_bounds__(512 / PX) void k_fan_adj(const Tile* __restrict__ t
                     l[p] = s_ab[kk] + i;
                     v[p] = s_v[kk] + i;
                 }
+                int nl = n;
+                if (OWN && n > 2) {
+                    // the lane's own half-width: its derivatives at the least depth one pixel away
+                    const float den = fmaf(-Xf[0], as, yc), in1 = __builtin_amdgcn_rcpf(den - 1.f);
+                    const float mv = fmaxf(fabsf(fmaf(agc, dsof, Yf * gscf)), fabsf(fmaf(ags, dsof, -Xf[0] * gscf)));
+                    const float hh = uniform(a.h), hl = fminf(fmaf(mv * 1.00001f, in1 * in1, margin), hh);
+                    nl = max((int)(2.f * hl) + 1, 2);
+                    int i = (int)fmaf(fmaf(Xf[0], agc, ys), __builtin_amdgcn_rcpf(den), aoff + (hh - hl));
+                    i = min(max(i, 0), cnt - nl);
+                    l[0] = s_ab[kk] + i;
+                    v[0] = s_v[kk] + i;
+                }
+                const int last = OWN ? nl : n;
                 // candidate q of every pixel: its distance from the crossing of its row (column)
                 auto cand = [&](int q, bool rows) {
 #pragma unroll
@@ -921,16 +939,16 @@ __global__ __launch_bounds__(512 / PX) void k_fan_adj(const Tile* __restrict__ t
                 if (ncol == 0) {
                     cand(0, true);
                     if (n > 1) cand(1, true);
-                    for (int q = 2; q < n; ++q) cand(q, true);
+                    for (int q = 2; q < last; ++q) cand(q, true);
                 } else if (ncol == nray) {
                     cand(0, false);
                     if (n > 1) cand(1, false);
-                    for (int q = 2; q < n; ++q) cand(q, false);
+                    for (int q = 2; q < last; ++q) cand(q, false);
                 } else {
 #pragma unroll
                     for (int p = 0; p < PX; ++p) {
                         const int i0 = (int)(v[p] - s_v[kk]);
-                        for (int q = 0; q < n; ++q) {
+                        for (int q = 0; q < last; ++q) {
                             const double2 e = l[p][q];
                             const bool col = (s_cols[kk][(i0 + q) >> 5] >> ((i0 + q) & 31)) & 1u;
                             const double own = col ? yd : xd[p], oth = col ? xd[p] : yd;
@@ -1040,10 +1058,15 @@ void launch_fan_adj(Ctx& c, Plan& p, int dt, const void* b, void* u) {
         using T = decltype(z);
         ScopedTime st(&c, "fan_adj", (double)sizeof(T) * (p.n + p.m), 0.0);
         // with less than two tiles per CU a lane takes one pixel: a wave then has half the chain
-        // (10 frames of 28 x 36, 46 angles: 39 us, 66 with two pixels)
+        // (10 frames of 28 x 36, 46 angles: 39 us, 66 with two pixels).  On frames of up to 48 pixels (FP64: 40) the
+        // half-width changes much across a tile: half a tile per workgroup and each lane's own half-width (FP32 / FP64:
+        // 10 x 32 x 32, 46 angles 41 / 43 -> 32 / 32 us, 1000 x 32 x 32, 30 angles 115 / 123 -> 98 / 112, 400 x 48 x 48
+        // 100 / 107 -> 100 / 118, 100 x 48 x 48 38 / 40 -> 31 / 41; 300 x 64 x 64 88 / 94 against 97 / 113)
         const bool one = p.n_tiles_a < 2 * 256;
-        auto k = one ? k_fan_adj<T, 1> : k_fan_adj<T, 2>;
-        hipLaunchKernelGGL(k, dim3((unsigned)p.n_tiles_a), dim3(one ? 512 : 256), 0, c.stream, p.d_tiles_a.as<Tile>(),
+        const bool half = std::max(p.geom->max_nx, p.geom->max_ny) <= (sizeof(T) == 4 ? 48 : 40);
+        auto k = half ? k_fan_adj<T, 1, ATH / 2> : one ? k_fan_adj<T, 1, ATH> : k_fan_adj<T, 2, ATH>;
+        hipLaunchKernelGGL(k, dim3((unsigned)(half ? 2 * p.n_tiles_a : p.n_tiles_a)), dim3(one && !half ? 512 : 256), 0,
+                           c.stream, p.d_tiles_a.as<Tile>(),
                            p.d_rinfo.as<RadonFrame>(), p.d_trig.as<double2>(), p.d_fanrays.as<double4>(),
                            (const T*)b, (T*)u, geo, margin, (int)fp32);
         MMOF_LAUNCH_CHECK();
