@@ -1058,12 +1058,12 @@ void launch_fan_adj(Ctx& c, Plan& p, int dt, const void* b, void* u) {
         using T = decltype(z);
         ScopedTime st(&c, "fan_adj", (double)sizeof(T) * (p.n + p.m), 0.0);
         // with less than two tiles per CU a lane takes one pixel: a wave then has half the chain
-        // (10 frames of 28 x 36, 46 angles: 39 us, 66 with two pixels).  On frames of up to 48 pixels (FP64: 40) the
+        // (10 frames of 28 x 36, 46 angles: 39 us, 66 with two pixels).  On frames of up to 48 pixels (FP64: 36) the
         // half-width changes much across a tile: half a tile per workgroup and each lane's own half-width (FP32 / FP64:
         // 10 x 32 x 32, 46 angles 41 / 43 -> 32 / 32 us, 1000 x 32 x 32, 30 angles 115 / 123 -> 98 / 112, 400 x 48 x 48
-        // 100 / 107 -> 100 / 118, 100 x 48 x 48 38 / 40 -> 31 / 41; 300 x 64 x 64 88 / 94 against 97 / 113)
+        // 100 / 107 -> 100 / 118, 400 x 40 x 40 107 / 114 -> 103 / 120; 300 x 64 x 64 88 / 94 against 97 / 113)
         const bool one = p.n_tiles_a < 2 * 256;
-        const bool half = std::max(p.geom->max_nx, p.geom->max_ny) <= (sizeof(T) == 4 ? 48 : 40);
+        const bool half = std::max(p.geom->max_nx, p.geom->max_ny) <= (sizeof(T) == 4 ? 48 : 36);
         auto k = half ? k_fan_adj<T, 1, ATH / 2> : one ? k_fan_adj<T, 1, ATH> : k_fan_adj<T, 2, ATH>;
         hipLaunchKernelGGL(k, dim3((unsigned)(half ? 2 * p.n_tiles_a : p.n_tiles_a)), dim3(one && !half ? 512 : 256), 0,
                            c.stream, p.d_tiles_a.as<Tile>(),
