@@ -1017,9 +1017,9 @@ void launch_fan_fwd(Ctx& c, Plan& p, int dt, const void* u, void* b) {
         T* ut = static_cast<T*>(c.work("radon_transpose", sizeof(T) * p.n));
         launch_transpose<T>(c, p, (const T*)u, ut);
         ScopedTime st(&c, "fan_fwd", (double)sizeof(T) * (p.n + p.m), 0.0);
-        // the fewest waves per ray that fill the chip twice (2 x 256 CUs x 32 waves), at most 4:
+        // the fewest waves per ray that fill the chip twice (2 x 32 waves a CU), at most 4:
         // 10 frames of 28 x 36, 46 angles, 17 us with one and 4.4 with four
-        const int64_t waves = 4 * p.n_rays[2], full = 2 * 256 * 32;
+        const int64_t waves = 4 * p.n_rays[2], full = (int64_t)2 * c.cu_count * 32;
         const int gi = waves >= full ? 2 : 2 * waves >= full ? 1 : 0;  // angles per workgroup: 4, 2, 1
         auto k = gi == 2 ? k_fan_fwd<T, 1> : gi == 1 ? k_fan_fwd<T, 2> : k_fan_fwd<T, 4>;
         hipLaunchKernelGGL(k, dim3((unsigned)p.n_rays[gi]), dim3(256), 0, c.stream, p.d_rays[gi].as<RayTile>(),
@@ -1062,7 +1062,7 @@ void launch_fan_adj(Ctx& c, Plan& p, int dt, const void* b, void* u) {
         // half-width changes much across a tile: half a tile per workgroup and each lane's own half-width (FP32 / FP64:
         // 10 x 32 x 32, 46 angles 41 / 43 -> 32 / 32 us, 1000 x 32 x 32, 30 angles 115 / 123 -> 98 / 112, 400 x 48 x 48
         // 100 / 107 -> 100 / 118, 400 x 40 x 40 107 / 114 -> 103 / 120; 300 x 64 x 64 88 / 94 against 97 / 113)
-        const bool one = p.n_tiles_a < 2 * 256;
+        const bool one = p.n_tiles_a < 2 * c.cu_count;
         const bool half = std::max(p.geom->max_nx, p.geom->max_ny) <= (sizeof(T) == 4 ? 48 : 36);
         auto k = half ? k_fan_adj<T, 1, ATH / 2> : one ? k_fan_adj<T, 1, ATH> : k_fan_adj<T, 2, ATH>;
         hipLaunchKernelGGL(k, dim3((unsigned)(half ? 2 * p.n_tiles_a : p.n_tiles_a)), dim3(one && !half ? 512 : 256), 0,
@@ -1078,8 +1078,10 @@ const int kRadonCandidates = 4;  // angle groups of 1, 2, 4, 8 per workgroup
 int radon_fwd_choice(Plan& p, int dt) {
     auto it = p.geom->tuned.find(std::string("radon_fwd") + (dt == MMOF_F32 ? "/f32" : "/f64"));
     if (it != p.geom->tuned.end()) return it->second;
-    // untuned: one angle per workgroup, the best or within 2% of it from 32 x 32 to 1024 x 1024 (16
-    // frames of 256 x 256, 30 angles: 28 us, with 2, 4, 8 angles 32, 33, 42)
+    // untuned: one angle per workgroup, the best or within 2% of it from 32 x 32 to 768 x 768 (16 frames of 256 x 256,
+    // 90 angles: 63 us, with 2, 4, 8 angles 66, 69, 75).  On 64 frames of 1024 x 1024 four angles depend on the
+    // plan's: in order 2.64 ms against 2.70 in FP32 and 5.63 against 5.91 in FP64, in no order 2.84 against 2.70
+    // and 6.05 against 5.86 (a group is placed by its first angle); the autotuner times the plan's own.
     return 0;
 }
 
