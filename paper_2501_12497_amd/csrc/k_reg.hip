@@ -13,9 +13,9 @@ namespace mmof {
 
 static constexpr int RB = 256;   // threads per workgroup
 
-// r[pair_off + p] = u[off + ny nx + p] - u[off + p] for the frames that begin a pair; V pixels per access
-// as below (64 x 1024 x 1024, FP32: 238 us with four single accesses per lane, 4 pixels apart, 90 now).
-template <class TX, int V>
+// r[pair_off + p] = u[off + ny nx + p] - u[off + p] for the frames that begin a pair; four pixels per access
+// (64 x 1024 x 1024, FP32: 238 us with four single accesses per lane, 4 pixels apart, 90 now).
+template <class TX>
 __global__ __launch_bounds__(RB) void k_tdiff_fwd(const FrameInfo* __restrict__ frames, const TX* __restrict__ u,
                                                   TX* __restrict__ r) {
     const FrameInfo f = frames[blockIdx.y];
@@ -23,24 +23,20 @@ __global__ __launch_bounds__(RB) void k_tdiff_fwd(const FrameInfo* __restrict__ 
     const int64_t np = (int64_t)f.ny * f.nx;
     const TX* __restrict__ a = u + f.off;
     TX* __restrict__ out = r + f.pair_off;
-    for (int64_t p = ((int64_t)blockIdx.x * RB + threadIdx.x) * V; p < np; p += (int64_t)gridDim.x * RB * V) {
-        if constexpr (V == 4) {
-            const int nv = (int)min((int64_t)V, np - p);
-            Quad<TX> x = ld4n(a + p, nv), y = ld4n(a + np + p, nv);
+    for (int64_t p = ((int64_t)blockIdx.x * RB + threadIdx.x) * 4; p < np; p += (int64_t)gridDim.x * RB * 4) {
+        const int nv = (int)min((int64_t)4, np - p);
+        Quad<TX> x = ld4n(a + p, nv), y = ld4n(a + np + p, nv);
 #pragma unroll
-            for (int q = 0; q < V; ++q) y.v[q] -= x.v[q];
-            st4n(out + p, y, nv);
-        } else {
-            out[p] = a[np + p] - a[p];
-        }
+        for (int q = 0; q < 4; ++q) y.v[q] -= x.v[q];
+        st4n(out + p, y, nv);
     }
 }
 
 // u[off + p] (+)= r_{t-1}[p] (t >= 1) - r_t[p] (t < n_t - 1): the transpose, a gather; with cout (may
-// be null) the residual cout = cx + lambda u instead of u (ResidualOut).  V pixels per access (4, or
-// 1 for operands that are not element-aligned).  Bound by memory (64 x 1024 x 1024, FP32: 270 us with
-// four single accesses per lane, 4 pixels apart, and 191 us for the residual's own pass; 219 us with both).
-template <class TX, int V>
+// be null) the residual cout = cx + lambda u instead of u (ResidualOut).  Four pixels per access.  Bound
+// by memory (64 x 1024 x 1024, FP32: 270 us with four single accesses per lane, 4 pixels apart, and 191 us
+// for the residual's own pass; 219 us with both).
+template <class TX>
 __global__ __launch_bounds__(RB) void k_tdiff_adj(const FrameInfo* __restrict__ frames, const TX* __restrict__ r,
                                                   TX* __restrict__ u, int accumulate, const TX* __restrict__ cx,
                                                   const double* __restrict__ clam, double* __restrict__ cout) {
@@ -51,36 +47,25 @@ __global__ __launch_bounds__(RB) void k_tdiff_adj(const FrameInfo* __restrict__ 
     const TX* __restrict__ cur = f.t + 1 < f.n_t ? r + f.pair_off : nullptr;
     TX* __restrict__ out = u + f.off;
     const double lam = cout ? clam[0] : 0.0;
-    auto ld = [&](const TX* p, int nv) {
-        if constexpr (V == 4) return ld4n(p, nv);
-        Quad<TX> q = zero4<TX>();
-        q.v[0] = *p;
-        return q;
-    };
-    for (int64_t p = ((int64_t)blockIdx.x * RB + threadIdx.x) * V; p < np; p += (int64_t)gridDim.x * RB * V) {
-        const int nv = (int)min((int64_t)V, np - p);
+    for (int64_t p = ((int64_t)blockIdx.x * RB + threadIdx.x) * 4; p < np; p += (int64_t)gridDim.x * RB * 4) {
+        const int nv = (int)min((int64_t)4, np - p);
         Quad<TX> v = zero4<TX>(), b = zero4<TX>(), o = zero4<TX>();
-        if (prev) v = ld(prev + p, nv);
-        if (cur) b = ld(cur + p, nv);
-        if (accumulate) o = ld(out + p, nv);
+        if (prev) v = ld4n(prev + p, nv);
+        if (cur) b = ld4n(cur + p, nv);
+        if (accumulate) o = ld4n(out + p, nv);
 #pragma unroll
-        for (int q = 0; q < V; ++q) {
+        for (int q = 0; q < 4; ++q) {
             if (cur) v.v[q] -= b.v[q];
             if (accumulate) v.v[q] = o.v[q] + v.v[q];
         }
         if (cout) {
-            const Quad<TX> x = ld(cx + f.off + p, nv);
+            const Quad<TX> x = ld4n(cx + f.off + p, nv);
             Quad<double> w;
 #pragma unroll
             for (int q = 0; q < 4; ++q) w.v[q] = (double)x.v[q] + lam * (double)v.v[q];
-            if constexpr (V == 4)
-                st4n(cout + f.off + p, w, nv);
-            else
-                cout[f.off + p] = w.v[0];
-        } else if constexpr (V == 4) {
-            st4n(out + p, v, nv);
+            st4n(cout + f.off + p, w, nv);
         } else {
-            out[p] = v.v[0];
+            st4n(out + p, v, nv);
         }
     }
 }
@@ -157,8 +142,7 @@ void launch_tdiff(Ctx& c, Geom& g, int dt, bool transpose, const void* in, void*
                   const ResidualOut* res) {
     MMOF_CHECK(g.n_frames <= 65535, MMOF_ERR_SHAPE, "too many frames for one launch (at most 65535)");
     const size_t es = dt == MMOF_F32 ? 4 : 8;
-    const bool vec = aligned_to(es, {in, out});
-    const dim3 grid = frame_grid(g, RB * (vec ? 4 : 1));
+    const dim3 grid = frame_grid(g, RB * 4);
     // one read and one write per pair pixel (forward) or per frame pixel (transpose, which
     // reads up to two residuals and, when accumulating, the output)
     const double bytes = transpose ? (double)(2 * g.pair_px + (accumulate ? 2 : 1) * g.n) : 3.0 * (double)g.pair_px;
@@ -166,13 +150,11 @@ void launch_tdiff(Ctx& c, Geom& g, int dt, bool transpose, const void* in, void*
     dispatch(dt, [&](auto z) {
         using TX = decltype(z);
         if (transpose) {
-            auto k = vec ? k_tdiff_adj<TX, 4> : k_tdiff_adj<TX, 1>;
-            hipLaunchKernelGGL(k, grid, dim3(RB), 0, c.stream, g.dframes(), (const TX*)in, (TX*)out, accumulate ? 1 : 0,
-                               res ? (const TX*)res->x : (const TX*)nullptr, res ? res->lam : nullptr,
-                               res ? res->out : nullptr);
+            hipLaunchKernelGGL(k_tdiff_adj<TX>, grid, dim3(RB), 0, c.stream, g.dframes(), (const TX*)in, (TX*)out,
+                               accumulate ? 1 : 0, res ? (const TX*)res->x : (const TX*)nullptr,
+                               res ? res->lam : nullptr, res ? res->out : nullptr);
         } else {
-            auto k = vec ? k_tdiff_fwd<TX, 4> : k_tdiff_fwd<TX, 1>;
-            hipLaunchKernelGGL(k, grid, dim3(RB), 0, c.stream, g.dframes(), (const TX*)in, (TX*)out);
+            hipLaunchKernelGGL(k_tdiff_fwd<TX>, grid, dim3(RB), 0, c.stream, g.dframes(), (const TX*)in, (TX*)out);
         }
     });
     MMOF_LAUNCH_CHECK();
