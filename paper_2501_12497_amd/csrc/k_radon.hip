@@ -217,10 +217,9 @@ __device__ __forceinline__ T hat_row2(const T* __restrict__ line, double xs, T a
 // them stay inside.  Bound by the cache's accesses (16 to 18 per gather: four lanes a cycle) and vector
 // issue (12.5 instructions per ray and row).  Measured against waves whose lanes started at rows of
 // their own and, on blocks of less than 48 rows, checked every pixel: FP32 128 x 128 x 16, 30 angles
-// 24 -> 11 us, 256 x 256 x 16 63 -> 28 us, 1024 x 1024 x 64, 90 angles 2.99 -> 2.64 ms; FP64 251 x 310 x
-// 16, 45 angles 137 -> 87 us, 1024 x 1024 x 16, 90 angles 1.60 -> 1.49 ms.
-// ANG = 1 finds frame and angle in its record, where they were three loads one after the other (16 x 128 x 128, FP32, 30
-// angles 11.7 -> 11.0 us).
+// 23 -> 12 us, 256 x 256 x 16 61 -> 27 us, 1024 x 1024 x 64, 90 angles 2.99 -> 2.71 ms; FP64 251 x 310 x
+// 16, 45 angles 126 -> 70 us, 1024 x 1024 x 16, 90 angles 1.59 -> 1.46 ms.
+// ANG = 1 finds frame and angle in its record, where they were three loads one after the other (0.7 us of the first).
 template <class T, int ANG>
 __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ rays, const RadonFrame* __restrict__ rf,
                                                    const double2* __restrict__ trig, const RayRec* __restrict__ recs,
@@ -265,17 +264,21 @@ __global__ __launch_bounds__(512) void k_radon_fwd(const RayTile* __restrict__ r
         const double x_in_lo = 0.5 + INTERIOR_MARGIN, x_in_hi = (double)ncol - 1.5 - INTERIOR_MARGIN;
         const int q_n = ((nrow + RSL - 1) / RSL + G - 1) / G * G;
         const int q_hi = min(nrow, (sl + 1) * q_n);
-        for (int q = sl * q_n; q < q_hi; q += G) {
+        int q = sl * q_n;
+        for (; ncol < 3 && q < q_hi; q += G) {
+            const double xb = fma((double)q, step, xs0), xe = fma((double)(G - 1), step, xb);
+            if (!__any(fmax(xb, xe) > -1.5 && fmin(xb, xe) < (double)ncol + 0.5)) continue;
+            for (int r = q; r < min(q + G, q_hi); ++r)
+                acc += hat_row2(img + (int64_t)r * ncol, fma((double)r, step, xs0), aa);
+        }
+        for (; q < q_hi; q += G) {
             const T* line = img + (int64_t)q * ncol;
             const double xb = fma((double)q, step, xs0), xe = fma((double)(G - 1), step, xb);
             const double lo = fmin(xb, xe), hi = fmax(xb, xe);
             // (a ray weighs on pixels within sqrt(2) of its centre)
             const bool near = hi > -1.5 && lo < (double)ncol + 0.5;
             if (!__any(near)) continue;
-            if (ncol < 3) {
-                for (int r = q; r < min(q + G, q_hi); ++r, line += ncol)
-                    acc += hat_row2(line, fma((double)r, step, xs0), aa);
-            } else if (q + G <= q_hi) {
+            if (q + G <= q_hi) {
                 const bool inner = __all(!near || (lo >= x_in_lo && hi < x_in_hi));
                 if (near) {
                     // (the unchecked form also multiplies pixels of weight 0, which must not count when they are not
@@ -664,7 +667,7 @@ __device__ __forceinline__ double fan_rows(const double* __restrict__ line, int 
 // measured 162e6 accesses for 6.7e6 loads); a group of lines takes the unchecked form when the
 // positions of all its rays stay inside, and is skipped when none comes near.  Bound by the cache's
 // accesses (17 per gather: four lanes a cycle) and vector issue.  FP32, 512 x 512 x 16, 90 angles,
-// 725 bins: 474 -> 264 us; 128 x 128 x 16, 30 angles: 45 -> 12 us (the ray split over four waves).
+// 725 bins: 455 -> 241 us; 128 x 128 x 16, 30 angles: 43 -> 12 us (the ray split over four waves).
 template <class T, int RSL>
 __global__ __launch_bounds__(256) void k_fan_fwd(const RayTile* __restrict__ rays, const RadonFrame* __restrict__ rf,
                                                  const double4* __restrict__ table, const T* __restrict__ u,
@@ -775,7 +778,7 @@ struct FanAngle {
 // candidates between the FP64 projections of the pixel's four neighbours, from the table.
 // Bound by vector issue: 46 instructions per pixel and angle, about 8 of them per candidate (four
 // projections per pixel and 20 per candidate before).  FP32, 512 x 512 x 16, 90 angles, 725 bins:
-// 1126 -> 595 us; 128 x 128 x 16, 30 angles: 35 -> 29 us.
+// 1008 -> 534 us; 128 x 128 x 16, 30 angles: 33 -> 26 us.
 template <class T, int PX, int TH>
 __global__ __launch_bounds__(ATW * TH / PX) void k_fan_adj(const Tile* __restrict__ tiles,
                                                       const RadonFrame* __restrict__ rf,
