@@ -14,8 +14,8 @@
 // blocks of the factored columns, the factor in LDS.  Broadcasts within 16 lanes are DPP operands of
 // the FMAs.  D^2 and its derivative only need forward solves (d^T z = ||L^{-1} d||^2,
 // w^T M^{-1} w = ||L^{-1} w||^2) plus one backward solve for z.
-// 64 < K <= 256: eight wavefronts by the same steps, the matrix in their accumulators and the factor in
-// an L2-resident global workspace.  The root search is the same for both.
+// 64 < K <= 256: eight wavefronts by the same steps, the matrix in their accumulators, the factor in the
+// LDS up to 128 columns and in an L2-resident global workspace beyond.  The root search is the same for both.
 #include "dev.h"
 #include "krylov.h"
 
@@ -85,8 +85,8 @@ __device__ __forceinline__ void wave_sum2(double& a, double& b) {
 // lane holds its row's 16 entries and, in every row of 16 lanes, a copy of the diagonal block's row
 // l % 16, so that a pivot and the entries of its column reach all lanes as DPP operands (one FMA per
 // entry; two readlanes and an FMA before).  The last block column has no rows below its diagonal
-// block.  Bound by the instructions one wave issues, 11 cycles apart; the factorization and its solves take 6 us at
-// K <= 16, 12 at 39 and 17 at 64 (9, 22 and 32 with readlane broadcasts and masked steps; a cold start at K = 39, eight
+// block.  Bound by the instructions one wave issues, 11 cycles apart; the factorization and its solves take 4 us at
+// K = 16, 12 at 39 and 17 at 64 (9, 22 and 32 with readlane broadcasts and masked steps; a cold start at K = 39, eight
 // of them, 180 -> 95 us).
 // Returns false on a pivot that is not positive (uniform across the wave); on success *inv holds
 // 1 / p[lane].
@@ -412,9 +412,9 @@ __global__ __launch_bounds__(64) void k_small_solve(int K, const double* __restr
 // rows, with the steps of factor(), and updates the blocks right of it on the matrix cores from there.  The factor stays
 // in the LDS up to 128 columns (the largest square that fits beside the rest) and goes to an L2-resident workspace
 // beyond, by columns and by rows, for the triangular solves: thread i < 256 owns row i, and every row of 16 lanes solves
-// a copy of the diagonal block (one barrier per block).  An evaluation takes 24 us at K = 80, 40 at 120, 67 at 130 and
-// 112 at 200 (34 and 57 at 80 and 120 with the factor in L2; 126, 261 and 514 at 80, 130 and 200 with the trailing matrix
-// there too, updated entry by entry).
+// a copy of the diagonal block (one barrier per block of a solve, three of the factorization).  An evaluation takes 25 us
+// at K = 80, 41 at 120, 67 at 130 and 111 at 200 (34 and 57 at 80 and 120 with the factor in L2; 126, 261 and 514 at 80,
+// 130 and 200 with the trailing matrix there too, updated entry by entry).
 
 static constexpr int BIG_T = 512, BIG_W = BIG_T / 64;  // threads, waves
 

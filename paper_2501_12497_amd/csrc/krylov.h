@@ -105,7 +105,7 @@ void put_rowcol(Ctx& c, double* G, int ldg, int j, const double* h);
 template <class TX>
 void weight_mul(Ctx& c, int64_t n, const double* w, const TX* x, TX* y);
 
-// Small projected solve (one wavefront for K <= 64, four above).  Inputs on the device: GA, GT
+// Small projected solve (one wavefront for K <= 64, eight above).  Inputs on the device: GA, GT
 // (K x K, leading dimension KLD),
 // d (K), and the scalars bb = ||b||^2 and target = (eta*delta)^2 in sc[0..1].
 // Writes z (K), and res[0] = lambda, res[1] = discrepancy^2, res[2] = status (0 root, 2 clamped,

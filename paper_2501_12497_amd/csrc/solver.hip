@@ -554,8 +554,9 @@ struct Solver {
                         w.gks = gks;
                         fm.gamma = gamma;
                         flow_update_core(c, g, gs, dt, u_op, flow_v, fscale, p.delta_r, fm, w);
-                        // (a reverse flow is a mean of the flow's velocities, so none is longer; the adjoint's
-                        // values do not depend on the radius of the window that holds them)
+                        // (a reverse flow is a mean of the flow's velocities, all shorter than the integer R of the radius:
+                        // rounding carries no partial sum of k of them past k R and no mean past R, where the fraction
+                        // is 0; the adjoint's values do not depend on the radius of the window that holds them)
                         launch_flow_radius(c, g, dt, flow_v, rad_v, rad_vr);
                         if (p.use_reverse) launch_reverse_flow(c, g, dt, flow_v, flow_vr, rad_v);
                     });
