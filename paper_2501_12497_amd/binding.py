@@ -543,15 +543,21 @@ def projected_solve(GA: torch.Tensor, GT: torch.Tensor, d: torch.Tensor, bnorm2:
     K = d.numel()
     if not 1 <= K <= KRYLOV_MAX:
         raise ValueError(f"K must be in [1, {KRYLOV_MAX}] (got {K})")
-    # (the solve reads the K x K entries only; the scalars by fills on the stream: a copy from the host would wait for
-    # the Gram matrices queued before)
-    for M, name in ((GA, "GA"), (GT, "GT")):
+
+    def square(M, name):
+        if M.shape == (K, K):
+            return M
         if M.shape[-2:] != (K, K) or M.numel() != K * K:   # (a copy would spread a smaller one)
             raise ValueError(f"{name} must be {K} x {K} (got {tuple(M.shape)})")
+        return M.reshape(K, K)
+
+    GA, GT = square(GA, "GA"), square(GT, "GT")
+    # (the solve reads the K x K entries only; the scalars by fills on the stream: a copy from the host would wait for
+    # the Gram matrices queued before)
     AT = torch.empty((2, KRYLOV_MAX, KRYLOV_MAX), dtype=torch.float64, device=d.device)
     A64, T64 = AT[0], AT[1]
-    A64[:K, :K].copy_(GA.reshape(K, K))
-    T64[:K, :K].copy_(GT.reshape(K, K))
+    A64[:K, :K].copy_(GA)
+    T64[:K, :K].copy_(GT)
     sc = torch.empty(3, dtype=torch.float64, device=d.device)
     for q, val in enumerate((bnorm2, target, prev_lambda)):
         sc[q].fill_(float(val))
